@@ -54,77 +54,115 @@ __device__ __forceinline__ bf16x4 load4(const bf16 *p)
 // ---------------------------------------------------------------------------------------
 // 3x3x3 convolution (zero padding): Y[v][co] = act(bias[co] + sum_{tap,ci} W[co][tap][ci] X[v+tap][ci])
 // ---------------------------------------------------------------------------------------
-template <int NG, bool RELU, bool BIAS, typename TO>
-__global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, const bf16 *__restrict__ X,
+// Rows of 16 channels staged in LDS for a run of voxels [v, v + len) and its tap neighbours of
+// one z-offset: tap (dy, dx) of the run's l-th voxel is row l + dy * dys + dx.  One contiguous
+// range of len + 2 n + 2 voxels holds all nine (dys = n); where 2 n + 2 rows more than the
+// run's own would cost more than three ranges of len + 2, one per dy (dys = len + 2).
+struct TapRows {
+    int dys, seg, nseg;      // row stride of dy, rows of a range, ranges
+};
+inline TapRows tap_rows(int n, int len)
+{
+    if (2 * n + 2 + len <= 3 * (len + 2)) return TapRows{n, len + 2 * n + 2, 1};
+    return TapRows{len + 2, len + 2, 3};
+}
+// rows of z-offset dz (0 .. 2) of the voxels from v on: 16 channels from channel c of X
+// (voxel pitch C) as two 16-byte halves; rows outside the tensor are zero
+__device__ __forceinline__ void stage_taps(const TapRows &tr, int n, int V, int v, int dz, int C, int c,
+                                           const bf16 *__restrict__ X, uint4 *rows, int tid, int nt)
+{
+    for (int q = 0; q < tr.nseg; ++q) {
+        const int u0 = v + (dz - 1) * n * n + (tr.nseg == 1 ? -n : (q - 1) * n) - 1;
+        for (int h = tid; h < 2 * tr.seg; h += nt) {
+            const int u = u0 + (h >> 1);
+            uint4 val{0u, 0u, 0u, 0u};
+            if (u >= 0 && u < V) val = *reinterpret_cast<const uint4 *>(X + (size_t)u * C + c + 8 * (h & 1));
+            rows[2 * q * tr.seg + h] = val;
+        }
+    }
+}
+
+// A block computes 64 M voxels x 16 NG output channels; wave w the 16 M voxels from 16 M w on.
+// Sums run over (z-offset, channel slice, tap in the plane), a fixed order whatever NG and M:
+// for each z-offset and 16-channel slice the block stages the rows of X that the nine taps of
+// its voxels reach and the nine taps' weights, so a row is read from memory once per slice
+// and a weight once per block; a wave's weight operands are read from LDS once for its M
+// voxel groups.  Taps outside the grid are zeroed by the voxel's tap mask.  Per MFMA the
+// kernel reads 1 / NG + 1 / M operands from LDS, which bounds it.
+// Measured at 64^3, batch 8, all 27 convolutions of a training step: 5.75 ms with the operands
+// of every 16 voxels loaded from memory, 2.58 ms here.
+template <int NG, int M, bool ACT, typename TO>
+__global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, TapRows tr, const bf16 *__restrict__ X,
                                                const bf16 *__restrict__ Wk, const float *__restrict__ bias,
                                                TO *__restrict__ Y)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int v0 = wave * 16;
-    if (v0 >= V) return;
+    extern __shared__ uint4 lds[];
+    uint4 *ws = lds + 2 * tr.nseg * tr.seg;                   // [9][16 NG] rows of 16 weights
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int row = lane & 15, kq = lane >> 4;
-    const int g0 = blockIdx.y * NG;
-    const int n3 = n * n * n;
-    const int v = v0 + row;
-    const bool vin = v < V;
-    int b = 0, z = 0, y = 0, x = 0;
-    if (vin) {
-        b = v / n3;
-        int r = v - b * n3;
-        z = r / (n * n);
-        y = (r / n) % n;
-        x = r % n;
+    const int vb = blockIdx.x * (64 * M), g0 = blockIdx.y * NG;
+    // bit t of vm: tap t of the lane's voxel lies in the grid
+    unsigned vm[M];
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+        const int v = vb + 16 * (M * wv + q) + row;
+        const int x = v % n, y = (v / n) % n, z = (v / (n * n)) % n;
+        const unsigned bx = (x > 0 ? 1u : 0u) | 2u | (x < n - 1 ? 4u : 0u);
+        const unsigned by = (y > 0 ? bx : 0u) | bx << 3 | (y < n - 1 ? bx << 6 : 0u);
+        vm[q] = (z > 0 ? by : 0u) | by << 9 | (z < n - 1 ? by << 18 : 0u);
     }
-    f32x4 acc[NG];
+    f32x4 acc[M][NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // The nine taps of one z-offset at a time: all their input and weight loads are issued
-    // before the first of their MFMAs, so a wavefront waits for memory three times per
-    // 16-channel slice instead of at every tap.  Sums run over (z-offset, channel slice, tap
-    // in the plane): a fixed order.
-    for (int tz = 0; tz < 3; ++tz) {
-        const int zz = z + tz - 1;
-        const bf16 *xp[9];
-        bool ok[9];
+    for (int q = 0; q < M; ++q)
 #pragma unroll
-        for (int t9 = 0; t9 < 9; ++t9) {
-            const int yy = y + t9 / 3 - 1, xx = x + t9 % 3 - 1;
-            ok[t9] = vin && zz >= 0 && yy >= 0 && xx >= 0 && zz < n && yy < n && xx < n;
-            xp[t9] = X + (size_t)(b * n3 + (zz * n + yy) * n + xx) * Cin + 4 * kq;
-        }
+        for (int g = 0; g < NG; ++g) acc[q][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bf16 *xw = reinterpret_cast<const bf16 *>(lds) + (16 * M * wv + row) * 16 + 4 * kq;
+    const bf16 *ww = reinterpret_cast<const bf16 *>(ws) + row * 16 + 4 * kq;
+    for (int tz = 0; tz < 3; ++tz)
         for (int c0 = 0; c0 < Cin; c0 += 16) {
-            bf16x4 a[9], w[9][NG];
-#pragma unroll
-            for (int t9 = 0; t9 < 9; ++t9) {
-                a[t9] = ok[t9] ? load4(xp[t9] + c0) : bf16x4{0, 0, 0, 0};
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    const int co = (g0 + g) * 16 + row;
-                    w[t9][g] = load4(Wk + ((size_t)co * 27 + tz * 9 + t9) * Cin + c0 + 4 * kq);
-                }
+            stage_taps(tr, n, V, vb, tz, Cin, c0, X, lds, tid, 256);
+            for (int h = tid; h < 9 * 32 * NG; h += 256) {
+                const int t9 = h / (32 * NG), co = (h >> 1) % (16 * NG);
+                ws[h] = *reinterpret_cast<const uint4 *>(Wk + ((size_t)(16 * g0 + co) * 27 + tz * 9 + t9) * Cin + c0 +
+                                                         8 * (h & 1));
             }
+            __syncthreads();
+            bf16x4 w[9][NG];
 #pragma unroll
             for (int t9 = 0; t9 < 9; ++t9)
 #pragma unroll
-                for (int g = 0; g < NG; ++g)
-                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[t9], w[t9][g], acc[g], 0, 0, 0);
+                for (int g = 0; g < NG; ++g) w[t9][g] = load4(ww + (t9 * NG + g) * 256);
+#pragma unroll
+            for (int q = 0; q < M; ++q)
+#pragma unroll
+                for (int t9 = 0; t9 < 9; ++t9) {
+                    uint2 a = *reinterpret_cast<const uint2 *>(xw + (16 * q + (t9 / 3) * tr.dys + t9 % 3) * 16);
+                    const unsigned k = 0u - ((vm[q] >> (9 * tz + t9)) & 1u);
+                    a.x &= k;
+                    a.y &= k;
+#pragma unroll
+                    for (int g = 0; g < NG; ++g)
+                        acc[q][g] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, a), w[t9][g],
+                                                                              acc[q][g], 0, 0, 0);
+                }
+            __syncthreads();
         }
-    }
     // D[voxel 4 kq + i][co = row]
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         const int co = (g0 + g) * 16 + row;
-        const float bco = BIAS ? bias[co] : 0.f;
+        const float bco = ACT ? bias[co] : 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int vo = v0 + 4 * kq + i;
-            if (vo >= V) continue;
-            float val = acc[g][i] + bco;
-            if (RELU) val = val > 0.f ? val : 0.f;
-            if constexpr (sizeof(TO) == 2) Y[(size_t)vo * Cout + co] = f2bf(val);
-            else Y[(size_t)vo * Cout + co] = val;
-        }
+        for (int q = 0; q < M; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int vo = vb + 16 * (M * wv + q) + 4 * kq + i;
+                if (vo >= V) continue;
+                float val = acc[q][g][i] + bco;
+                if (ACT) val = val > 0.f ? val : 0.f;
+                if constexpr (sizeof(TO) == 2) Y[(size_t)vo * Cout + co] = f2bf(val);
+                else Y[(size_t)vo * Cout + co] = val;
+            }
     }
 }
 
@@ -132,105 +170,155 @@ __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, 
 // weight gradient: P[chunk][co][tap][ci] = sum_{v in chunk} G[v][co] X[v+tap][ci]
 // ---------------------------------------------------------------------------------------
 // voxels per block: enough blocks to fill the GPU (about 2048 with the 27 taps), at most 4096
-// voxels (fewer chunk partials to reduce), a multiple of WG_VS
+// voxels (fewer chunk partials to reduce), a multiple of 64
 inline int wgrad_chunk(int V)
 {
     const int c = (int)std::min<long>(4096, std::max<long>(256, (long)V * 27 / 2048));
     return (c + 63) / 64 * 64;
 }
-constexpr int WG_VS = 64;        // voxels staged in LDS per barrier: four 16-voxel MFMA steps
-constexpr int WG_MAXT = 7;       // 16x16 tiles per wave (Cout/16 * Cin/16 <= 28)
+constexpr int WG_VS = 256;       // voxels staged in LDS per round: sixteen 16-voxel MFMA steps
+constexpr int WG_RED_TAPS = 3;   // taps per dz whose wave sums are exchanged at a time (SPLIT)
 
-// A block stages WG_VS voxels of G and of the tap-shifted X at a time (8-byte loads).  With
-// at least four 16x16 output tiles, wave w takes tiles w, w + 4, ... over all staged voxels;
-// with fewer (the 16-channel layers, which run on the largest grids), wave w takes the w-th
-// 16-voxel step of every tile and the four waves' sums are added in wave order at the end,
-// so that no wave idles.
-__global__ void __launch_bounds__(256) k_wgrad(int n, int V, int Cin, int Cout, int wchunk, const bf16 *__restrict__ G,
-                                               const bf16 *__restrict__ X, float *__restrict__ P)
+// Four consecutive rows (voxels) of one column (channel) from rows of 16 BF16 in LDS: lane
+// (m, kq) of a wavefront receives column m of rows 4 kq .. 4 kq + 3 after row r0 -- the K-major
+// operand of the voxel GEMM -- by the transposing LDS read, for which lane m of each group of
+// 16 points at four columns of row m / 4.
+__device__ __forceinline__ bf16x4 load_rows4(const bf16 *rows, int r0, int m, int kq)
 {
-    __shared__ bf16 sG[WG_VS][64 + 4];
-    __shared__ bf16 sX[WG_VS][112 + 4];
-    __shared__ f32x4 red[3][3][64];
-    const int tap = blockIdx.y, chunk = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int n3 = n * n * n;
-    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-    const int tco = Cout / 16, tci = Cin / 16, ntiles = tco * tci;
-    const bool split = ntiles < 4;
-    f32x4 acc[WG_MAXT];
-#pragma unroll
-    for (int t = 0; t < WG_MAXT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int vbeg = chunk * wchunk, vend = min(vbeg + wchunk, V);
-    const int g4 = Cout / 4, x4 = Cin / 4;
-    const int m = lane & 15, kq = lane >> 4;
-    for (int vs = vbeg; vs < vend; vs += WG_VS) {
-        for (int q = tid; q < WG_VS * g4; q += 256) {
-            const int r = q / g4, c = 4 * (q - r * g4), v = vs + r;
-            const bf16x4 val = (v < vend) ? load4(G + (size_t)v * Cout + c) : bf16x4{0, 0, 0, 0};
-            *reinterpret_cast<bf16x4 *>(&sG[r][c]) = val;
-        }
-        for (int q = tid; q < WG_VS * x4; q += 256) {
-            const int r = q / x4, c = 4 * (q - r * x4), v = vs + r;
-            bf16x4 val{0, 0, 0, 0};
-            if (v < vend) {
-                const int b = v / n3, rr = v - b * n3;
-                const int z = rr / (n * n) + dz, y = (rr / n) % n + dy, x = rr % n + dx;
-                if (z >= 0 && y >= 0 && x >= 0 && z < n && y < n && x < n)
-                    val = load4(X + (size_t)(b * n3 + (z * n + y) * n + x) * Cin + c);
-            }
-            *reinterpret_cast<bf16x4 *>(&sX[r][c]) = val;
-        }
-        __syncthreads();
-        for (int ks = 0; ks < WG_VS / 16; ++ks) {
-            if (split && ks != wv) continue;
-#pragma unroll
-            for (int t = 0; t < WG_MAXT; ++t) {
-                const int tile = split ? t : wv + 4 * t;
-                if (tile >= ntiles) break;
-                const int cog = tile / tci, cig = tile - cog * tci;
-                bf16x4 a, bb;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    a[j] = (short)sG[16 * ks + 4 * kq + j][cog * 16 + m];    // A[co][v]
-                    bb[j] = (short)sX[16 * ks + 4 * kq + j][cig * 16 + m];   // B[v][ci]
-                }
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bb, acc[t], 0, 0, 0);
-            }
-        }
-        __syncthreads();
-    }
-    if (split) {
-        if (wv > 0)
-            for (int t = 0; t < ntiles; ++t) red[wv - 1][t][lane] = acc[t];
-        __syncthreads();
-        if (wv > 0) return;
-        for (int t = 0; t < ntiles; ++t)
-            for (int w = 0; w < 3; ++w) acc[t] += red[w][t][lane];
-    }
-#pragma unroll
-    for (int t = 0; t < WG_MAXT; ++t) {
-        const int tile = split ? t : wv + 4 * t;
-        if (tile >= ntiles) break;
-        const int cog = tile / tci, cig = tile - cog * tci;
-        for (int i = 0; i < 4; ++i) {
-            const int co = cog * 16 + 4 * kq + i, ci = cig * 16 + m;   // D[co][ci]
-            P[(((size_t)chunk * Cout + co) * 27 + tap) * Cin + ci] = acc[t][i];
-        }
-    }
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+    const bf16 *p = rows + (r0 + 4 * kq + (m >> 2)) * 16 + 4 * (m & 3);
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4 *)p);
 }
 
-// sum over chunks (fixed order) into the canonical gradient W[co][ci][tap] (ci < ci_real)
+__device__ __forceinline__ bf16x4 mask4(bf16x4 a, uint2 k)
+{
+    uint2 u = __builtin_bit_cast(uint2, a);
+    u.x &= k.x;
+    u.y &= k.y;
+    return __builtin_bit_cast(bf16x4, u);
+}
+
+// A block takes one chunk of voxels and, of the 16 x 16 output tiles (co, ci), either all
+// those of one ci group (blockIdx.y; a wave per co group and dz) or, for layers with fewer
+// than four tiles (SPLIT: the 16-channel layers on the largest grids), the tile blockIdx.y,
+// whose 16-voxel steps go round four waves per dz; the four sums are added in wave order.
+// A wave holds the nine taps of its dz (36 accumulator registers).  WG_VS voxels of G and the
+// rows of X that their 27 taps reach are staged at a time; both MFMA operands are K-major
+// (voxels) and come from the transposing LDS read.  A tap outside the grid is dropped by
+// zeroing G's voxels (masks per voxel and side of the grid, staged with them), so the staged
+// rows serve every tap.  The kernel is bound by LDS reads: 15 (9 of X, 1 of G, 5 masks) for
+// nine MFMAs.
+// Measured at 64^3, batch 8: 734 us per layer on average for the version that staged X once
+// per tap and gathered its operands by 2-byte LDS reads, 110 us for this one (10.3 -> 1.54 ms of a training step).
+template <bool SPLIT>
+__global__ void __launch_bounds__(768) k_wgrad(int n, int V, int Cin, int Cout, int wchunk, TapRows tr,
+                                               const bf16 *__restrict__ G, const bf16 *__restrict__ X,
+                                               float *__restrict__ P)
+{
+    extern __shared__ uint4 lds[];
+    const int tci = Cin / 16, tco = SPLIT ? 1 : Cout / 16;    // tco: co groups of the block
+    const int zrows = tr.nseg * tr.seg;                        // rows of X per dz
+    uint4 *xs = lds, *gs = lds + 2 * 3 * zrows;                // [3][zrows], [tco][WG_VS] rows
+    uint16_t *mk = reinterpret_cast<uint16_t *>(gs + 2 * tco * WG_VS);   // [6][WG_VS]
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
+    const int m = lane & 15, kq = lane >> 4;
+    const int chunk = blockIdx.x, cig = SPLIT ? blockIdx.y % tci : blockIdx.y;
+    const int cog0 = SPLIT ? blockIdx.y / tci : 0;             // first co group of the block
+    const int wz = wv % 3, wq = wv / 3;                        // the wave's dz; co group or step residue
+    const bf16 *xw = reinterpret_cast<const bf16 *>(xs + 2 * wz * zrows);
+    const bf16 *gw = reinterpret_cast<const bf16 *>(gs + (SPLIT ? 0 : 2 * wq * WG_VS));
+    f32x4 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int vbeg = chunk * wchunk, vend = min(vbeg + wchunk, V);
+    for (int vs = vbeg; vs < vend; vs += WG_VS) {
+        for (int dz = 0; dz < 3; ++dz)
+            stage_taps(tr, n, V, vs, dz, Cin, 16 * cig, X, xs + 2 * dz * zrows, tid, nt);
+        for (int h = tid; h < 2 * tco * WG_VS; h += nt) {
+            const int g = h / (2 * WG_VS), r = (h >> 1) % WG_VS, v = vs + r;
+            uint4 val{0u, 0u, 0u, 0u};
+            if (v < vend)
+                val = *reinterpret_cast<const uint4 *>(G + (size_t)v * Cout + 16 * (cog0 + g) + 8 * (h & 1));
+            gs[h] = val;
+        }
+        for (int r = tid; r < WG_VS; r += nt) {
+            const int v = vs + r, x = v % n, y = (v / n) % n, z = (v / (n * n)) % n;
+            mk[0 * WG_VS + r] = x > 0 ? 0xFFFFu : 0u;
+            mk[1 * WG_VS + r] = x < n - 1 ? 0xFFFFu : 0u;
+            mk[2 * WG_VS + r] = y > 0 ? 0xFFFFu : 0u;
+            mk[3 * WG_VS + r] = y < n - 1 ? 0xFFFFu : 0u;
+            mk[4 * WG_VS + r] = z > 0 ? 0xFFFFu : 0u;
+            mk[5 * WG_VS + r] = z < n - 1 ? 0xFFFFu : 0u;
+        }
+        __syncthreads();
+        const int nst = (min(WG_VS, vend - vs) + 15) / 16;
+        for (int ks = SPLIT ? wq : 0; ks < nst; ks += SPLIT ? 4 : 1) {
+            const int r0 = 16 * ks;
+            auto side = [&](int q) { return *reinterpret_cast<const uint2 *>(mk + q * WG_VS + r0 + 4 * kq); };
+            bf16x4 a = load_rows4(gw, r0, m, kq);                 // A[co][v]
+            if (wz != 1) a = mask4(a, side(wz == 0 ? 4 : 5));
+            const uint2 x0 = side(0), x2 = side(1);
+            const bf16x4 ay[3] = {mask4(a, side(2)), a, mask4(a, side(3))};
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                const int dy = t / 3, dx = t % 3;
+                const bf16x4 am = dx == 0 ? mask4(ay[dy], x0) : (dx == 2 ? mask4(ay[dy], x2) : ay[dy]);
+                const bf16x4 b = load_rows4(xw, r0 + dy * tr.dys + dx, m, kq);   // B[v][ci]
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(am, b, acc[t], 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    }
+    if (SPLIT) {
+        f32x4 *red = reinterpret_cast<f32x4 *>(lds);            // [3 waves][3 dz][WG_RED_TAPS][64]
+#pragma unroll
+        for (int t0 = 0; t0 < 9; t0 += WG_RED_TAPS) {
+            if (wq > 0)
+#pragma unroll
+                for (int t = 0; t < WG_RED_TAPS; ++t) red[(((wq - 1) * 3 + wz) * WG_RED_TAPS + t) * 64 + lane] = acc[t0 + t];
+            __syncthreads();
+            if (wq == 0)
+#pragma unroll
+                for (int t = 0; t < WG_RED_TAPS; ++t)
+                    for (int w = 0; w < 3; ++w) acc[t0 + t] += red[((w * 3 + wz) * WG_RED_TAPS + t) * 64 + lane];
+            __syncthreads();
+        }
+        if (wq > 0) return;
+    }
+    const int cog = SPLIT ? cog0 : wq;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int co = cog * 16 + 4 * kq + i, ci = cig * 16 + m;   // D[co][ci]
+            P[(((size_t)chunk * Cout + co) * 27 + 9 * wz + t) * Cin + ci] = acc[t][i];
+        }
+}
+
+// sum over chunks (fixed order) into the canonical gradient W[co][ci][tap] (ci < ci_real).
+// The order is sequential per output and the outputs are few, so the loads of 32 chunks are
+// issued before their additions (one memory round trip for 32 chunks instead of one for each).
 __global__ void k_wgrad_reduce(int nchunk, int Cin, int Cout, int ci_real, const float *__restrict__ P,
                                float *__restrict__ gW)
 {
+    constexpr int NB = 32;
     // thread order (co, tap, ci): consecutive threads read consecutive partials of a chunk
     int q = blockIdx.x * blockDim.x + threadIdx.x;
     int total = Cout * ci_real * 27;
     if (q >= total) return;
     int ci = q % ci_real, tap = (q / ci_real) % 27, co = q / (27 * ci_real);
+    const float *p = P + ((size_t)co * 27 + tap) * Cin + ci;
+    const size_t pitch = (size_t)Cout * 27 * Cin;
     float s = 0.f;
-    for (int c = 0; c < nchunk; ++c) s += P[(((size_t)c * Cout + co) * 27 + tap) * Cin + ci];
+    int c = 0;
+    for (; c + NB <= nchunk; c += NB) {
+        float v[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) v[u] = p[(size_t)(c + u) * pitch];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) s += v[u];
+    }
+    for (; c < nchunk; ++c) s += p[(size_t)c * pitch];
     gW[((size_t)co * ci_real + ci) * 27 + tap] = s;
 }
 
@@ -770,34 +858,56 @@ void layer_table(const int ch[4], int cin, LayerInfo L[NLAYER])
 
 int skip_of(int q) { return q == 8 ? 5 : (q == 10 ? 3 : 1); }
 
-void launch_conv(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const float *bias, bool relu,
+template <int NG, int M>
+void launch_conv_as(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const float *bias,
+                    void *Y, bool fp32out)
+{
+    const TapRows tr = tap_rows(n, 64 * M);
+    const size_t lds = 32 * ((size_t)tr.nseg * tr.seg + 9 * 16 * NG);
+    const dim3 grid(nblk((size_t)V, 64 * M), Cout / 16 / NG);
+    if (fp32out)
+        k_conv3<NG, M, false, float><<<grid, 256, lds, m->stream>>>(n, V, Cin, Cout, tr, X, W, nullptr, (float *)Y);
+    else
+        k_conv3<NG, M, true, bf16><<<grid, 256, lds, m->stream>>>(n, V, Cin, Cout, tr, X, W, bias, (bf16 *)Y);
+}
+
+// Shape of the convolution's blocks: the widest of the listed ones (fewest LDS reads per
+// MFMA first) whose launch still has CONV_MIN_BLOCKS blocks; the narrowest otherwise.
+constexpr int CONV_MIN_BLOCKS = 512;
+void launch_conv(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const float *bias,
                  void *Y, bool fp32out)
 {
     const int groups = Cout / 16;
-    int NG = (groups % 4 == 0) ? 4 : (groups % 3 == 0) ? 3 : (groups % 2 == 0) ? 2 : 1;
-    // A wavefront computes NG groups of 16 output channels from one load of its inputs.  On
-    // the coarse levels (few voxels) that leaves most of the GPU idle, so there each
-    // wavefront takes fewer groups and more blocks share the work (every output's sum runs
-    // in the same order either way).
-    const unsigned vblk = nblk((size_t)((V + 15) / 16) * 64);
-    while (NG > 1 && (size_t)vblk * (groups / NG) < 1024) {
-        int ng = NG - 1;
-        while (groups % ng) --ng;
-        NG = ng;
-    }
-    dim3 grid(vblk, groups / NG);
-    hipStream_t s = m->stream;
-#define CONV(NGv)                                                                                                    \
-    if (NG == NGv) {                                                                                                 \
-        if (fp32out)                                                                                                 \
-            k_conv3<NGv, false, false, float><<<grid, 256, 0, s>>>(n, V, Cin, Cout, X, W, nullptr, (float *)Y);     \
-        else if (relu)                                                                                               \
-            k_conv3<NGv, true, true, bf16><<<grid, 256, 0, s>>>(n, V, Cin, Cout, X, W, bias, (bf16 *)Y);            \
-        else                                                                                                         \
-            k_conv3<NGv, false, true, bf16><<<grid, 256, 0, s>>>(n, V, Cin, Cout, X, W, bias, (bf16 *)Y);           \
-    }
-    CONV(1) CONV(2) CONV(3) CONV(4)
+    auto fits = [&](int NG, int M) {
+        return groups % NG == 0 && (size_t)nblk((size_t)V, 64 * M) * (groups / NG) >= (size_t)CONV_MIN_BLOCKS;
+    };
+#define CONV(NG, M) launch_conv_as<NG, M>(m, n, V, Cin, Cout, X, W, bias, Y, fp32out)
+    if (fits(3, 4)) CONV(3, 4);
+    else if (fits(2, 4)) CONV(2, 4);
+    else if (fits(3, 2)) CONV(3, 2);
+    else if (fits(2, 2)) CONV(2, 2);
+    else if (fits(1, 4)) CONV(1, 4);
+    else if (fits(2, 1)) CONV(2, 1);
+    else if (fits(1, 2)) CONV(1, 2);
+    else CONV(1, 1);
 #undef CONV
+}
+
+void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int nchunk, const bf16 *G, const bf16 *X)
+{
+    const int tco = Cout / 16, tci = Cin / 16;
+    const bool split = tco * tci < 4;
+    const TapRows tr = tap_rows(n, WG_VS);
+    const size_t rows = 3 * (size_t)tr.nseg * tr.seg + (split ? 1 : tco) * WG_VS;
+    const size_t red = split ? sizeof(f32x4) * 9 * WG_RED_TAPS * 64 : 0;
+    const size_t lds = std::max(rows * 32 + 6 * WG_VS * sizeof(uint16_t), red);
+    const void *fn = split ? reinterpret_cast<const void *>(&k_wgrad<true>) : reinterpret_cast<const void *>(&k_wgrad<false>);
+    // more than 64 KB of LDS (grids of more than about 128 cells per axis) has to be asked for
+    if (lds > 65536) nck(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (split)
+        k_wgrad<true><<<dim3(nchunk, tco * tci), 768, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
+    else
+        k_wgrad<false><<<dim3(nchunk, tci), 192 * tco, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
 }
 
 void repack(cps_model *m)
@@ -826,8 +936,7 @@ void forward(cps_model *m, int B)
             k_upcat<<<nblk((size_t)V * l.cip), 256, 0, m->stream>>>(B, n / 2, m->L[q - 1].co, m->L[sk].co, m->out[q - 1],
                                                                     m->out[sk], m->in[q]);
         }
-        launch_conv(m, n, V, l.cip, l.co, m->in[q], m->Wk[q], m->w + l.off + (long)l.co * l.ci * 27, true, m->out[q],
-                    false);
+        launch_conv(m, n, V, l.cip, l.co, m->in[q], m->Wk[q], m->w + l.off + (long)l.co * l.ci * 27, m->out[q], false);
     }
     k_head<<<nblk(V0), 256, 0, m->stream>>>(V0, m->L[NLAYER - 1].co, m->out[NLAYER - 1], m->w + m->head_off, m->pred);
 }
@@ -858,7 +967,7 @@ void backward(cps_model *m, int B)
         k_relu_bwd<<<nblk(nout), 256, 0, m->stream>>>(nout, m->gout[q], m->out[q], m->gb);
         // weight and bias gradients
         const int wchunk = wgrad_chunk(V), nchunk = (V + wchunk - 1) / wchunk;
-        k_wgrad<<<dim3(nchunk, 27), 256, 0, m->stream>>>(n, V, l.cip, l.co, wchunk, m->gb, m->in[q], m->wpart);
+        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, m->gb, m->in[q]);
         k_wgrad_reduce<<<nblk((size_t)l.co * l.ci * 27), 256, 0, m->stream>>>(nchunk, l.cip, l.co, l.ci, m->wpart,
                                                                               m->g + l.off);
         k_colsum_part<<<COLSUM_BLOCKS, 256, 0, m->stream>>>(V, l.co, m->gb, m->cpart);
@@ -866,7 +975,7 @@ void backward(cps_model *m, int B)
                                                                  m->g + l.off + (long)l.co * l.ci * 27);
         if (q == 0) break;
         // data gradient into the producer of this layer's input
-        launch_conv(m, n, V, l.co, l.cip, m->gb, m->Wf[q], nullptr, false, m->gtmp, true);
+        launch_conv(m, n, V, l.co, l.cip, m->gb, m->Wf[q], nullptr, m->gtmp, true);
         if (q == 2 || q == 4 || q == 6) {
             size_t nin = (size_t)B * (2 * n) * (2 * n) * (2 * n) * l.cip;
             k_pool_bwd<<<nblk(nin), 256, 0, m->stream>>>(B, 2 * n, l.cip, m->gtmp, m->gout[q - 1]);
