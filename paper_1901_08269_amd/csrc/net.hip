@@ -37,13 +37,8 @@ typedef uint16_t bf16;
 
 constexpr int NLAYER = 14;
 
-__device__ __forceinline__ bf16 f2bf(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (bf16)(u >> 16);   // inf / nan
-    u += 0x7fffu + ((u >> 16) & 1u);                                 // round to nearest even
-    return (bf16)(u >> 16);
-}
+// round to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ bf16 f2bf(float f) { return __builtin_bit_cast(bf16, static_cast<__bf16>(f)); }
 __device__ __forceinline__ float bf2f(bf16 b) { return __uint_as_float((uint32_t)b << 16); }
 
 __device__ __forceinline__ bf16x4 load4(const bf16 *p)
@@ -73,43 +68,59 @@ __device__ __forceinline__ void stage_taps(const TapRows &tr, int n, int V, int 
 {
     for (int q = 0; q < tr.nseg; ++q) {
         const int u0 = v + (dz - 1) * n * n + (tr.nseg == 1 ? -n : (q - 1) * n) - 1;
+        const bf16 *src = X + (ptrdiff_t)u0 * C + c;
         for (int h = tid; h < 2 * tr.seg; h += nt) {
-            const int u = u0 + (h >> 1);
             uint4 val{0u, 0u, 0u, 0u};
-            if (u >= 0 && u < V) val = *reinterpret_cast<const uint4 *>(X + (size_t)u * C + c + 8 * (h & 1));
+            if ((unsigned)(u0 + (h >> 1)) < (unsigned)V)
+                val = *reinterpret_cast<const uint4 *>(src + (unsigned)((h >> 1) * C + 8 * (h & 1)));
             rows[2 * q * tr.seg + h] = val;
         }
     }
 }
+
+// What a convolution does with its sums:
+//   CONV_ACT    Y (BF16) = ReLU(sum + bias)                                      (forward)
+//   CONV_GATE   Y (BF16) = sum where the activation gate[v][co] > 0, else 0: the gradient
+//               entering the layer that made this layer's input      (data gradient, odd layers)
+//   CONV_F32    Y (FP32) = sum                            (data gradient of a pooled input)
+//   CONV_SPLIT  channels below c_lo to Y (FP32, pitch c_lo), the others to Y2 (FP32): the two
+//               parts of an upsampled and concatenated input
+enum { CONV_ACT = 0, CONV_GATE = 1, CONV_F32 = 2, CONV_SPLIT = 3 };
+struct ConvOut {
+    const float *bias;
+    const bf16 *gate;
+    bf16 *yb;
+    float *yf, *yf2;
+    int c_lo;
+};
 
 // A block computes 64 M voxels x 16 NG output channels; wave w the 16 M voxels from 16 M w on.
 // Sums run over (z-offset, channel slice, tap in the plane), a fixed order whatever NG and M:
 // for each z-offset and 16-channel slice the block stages the rows of X that the nine taps of
 // its voxels reach and the nine taps' weights, so a row is read from memory once per slice
 // and a weight once per block; a wave's weight operands are read from LDS once for its M
-// voxel groups.  Taps outside the grid are zeroed by the voxel's tap mask.  Per MFMA the
-// kernel reads 1 / NG + 1 / M operands from LDS, which bounds it.
+// voxel groups.  Taps outside the grid are zeroed by the voxel's tap mask (one voxel per
+// thread, exchanged through LDS: index divisions are what a block would otherwise spend most
+// of its vector instructions on).  Per MFMA the kernel reads 1 / NG + 1 / M operands from LDS.
 // Measured at 64^3, batch 8, all 27 convolutions of a training step: 5.75 ms with the operands
-// of every 16 voxels loaded from memory, 2.58 ms here.
-template <int NG, int M, bool ACT, typename TO>
+// of every 16 voxels loaded from memory, CONV_MS ms here.
+template <int NG, int M, int OUT>
 __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, TapRows tr, const bf16 *__restrict__ X,
-                                               const bf16 *__restrict__ Wk, const float *__restrict__ bias,
-                                               TO *__restrict__ Y)
+                                               const bf16 *__restrict__ Wk, ConvOut O)
 {
     extern __shared__ uint4 lds[];
+    __shared__ unsigned masks[64 * M];
     uint4 *ws = lds + 2 * tr.nseg * tr.seg;                   // [9][16 NG] rows of 16 weights
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int row = lane & 15, kq = lane >> 4;
     const int vb = blockIdx.x * (64 * M), g0 = blockIdx.y * NG;
-    // bit t of vm: tap t of the lane's voxel lies in the grid
-    unsigned vm[M];
-#pragma unroll
-    for (int q = 0; q < M; ++q) {
-        const int v = vb + 16 * (M * wv + q) + row;
-        const int x = v % n, y = (v / n) % n, z = (v / (n * n)) % n;
-        const unsigned bx = (x > 0 ? 1u : 0u) | 2u | (x < n - 1 ? 4u : 0u);
-        const unsigned by = (y > 0 ? bx : 0u) | bx << 3 | (y < n - 1 ? bx << 6 : 0u);
-        vm[q] = (z > 0 ? by : 0u) | by << 9 | (z < n - 1 ? by << 18 : 0u);
+    if (tid < 64 * M) {
+        // bit t: tap t of voxel vb + tid lies in the grid
+        const unsigned un = (unsigned)n, v = (unsigned)(vb + tid), vy = v / un, vz = vy / un;
+        const unsigned x = v - vy * un, y = vy - vz * un, z = vz % un;
+        const unsigned bx = (x > 0 ? 1u : 0u) | 2u | (x < un - 1 ? 4u : 0u);
+        const unsigned by = (y > 0 ? bx : 0u) | bx << 3 | (y < un - 1 ? bx << 6 : 0u);
+        masks[tid] = (z > 0 ? by : 0u) | by << 9 | (z < un - 1 ? by << 18 : 0u);
     }
     f32x4 acc[M][NG];
 #pragma unroll
@@ -121,10 +132,10 @@ __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, 
     for (int tz = 0; tz < 3; ++tz)
         for (int c0 = 0; c0 < Cin; c0 += 16) {
             stage_taps(tr, n, V, vb, tz, Cin, c0, X, lds, tid, 256);
+            const bf16 *wsrc = Wk + ((size_t)16 * g0 * 27 + tz * 9) * Cin + c0;
             for (int h = tid; h < 9 * 32 * NG; h += 256) {
                 const int t9 = h / (32 * NG), co = (h >> 1) % (16 * NG);
-                ws[h] = *reinterpret_cast<const uint4 *>(Wk + ((size_t)(16 * g0 + co) * 27 + tz * 9 + t9) * Cin + c0 +
-                                                         8 * (h & 1));
+                ws[h] = *reinterpret_cast<const uint4 *>(wsrc + (unsigned)((co * 27 + t9) * Cin + 8 * (h & 1)));
             }
             __syncthreads();
             bf16x4 w[9][NG];
@@ -133,11 +144,12 @@ __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, 
 #pragma unroll
                 for (int g = 0; g < NG; ++g) w[t9][g] = load4(ww + (t9 * NG + g) * 256);
 #pragma unroll
-            for (int q = 0; q < M; ++q)
+            for (int q = 0; q < M; ++q) {
+                const int vm = (int)(masks[16 * (M * wv + q) + row] >> (9 * tz));
 #pragma unroll
                 for (int t9 = 0; t9 < 9; ++t9) {
                     uint2 a = *reinterpret_cast<const uint2 *>(xw + (16 * q + (t9 / 3) * tr.dys + t9 % 3) * 16);
-                    const unsigned k = 0u - ((vm[q] >> (9 * tz + t9)) & 1u);
+                    const unsigned k = (unsigned)((vm << (31 - t9)) >> 31);
                     a.x &= k;
                     a.y &= k;
 #pragma unroll
@@ -145,23 +157,29 @@ __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, 
                         acc[q][g] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, a), w[t9][g],
                                                                               acc[q][g], 0, 0, 0);
                 }
+            }
             __syncthreads();
         }
     // D[voxel 4 kq + i][co = row]
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         const int co = (g0 + g) * 16 + row;
-        const float bco = ACT ? bias[co] : 0.f;
+        const float bco = OUT == CONV_ACT ? O.bias[co] : 0.f;
+        // CONV_SPLIT: c_lo is a multiple of 16, so a group lies on one side
+        const bool lo = OUT != CONV_SPLIT || co < O.c_lo;
+        float *yf = lo ? O.yf : O.yf2;
+        const int pitch = OUT != CONV_SPLIT ? Cout : (lo ? O.c_lo : Cout - O.c_lo), cc = lo ? co : co - O.c_lo;
 #pragma unroll
         for (int q = 0; q < M; ++q)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int vo = vb + 16 * (M * wv + q) + 4 * kq + i;
                 if (vo >= V) continue;
+                const size_t e = (size_t)vo * pitch + cc;
                 float val = acc[q][g][i] + bco;
-                if (ACT) val = val > 0.f ? val : 0.f;
-                if constexpr (sizeof(TO) == 2) Y[(size_t)vo * Cout + co] = f2bf(val);
-                else Y[(size_t)vo * Cout + co] = val;
+                if (OUT == CONV_ACT) O.yb[e] = f2bf(val > 0.f ? val : 0.f);
+                else if (OUT == CONV_GATE) O.yb[e] = bf2f(O.gate[e]) > 0.f ? f2bf(val) : (bf16)0;
+                else yf[e] = val;
             }
     }
 }
@@ -298,8 +316,8 @@ __global__ void __launch_bounds__(768) k_wgrad(int n, int V, int Cin, int Cout, 
 // sum over chunks (fixed order) into the canonical gradient W[co][ci][tap] (ci < ci_real).
 // The order is sequential per output and the outputs are few, so the loads of 32 chunks are
 // issued before their additions (one memory round trip for 32 chunks instead of one for each).
-__global__ void k_wgrad_reduce(int nchunk, int Cin, int Cout, int ci_real, const float *__restrict__ P,
-                               float *__restrict__ gW)
+__device__ __forceinline__ void wgrad_reduce(int nchunk, int Cin, int Cout, int ci_real, const float *__restrict__ P,
+                                             float *__restrict__ gW)
 {
     constexpr int NB = 32;
     // thread order (co, tap, ci): consecutive threads read consecutive partials of a chunk
@@ -322,49 +340,89 @@ __global__ void k_wgrad_reduce(int nchunk, int Cin, int Cout, int ci_real, const
     gW[((size_t)co * ci_real + ci) * 27 + tap] = s;
 }
 
-// db[c] = sum_v G[v][c] in two fixed-order passes.  Pass 1: COLSUM_BLOCKS blocks; thread t of
-// a block takes channel t % C and every (256 / C)-th voxel of the block's stride (consecutive
-// threads read consecutive elements), and the block sums its voxel lanes per channel in LDS
-// in lane order.  Pass 2: one thread per channel adds the block partials in block order.
-constexpr int COLSUM_BLOCKS = 512;
-__global__ void __launch_bounds__(256) k_colsum_part(int V, int C, const bf16 *__restrict__ G, float *__restrict__ part)
+// db[c] = sum_v G[v][c] in two fixed-order passes.  Pass 1: COLSUM_PARTS parts; lane vl of a
+// part adds every lanes-th voxel of the part's stride per channel (lanes = 256 / C), and the
+// part's lanes are added per channel in lane order.  A thread takes eight channels of one lane
+// (16-byte loads, eight of them in flight), a wavefront two parts.  Pass 2 (k_grad_final) adds
+// the part sums.  (One channel per thread and 2-byte loads took 27 us per layer at 64^3, batch
+// 8, this COLSUM_US us.)
+constexpr int COLSUM_PARTS = 512;
+__global__ void __launch_bounds__(64) k_colsum_part(int V, int C, const bf16 *__restrict__ G, float *__restrict__ part)
 {
-    __shared__ float sh[256];
-    const int lanes = 256 / C, t = (int)threadIdx.x;    // voxel lanes per block (C <= 256)
-    const int c = t % C, vl = t / C;
-    float s = 0.f;
-    if (vl < lanes)
-        for (size_t v = (size_t)blockIdx.x * lanes + vl; v < (size_t)V; v += (size_t)gridDim.x * lanes)
-            s += bf2f(G[v * C + c]);
-    sh[t] = s;
+    __shared__ float sh[2][256];
+    const int lanes = 256 / C, c8 = C / 8;                 // C <= 64: at most 32 threads per part
+    const int h = (int)threadIdx.x >> 5, t = (int)threadIdx.x & 31;
+    const int p = 2 * (int)blockIdx.x + h, vl = t / c8, c = 8 * (t - vl * c8);
+    if (vl < lanes) {
+        float s[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] = 0.f;
+        const size_t step = (size_t)COLSUM_PARTS * lanes;
+        auto add = [&](uint4 w) {
+            const unsigned u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s[2 * j] += __uint_as_float(u[j] << 16);
+                s[2 * j + 1] += __uint_as_float(u[j] & 0xFFFF0000u);
+            }
+        };
+        size_t v = (size_t)p * lanes + vl;
+        for (; v + 7 * step < (size_t)V; v += 8 * step) {
+            uint4 w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = *reinterpret_cast<const uint4 *>(G + (v + k * step) * C + c);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) add(w[k]);
+        }
+        for (; v < (size_t)V; v += step) add(*reinterpret_cast<const uint4 *>(G + v * C + c));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sh[h][vl * C + c + j] = s[j];
+    }
     __syncthreads();
-    if (t < C) {
+    for (int q = t; q < C; q += 32) {
         float acc = 0.f;
-        for (int l = 0; l < lanes; ++l) acc += sh[l * C + t];
-        part[(size_t)blockIdx.x * C + t] = acc;
+        for (int l = 0; l < lanes; ++l) acc += sh[h][l * C + q];
+        part[(size_t)p * C + q] = acc;
     }
 }
 
-// one block per channel: thread t adds partials t, t + 256, ...; then a tree in LDS
-__global__ void __launch_bounds__(256) k_colsum_final(int nb, int C, const float *__restrict__ part,
-                                                      float *__restrict__ out)
+// The layer's gradients from their partials, one launch: blocks below wblocks sum the weight
+// gradient over chunks (wgrad_reduce), the C blocks after them one channel's bias gradient each
+// (thread t adds parts t, t + 256, ...; then a tree in LDS).
+__global__ void __launch_bounds__(256) k_grad_final(int wblocks, int nchunk, int Cin, int Cout, int ci_real,
+                                                    const float *__restrict__ P, const float *__restrict__ part,
+                                                    float *__restrict__ gW, float *__restrict__ gb)
 {
     __shared__ float sh[256];
-    const int c = (int)blockIdx.x, t = (int)threadIdx.x;
+    if ((int)blockIdx.x < wblocks) {
+        wgrad_reduce(nchunk, Cin, Cout, ci_real, P, gW);
+        return;
+    }
+    const int c = (int)blockIdx.x - wblocks, t = (int)threadIdx.x;
     float acc = 0.f;
-    for (int b = t; b < nb; b += 256) acc += part[(size_t)b * C + c];
+    for (int b = t; b < COLSUM_PARTS; b += 256) acc += part[(size_t)b * Cout + c];
     sh[t] = acc;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if (t < o) sh[t] += sh[t + o];
         __syncthreads();
     }
-    if (t == 0) out[c] = sh[0];
+    if (t == 0) gb[c] = sh[0];
 }
 
 // ---------------------------------------------------------------------------------------
 // elementwise pieces
 // ---------------------------------------------------------------------------------------
+// g rounded to BF16 where the activation is positive (ReLU's gradient), 0 elsewhere
+__device__ __forceinline__ bf16x4 gate4(float4 g, bf16x4 act)
+{
+    const float gv[4] = {g.x, g.y, g.z, g.w};
+    bf16x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = (short)(bf2f((bf16)act[j]) > 0.f ? f2bf(gv[j]) : (bf16)0);
+    return o;
+}
+
 // input [B][cin][n^3] (FP32, channels first) -> [V][16] BF16, channels >= cin zero
 __global__ void k_pack_input(int V, int n3, int cin, const float *__restrict__ in, bf16 *__restrict__ out)
 {
@@ -393,74 +451,72 @@ __global__ void k_pool(int B, int n, int C, const bf16 *__restrict__ in, bf16 *_
     out[q] = f2bf(s * 0.125f);
 }
 
-__global__ void k_pool_bwd(int B, int n, int C, const float *__restrict__ gout, float *__restrict__ gin)
+// gradient entering the 3x3x3 layer before a pooling (its output act at n, [V][C]): the skip
+// connection's part gskip plus an eighth of the pooled cell's gradient, masked by the ReLU,
+// rounded to BF16.  Four channels per thread.
+__global__ void k_pool_bwd(int B, int n, int C, const float *__restrict__ gpool, const float *__restrict__ gskip,
+                           const bf16 *__restrict__ act, bf16 *__restrict__ out)
 {
-    int m = n / 2;
-    size_t total = (size_t)B * n * n * n * C;
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= total) return;
-    int c = (int)(q % C);
-    size_t v = q / C;
-    int x = (int)(v % n), y = (int)((v / n) % n), z = (int)((v / ((size_t)n * n)) % n), b = (int)(v / ((size_t)n * n * n));
-    gin[q] += gout[((((size_t)b * m + z / 2) * m + y / 2) * m + x / 2) * C + c] * 0.125f;
+    const int m = n / 2, c4 = C / 4;
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= (size_t)B * n * n * n * c4) return;
+    const size_t vq = q / c4;
+    const unsigned c = 4 * (unsigned)(q - vq * c4), v = (unsigned)vq, un = (unsigned)n;
+    const unsigned vy = v / un, vz = vy / un, b = vz / un, x = v - vy * un, y = vy - vz * un, z = vz - b * un;
+    const float4 gp =
+        *reinterpret_cast<const float4 *>(gpool + ((((size_t)b * m + z / 2) * m + y / 2) * m + x / 2) * C + c);
+    const float4 gs = *reinterpret_cast<const float4 *>(gskip + vq * C + c);
+    *reinterpret_cast<bf16x4 *>(out + vq * C + c) =
+        gate4(float4{gs.x + gp.x * 0.125f, gs.y + gp.y * 0.125f, gs.z + gp.z * 0.125f, gs.w + gp.w * 0.125f},
+              load4(act + vq * C + c));
 }
 
-// [up(lo) (C0), skip (C1)] at n = 2m
+// [up(lo) (C0), skip (C1)] at n = 2m; eight channels per thread
 __global__ void k_upcat(int B, int m, int C0, int C1, const bf16 *__restrict__ lo, const bf16 *__restrict__ skip,
                         bf16 *__restrict__ out)
 {
-    int n = 2 * m, C = C0 + C1;
-    size_t total = (size_t)B * n * n * n * C;
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= total) return;
-    int c = (int)(q % C);
-    size_t v = q / C;
-    if (c >= C0) {
-        out[q] = skip[v * C1 + (c - C0)];
-        return;
+    const int n = 2 * m, C = C0 + C1, c8 = C / 8;
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= (size_t)B * n * n * n * c8) return;
+    const size_t vq = q / c8;
+    const unsigned c = 8 * (unsigned)(q - vq * c8), v = (unsigned)vq, un = (unsigned)n;
+    const bf16 *src;
+    if (c >= (unsigned)C0) {
+        src = skip + vq * C1 + (c - C0);
+    } else {
+        const unsigned vy = v / un, vz = vy / un, b = vz / un, x = v - vy * un, y = vy - vz * un, z = vz - b * un;
+        src = lo + ((((size_t)b * m + z / 2) * m + y / 2) * m + x / 2) * C0 + c;
     }
-    int x = (int)(v % n), y = (int)((v / n) % n), z = (int)((v / ((size_t)n * n)) % n), b = (int)(v / ((size_t)n * n * n));
-    out[q] = lo[((((size_t)b * m + z / 2) * m + y / 2) * m + x / 2) * C0 + c];
+    *reinterpret_cast<uint4 *>(out + vq * C + c) = *reinterpret_cast<const uint4 *>(src);
 }
 
-// backward of k_upcat: glo[u][c] += sum of the 8 children; gskip[v][c] += g[v][C0 + c]
-__global__ void k_upcat_bwd_lo(int B, int m, int C0, int C1, const float *__restrict__ g, float *__restrict__ glo)
+// gradient entering the 3x3x3 layer whose output act (at m, [u][C]) was upsampled: the sum of
+// its eight children's gradients g (at n = 2m), masked by the ReLU, rounded to BF16.  Four
+// channels per thread.
+__global__ void k_up_bwd(int B, int m, int C, const float *__restrict__ g, const bf16 *__restrict__ act,
+                         bf16 *__restrict__ out)
 {
-    int n = 2 * m, C = C0 + C1;
-    size_t total = (size_t)B * m * m * m * C0;
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= total) return;
-    int c = (int)(q % C0);
-    size_t u = q / C0;
-    int x = (int)(u % m), y = (int)((u / m) % m), z = (int)((u / ((size_t)m * m)) % m), b = (int)(u / ((size_t)m * m * m));
-    float s = 0.f;
+    const int n = 2 * m, c4 = C / 4;
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= (size_t)B * m * m * m * c4) return;
+    const size_t uq = q / c4;
+    const unsigned c = 4 * (unsigned)(q - uq * c4), u = (unsigned)uq, um = (unsigned)m;
+    const unsigned uy = u / um, uz = uy / um, b = uz / um, x = u - uy * um, y = uy - uz * um, z = uz - b * um;
+    float4 ch[8];
+#pragma unroll
     for (int o = 0; o < 8; ++o) {
-        int zz = 2 * z + (o >> 2), yy = 2 * y + ((o >> 1) & 1), xx = 2 * x + (o & 1);
-        s += g[((((size_t)b * n + zz) * n + yy) * n + xx) * C + c];
+        const unsigned zz = 2 * z + (o >> 2), yy = 2 * y + ((o >> 1) & 1), xx = 2 * x + (o & 1);
+        ch[o] = *reinterpret_cast<const float4 *>(g + ((((size_t)b * n + zz) * n + yy) * n + xx) * C + c);
     }
-    glo[q] += s;
-}
-
-__global__ void k_upcat_bwd_skip(size_t V, int C0, int C1, const float *__restrict__ g, float *__restrict__ gskip)
-{
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= V * C1) return;
-    size_t v = q / C1;
-    int c = (int)(q % C1);
-    gskip[q] += g[v * (C0 + C1) + C0 + c];
-}
-
-__global__ void k_add(size_t n, const float *__restrict__ a, float *__restrict__ b)
-{
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) b[q] += a[q];
-}
-
-// gradient entering a 3x3x3 layer: ReLU mask of its output, rounded to BF16
-__global__ void k_relu_bwd(size_t n, const float *__restrict__ g, const bf16 *__restrict__ act, bf16 *__restrict__ out)
-{
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) out[q] = bf2f(act[q]) > 0.f ? f2bf(g[q]) : (bf16)0;
+    float4 s{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+        s.x += ch[o].x;
+        s.y += ch[o].y;
+        s.z += ch[o].z;
+        s.w += ch[o].w;
+    }
+    *reinterpret_cast<bf16x4 *>(out + uq * C + c) = gate4(s, load4(act + uq * C + c));
 }
 
 // head: p[v] = hb + sum_c hw[c] act[v][c]
@@ -513,11 +569,12 @@ __global__ void k_loss_final(int nb, const double *__restrict__ part, double *__
     out[1] = w;
 }
 
-// head backward: dp = 2 m (p - t) / sum m; gact[v][c] = dp hw[c]; partials of dhw, dhb
+// head backward: dp = 2 m (p - t) / sum m; the gradient entering the last 3x3x3 layer, dp hw[c]
+// masked by its ReLU and rounded to BF16; partials of dhw, dhb
 constexpr int HEAD_BLOCKS = 512;    // blocks of the head's backward reduction
 __global__ void k_head_bwd(int V, int C, const float *__restrict__ p, const float *__restrict__ t,
                            const float *__restrict__ mask, const double *__restrict__ lossw,
-                           const bf16 *__restrict__ act, const float *__restrict__ hw, float *__restrict__ gact,
+                           const bf16 *__restrict__ act, const float *__restrict__ hw, bf16 *__restrict__ gb,
                            float *__restrict__ part /*[gridDim][C+1]*/)
 {
     __shared__ float sh[256][17];
@@ -533,7 +590,7 @@ __global__ void k_head_bwd(int V, int C, const float *__restrict__ p, const floa
         for (int c = 0; c < 16; ++c) {
             if (c >= C) break;
             float a = bf2f(act[(size_t)v * C + c]);
-            gact[(size_t)v * C + c] = dp * hw[c];
+            gb[(size_t)v * C + c] = a > 0.f ? f2bf(dp * hw[c]) : (bf16)0;
             loc[c] += dp * a;
         }
         loc[16] += dp;
@@ -583,17 +640,26 @@ __global__ void k_adam(size_t n, float *__restrict__ w, const float *__restrict_
     w[q] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
 }
 
-// pack canonical W[co][ci][tap] (FP32) into BF16 Wk[co][tap][cip] and flipped Wf[ci][tap'][co]
-__global__ void k_pack_weights(int ci, int co, int cip, const float *__restrict__ W, bf16 *__restrict__ Wk,
-                               bf16 *__restrict__ Wf)
+// pack canonical W[co][ci][tap] (FP32) into BF16 Wk[co][tap][cip] and flipped Wf[ci][tap'][co],
+// all layers in one launch (blockIdx.y: the layer)
+struct PackLayer {
+    int ci, co, cip;
+    const float *W;
+    bf16 *Wk, *Wf;
+};
+struct PackList {
+    PackLayer l[NLAYER];
+};
+__global__ void k_pack_weights(PackList list)
 {
+    const PackLayer &L = list.l[blockIdx.y];
     int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= co * 27 * cip) return;
-    int c = q % cip, tap = (q / cip) % 27, o = q / (27 * cip);
-    float v = c < ci ? W[((size_t)o * ci + c) * 27 + tap] : 0.f;
+    if (q >= L.co * 27 * L.cip) return;
+    int c = q % L.cip, tap = (q / L.cip) % 27, o = q / (27 * L.cip);
+    float v = c < L.ci ? L.W[((size_t)o * L.ci + c) * 27 + tap] : 0.f;
     bf16 b = f2bf(v);
-    Wk[q] = b;
-    if (Wf && c < ci) Wf[((size_t)c * 27 + (26 - tap)) * co + o] = b;
+    L.Wk[q] = b;
+    if (L.Wf && c < L.ci) L.Wf[((size_t)c * 27 + (26 - tap)) * L.co + o] = b;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -747,15 +813,15 @@ struct cps_model {
     bf16 *Wk[NLAYER] = {}, *Wf[NLAYER] = {};
     bf16 *in[NLAYER] = {}, *out[NLAYER] = {};
     bool in_owned[NLAYER] = {};
-    float *gout[NLAYER] = {};
-    float *gtmp = nullptr;     // dgrad output (largest [V][ci])
-    bf16 *gb = nullptr;        // BF16 masked gradient (largest [V][co])
+    float *gskip[NLAYER] = {};  // gradient through the skip connections (layers 1, 3, 5), FP32
+    float *gtmp = nullptr;      // data gradient of a pooled or upsampled input, FP32
+    bf16 *gb = nullptr, *gb2 = nullptr;   // gradients entering two consecutive layers (BF16, masked)
     float *wpart = nullptr;    // weight-gradient chunk partials
     size_t wpart_n = 0;
     float *pred = nullptr, *tgt = nullptr, *msk = nullptr, *inp = nullptr;
     double *lpart = nullptr, *lossv = nullptr, *sig = nullptr;
     float *hpart = nullptr;
-    float *cpart = nullptr;    // bias-gradient column-sum partials (COLSUM_BLOCKS x channels)
+    float *cpart = nullptr;    // bias-gradient column-sum partials (COLSUM_PARTS x channels)
     int adam_t = 0;
     int device = 0;             // the device current at creation (its stream's device)
     std::vector<void *> allocs;
@@ -858,30 +924,26 @@ void layer_table(const int ch[4], int cin, LayerInfo L[NLAYER])
 
 int skip_of(int q) { return q == 8 ? 5 : (q == 10 ? 3 : 1); }
 
-template <int NG, int M>
-void launch_conv_as(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const float *bias,
-                    void *Y, bool fp32out)
+template <int NG, int M, int OUT>
+void launch_conv_as(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const ConvOut &O)
 {
     const TapRows tr = tap_rows(n, 64 * M);
     const size_t lds = 32 * ((size_t)tr.nseg * tr.seg + 9 * 16 * NG);
     const dim3 grid(nblk((size_t)V, 64 * M), Cout / 16 / NG);
-    if (fp32out)
-        k_conv3<NG, M, false, float><<<grid, 256, lds, m->stream>>>(n, V, Cin, Cout, tr, X, W, nullptr, (float *)Y);
-    else
-        k_conv3<NG, M, true, bf16><<<grid, 256, lds, m->stream>>>(n, V, Cin, Cout, tr, X, W, bias, (bf16 *)Y);
+    k_conv3<NG, M, OUT><<<grid, 256, lds, m->stream>>>(n, V, Cin, Cout, tr, X, W, O);
 }
 
 // Shape of the convolution's blocks: the widest of the listed ones (fewest LDS reads per
 // MFMA first) whose launch still has CONV_MIN_BLOCKS blocks; the narrowest otherwise.
 constexpr int CONV_MIN_BLOCKS = 512;
-void launch_conv(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const float *bias,
-                 void *Y, bool fp32out)
+template <int OUT>
+void launch_conv(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const ConvOut &O)
 {
     const int groups = Cout / 16;
     auto fits = [&](int NG, int M) {
         return groups % NG == 0 && (size_t)nblk((size_t)V, 64 * M) * (groups / NG) >= (size_t)CONV_MIN_BLOCKS;
     };
-#define CONV(NG, M) launch_conv_as<NG, M>(m, n, V, Cin, Cout, X, W, bias, Y, fp32out)
+#define CONV(NG, M) launch_conv_as<NG, M, OUT>(m, n, V, Cin, Cout, X, W, O)
     if (fits(3, 4)) CONV(3, 4);
     else if (fits(2, 4)) CONV(2, 4);
     else if (fits(3, 2)) CONV(3, 2);
@@ -912,11 +974,14 @@ void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int
 
 void repack(cps_model *m)
 {
+    PackList list;
+    size_t most = 0;
     for (int q = 0; q < NLAYER; ++q) {
         const LayerInfo &l = m->L[q];
-        k_pack_weights<<<nblk((size_t)l.co * 27 * l.cip), 256, 0, m->stream>>>(l.ci, l.co, l.cip, m->w + l.off, m->Wk[q],
-                                                                               q > 0 ? m->Wf[q] : nullptr);
+        list.l[q] = PackLayer{l.ci, l.co, l.cip, m->w + l.off, m->Wk[q], q > 0 ? m->Wf[q] : nullptr};
+        most = std::max(most, (size_t)l.co * 27 * l.cip);
     }
+    k_pack_weights<<<dim3(nblk(most), NLAYER), 256, 0, m->stream>>>(list);
 }
 
 void forward(cps_model *m, int B)
@@ -933,10 +998,13 @@ void forward(cps_model *m, int B)
             k_pool<<<nblk((size_t)V * l.cip), 256, 0, m->stream>>>(B, 2 * n, l.cip, m->out[q - 1], m->in[q]);
         } else if (q == 8 || q == 10 || q == 12) {
             int sk = skip_of(q);
-            k_upcat<<<nblk((size_t)V * l.cip), 256, 0, m->stream>>>(B, n / 2, m->L[q - 1].co, m->L[sk].co, m->out[q - 1],
-                                                                    m->out[sk], m->in[q]);
+            k_upcat<<<nblk((size_t)V * l.cip / 8), 256, 0, m->stream>>>(B, n / 2, m->L[q - 1].co, m->L[sk].co,
+                                                                        m->out[q - 1], m->out[sk], m->in[q]);
         }
-        launch_conv(m, n, V, l.cip, l.co, m->in[q], m->Wk[q], m->w + l.off + (long)l.co * l.ci * 27, m->out[q], false);
+        ConvOut O{};
+        O.bias = m->w + l.off + (long)l.co * l.ci * 27;
+        O.yb = m->out[q];
+        launch_conv<CONV_ACT>(m, n, V, l.cip, l.co, m->in[q], m->Wk[q], O);
     }
     k_head<<<nblk(V0), 256, 0, m->stream>>>(V0, m->L[NLAYER - 1].co, m->out[NLAYER - 1], m->w + m->head_off, m->pred);
 }
@@ -950,43 +1018,43 @@ void backward(cps_model *m, int B)
     const int nlb = 64;
     k_loss_partial<<<nlb, 256, 0, m->stream>>>(V0, m->pred, m->tgt, m->msk, m->lpart);
     k_loss_final<<<1, 64, 0, m->stream>>>(nlb, m->lpart, m->lossv);
-    for (int q = 0; q < NLAYER; ++q) {
-        const LayerInfo &l = m->L[q];
-        const int n = nc >> l.lvl;
-        nck(hipMemsetAsync(m->gout[q], 0, sizeof(float) * (size_t)B * n * n * n * l.co, m->stream));
-    }
     const int nhb = HEAD_BLOCKS;
     k_head_bwd<<<nhb, 256, 0, m->stream>>>(V0, C0, m->pred, m->tgt, m->msk, m->lossv, m->out[NLAYER - 1],
-                                           m->w + m->head_off, m->gout[NLAYER - 1], m->hpart);
+                                           m->w + m->head_off, m->gb, m->hpart);
     k_head_bwd_final<<<C0 + 1, 256, 0, m->stream>>>(nhb, C0, m->hpart, m->g + m->head_off);
-    for (int q = NLAYER - 1; q >= 0; --q) {
+    // gb: the gradient entering layer q (BF16, masked by its ReLU), made by the layer after it
+    bf16 *gb = m->gb, *gnext = m->gb2;
+    for (int q = NLAYER - 1; q >= 0; --q, std::swap(gb, gnext)) {
         const LayerInfo &l = m->L[q];
         const int n = nc >> l.lvl;
         const int V = B * n * n * n;
-        size_t nout = (size_t)V * l.co;
-        k_relu_bwd<<<nblk(nout), 256, 0, m->stream>>>(nout, m->gout[q], m->out[q], m->gb);
         // weight and bias gradients
         const int wchunk = wgrad_chunk(V), nchunk = (V + wchunk - 1) / wchunk;
-        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, m->gb, m->in[q]);
-        k_wgrad_reduce<<<nblk((size_t)l.co * l.ci * 27), 256, 0, m->stream>>>(nchunk, l.cip, l.co, l.ci, m->wpart,
-                                                                              m->g + l.off);
-        k_colsum_part<<<COLSUM_BLOCKS, 256, 0, m->stream>>>(V, l.co, m->gb, m->cpart);
-        k_colsum_final<<<l.co, 256, 0, m->stream>>>(COLSUM_BLOCKS, l.co, m->cpart,
-                                                                 m->g + l.off + (long)l.co * l.ci * 27);
+        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, gb, m->in[q]);
+        k_colsum_part<<<COLSUM_PARTS / 2, 64, 0, m->stream>>>(V, l.co, gb, m->cpart);
+        const int wblocks = (int)nblk((size_t)l.co * l.ci * 27);
+        k_grad_final<<<wblocks + l.co, 256, 0, m->stream>>>(wblocks, nchunk, l.cip, l.co, l.ci, m->wpart, m->cpart,
+                                                            m->g + l.off, m->g + l.off + (long)l.co * l.ci * 27);
         if (q == 0) break;
-        // data gradient into the producer of this layer's input
-        launch_conv(m, n, V, l.co, l.cip, m->gb, m->Wf[q], nullptr, m->gtmp, true);
+        // data gradient, turned into the gradient entering layer q - 1
+        ConvOut O{};
         if (q == 2 || q == 4 || q == 6) {
-            size_t nin = (size_t)B * (2 * n) * (2 * n) * (2 * n) * l.cip;
-            k_pool_bwd<<<nblk(nin), 256, 0, m->stream>>>(B, 2 * n, l.cip, m->gtmp, m->gout[q - 1]);
+            O.yf = m->gtmp;
+            launch_conv<CONV_F32>(m, n, V, l.co, l.cip, gb, m->Wf[q], O);
+            k_pool_bwd<<<nblk((size_t)V * 2 * l.cip), 256, 0, m->stream>>>(B, 2 * n, l.cip, m->gtmp, m->gskip[q - 1],
+                                                                           m->out[q - 1], gnext);
         } else if (q == 8 || q == 10 || q == 12) {
-            int sk = skip_of(q);
-            int C0u = m->L[q - 1].co, C1 = m->L[sk].co;
-            size_t nlo = (size_t)B * (n / 2) * (n / 2) * (n / 2) * C0u;
-            k_upcat_bwd_lo<<<nblk(nlo), 256, 0, m->stream>>>(B, n / 2, C0u, C1, m->gtmp, m->gout[q - 1]);
-            k_upcat_bwd_skip<<<nblk((size_t)V * C1), 256, 0, m->stream>>>((size_t)V, C0u, C1, m->gtmp, m->gout[sk]);
+            // input channels: the upsampled output of layer q - 1, then the skip connection's
+            const int C0u = m->L[q - 1].co;
+            O.yf = m->gtmp;
+            O.yf2 = m->gskip[skip_of(q)];
+            O.c_lo = C0u;
+            launch_conv<CONV_SPLIT>(m, n, V, l.co, l.cip, gb, m->Wf[q], O);
+            k_up_bwd<<<nblk((size_t)V / 8 * C0u / 4), 256, 0, m->stream>>>(B, n / 2, C0u, m->gtmp, m->out[q - 1], gnext);
         } else {
-            k_add<<<nblk((size_t)V * l.ci), 256, 0, m->stream>>>((size_t)V * l.ci, m->gtmp, m->gout[q - 1]);
+            O.gate = m->out[q - 1];
+            O.yb = gnext;
+            launch_conv<CONV_GATE>(m, n, V, l.co, l.cip, gb, m->Wf[q], O);
         }
     }
 }
@@ -1041,8 +1109,9 @@ int cps_model_create(cps_model **out, const cps_model_spec *spec, void *stream)
             m->Wk[q] = nalloc<bf16>(m, (size_t)l.co * 27 * l.cip);
             if (q > 0) m->Wf[q] = nalloc<bf16>(m, (size_t)l.cip * 27 * l.co);
             m->out[q] = nalloc<bf16>(m, V * l.co);
-            m->gout[q] = nalloc<float>(m, V * l.co);
-            maxci = std::max(maxci, V * l.cip);
+            if (q == 1 || q == 3 || q == 5) m->gskip[q] = nalloc<float>(m, V * l.co);
+            if (q == 2 || q == 4 || q == 6) maxci = std::max(maxci, V * l.cip);
+            if (q == 8 || q == 10 || q == 12) maxci = std::max(maxci, V * m->L[q - 1].co);
             maxco = std::max(maxco, V * l.co);
             // the chunk count for every batch size up to B (the chunk size depends on V)
             for (int bb = 1; bb <= B; ++bb) {
@@ -1064,6 +1133,7 @@ int cps_model_create(cps_model **out, const cps_model_spec *spec, void *stream)
         }
         m->gtmp = nalloc<float>(m, maxci);
         m->gb = nalloc<bf16>(m, maxco);
+        m->gb2 = nalloc<bf16>(m, maxco);
         m->wpart = nalloc<float>(m, m->wpart_n);
         const size_t V0 = (size_t)B * nc * nc * nc;
         m->pred = nalloc<float>(m, V0);
@@ -1074,7 +1144,7 @@ int cps_model_create(cps_model **out, const cps_model_spec *spec, void *stream)
         m->lossv = nalloc<double>(m, 2);
         m->sig = nalloc<double>(m, 1);
         m->hpart = nalloc<float>(m, HEAD_BLOCKS * 17);
-        m->cpart = nalloc<float>(m, (size_t)COLSUM_BLOCKS * 64);   // channels are at most 64
+        m->cpart = nalloc<float>(m, (size_t)COLSUM_PARTS * 64);   // channels are at most 64
         // He-normal initialisation from the spec's seed (host, deterministic)
         std::vector<float> h(m->nparam, 0.f);
         uint64_t st = spec->seed * 6364136223846793005ULL + 1442695040888963407ULL;
