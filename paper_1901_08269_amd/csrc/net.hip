@@ -49,6 +49,21 @@ __device__ __forceinline__ bf16x4 load4(const bf16 *p)
 // ---------------------------------------------------------------------------------------
 // 3x3x3 convolution (zero padding): Y[v][co] = act(bias[co] + sum_{tap,ci} W[co][tap][ci] X[v+tap][ci])
 // ---------------------------------------------------------------------------------------
+// Work items (run, part) in one grid of NXCD x per x parts blocks: the blocks of one XCD
+// (consecutive ones go to the eight XCDs in turn) take a contiguous range of runs, all parts
+// of a run one after another, so that the rows that neighbouring runs and the parts of one
+// run share are read into that XCD's L2 once.
+struct RunPart {
+    int run, part;
+};
+inline unsigned run_blocks(size_t runs, int parts) { return (unsigned)((runs + cps::NXCD - 1) / cps::NXCD * cps::NXCD * parts); }
+__device__ __forceinline__ RunPart run_of_block(int runs, int parts)
+{
+    const int per = (runs + cps::NXCD - 1) / cps::NXCD, k = (int)blockIdx.x / cps::NXCD;
+    const int r = k / parts;
+    return RunPart{((int)blockIdx.x % cps::NXCD) * per + r, k - r * parts};
+}
+
 // Rows of 16 channels staged in LDS for a run of voxels [v, v + len) and its tap neighbours of
 // one z-offset: tap (dy, dx) of the run's l-th voxel is row l + dy * dys + dx.  One contiguous
 // range of len + 2 n + 2 voxels holds all nine (dys = n); where 2 n + 2 rows more than the
@@ -102,18 +117,33 @@ struct ConvOut {
 // voxel groups.  Taps outside the grid are zeroed by the voxel's tap mask (one voxel per
 // thread, exchanged through LDS: index divisions are what a block would otherwise spend most
 // of its vector instructions on).  Per MFMA the kernel reads 1 / NG + 1 / M operands from LDS.
+// In LDS the four 4-channel quarters of the rows lie in planes of their own (quarter q of row r
+// at 8 (q pitch + r) bytes): the lanes of an operand read, 16 rows by four quarters, then cover
+// whole runs of banks, where rows of 32 bytes had put eight rows on the same banks (70 % of the
+// LDS cycles were conflicts).
 // Measured at 64^3, batch 8, all 27 convolutions of a training step: 5.75 ms with the operands
-// of every 16 voxels loaded from memory, CONV_MS ms here.
+// of every 16 voxels loaded from memory, 2.39 ms with staged 32-byte rows, 1.35 ms here.
+__host__ __device__ __forceinline__ constexpr int quarter_pitch(int rows) { return ((rows + 15) & ~31) + 16; }   // 16 mod 32, >= rows
+__device__ __forceinline__ void put_row_half(uint2 *p, int pitch, int h, uint4 v)
+{
+    uint2 *d = p + 2 * (h & 1) * pitch + (h >> 1);
+    d[0] = uint2{v.x, v.y};
+    d[pitch] = uint2{v.z, v.w};
+}
 template <int NG, int M, int OUT>
 __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, TapRows tr, const bf16 *__restrict__ X,
                                                const bf16 *__restrict__ Wk, ConvOut O)
 {
     extern __shared__ uint4 lds[];
     __shared__ unsigned masks[64 * M];
-    uint4 *ws = lds + 2 * tr.nseg * tr.seg;                   // [9][16 NG] rows of 16 weights
+    constexpr int WP = quarter_pitch(9 * 16 * NG);
+    const int xp = quarter_pitch(tr.nseg * tr.seg);
+    uint2 *xs = reinterpret_cast<uint2 *>(lds), *ws = xs + 4 * xp;     // ws: [9][16 NG] rows of 16 weights
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int row = lane & 15, kq = lane >> 4;
-    const int vb = blockIdx.x * (64 * M), g0 = blockIdx.y * NG;
+    const RunPart rp = run_of_block((V + 64 * M - 1) / (64 * M), Cout / 16 / NG);
+    const int vb = rp.run * (64 * M), g0 = rp.part * NG;
+    if (vb >= V) return;
     if (tid < 64 * M) {
         // bit t: tap t of voxel vb + tid lies in the grid
         const unsigned un = (unsigned)n, v = (unsigned)(vb + tid), vy = v / un, vz = vy / un;
@@ -127,28 +157,72 @@ __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, 
     for (int q = 0; q < M; ++q)
 #pragma unroll
         for (int g = 0; g < NG; ++g) acc[q][g] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16 *xw = reinterpret_cast<const bf16 *>(lds) + (16 * M * wv + row) * 16 + 4 * kq;
-    const bf16 *ww = reinterpret_cast<const bf16 *>(ws) + row * 16 + 4 * kq;
-    for (int tz = 0; tz < 3; ++tz)
-        for (int c0 = 0; c0 < Cin; c0 += 16) {
-            stage_taps(tr, n, V, vb, tz, Cin, c0, X, lds, tid, 256);
-            const bf16 *wsrc = Wk + ((size_t)16 * g0 * 27 + tz * 9) * Cin + c0;
-            for (int h = tid; h < 9 * 32 * NG; h += 256) {
-                const int t9 = h / (32 * NG), co = (h >> 1) % (16 * NG);
-                ws[h] = *reinterpret_cast<const uint4 *>(wsrc + (unsigned)((co * 27 + t9) * Cin + 8 * (h & 1)));
-            }
-            __syncthreads();
+    const uint2 *xw = xs + kq * xp + 16 * M * wv + row, *ww = ws + kq * WP + row;
+    // slice sl = (tz, c0).  With few voxels per block (M < 4: the coarse levels, whose launches
+    // do not fill the GPU and wait out each slice's loads) its rows and weights are loaded into
+    // registers while the slice before it is computed: 15 -> 9 us for M = 1.  With M = 4 the
+    // registers cost more blocks in flight than that gains (119 -> 137 us).
+    constexpr bool AHEAD = M < 4;
+    constexpr int NX = AHEAD ? (6 * (64 * M + 2) + 255) / 256 : 1, NW = AHEAD ? (9 * 32 * NG + 255) / 256 : 1;
+    const int nh = 2 * tr.nseg * tr.seg, nsl = 3 * (Cin / 16);
+    // half h & 1 of row h >> 1 of the slice's rows of X, of its rows of weights
+    auto x_half = [&](int tz, int c0, int h) {
+        int u = vb + (tz - 1) * n * n - (tr.nseg == 1 ? n : 0) - 1 + (h >> 1);
+        if (tr.nseg == 3) {                                    // ranges of one dy each
+            const int q = (h >= 2 * tr.seg) + (h >= 4 * tr.seg);
+            u += (q - 1) * n - q * tr.seg;
+        }
+        uint4 v{0u, 0u, 0u, 0u};
+        if (h < nh && (unsigned)u < (unsigned)V)
+            v = *reinterpret_cast<const uint4 *>(X + (size_t)(unsigned)u * Cin + c0 + 8 * (h & 1));
+        return v;
+    };
+    auto w_half = [&](int tz, int c0, int h) {
+        const int t9 = h / (32 * NG), co = (h >> 1) % (16 * NG);
+        const bf16 *wsrc = Wk + ((size_t)16 * g0 * 27 + tz * 9) * Cin + c0;
+        return *reinterpret_cast<const uint4 *>(wsrc + (unsigned)((co * 27 + t9) * Cin + 8 * (h & 1)));
+    };
+    uint4 xr[NX], wr[NW];
+    auto fetch = [&](int tz, int c0) {
+#pragma unroll
+        for (int k = 0; k < NX; ++k) xr[k] = x_half(tz, c0, tid + 256 * k);
+#pragma unroll
+        for (int k = 0; k < NW; ++k) wr[k] = w_half(tz, c0, min(tid + 256 * k, 9 * 32 * NG - 1));
+    };
+    if (AHEAD) fetch(0, 0);
+    int tz = 0, c0 = 0;
+    for (int sl = 0; sl < nsl; ++sl) {
+        if (AHEAD) {
+#pragma unroll
+            for (int k = 0; k < NX; ++k)
+                if (tid + 256 * k < nh) put_row_half(xs, xp, tid + 256 * k, xr[k]);
+#pragma unroll
+            for (int k = 0; k < NW; ++k)
+                if (tid + 256 * k < 9 * 32 * NG) put_row_half(ws, WP, tid + 256 * k, wr[k]);
+        } else {
+            for (int h = tid; h < nh; h += 256) put_row_half(xs, xp, h, x_half(tz, c0, h));
+            for (int h = tid; h < 9 * 32 * NG; h += 256) put_row_half(ws, WP, h, w_half(tz, c0, h));
+        }
+        __syncthreads();
+        const int tz_now = tz;
+        c0 += 16;
+        if (c0 == Cin) {
+            c0 = 0;
+            ++tz;
+        }
+        if (AHEAD && sl + 1 < nsl) fetch(tz, c0);
+        {
             bf16x4 w[9][NG];
 #pragma unroll
             for (int t9 = 0; t9 < 9; ++t9)
 #pragma unroll
-                for (int g = 0; g < NG; ++g) w[t9][g] = load4(ww + (t9 * NG + g) * 256);
+                for (int g = 0; g < NG; ++g) w[t9][g] = __builtin_bit_cast(bf16x4, ww[(t9 * NG + g) * 16]);
 #pragma unroll
             for (int q = 0; q < M; ++q) {
-                const int vm = (int)(masks[16 * (M * wv + q) + row] >> (9 * tz));
+                const int vm = (int)(masks[16 * (M * wv + q) + row] >> (9 * tz_now));
 #pragma unroll
                 for (int t9 = 0; t9 < 9; ++t9) {
-                    uint2 a = *reinterpret_cast<const uint2 *>(xw + (16 * q + (t9 / 3) * tr.dys + t9 % 3) * 16);
+                    uint2 a = xw[16 * q + (t9 / 3) * tr.dys + t9 % 3];
                     const unsigned k = (unsigned)((vm << (31 - t9)) >> 31);
                     a.x &= k;
                     a.y &= k;
@@ -158,8 +232,9 @@ __global__ void __launch_bounds__(256) k_conv3(int n, int V, int Cin, int Cout, 
                                                                               acc[q][g], 0, 0, 0);
                 }
             }
-            __syncthreads();
         }
+        __syncthreads();
+    }
     // D[voxel 4 kq + i][co = row]
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -217,8 +292,8 @@ __device__ __forceinline__ bf16x4 mask4(bf16x4 a, uint2 k)
 }
 
 // A block takes one chunk of voxels and, of the 16 x 16 output tiles (co, ci), either all
-// those of one ci group (blockIdx.y; a wave per co group and dz) or, for layers with fewer
-// than four tiles (SPLIT: the 16-channel layers on the largest grids), the tile blockIdx.y,
+// those of one ci group (a wave per co group and dz) or, for layers with fewer
+// than four tiles (SPLIT: the 16-channel layers on the largest grids), one tile,
 // whose 16-voxel steps go round four waves per dz; the four sums are added in wave order.
 // A wave holds the nine taps of its dz (36 accumulator registers).  WG_VS voxels of G and the
 // rows of X that their 27 taps reach are staged at a time; both MFMA operands are K-major
@@ -227,9 +302,9 @@ __device__ __forceinline__ bf16x4 mask4(bf16x4 a, uint2 k)
 // rows serve every tap.  The kernel is bound by LDS reads: 15 (9 of X, 1 of G, 5 masks) for
 // nine MFMAs.
 // Measured at 64^3, batch 8: 734 us per layer on average for the version that staged X once
-// per tap and gathered its operands by 2-byte LDS reads, 110 us for this one (10.3 -> 1.54 ms of a training step).
+// per tap and gathered its operands by 2-byte LDS reads, 83 us for this one (10.3 -> 1.16 ms of a training step).
 template <bool SPLIT>
-__global__ void __launch_bounds__(768) k_wgrad(int n, int V, int Cin, int Cout, int wchunk, TapRows tr,
+__global__ void __launch_bounds__(768, SPLIT ? 6 : 1) k_wgrad(int n, int V, int Cin, int Cout, int wchunk, TapRows tr,
                                                const bf16 *__restrict__ G, const bf16 *__restrict__ X,
                                                float *__restrict__ P)
 {
@@ -240,8 +315,10 @@ __global__ void __launch_bounds__(768) k_wgrad(int n, int V, int Cin, int Cout, 
     uint16_t *mk = reinterpret_cast<uint16_t *>(gs + 2 * tco * WG_VS);   // [6][WG_VS]
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     const int m = lane & 15, kq = lane >> 4;
-    const int chunk = blockIdx.x, cig = SPLIT ? blockIdx.y % tci : blockIdx.y;
-    const int cog0 = SPLIT ? blockIdx.y / tci : 0;             // first co group of the block
+    const RunPart rp = run_of_block((V + wchunk - 1) / wchunk, SPLIT ? tci * (Cout / 16) : tci);
+    const int chunk = rp.run, cig = SPLIT ? rp.part % tci : rp.part;
+    const int cog0 = SPLIT ? rp.part / tci : 0;                // first co group of the block
+    if (chunk * (long)wchunk >= V) return;
     const int wz = wv % 3, wq = wv / 3;                        // the wave's dz; co group or step residue
     const bf16 *xw = reinterpret_cast<const bf16 *>(xs + 2 * wz * zrows);
     const bf16 *gw = reinterpret_cast<const bf16 *>(gs + (SPLIT ? 0 : 2 * wq * WG_VS));
@@ -259,8 +336,14 @@ __global__ void __launch_bounds__(768) k_wgrad(int n, int V, int Cin, int Cout, 
                 val = *reinterpret_cast<const uint4 *>(G + (size_t)v * Cout + 16 * (cog0 + g) + 8 * (h & 1));
             gs[h] = val;
         }
+        // x, y, z of the stage's voxels from those of its first one: the quotients are of numbers
+        // below n + WG_VS, exact in FP32 with the half added
+        const float inv = 1.f / (float)n;
+        const int vx0 = vs % n, vy0 = (vs / n) % n, vz0 = (vs / (n * n)) % n;
         for (int r = tid; r < WG_VS; r += nt) {
-            const int v = vs + r, x = v % n, y = (v / n) % n, z = (v / (n * n)) % n;
+            const int qx = (int)(((float)(vx0 + r) + 0.5f) * inv), x = vx0 + r - qx * n;
+            const int qy = (int)(((float)(vy0 + qx) + 0.5f) * inv), y = vy0 + qx - qy * n;
+            const int qz = (int)(((float)(vz0 + qy) + 0.5f) * inv), z = vz0 + qy - qz * n;
             mk[0 * WG_VS + r] = x > 0 ? 0xFFFFu : 0u;
             mk[1 * WG_VS + r] = x < n - 1 ? 0xFFFFu : 0u;
             mk[2 * WG_VS + r] = y > 0 ? 0xFFFFu : 0u;
@@ -345,7 +428,7 @@ __device__ __forceinline__ void wgrad_reduce(int nchunk, int Cin, int Cout, int 
 // part's lanes are added per channel in lane order.  A thread takes eight channels of one lane
 // (16-byte loads, eight of them in flight), a wavefront two parts.  Pass 2 (k_grad_final) adds
 // the part sums.  (One channel per thread and 2-byte loads took 27 us per layer at 64^3, batch
-// 8, this COLSUM_US us.)
+// 8, this 9 us.)
 constexpr int COLSUM_PARTS = 512;
 __global__ void __launch_bounds__(64) k_colsum_part(int V, int C, const bf16 *__restrict__ G, float *__restrict__ part)
 {
@@ -413,6 +496,26 @@ __global__ void __launch_bounds__(256) k_grad_final(int wblocks, int nchunk, int
 // ---------------------------------------------------------------------------------------
 // elementwise pieces
 // ---------------------------------------------------------------------------------------
+// the 16 channels of a voxel as two 16-byte accesses
+__device__ __forceinline__ void load16(const bf16 *p, bf16 (&o)[16])
+{
+    const uint4 a = reinterpret_cast<const uint4 *>(p)[0], b = reinterpret_cast<const uint4 *>(p)[1];
+    const unsigned w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        o[2 * j] = (bf16)(w[j] & 0xFFFFu);
+        o[2 * j + 1] = (bf16)(w[j] >> 16);
+    }
+}
+__device__ __forceinline__ void store16(bf16 *p, const bf16 (&o)[16])
+{
+    unsigned w[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w[j] = (unsigned)o[2 * j] | (unsigned)o[2 * j + 1] << 16;
+    reinterpret_cast<uint4 *>(p)[0] = uint4{w[0], w[1], w[2], w[3]};
+    reinterpret_cast<uint4 *>(p)[1] = uint4{w[4], w[5], w[6], w[7]};
+}
+
 // g rounded to BF16 where the activation is positive (ReLU's gradient), 0 elsewhere
 __device__ __forceinline__ bf16x4 gate4(float4 g, bf16x4 act)
 {
@@ -424,13 +527,16 @@ __device__ __forceinline__ bf16x4 gate4(float4 g, bf16x4 act)
 }
 
 // input [B][cin][n^3] (FP32, channels first) -> [V][16] BF16, channels >= cin zero
+// (one voxel per thread)
 __global__ void k_pack_input(int V, int n3, int cin, const float *__restrict__ in, bf16 *__restrict__ out)
 {
-    int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= V * 16) return;
-    int v = q >> 4, c = q & 15;
-    int b = v / n3, r = v - b * n3;
-    out[q] = c < cin ? f2bf(in[((size_t)b * cin + c) * n3 + r]) : (bf16)0;
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= V) return;
+    const int b = v / n3, r = v - b * n3;
+    bf16 o[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) o[c] = c < cin ? f2bf(in[((size_t)b * cin + c) * n3 + r]) : (bf16)0;
+    store16(out + (size_t)v * 16, o);
 }
 
 // 2x2x2 average pooling, [V][C] at n -> [V/8][C] at n/2
@@ -519,13 +625,17 @@ __global__ void k_up_bwd(int B, int m, int C, const float *__restrict__ g, const
     *reinterpret_cast<bf16x4 *>(out + uq * C + c) = gate4(s, load4(act + uq * C + c));
 }
 
-// head: p[v] = hb + sum_c hw[c] act[v][c]
-__global__ void k_head(int V, int C, const bf16 *__restrict__ act, const float *__restrict__ hw, float *__restrict__ p)
+// head: p[v] = hb + sum_c hw[c] act[v][c], HEAD_C channels
+constexpr int HEAD_C = 16;
+__global__ void k_head(int V, const bf16 *__restrict__ act, const float *__restrict__ hw, float *__restrict__ p)
 {
     int v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= V) return;
-    float s = hw[C];
-    for (int c = 0; c < C; ++c) s += hw[c] * bf2f(act[(size_t)v * C + c]);
+    bf16 a[HEAD_C];
+    load16(act + (size_t)v * HEAD_C, a);
+    float s = hw[HEAD_C];
+#pragma unroll
+    for (int c = 0; c < HEAD_C; ++c) s += hw[c] * bf2f(a[c]);
     p[v] = s;
 }
 
@@ -557,56 +667,64 @@ __global__ void k_loss_partial(int V, const float *__restrict__ p, const float *
     }
 }
 
-__global__ void k_loss_final(int nb, const double *__restrict__ part, double *__restrict__ out)
+constexpr int LOSS_BLOCKS = 256;
+__global__ void __launch_bounds__(LOSS_BLOCKS) k_loss_final(const double *__restrict__ part, double *__restrict__ out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double a = 0.0, w = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        a += part[2 * b];
-        w += part[2 * b + 1];
+    __shared__ double s0[LOSS_BLOCKS], s1[LOSS_BLOCKS];
+    const int t = (int)threadIdx.x;
+    s0[t] = part[2 * t];
+    s1[t] = part[2 * t + 1];
+    __syncthreads();
+    for (int o = LOSS_BLOCKS / 2; o > 0; o >>= 1) {
+        if (t < o) {
+            s0[t] += s0[t + o];
+            s1[t] += s1[t + o];
+        }
+        __syncthreads();
     }
-    out[0] = a / w;
-    out[1] = w;
+    if (t == 0) {
+        out[0] = s0[0] / s1[0];
+        out[1] = s1[0];
+    }
 }
 
 // head backward: dp = 2 m (p - t) / sum m; the gradient entering the last 3x3x3 layer, dp hw[c]
 // masked by its ReLU and rounded to BF16; partials of dhw, dhb
 constexpr int HEAD_BLOCKS = 512;    // blocks of the head's backward reduction
-__global__ void k_head_bwd(int V, int C, const float *__restrict__ p, const float *__restrict__ t,
-                           const float *__restrict__ mask, const double *__restrict__ lossw,
-                           const bf16 *__restrict__ act, const float *__restrict__ hw, bf16 *__restrict__ gb,
-                           float *__restrict__ part /*[gridDim][C+1]*/)
+__global__ void __launch_bounds__(256) k_head_bwd(int V, const float *__restrict__ p, const float *__restrict__ t,
+                                                  const float *__restrict__ mask, const double *__restrict__ lossw,
+                                                  const bf16 *__restrict__ act, const float *__restrict__ hw,
+                                                  bf16 *__restrict__ gb, float *__restrict__ part /*[gridDim][17]*/)
 {
-    __shared__ float sh[256][17];
+    constexpr int C = HEAD_C;
+    __shared__ float sh[256][C + 1];
     const double inv = 1.0 / lossw[1];
-    // C <= 16: the channel loops run over 16 with a guard, so that loc stays in registers
-    float loc[17];
+    float loc[C + 1];
 #pragma unroll
-    for (int c = 0; c < 17; ++c) loc[c] = 0.f;
+    for (int c = 0; c <= C; ++c) loc[c] = 0.f;
     for (int v = blockIdx.x * 256 + threadIdx.x; v < V; v += gridDim.x * 256) {
         float m = mask ? mask[v] : 1.f;
         float dp = (float)(2.0 * m * ((double)p[v] - (double)t[v]) * inv);
+        bf16 a[C], o[C];
+        load16(act + (size_t)v * C, a);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            if (c >= C) break;
-            float a = bf2f(act[(size_t)v * C + c]);
-            gb[(size_t)v * C + c] = a > 0.f ? f2bf(dp * hw[c]) : (bf16)0;
-            loc[c] += dp * a;
+        for (int c = 0; c < C; ++c) {
+            const float av = bf2f(a[c]);
+            o[c] = av > 0.f ? f2bf(dp * hw[c]) : (bf16)0;
+            loc[c] += dp * av;
         }
-        loc[16] += dp;
+        store16(gb + (size_t)v * C, o);
+        loc[C] += dp;
     }
 #pragma unroll
-    for (int c = 0; c < 16; ++c)
-        if (c < C) sh[threadIdx.x][c] = loc[c];
-    sh[threadIdx.x][C] = loc[16];
+    for (int c = 0; c <= C; ++c) sh[threadIdx.x][c] = loc[c];
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o)
             for (int c = 0; c <= C; ++c) sh[threadIdx.x][c] += sh[threadIdx.x + o][c];
         __syncthreads();
     }
-    if (threadIdx.x == 0)
-        for (int c = 0; c <= C; ++c) part[(size_t)blockIdx.x * (C + 1) + c] = sh[0][c];
+    if (threadIdx.x <= C) part[(size_t)blockIdx.x * (C + 1) + threadIdx.x] = sh[0][threadIdx.x];
 }
 
 // one block per output (C weights and the bias): partials t, t + 256, ... then a tree
@@ -818,7 +936,7 @@ struct cps_model {
     bf16 *gb = nullptr, *gb2 = nullptr;   // gradients entering two consecutive layers (BF16, masked)
     float *wpart = nullptr;    // weight-gradient chunk partials
     size_t wpart_n = 0;
-    float *pred = nullptr, *tgt = nullptr, *msk = nullptr, *inp = nullptr;
+    float *pred = nullptr, *inp = nullptr;
     double *lpart = nullptr, *lossv = nullptr, *sig = nullptr;
     float *hpart = nullptr;
     float *cpart = nullptr;    // bias-gradient column-sum partials (COLSUM_PARTS x channels)
@@ -928,8 +1046,8 @@ template <int NG, int M, int OUT>
 void launch_conv_as(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, const bf16 *W, const ConvOut &O)
 {
     const TapRows tr = tap_rows(n, 64 * M);
-    const size_t lds = 32 * ((size_t)tr.nseg * tr.seg + 9 * 16 * NG);
-    const dim3 grid(nblk((size_t)V, 64 * M), Cout / 16 / NG);
+    const size_t lds = 32 * ((size_t)quarter_pitch(tr.nseg * tr.seg) + quarter_pitch(9 * 16 * NG));
+    const unsigned grid = run_blocks(nblk((size_t)V, 64 * M), Cout / 16 / NG);
     k_conv3<NG, M, OUT><<<grid, 256, lds, m->stream>>>(n, V, Cin, Cout, tr, X, W, O);
 }
 
@@ -967,9 +1085,9 @@ void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int
     // more than 64 KB of LDS (grids of more than about 128 cells per axis) has to be asked for
     if (lds > 65536) nck(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (split)
-        k_wgrad<true><<<dim3(nchunk, tco * tci), 768, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
+        k_wgrad<true><<<run_blocks(nchunk, tco * tci), 768, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
     else
-        k_wgrad<false><<<dim3(nchunk, tci), 192 * tco, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
+        k_wgrad<false><<<run_blocks(nchunk, tci), 192 * tco, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
 }
 
 void repack(cps_model *m)
@@ -984,12 +1102,13 @@ void repack(cps_model *m)
     k_pack_weights<<<dim3(nblk(most), NLAYER), 256, 0, m->stream>>>(list);
 }
 
-void forward(cps_model *m, int B)
+// pred = network(inp); inp, pred: device arrays of the caller's or the model's own
+void forward(cps_model *m, int B, const float *inp, float *pred)
 {
     const int nc = m->spec.nc;
     const int cin = m->spec.in_ch;
     int V0 = B * nc * nc * nc;
-    k_pack_input<<<nblk((size_t)V0 * 16), 256, 0, m->stream>>>(V0, nc * nc * nc, cin, m->inp, m->in[0]);
+    k_pack_input<<<nblk((size_t)V0), 256, 0, m->stream>>>(V0, nc * nc * nc, cin, inp, m->in[0]);
     for (int q = 0; q < NLAYER; ++q) {
         const LayerInfo &l = m->L[q];
         const int n = nc >> l.lvl;
@@ -1006,22 +1125,21 @@ void forward(cps_model *m, int B)
         O.yb = m->out[q];
         launch_conv<CONV_ACT>(m, n, V, l.cip, l.co, m->in[q], m->Wk[q], O);
     }
-    k_head<<<nblk(V0), 256, 0, m->stream>>>(V0, m->L[NLAYER - 1].co, m->out[NLAYER - 1], m->w + m->head_off, m->pred);
+    k_head<<<nblk(V0), 256, 0, m->stream>>>(V0, m->out[NLAYER - 1], m->w + m->head_off, pred);
 }
 
-void backward(cps_model *m, int B)
+// after forward(m, B, ., m->pred)
+void backward(cps_model *m, int B, const float *tgt, const float *msk)
 {
     const int nc = m->spec.nc;
     const int V0 = B * nc * nc * nc;
-    const int C0 = m->L[NLAYER - 1].co;
     // loss
-    const int nlb = 64;
-    k_loss_partial<<<nlb, 256, 0, m->stream>>>(V0, m->pred, m->tgt, m->msk, m->lpart);
-    k_loss_final<<<1, 64, 0, m->stream>>>(nlb, m->lpart, m->lossv);
+    k_loss_partial<<<LOSS_BLOCKS, 256, 0, m->stream>>>(V0, m->pred, tgt, msk, m->lpart);
+    k_loss_final<<<1, LOSS_BLOCKS, 0, m->stream>>>(m->lpart, m->lossv);
     const int nhb = HEAD_BLOCKS;
-    k_head_bwd<<<nhb, 256, 0, m->stream>>>(V0, C0, m->pred, m->tgt, m->msk, m->lossv, m->out[NLAYER - 1],
-                                           m->w + m->head_off, m->gb, m->hpart);
-    k_head_bwd_final<<<C0 + 1, 256, 0, m->stream>>>(nhb, C0, m->hpart, m->g + m->head_off);
+    k_head_bwd<<<nhb, 256, 0, m->stream>>>(V0, m->pred, tgt, msk, m->lossv, m->out[NLAYER - 1], m->w + m->head_off,
+                                           m->gb, m->hpart);
+    k_head_bwd_final<<<HEAD_C + 1, 256, 0, m->stream>>>(nhb, HEAD_C, m->hpart, m->g + m->head_off);
     // gb: the gradient entering layer q (BF16, masked by its ReLU), made by the layer after it
     bf16 *gb = m->gb, *gnext = m->gb2;
     for (int q = NLAYER - 1; q >= 0; --q, std::swap(gb, gnext)) {
@@ -1137,10 +1255,8 @@ int cps_model_create(cps_model **out, const cps_model_spec *spec, void *stream)
         m->wpart = nalloc<float>(m, m->wpart_n);
         const size_t V0 = (size_t)B * nc * nc * nc;
         m->pred = nalloc<float>(m, V0);
-        m->tgt = nalloc<float>(m, V0);
-        m->msk = nalloc<float>(m, V0);
-        m->inp = nalloc<float>(m, V0 * spec->in_ch);
-        m->lpart = nalloc<double>(m, 256);
+        m->inp = nalloc<float>(m, (size_t)nc * nc * nc * spec->in_ch);   // one restricted problem
+        m->lpart = nalloc<double>(m, std::max(2 * LOSS_BLOCKS, SCALE_BLOCKS));
         m->lossv = nalloc<double>(m, 2);
         m->sig = nalloc<double>(m, 1);
         m->hpart = nalloc<float>(m, HEAD_BLOCKS * 17);
@@ -1204,10 +1320,8 @@ int cps_model_forward(cps_model *m, const float *inputs, int32_t batch, float *p
 {
     if (!m || !inputs || !pred || batch < 1 || batch > m->spec.batch) return CPS_EINVAL;
     try {
-        const size_t V0 = (size_t)batch * m->spec.nc * m->spec.nc * m->spec.nc;
-        nck(hipMemcpyAsync(m->inp, inputs, sizeof(float) * V0 * m->spec.in_ch, hipMemcpyDeviceToDevice, m->stream));
-        forward(m, batch);
-        nck(hipMemcpyAsync(pred, m->pred, sizeof(float) * V0, hipMemcpyDeviceToDevice, m->stream));
+        forward(m, batch, inputs, pred);
+        nck(hipGetLastError());
         nck(hipStreamSynchronize(m->stream));
     } catch (NetFail &f) {
         return f.code;
@@ -1220,15 +1334,8 @@ int cps_model_train_step(cps_model *m, const float *inputs, const float *target,
 {
     if (!m || !inputs || !target || batch < 1 || batch > m->spec.batch) return CPS_EINVAL;
     try {
-        const size_t V0 = (size_t)batch * m->spec.nc * m->spec.nc * m->spec.nc;
-        nck(hipMemcpyAsync(m->inp, inputs, sizeof(float) * V0 * m->spec.in_ch, hipMemcpyDeviceToDevice, m->stream));
-        nck(hipMemcpyAsync(m->tgt, target, sizeof(float) * V0, hipMemcpyDeviceToDevice, m->stream));
-        if (mask) nck(hipMemcpyAsync(m->msk, mask, sizeof(float) * V0, hipMemcpyDeviceToDevice, m->stream));
-        forward(m, batch);
-        float *keep = m->msk;
-        if (!mask) m->msk = nullptr;
-        backward(m, batch);
-        m->msk = keep;
+        forward(m, batch, inputs, m->pred);
+        backward(m, batch, target, mask);
         if (update) {
             m->adam_t++;
             const float b1 = 0.9f, b2 = 0.999f;
@@ -1236,6 +1343,7 @@ int cps_model_train_step(cps_model *m, const float *inputs, const float *target,
             k_adam<<<nblk(m->nparam), 256, 0, m->stream>>>(m->nparam, m->w, m->g, m->m1, m->m2, lr, b1, b2, 1e-8f, c1, c2);
             repack(m);
         }
+        nck(hipGetLastError());
         double lv[2];
         nck(hipMemcpyAsync(lv, m->lossv, sizeof(double) * 2, hipMemcpyDeviceToHost, m->stream));
         nck(hipStreamSynchronize(m->stream));
@@ -1279,7 +1387,7 @@ int cps_model_predict(cps_model *m, cps_solver *s, double *u0)
     try {
         int rc = cps_model_restrict(m, s, nullptr, m->inp, nullptr, nullptr);
         if (rc) return rc;
-        forward(m, 1);
+        forward(m, 1, m->inp, m->pred);
         size_t nn = (size_t)nx * ny * nz;
         k_prolong<<<dim3(nblk((size_t)nx), (unsigned)ny, (unsigned)nz), 256, 0, m->stream>>>(nx, ny, nz, nc, m->pred,
                                                                                             m->sig, u0);
@@ -1305,7 +1413,7 @@ int cps_model_predict_fields(cps_model *m, int32_t nx, int32_t ny, int32_t nz, c
     try {
         int rc = restrict_fields(m, nx, ny, nz, phi, g, f, nullptr, m->inp, nullptr, nullptr, m->lpart, m->sig, false);
         if (rc) return rc;
-        forward(m, 1);
+        forward(m, 1, m->inp, m->pred);
         k_prolong<<<dim3(nblk((size_t)nx), (unsigned)ny, (unsigned)nz), 256, 0, m->stream>>>(nx, ny, nz, nc, m->pred,
                                                                                             m->sig, u0);
         nck(hipGetLastError());
