@@ -19,11 +19,19 @@
 // L v = r, U delta = v, phi += delta.
 //
 // The factorisation and both substitutions are recurrences along all three axes: node
-// (i, j, k) needs its -x, -y, -z neighbours first (the +x, +y, +z ones going back).  The nodes
-// of one hyperplane i + j + k = s depend only on the hyperplane before, so each hyperplane is
-// one launch over its nodes (one thread per (j, k) with i = s - j - k); a grid of n^3 points
-// takes 3 (n - 2) - 2 launches per substitution.  This is inherently sequential work (the
-// paper's inner solver is too): the library's default inner solvers are the parallel ones.
+// (i, j, k) needs its -x, -y, -z neighbours first (the +x, +y, +z ones going back), so the
+// nodes of one hyperplane i + j + k = s depend only on the hyperplane before.  The interior is
+// cut into tiles of SIP_TS^3 nodes, and the tiles of one hyperplane of tiles are one launch, a
+// block each: a block loads its tile and the three faces next to it into LDS and walks the
+// tile's 3 SIP_TS - 2 hyperplanes there, one barrier apart.  A substitution on n^3 interior
+// nodes takes 3 n / 16 - 2 launches instead of 3 n - 2 (one per hyperplane of nodes, 3 us
+// each: 64^3 in FP64, 570 us per substitution; in tiles 10 launches of 13.5 us, of which the steps take 8).  What is left is the chain of
+// the hyperplanes: an LDS read, three multiply-adds, a division and a barrier per step.
+//
+// Factors are stored per tile in hyperplane order (the nodes of a step are consecutive), in two
+// arrays of four values: b, c, d, e for the forward substitution and f, g, h, 0 for the
+// backward one.  Nodes that are not unknowns, and those of a tile beyond the interior, have
+// b = c = d = f = g = h = 0 and e = 1: their value stays 0 without a test.
 #include <hip/hip_runtime.h>
 
 #include "cps_kernels.h"
@@ -32,146 +40,343 @@ namespace cps {
 
 namespace {
 
+constexpr int TS = SIP_TS, TN = SIP_TN;
+constexpr int STEPS = 3 * TS - 2;         // hyperplanes of a tile
+// LDS tile (the tile and one face layer per axis): strides of j and k for which the nodes of a
+// hyperplane, at s + (LY - 1) j + (LZ - 1) k, fall on different banks (17 j + 16 k modulo 32
+// double or 64 float banks).  With strides 17 and 289 (16 j + 288 k) 32 lanes met on two banks:
+// 18 us per launch at 64^3 in FP64, 13.5 us with these.
+constexpr int LY = TS + 2, LZ = 337, LSIZE = LZ * (TS + 1);
+static_assert(LZ >= LY * (TS + 1), "planes do not overlap");
+constexpr int SIP_THREADS = 256;          // at least the nodes of the largest hyperplane (192)
+// steps whose factors are loaded ahead: a step takes 0.16 us, a load up to about a microsecond
+// (going back 14.2 us per launch with 4, 13.4 with 8)
+constexpr int AHEAD = 8;
+
+// The tile's nodes (packed i + TS j + TS^2 k) in hyperplane order, each node's position in
+// it, and the first position of each hyperplane.
+struct SipOrder {
+    alignas(16) uint16_t cell[TN];
+    uint16_t node[TN], pos[TN];             // cell: the node's place in the LDS tile without its face layer
+    int start[STEPS + 1];
+};
+constexpr SipOrder make_order()
+{
+    SipOrder o{};
+    int q = 0;
+    for (int s = 0; s < STEPS; ++s) {
+        o.start[s] = q;
+        for (int k = 0; k < TS; ++k)
+            for (int j = 0; j < TS; ++j) {
+                const int i = s - j - k;
+                if (i < 0 || i >= TS) continue;
+                const int n = i + TS * (j + TS * k);
+                o.node[q] = (uint16_t)n;
+                o.cell[q] = (uint16_t)(i + LY * j + LZ * k);
+                o.pos[n] = (uint16_t)q;
+                ++q;
+            }
+    }
+    o.start[STEPS] = q;
+    return o;
+}
+constexpr SipOrder ORDER = make_order();
+__device__ const SipOrder order = ORDER;
+
 __device__ __forceinline__ bool unk(int8_t t) { return t == 1 || t == 2; }
 
-struct Plane {
+// a hyperplane of tiles: blocks over (tile j, tile k), tile i = s - tile j - tile k
+struct TilePlane {
     int s, klo;
 };
 
-// the node of hyperplane s handled by this thread, or -1
-__device__ __forceinline__ long long plane_node(int nx, int ny, const Plane &p, int &i, int &j, int &k)
+struct Tile {
+    int i, j, k;                          // tile indices
+    int o[3];                             // first node
+    size_t base;                          // first entry of its factors
+    bool ok;
+};
+__device__ __forceinline__ Tile tile_of(int nx, int ny, const TilePlane &p)
 {
-    j = 1 + (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    k = p.klo + (int)blockIdx.y;
-    i = p.s - j - k;
-    if (j > ny - 2 || i < 1 || i > nx - 2) return -1;
-    return (long long)i + (long long)nx * ((long long)j + (long long)ny * k);
+    const int ntx = (nx - 2 + TS - 1) / TS, nty = (ny - 2 + TS - 1) / TS;
+    Tile t;
+    t.j = (int)blockIdx.x;
+    t.k = p.klo + (int)blockIdx.y;
+    t.i = p.s - t.j - t.k;
+    t.ok = t.i >= 0 && t.i < ntx;
+    t.o[0] = 1 + TS * t.i;
+    t.o[1] = 1 + TS * t.j;
+    t.o[2] = 1 + TS * t.k;
+    t.base = ((size_t)t.i + (size_t)ntx * (t.j + (size_t)nty * t.k)) * TN;
+    return t;
 }
 
-__global__ void k_sip_factor(int nx, int ny, int nz, Plane p, Coef<double> cf, const int8_t *__restrict__ type,
-                             const int *__restrict__ irr_map, const double *__restrict__ k7, double alpha,
-                             double *__restrict__ F, float *__restrict__ F32)
-{
-    int i, j, k;
-    const long long e = plane_node(nx, ny, p, i, j, k);
-    if (e < 0) return;
-    const int8_t t = type[e];
-    if (!unk(t)) return;
-    const long long sy = nx, sz = (long long)nx * ny;
-    double co[7];
-    if (t == 2) {
-        const double *r = k7 + 7 * (size_t)irr_map[e];
-#pragma unroll
-        for (int q = 0; q < 7; ++q) co[q] = r[q];
-    } else {
-        const double *cx = cf.c[0] + 8 * i, *cy = cf.c[1] + 8 * j, *cz = cf.c[2] + 8 * k;
-        co[0] = (cx[6] + cy[6]) + cz[6];
-        co[1] = unk(type[e - 1]) ? cx[5] : 0.0;
-        co[2] = unk(type[e + 1]) ? cx[7] : 0.0;
-        co[3] = unk(type[e - sy]) ? cy[5] : 0.0;
-        co[4] = unk(type[e + sy]) ? cy[7] : 0.0;
-        co[5] = unk(type[e - sz]) ? cz[5] : 0.0;
-        co[6] = unk(type[e + sz]) ? cz[7] : 0.0;
-    }
-    // factors of the -z, -y, -x neighbours (zero at nodes that are not unknowns)
-    const double *FB = F + 8 * (e - sz), *FS = F + 8 * (e - sy), *FW = F + 8 * (e - 1);
-    const double b = co[5] / (1.0 + alpha * (FB[4] + FB[5]));
-    const double c = co[3] / (1.0 + alpha * (FS[4] + FS[6]));
-    const double d = co[1] / (1.0 + alpha * (FW[5] + FW[6]));
-    const double X1 = b * FB[4], X2 = b * FB[5], X3 = c * FS[4], X4 = c * FS[6], X5 = d * FW[5], X6 = d * FW[6];
-    const double ee = co[0] - b * FB[6] - c * FS[5] - d * FW[4] + alpha * (X1 + X2 + X3 + X4 + X5 + X6);
-    double out[8];
-    out[0] = b;
-    out[1] = c;
-    out[2] = d;
-    out[3] = ee;
-    out[4] = unk(type[e + 1]) ? (co[2] - alpha * (X1 + X3)) / ee : 0.0;
-    out[5] = unk(type[e + sy]) ? (co[4] - alpha * (X2 + X5)) / ee : 0.0;
-    out[6] = unk(type[e + sz]) ? (co[6] - alpha * (X4 + X6)) / ee : 0.0;
-    out[7] = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        F[8 * e + q] = out[q];
-        F32[8 * e + q] = (float)out[q];
-    }
-}
-
-// L v = r on hyperplane s: v = (r - b v_B - c v_S - d v_W) / e
 template <typename T>
-__global__ void k_sip_fwd(int nx, int ny, Plane p, const int8_t *__restrict__ type, const T *__restrict__ F,
-                          const T *__restrict__ r, T *__restrict__ v, const DevState *st)
+struct alignas(4 * sizeof(T)) Four {
+    T v[4];
+};
+
+// Factors of one hyperplane of tiles.  f, g, h of the tile and of the three faces below it
+// live in LDS (index i + LY j + LZ k, 0 being the face).
+__global__ void __launch_bounds__(SIP_THREADS) k_sip_factor(int nx, int ny, int nz, TilePlane p, Coef<double> cf,
+                                                            const int8_t *__restrict__ type,
+                                                            const int *__restrict__ irr_map,
+                                                            const double *__restrict__ k7, double alpha,
+                                                            Four<double> *__restrict__ L, Four<double> *__restrict__ U,
+                                                            Four<float> *__restrict__ L32, Four<float> *__restrict__ U32)
 {
-    if (st && st->done) return;
-    int i, j, k;
-    const long long e = plane_node(nx, ny, p, i, j, k);
-    if (e < 0 || !unk(type[e])) return;
-    const long long sy = nx, sz = (long long)nx * ny;
-    const T *f = F + 8 * e;
-    v[e] = (r[e] - f[0] * v[e - sz] - f[1] * v[e - sy] - f[2] * v[e - 1]) / f[3];
+    __shared__ double sf[3][LSIZE];
+    const Tile t = tile_of(nx, ny, p);
+    if (!t.ok) return;
+    const int tid = (int)threadIdx.x;
+    const size_t ntx = (nx - 2 + TS - 1) / TS, nty = (ny - 2 + TS - 1) / TS;
+    // the faces: the last layer of the tiles before, zero at the walls
+    const int fa = tid % TS, fb = tid / TS;
+    const int last = TS - 1;
+    const size_t back[3] = {TN, TN * ntx, TN * ntx * nty};
+    const int at[3] = {LY * (fa + 1) + LZ * (fb + 1), fa + 1 + LZ * (fb + 1), fa + 1 + LY * (fb + 1)};
+    const int nb[3] = {last + TS * (fa + TS * fb), fa + TS * (last + TS * fb), fa + TS * (fb + TS * last)};
+    const int tix[3] = {t.i, t.j, t.k};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        Four<double> u{};
+        if (tix[d] > 0) u = U[t.base - back[d] + order.pos[nb[d]]];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sf[q][at[d]] = u.v[q];
+    }
+    __syncthreads();
+    const size_t sy = nx, sz = (size_t)nx * ny;
+    for (int s = 0; s < STEPS; ++s) {
+        const int q = order.start[s] + tid;
+        if (q < order.start[s + 1]) {
+            const int n = order.node[q], li = n % TS, lj = (n / TS) % TS, lk = n / (TS * TS);
+            const int i = t.o[0] + li, j = t.o[1] + lj, k = t.o[2] + lk;
+            const int c0 = (li + 1) + LY * (lj + 1) + LZ * (lk + 1);
+            double lo[4] = {0.0, 0.0, 0.0, 1.0}, up[4] = {0.0, 0.0, 0.0, 0.0};
+            const bool in = i <= nx - 2 && j <= ny - 2 && k <= nz - 2;
+            const size_t e = in ? (size_t)i + sy * j + sz * k : 0;
+            const int8_t ty = in ? type[e] : (int8_t)0;
+            if (unk(ty)) {
+                const bool xe = unk(type[e + 1]), yn = unk(type[e + sy]), zt = unk(type[e + sz]);
+                double co[7];
+                if (ty == 2) {
+                    const double *r = k7 + 7 * (size_t)irr_map[e];
+#pragma unroll
+                    for (int w = 0; w < 7; ++w) co[w] = r[w];
+                } else {
+                    const double *cx = cf.c[0] + 8 * i, *cy = cf.c[1] + 8 * j, *cz = cf.c[2] + 8 * k;
+                    co[0] = (cx[6] + cy[6]) + cz[6];
+                    co[1] = unk(type[e - 1]) ? cx[5] : 0.0;
+                    co[2] = xe ? cx[7] : 0.0;
+                    co[3] = unk(type[e - sy]) ? cy[5] : 0.0;
+                    co[4] = yn ? cy[7] : 0.0;
+                    co[5] = unk(type[e - sz]) ? cz[5] : 0.0;
+                    co[6] = zt ? cz[7] : 0.0;
+                }
+                // f, g, h of the -z, -y, -x neighbours (zero at nodes that are not unknowns)
+                const int cB = c0 - LZ, cS = c0 - LY, cW = c0 - 1;
+                const double fB = sf[0][cB], gB = sf[1][cB], hB = sf[2][cB];
+                const double fS = sf[0][cS], gS = sf[1][cS], hS = sf[2][cS];
+                const double fW = sf[0][cW], gW = sf[1][cW], hW = sf[2][cW];
+                const double b = co[5] / (1.0 + alpha * (fB + gB));
+                const double c = co[3] / (1.0 + alpha * (fS + hS));
+                const double d = co[1] / (1.0 + alpha * (gW + hW));
+                const double X1 = b * fB, X2 = b * gB, X3 = c * fS, X4 = c * hS, X5 = d * gW, X6 = d * hW;
+                const double ee = co[0] - b * hB - c * gS - d * fW + alpha * (X1 + X2 + X3 + X4 + X5 + X6);
+                lo[0] = b;
+                lo[1] = c;
+                lo[2] = d;
+                lo[3] = ee;
+                up[0] = xe ? (co[2] - alpha * (X1 + X3)) / ee : 0.0;
+                up[1] = yn ? (co[4] - alpha * (X2 + X5)) / ee : 0.0;
+                up[2] = zt ? (co[6] - alpha * (X4 + X6)) / ee : 0.0;
+            }
+#pragma unroll
+            for (int w = 0; w < 3; ++w) sf[w][c0] = up[w];
+            Four<double> l4, u4;
+            Four<float> l4f, u4f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                l4.v[w] = lo[w];
+                u4.v[w] = up[w];
+                l4f.v[w] = (float)lo[w];
+                u4f.v[w] = (float)up[w];
+            }
+            L[t.base + q] = l4;
+            U[t.base + q] = u4;
+            L32[t.base + q] = l4f;
+            U32[t.base + q] = u4f;
+        }
+        __syncthreads();
+    }
 }
 
-// U delta = v on hyperplane s (delta over v): delta = v - f delta_E - g delta_N - h delta_T;
-// phi = delta (first iteration) or phi += delta
-template <typename T>
-__global__ void k_sip_bwd(int nx, int ny, Plane p, const int8_t *__restrict__ type, const T *__restrict__ F,
-                          T *__restrict__ v, T *__restrict__ phi, int first, const DevState *st)
+// One hyperplane of tiles of a substitution.
+//   FWD  L v = r:      v = (r - b v_B - c v_S - d v_W) / e
+//   else U delta = v:  delta = v - (f delta_E + g delta_N + h delta_T), delta over v, and
+//                      phi = delta (first iteration) or phi += delta
+// The tile and the face layer it depends on (below it going forward, above it going back) are
+// in LDS; values are replaced in place, hyperplane by hyperplane.
+template <typename T, bool FWD>
+__global__ void __launch_bounds__(SIP_THREADS) k_sip_sub(int nx, int ny, int nz, TilePlane p,
+                                                         const Four<T> *__restrict__ F, const T *__restrict__ r, T *v,
+                                                         T *__restrict__ phi, int first, const DevState *st)
 {
-    if (st && st->done) return;
-    int i, j, k;
-    const long long e = plane_node(nx, ny, p, i, j, k);
-    if (e < 0 || !unk(type[e])) return;
-    const long long sy = nx, sz = (long long)nx * ny;
-    const T *f = F + 8 * e;
-    const T dl = v[e] - (f[4] * v[e + 1] + f[5] * v[e + sy] + f[6] * v[e + sz]);
-    v[e] = dl;
-    phi[e] = first ? dl : phi[e] + dl;
+    __shared__ T w[LSIZE];
+    __shared__ uint4 cells[TN / 8];       // the order's cells, staged with the tile
+    const Tile t = tile_of(nx, ny, p);
+    if (!t.ok) return;
+    const int done = st ? st->done : 0;   // used at the end: nothing waits for it
+    const int tid = (int)threadIdx.x;
+    const size_t sy = nx, sz = (size_t)nx * ny;
+    constexpr int SH = FWD ? 1 : 0;       // the face layer is LDS layer 0 (forward) or TS (back)
+    const T *src = FWD ? r : v;
+    // the hyperplanes' first positions, one per lane (read by step)
+    const int starts = order.start[min(tid & 63, STEPS)];
+    auto start_of = [&](int s) { return __builtin_amdgcn_readlane(starts, FWD ? s : STEPS - 1 - s); };
+    auto count_of = [&](int s) { return __builtin_amdgcn_readlane(starts, FWD ? s + 1 : STEPS - s) - start_of(s); };
+    const uint4 *cell_src = reinterpret_cast<const uint4 *>(order.cell);
+    const uint4 cl[2] = {cell_src[tid], cell_src[tid + SIP_THREADS]};
+    static_assert(TN == 16 * SIP_THREADS, "two loads per thread hold the cells");
+    // factors of the first steps
+    const Four<T> *Ft = F + t.base;
+    Four<T> fr[AHEAD];
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) fr[s] = Ft[min(start_of(s) + tid, TN - 1)];
+    // the tile and its faces (walls hold 0; nodes beyond the interior are taken as 0): all loads
+    // are issued before the first value is used, from clamped addresses (node 0 is a wall)
+    constexpr int NU = TN / SIP_THREADS;
+    T tv[NU], fv[3];
+    bool tin[NU], fin[3];
+    int fat[3];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int n = tid + SIP_THREADS * u, li = n % TS, lj = (n / TS) % TS, lk = n / (TS * TS);
+        const int i = t.o[0] + li, j = t.o[1] + lj, k = t.o[2] + lk;
+        tin[u] = i <= nx - 2 && j <= ny - 2 && k <= nz - 2;
+        tv[u] = src[tin[u] ? (size_t)i + sy * j + sz * k : 0];
+    }
+    const int fa = tid % TS, fb = tid / TS, off = FWD ? -1 : TS, at = FWD ? 0 : TS;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int l[3] = {d == 0 ? off : fa, d == 1 ? off : (d == 0 ? fa : fb), d == 2 ? off : fb};
+        const int c[3] = {d == 0 ? at : fa + SH, d == 1 ? at : (d == 0 ? fa : fb) + SH, d == 2 ? at : fb + SH};
+        const int i = t.o[0] + l[0], j = t.o[1] + l[1], k = t.o[2] + l[2];
+        fin[d] = i >= 1 && j >= 1 && k >= 1 && i <= nx - 2 && j <= ny - 2 && k <= nz - 2;
+        fv[d] = v[fin[d] ? (size_t)i + sy * j + sz * k : 0];
+        fat[d] = c[0] + LY * c[1] + LZ * c[2];
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int n = tid + SIP_THREADS * u, li = n % TS, lj = (n / TS) % TS, lk = n / (TS * TS);
+        w[(li + SH) + LY * (lj + SH) + LZ * (lk + SH)] = tin[u] ? tv[u] : T(0);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) w[fat[d]] = fin[d] ? fv[d] : T(0);
+    cells[tid] = cl[0];
+    cells[tid + SIP_THREADS] = cl[1];
+    __syncthreads();
+    const uint16_t *cell = reinterpret_cast<const uint16_t *>(cells);
+    int n_next = cell[min(start_of(0) + tid, TN - 1)];
+#pragma unroll
+    for (int s0 = 0; s0 < STEPS; s0 += AHEAD) {
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            const int s = s0 + a;
+            if (s >= STEPS) break;
+            const Four<T> f = fr[a];
+            const int n = n_next, cnt = count_of(s);
+            if (s + AHEAD < STEPS) fr[a] = Ft[min(start_of(s + AHEAD) + tid, TN - 1)];
+            if (s + 1 < STEPS) n_next = cell[min(start_of(s + 1) + tid, TN - 1)];
+            if (tid < cnt) {
+                const int c0 = n + SH * (1 + LY + LZ);
+                if (FWD) w[c0] = (w[c0] - f.v[0] * w[c0 - LZ] - f.v[1] * w[c0 - LY] - f.v[2] * w[c0 - 1]) / f.v[3];
+                else w[c0] = w[c0] - (f.v[0] * w[c0 + 1] + f.v[1] * w[c0 + LY] + f.v[2] * w[c0 + LZ]);
+            }
+            __syncthreads();
+        }
+    }
+    if (done) return;
+    T pv[NU];
+    if (!FWD)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int n = tid + SIP_THREADS * u, li = n % TS, lj = (n / TS) % TS, lk = n / (TS * TS);
+            pv[u] = first ? T(0) : phi[tin[u] ? (size_t)(t.o[0] + li) + sy * (t.o[1] + lj) + sz * (t.o[2] + lk) : 0];
+        }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int n = tid + SIP_THREADS * u, li = n % TS, lj = (n / TS) % TS, lk = n / (TS * TS);
+        if (!tin[u]) continue;
+        const size_t e = (size_t)(t.o[0] + li) + sy * (t.o[1] + lj) + sz * (t.o[2] + lk);
+        const T val = w[(li + SH) + LY * (lj + SH) + LZ * (lk + SH)];
+        v[e] = val;
+        if (!FWD) phi[e] = first ? val : pv[u] + val;
+    }
 }
 
-// launch shape of hyperplane s: threads over j, blocks over the k that reach it
-inline bool plane_launch(int nx, int ny, int nz, int s, Plane &p, dim3 &grid)
+// launch shape of a hyperplane of tiles: blocks over tile j, and the tile k that reach it
+inline bool plane_launch(int nx, int ny, int nz, int s, TilePlane &p, dim3 &grid)
 {
-    const int klo = std::max(1, s - (nx - 2) - (ny - 2)), khi = std::min(nz - 2, s - 2);
+    const int nt[3] = {(nx - 2 + TS - 1) / TS, (ny - 2 + TS - 1) / TS, (nz - 2 + TS - 1) / TS};
+    const int klo = std::max(0, s - (nt[0] - 1) - (nt[1] - 1)), khi = std::min(nt[2] - 1, s);
     if (khi < klo) return false;
     p.s = s;
     p.klo = klo;
-    grid = dim3((unsigned)((ny - 2 + 255) / 256), (unsigned)(khi - klo + 1));
+    grid = dim3((unsigned)nt[1], (unsigned)(khi - klo + 1));
     return true;
+}
+
+inline int tile_planes(int nx, int ny, int nz)
+{
+    return (nx - 2 + TS - 1) / TS + (ny - 2 + TS - 1) / TS + (nz - 2 + TS - 1) / TS - 2;
 }
 
 }  // namespace
 
+size_t sip_factor_nodes(int nx, int ny, int nz)
+{
+    return (size_t)((nx - 2 + TS - 1) / TS) * ((ny - 2 + TS - 1) / TS) * ((nz - 2 + TS - 1) / TS) * TN;
+}
+
 void launch_sip_factor(hipStream_t st, int nx, int ny, int nz, const Coef<double> &cf, const int8_t *type,
                        const int *irr_map, const double *k7, double alpha, double *F, float *F32)
 {
-    for (int s = 3; s <= (nx - 2) + (ny - 2) + (nz - 2); ++s) {
-        Plane p;
+    const size_t nf = sip_factor_nodes(nx, ny, nz);
+    Four<double> *L = reinterpret_cast<Four<double> *>(F);
+    Four<float> *L32 = reinterpret_cast<Four<float> *>(F32);
+    for (int s = 0; s < tile_planes(nx, ny, nz); ++s) {
+        TilePlane p;
         dim3 grid;
         if (plane_launch(nx, ny, nz, s, p, grid))
-            k_sip_factor<<<grid, 256, 0, st>>>(nx, ny, nz, p, cf, type, irr_map, k7, alpha, F, F32);
+            k_sip_factor<<<grid, SIP_THREADS, 0, st>>>(nx, ny, nz, p, cf, type, irr_map, k7, alpha, L, L + nf, L32,
+                                                       L32 + nf);
     }
 }
 
 template <typename T>
-void launch_sip_iteration(hipStream_t st, int nx, int ny, int nz, const int8_t *type, const T *F, const T *r, T *v,
-                          T *phi, int first, const DevState *dst)
+void launch_sip_iteration(hipStream_t st, int nx, int ny, int nz, const T *F, const T *r, T *v, T *phi, int first,
+                          const DevState *dst)
 {
-    const int smax = (nx - 2) + (ny - 2) + (nz - 2);
-    for (int s = 3; s <= smax; ++s) {
-        Plane p;
-        dim3 grid;
-        if (plane_launch(nx, ny, nz, s, p, grid)) k_sip_fwd<T><<<grid, 256, 0, st>>>(nx, ny, p, type, F, r, v, dst);
-    }
-    for (int s = smax; s >= 3; --s) {
-        Plane p;
+    const Four<T> *L = reinterpret_cast<const Four<T> *>(F), *U = L + sip_factor_nodes(nx, ny, nz);
+    const int np = tile_planes(nx, ny, nz);
+    for (int s = 0; s < np; ++s) {
+        TilePlane p;
         dim3 grid;
         if (plane_launch(nx, ny, nz, s, p, grid))
-            k_sip_bwd<T><<<grid, 256, 0, st>>>(nx, ny, p, type, F, v, phi, first, dst);
+            k_sip_sub<T, true><<<grid, SIP_THREADS, 0, st>>>(nx, ny, nz, p, L, r, v, nullptr, 0, dst);
+    }
+    for (int s = np - 1; s >= 0; --s) {
+        TilePlane p;
+        dim3 grid;
+        if (plane_launch(nx, ny, nz, s, p, grid))
+            k_sip_sub<T, false><<<grid, SIP_THREADS, 0, st>>>(nx, ny, nz, p, U, nullptr, v, phi, first, dst);
     }
 }
 
-template void launch_sip_iteration<double>(hipStream_t, int, int, int, const int8_t *, const double *, const double *,
-                                           double *, double *, int, const DevState *);
-template void launch_sip_iteration<float>(hipStream_t, int, int, int, const int8_t *, const float *, const float *,
-                                          float *, float *, int, const DevState *);
+template void launch_sip_iteration<double>(hipStream_t, int, int, int, const double *, const double *, double *,
+                                           double *, int, const DevState *);
+template void launch_sip_iteration<float>(hipStream_t, int, int, int, const float *, const float *, float *, float *,
+                                          int, const DevState *);
 
 }  // namespace cps

@@ -135,7 +135,7 @@ struct cps_solver {
     double *mg_ccd64 = nullptr;         // mg_cc1 | mg_cc2 on the device (one-workgroup coarsest solve)
     float *mg_ccd32 = nullptr;
     // strongly implicit procedure (opt.precond = CPS_PRECOND_SIP): factors b, c, d, e, f, g, h
-    // (and a zero) per node in FP64 and FP32, the irregular row of each irregular node, and
+    // (and a zero) per node of the tiles in FP64 and FP32, the irregular row of each irregular node, and
     // per precision the residual and substitution vectors
     double *sip64 = nullptr;
     float *sip32 = nullptr;
@@ -708,7 +708,7 @@ void sip_precond(cps_solver *s, const T *ps, T *dst, const DevState *st)
             launch_resid<T>(L, cf, ir, dst, ps, w[0], st, next_rev(s, 0));
             rin = w[0];
         }
-        launch_sip_iteration<T>(s->stream, s->nx, s->ny, s->nz, s->type, F, rin, w[1], dst, it == 0, st);
+        launch_sip_iteration<T>(s->stream, s->nx, s->ny, s->nz, F, rin, w[1], dst, it == 0, st);
     }
 }
 
@@ -717,10 +717,9 @@ void sip_build(cps_solver *s)
 {
     s->sip_map = dalloc<int>(s, s->nn);
     launch_mg_irr_map(s->stream, s->nirr, s->irr_node, s->sip_map);
-    s->sip64 = dalloc<double>(s, 8 * s->nn);
-    s->sip32 = dalloc<float>(s, 8 * s->nn);
-    launch_fill<double>(s->stream, 8 * s->nn, s->sip64, 0.0);
-    launch_fill<float>(s->stream, 8 * s->nn, s->sip32, 0.0f);
+    const size_t nf = 8 * sip_factor_nodes(s->nx, s->ny, s->nz);    // every one is written
+    s->sip64 = dalloc<double>(s, nf);
+    s->sip32 = dalloc<float>(s, nf);
     launch_sip_factor(s->stream, s->nx, s->ny, s->nz, s->cf64(), s->type, s->sip_map, s->irr_k64, s->opt.sip_alpha,
                       s->sip64, s->sip32);
 }

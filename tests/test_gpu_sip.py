@@ -73,6 +73,26 @@ def test_solve_with_sip_matches_oracle(precision):
     assert np.all(u[t == 3] == 0.0)
 
 
+# the substitutions run in tiles of 16^3 nodes: axes of exactly one and two tiles, one node more
+# and one node fewer than a tile, and grids thinner than a tile
+@pytest.mark.parametrize("shape", [(18, 34, 19), (17, 18, 35), (5, 50, 4), (3, 3, 3)])
+def test_sip_tile_edges_match_oracle(shape):
+    grids = tuple(W.tanh_grid(n, 0.7) for n in shape)
+    w = W.polynomial_case(0, [], rng_seed=2, grids=grids)
+    print(f"[case] sip tile edges {shape}", flush=True)
+    P = oracle.Problem.from_workload(w)
+    t = P.types()
+    unk = (t == 1) | (t == 2)
+    rho = np.random.Generator(np.random.PCG64(6)).standard_normal(P.shape) * unk
+    ref = P.precond_sip(rho, 3, factors=P.sip_factors(0.9))
+    S = cps.Solver.from_workload(w, precond="sip", sip_iters=3, sip_alpha=0.9)
+    for prec, bar in (("fp64", 1e-11), ("fp32", 2e-5)):
+        got = S.precond(rho, precision=prec).cpu().numpy()
+        assert np.max(np.abs(got - ref)) <= bar * np.max(np.abs(ref)), prec
+        assert np.all(got[~unk] == 0.0)
+    S.close()
+
+
 def test_sip_options_validated():
     w = _case("sphere_stretched")
     for kw in ({"sip_iters": 0}, {"sip_iters": 65}, {"sip_alpha": -0.1}, {"sip_alpha": 1.5}):
