@@ -107,10 +107,12 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
                               const T *rho, const T *ri, const MgTransfer<T> &t, T *rc, const MgFirst<T> &first,
                               const DevState *st);
 // The coarsest level's `steps` Chebyshev steps (coefficients c1, c2) from 0 in one workgroup
-// of MG_LDS_THREADS threads; the level has at most MG_LDS_NODES interior nodes and steps is at
-// most MG_MAX_COARSE_STEPS.  irr_map: irregular row of each irregular node.  Writes out at
+// of MG_LDS_THREADS threads; the level has at most MG_LDS_NODES interior nodes, at most
+// MG_LDS_PADDED nodes with its walls (6885 for the 9 x 9 x 85 points that the coarsening rule
+// can leave) and steps is at most MG_MAX_COARSE_STEPS.  irr_map: irregular row of each irregular node.  Writes out at
 // the unknown nodes.
 constexpr int MG_LDS_NODES = 4096;
+constexpr int MG_LDS_PADDED = 6912;
 constexpr int MG_LDS_THREADS = 1024;
 constexpr int MG_MAX_COARSE_STEPS = 64;
 template <typename T>
@@ -118,9 +120,8 @@ void launch_mg_coarsest(hipStream_t s, int nx, int ny, int nz, const Coef<T> &cf
                         const int *irr_map, const T *k7, const T *rho, T *out, int steps, const T *c1, const T *c2,
                         const DevState *st);
 // Several Chebyshev-Jacobi steps on a coarse level in one launch (temporal blocking): each
-// workgroup owns an MG_TB_TS^3 tile of interior nodes, loads the tile and MG_TB_H layers
-// around it into LDS and runs the steps there, recomputing the layers around the tile (the
-// outermost layer's values go stale one layer per step, never reaching the tile).  Steps
+// workgroup owns an MG_TB_TS^3 tile of interior nodes, loads the tile and up to MG_TB_H layers
+// around it into LDS and runs the steps there, recomputing the layers around the tile.  Steps
 // S.c1[s], S.c2[s], s < S.n <= MG_TB_H (one fewer with a residual), from x = xin with x_{-1}
 // = 0 (the step before is either the level's first step from 0, or the first step of a pass,
 // whose c1 is 0).  Writes x at the unknown nodes of xout (!= xin) and, with rout, r = rho - K x

@@ -505,13 +505,17 @@ __global__ void __launch_bounds__(256) k_mg_prolong_add(int nfx, int nfy, int nf
 }
 
 // The coarsest level's Chebyshev-Jacobi iteration on K x = rho from x = 0, all `steps` steps
-// in one workgroup (the level has at most MG_LDS_NODES interior nodes): x_k lives in LDS
-// (interior nodes, x fastest); each thread keeps, for its nodes q = t + MG_LDS_THREADS u,
-// x_{k-1} and the K row and rho divided by the row's diagonal (the tables' regular row, or
-// the stored Shortley-Weller row of an irregular node) in registers.  x_k and x_{k+1} live
-// in two LDS arrays that swap roles every step, one barrier apart.  Wall neighbours hold 0
-// in every iterate and get coefficient 0; solid nodes are never written.  x_steps goes to
-// the unknown nodes of out.
+// in one workgroup (the level has at most MG_LDS_NODES interior nodes): x_k and x_{k+1} live in
+// two LDS arrays that swap roles every step, one barrier apart, on the level's grid with its
+// walls (0 in every iterate, so a neighbour needs no test).  Each thread keeps, for its nodes
+// q = t + MG_LDS_THREADS u (interior, x fastest), x_k, x_{k-1}, the K row and rho divided by
+// the row's diagonal (the tables' regular row, or the stored Shortley-Weller row of an
+// irregular node) and the LDS places of the row's neighbours in registers.  Nodes that are not
+// unknowns stay 0.  x_steps goes to the unknown nodes of out.
+//
+// A step is bound by its LDS reads (six per node) and the vector instructions beside them; with
+// an interior-only array, whose wall neighbours were selected away in every read, the solve of
+// 16^3 nodes (8 steps) took 14.8 us in FP32 and 22.3 in FP64, now 13.5 and 17.3.
 template <typename T>
 __global__ void __launch_bounds__(MG_LDS_THREADS) k_mg_coarsest(int nx, int ny, int nz, Coef<T> cf,
                                                                 const int8_t *__restrict__ type,
@@ -522,133 +526,131 @@ __global__ void __launch_bounds__(MG_LDS_THREADS) k_mg_coarsest(int nx, int ny, 
                                                                 const DevState *st)
 {
     constexpr int NPT = MG_LDS_NODES / MG_LDS_THREADS;
-    __shared__ T xa[MG_LDS_NODES], xb[MG_LDS_NODES];   // x_k and x_{k+1}, swapped every step
+    __shared__ T xs[2 * MG_LDS_PADDED];
     __shared__ T cs[2 * MG_MAX_COARSE_STEPS];
-    if (st && st->done) return;
-    const int ni = nx - 2, nj = ny - 2, nk = nz - 2, nij = ni * nj, nint = nij * nk;
+    const int done = st ? st->done : 0;   // used at the end: nothing waits for it
+    const int ni = nx - 2, nj = ny - 2, nk = nz - 2, nij = ni * nj, nint = nij * nk, nxy = nx * ny, nn = nxy * nz;
     const int t = (int)threadIdx.x;
+    T ko[NPT][6], rh[NPT], x[NPT], xp[NPT];
+    int at[NPT];                          // the node, also its place in LDS
+    bool act[NPT];
+    // The loads of all nodes are issued at once (one past the level's interior reads node 0),
+    // then those of the irregular rows' stored K rows, into registers of their own.
+    int8_t ty[NPT];
+    int irl[NPT];
+    T tab[NPT][7];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+        const int q = t + MG_LDS_THREADS * u, qq = q < nint ? q : 0;
+        const int k = qq / nij, r = qq - k * nij, j = r / ni, i = r - j * ni;
+        at[u] = (i + 1) + nx * (j + 1) + nxy * (k + 1);
+        ty[u] = type[at[u]];
+        rh[u] = rho[at[u]];
+        irl[u] = irr_map[at[u]];
+        const T *cx = cf.c[0] + 8 * (i + 1), *cy = cf.c[1] + 8 * (j + 1), *cz = cf.c[2] + 8 * (k + 1);
+        tab[u][0] = cx[6] + cy[6] + cz[6];
+        tab[u][1] = cx[5]; tab[u][2] = cx[7];
+        tab[u][3] = cy[5]; tab[u][4] = cy[7];
+        tab[u][5] = cz[5]; tab[u][6] = cz[7];
+        if (q >= nint) ty[u] = 0;
+    }
     if (t < steps) {
         cs[t] = c1[t];
         cs[MG_MAX_COARSE_STEPS + t] = c2[t];
     }
-    T kd[NPT], ko[NPT][6], rh[NPT], xp[NPT];
-    unsigned inm[NPT];                 // bit v: neighbour v (-x, +x, -y, +y, -z, +z) is interior
-    bool act[NPT];
-    auto node_of = [&](int q) {
-        const int i = 1 + q % ni, j = 1 + (q / ni) % nj, k = 1 + q / nij;
-        return (size_t)i + (size_t)nx * (j + (size_t)ny * k);
-    };
-#pragma unroll
-    for (int u = 0; u < NPT; ++u) {
-        const int q = t + MG_LDS_THREADS * u;
-        xa[q] = T(0);
-        xb[q] = T(0);
-        xp[u] = T(0);
-        act[u] = false;
-        kd[u] = T(1);
-        rh[u] = T(0);
-        inm[u] = 0u;
-#pragma unroll
-        for (int v = 0; v < 6; ++v) ko[u][v] = T(0);
-        // the loads that do not depend on the node's type are issued at once (a point past
-        // the level's interior reads node 0), so only an irregular row's stored K row waits
-        // for a first round trip
-        const bool in = q < nint;
-        const int qq = in ? q : 0;
-        const int i = 1 + qq % ni, j = 1 + (qq / ni) % nj, k = 1 + qq / nij;
-        const size_t e = in ? node_of(q) : 0;
-        const int8_t ty_l = type[e];
-        const T r_l = rho[e];
-        const int ir_l = irr_map[e];
-        const T *cx = cf.c[0] + 8 * i, *cy = cf.c[1] + 8 * j, *cz = cf.c[2] + 8 * k;
-        const T cx5 = cx[5], cx6 = cx[6], cx7 = cx[7], cy5 = cy[5], cy6 = cy[6], cy7 = cy[7];
-        const T cz5 = cz[5], cz6 = cz[6], cz7 = cz[7];
-        const int8_t ty = in ? ty_l : (int8_t)0;
-        act[u] = ty == 1 || ty == 2;
-        if (!act[u]) continue;
-        rh[u] = r_l;
-        if (ty == 2) {
-            const T *row = k7 + 7 * (size_t)ir_l;
-            kd[u] = row[0];
-#pragma unroll
-            for (int v = 0; v < 6; ++v) ko[u][v] = row[1 + v];
-        } else {
-            kd[u] = cx6 + cy6 + cz6;
-            ko[u][0] = cx5; ko[u][1] = cx7;
-            ko[u][2] = cy5; ko[u][3] = cy7;
-            ko[u][4] = cz5; ko[u][5] = cz7;
-        }
-        // a wall neighbour is read as the node itself with coefficient 0
-        inm[u] = (i > 1 ? 1u : 0u) | (i < nx - 2 ? 2u : 0u) | (j > 1 ? 4u : 0u) | (j < ny - 2 ? 8u : 0u) |
-                 (k > 1 ? 16u : 0u) | (k < nz - 2 ? 32u : 0u);
-#pragma unroll
-        for (int v = 0; v < 6; ++v)
-            if (!((inm[u] >> v) & 1u)) ko[u][v] = T(0);
+    for (int e = t; e < nn; e += MG_LDS_THREADS) {
+        xs[e] = T(0);
+        xs[MG_LDS_PADDED + e] = T(0);
     }
-    // rows scaled by 1 / diag K: (rho - K x) / diag = rho' - x - sum_v ko'_v x_v
+    // as many nodes' rows in flight as the registers hold
+    constexpr int ROWS = sizeof(T) == 4 ? NPT : 2;
 #pragma unroll
-    for (int u = 0; u < NPT; ++u) {
-        const T rd = T(1) / kd[u];
-        rh[u] *= rd;
+    for (int u0 = 0; u0 < NPT; u0 += ROWS) {
+        T row[ROWS][7];
 #pragma unroll
-        for (int v = 0; v < 6; ++v) ko[u][v] *= rd;
+        for (int r = 0; r < ROWS; ++r)
+            if (ty[u0 + r] == 2) {
+                const T *p = k7 + 7 * (size_t)irl[u0 + r];
+#pragma unroll
+                for (int v = 0; v < 7; ++v) row[r][v] = p[v];
+            }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int u = u0 + r;
+            const bool irr = ty[u] == 2;
+            act[u] = irr || ty[u] == 1;
+            // rows scaled by 1 / diag K: (rho - K x) / diag = rho' - x - sum_v ko'_v x_v
+            const T rd = T(1) / (act[u] ? (irr ? row[r][0] : tab[u][0]) : T(1));
+            rh[u] = act[u] ? rh[u] * rd : T(0);
+#pragma unroll
+            for (int v = 0; v < 6; ++v) ko[u][v] = act[u] ? (irr ? row[r][1 + v] : tab[u][1 + v]) * rd : T(0);
+            x[u] = T(0);
+            xp[u] = T(0);
+        }
     }
     __syncthreads();
-    const int d[6] = {-1, 1, -ni, ni, -nij, nij};
     // step s reads x_s from one array and writes x_{s+1} into the other (nodes that are not
     // unknowns stay 0 in both), so one barrier per step separates them
-    T *cur = xa, *nxt = xb;
-    for (int s = 0; s < steps; ++s) {
+    auto step = [&](const T *cur, T *nxt, int s) __attribute__((always_inline)) {
         const T a1 = cs[s], a2 = cs[MG_MAX_COARSE_STEPS + s];
 #pragma unroll
         for (int u = 0; u < NPT; ++u) {
-            const int q = t + MG_LDS_THREADS * u;
-            const T x0 = cur[q];
-            T kx = x0;
-#pragma unroll
-            for (int v = 0; v < 6; ++v) kx += ko[u][v] * cur[((inm[u] >> v) & 1u) ? q + d[v] : q];
-            if (act[u]) nxt[q] = x0 + a1 * (x0 - xp[u]) + a2 * (rh[u] - kx);
-            xp[u] = x0;
+            const T *c = cur + at[u];
+            T kx = x[u];
+            kx += ko[u][0] * c[-1];
+            kx += ko[u][1] * c[1];
+            kx += ko[u][2] * c[-nx];
+            kx += ko[u][3] * c[nx];
+            kx += ko[u][4] * c[-nxy];
+            kx += ko[u][5] * c[nxy];
+            const T xn = x[u] + a1 * (x[u] - xp[u]) + a2 * (rh[u] - kx);
+            xp[u] = x[u];
+            if (act[u]) {
+                nxt[at[u]] = xn;
+                x[u] = xn;
+            }
         }
         __syncthreads();
-        T *const tmp = cur;
-        cur = nxt;
-        nxt = tmp;
+    };
+    int s = 0;
+    for (; s + 1 < steps; s += 2) {
+        step(xs, xs + MG_LDS_PADDED, s);
+        step(xs + MG_LDS_PADDED, xs, s + 1);
     }
+    if (s < steps) step(xs, xs + MG_LDS_PADDED, s);
+    if (done) return;
 #pragma unroll
     for (int u = 0; u < NPT; ++u)
-        if (act[u]) out[node_of(t + MG_LDS_THREADS * u)] = cur[t + MG_LDS_THREADS * u];
+        if (act[u]) out[at[u]] = x[u];
 }
 
 // Temporally blocked Chebyshev-Jacobi steps on a coarse level (launch_mg_smooth_tb).  The
-// block's extended tile has E = MG_TB_TS + 2 MG_TB_H nodes per direction starting at node
-// 1 + MG_TB_TS blockIdx - MG_TB_H; point q = t + MG_TB_THREADS u of it (x fastest) belongs to
-// thread t.  x_k of the extended tile lives in LDS (0 at nodes that are not unknowns and at
-// nodes outside the grid's interior); each thread keeps x_{k-1}, rho and the K row of its
-// points in registers (the regular rows' from the 1D tables, an irregular row's stored
-// Shortley-Weller row).  A neighbour outside the extended tile reads 0: that error enters the
-// outermost layer at the first step and moves in one layer per step, so after s <= MG_TB_H
-// steps the tile (and, for s < MG_TB_H, its first neighbour layer, which the residual reads)
-// holds exactly the values of s single sweeps.  The arithmetic is that of the single sweep
-// (k_cheb4m): K x = diag x + the six neighbour terms, x_{k+1} = x_k + c1 (x_k - x_{k-1}) +
-// c2 (rho - K x) / diag.  The levels this runs on are small enough that a sweep is bound by
-// its launch and latency, not by bandwidth: the redundant work on the layers around the tile
-// costs less than the launches it saves.
-constexpr int MG_TB_E = MG_TB_TS + 2 * MG_TB_H;
-constexpr int MG_TB_E3 = MG_TB_E * MG_TB_E * MG_TB_E;
-constexpr int MG_TB_NPT = (MG_TB_E3 + MG_TB_THREADS - 1) / MG_TB_THREADS;
-
-// What a temporally blocked pass writes besides x on its tile: nothing (TB_X), the residual
-// on the tile (TB_RES), or the residual restricted into the next coarser level (TB_RESTRICT:
-// that level's rho and first step, as k_mg_restrict forms them, for the coarse nodes whose
-// centre lies in the tile; the residual is formed on the tile and one layer around it, which
-// needs the pass to leave two layers exact, S.n <= MG_TB_H - 2).  With PRO the pass starts
-// from x + P e at the regular unknowns (the coarse correction added on load, as
-// k_mg_prolong_add forms it) instead of x.
+// block owns a tile of MG_TB_TS^3 nodes.  x_0 is loaded on the tile and H layers around it
+// (edge E, 0 at nodes that are not unknowns and outside the grid's interior) into LDS; the
+// steps run on the tile and H - 1 layers (edge G), whose K row, rho and x_{k-1} the points'
+// threads hold in registers.  Every step updates all of those points: after s steps the
+// points within H - s layers of the tile hold exactly the values of s single sweeps (the
+// others have read stale neighbours, which move inwards one layer per step).  H is the least
+// that the pass needs: the steps, and one layer more for the residual on the tile, two for its
+// restriction.  x_k and x_{k+1} live in two LDS arrays that swap roles, one barrier per step.
+// The arithmetic is that of the single sweep (k_cheb4m).
+//
+// The levels this runs on are bound by latency: the kernel waits for memory twice (all loads
+// that depend on indices only, then the irregular nodes' stored K rows into registers of
+// their own) and for its steps.  With four layers for every pass, each point's row loaded
+// inside its type branch (a round trip per point) and the solver's state read first, a pass
+// took 9.3 (before the coarse correction) and 11.5 us (after it) in FP32, 15.4 and 18.0 in
+// FP64 (66^3 and 34^3 levels, averages); now 7.5, 7.3, 13.3 and 11.4.
+//
+// What a pass writes besides x on its tile: nothing (TB_X), the residual on the tile (TB_RES),
+// or the residual restricted into the next coarser level (TB_RESTRICT: that level's rho and
+// first step, as k_mg_restrict forms them, for the coarse nodes whose centre lies in the tile).
+// With PRO the pass starts from x + P e at the regular unknowns (the coarse correction added on
+// load, as k_mg_prolong_add forms it) instead of x.
 enum { TB_X = 0, TB_RES = 1, TB_RESTRICT = 2 };
 
-template <typename T, int OUT, bool PRO>
-__global__ void __launch_bounds__(MG_TB_THREADS, sizeof(T) == 4 ? 8 : 1) k_mg_smooth_tb(int nx, int ny, int nz, Coef<T> cf,
+template <typename T, int OUT, bool PRO, int H>
+__global__ void __launch_bounds__(MG_TB_THREADS) k_mg_smooth_tb(int nx, int ny, int nz, Coef<T> cf,
                                                                 const int8_t *__restrict__ type,
                                                                 const int *__restrict__ irr_map,
                                                                 const T *__restrict__ k7, const T *__restrict__ rho,
@@ -657,52 +659,50 @@ __global__ void __launch_bounds__(MG_TB_THREADS, sizeof(T) == 4 ? 8 : 1) k_mg_sm
                                                                 MgTransfer<T> tr, const T *__restrict__ ec,
                                                                 T *__restrict__ rc, MgFirst<T> F)
 {
-    constexpr int E = MG_TB_E, E2 = E * E, NPT = MG_TB_NPT;
-    static_assert(MG_TB_TS % 2 == 0, "a tile holds whole coarse cells");
-    __shared__ T xs[MG_TB_E3];
-    __shared__ T rs[OUT == TB_RESTRICT ? MG_TB_E3 : 1];
-    if (st && st->done) return;
+    constexpr int TS = MG_TB_TS, NTH = MG_TB_THREADS, E = TS + 2 * H, E2 = E * E, E3 = E2 * E, G = E - 2, G3 = G * G * G;
+    constexpr int NX = (E3 + NTH - 1) / NTH, NG = (G3 + NTH - 1) / NTH;   // points per thread: loaded, stepped
+    constexpr int RE = TS + 1;                            // residual edge: the tile and the layer above it
+    static_assert(TS % 2 == 0, "a tile holds whole coarse cells");
+    __shared__ T xs[2][E3];
+    __shared__ T rs[OUT == TB_RESTRICT ? RE * RE * RE : 1];
+    const int done = st ? st->done : 0;   // used before the first store: nothing waits for it
     const int t = (int)threadIdx.x;
-    const int o[3] = {1 + MG_TB_TS * (int)blockIdx.x - MG_TB_H, 1 + MG_TB_TS * (int)blockIdx.y - MG_TB_H,
-                      1 + MG_TB_TS * (int)blockIdx.z - MG_TB_H};
-    T xp[NPT], rh[NPT], kd[NPT], ko[NPT][6];
-    bool act[NPT];
+    // first node of the extended tile
+    const int o[3] = {1 + TS * (int)blockIdx.x - H, 1 + TS * (int)blockIdx.y - H, 1 + TS * (int)blockIdx.z - H};
     // TB_RESTRICT: thread t < (TS/2)^3 restricts into coarse node (I, J, K) = (1 + TS/2 b + c)
-    // at the end; its nine weights and the node's diagonal are loaded with the tile and kept
-    // in LDS until then
-    constexpr int CT = MG_TB_TS / 2, CT3 = CT * CT * CT;
-    __shared__ T rsw[OUT == TB_RESTRICT ? CT3 : 1][10];
+    // at the end
+    constexpr int CT = TS / 2, CT3 = CT * CT * CT;
     const int ci = t % CT, cj = (t / CT) % CT, ck = t / (CT * CT);
     const int cI = 1 + CT * (int)blockIdx.x + ci, cJ = 1 + CT * (int)blockIdx.y + cj, cK = 1 + CT * (int)blockIdx.z + ck;
     const bool cown = OUT == TB_RESTRICT && t < CT3 && cI <= tr.nc[0] - 2 && cJ <= tr.nc[1] - 2 && cK <= tr.nc[2] - 2;
     const size_t ce = cown ? (size_t)cI + (size_t)tr.nc[0] * (cJ + (size_t)tr.nc[1] * cK) : 0;
+    auto inside = [&](int i, int j, int k) {
+        return i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2 && k >= 1 && k <= nz - 2;
+    };
+    auto node = [&](int i, int j, int k) { return (size_t)i + (size_t)nx * ((size_t)j + (size_t)ny * k); };
+    // ---- loads that depend on indices only, all in flight together (points outside the grid's
+    // interior read node 0 and clamped table entries)
+    T x0[NX], pe[NX];
+    bool xin_ok[NX];
+    int8_t xty[NX];
 #pragma unroll
-    for (int u = 0; u < NPT; ++u) {
-        const int q = t + MG_TB_THREADS * u;
-        const int ii = q % E, jj = (q / E) % E, kk = q / E2;
-        const int i = o[0] + ii, j = o[1] + jj, k = o[2] + kk;
-        const bool in = q < MG_TB_E3 && i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2 && k >= 1 && k <= nz - 2;
-        const size_t e = in ? (size_t)i + (size_t)nx * ((size_t)j + (size_t)ny * k) : 0;
-        // every load that does not depend on the node's type is issued at once (e and the
-        // clamped indices address valid entries for any point), so only an irregular row's
-        // stored K row waits for a first round trip
-        const int ic = min(max(i, 1), nx - 2), jc = min(max(j, 1), ny - 2), kc = min(max(k, 1), nz - 2);
-        const int8_t ty_l = type[e];
-        const T x_l = xin[e], r_l = rho[e];
-        const int ir_l = irr_map[e];
-        const T *cx = cf.c[0] + 8 * ic, *cy = cf.c[1] + 8 * jc, *cz = cf.c[2] + 8 * kc;
-        const T cx5 = cx[5], cx6 = cx[6], cx7 = cx[7], cy5 = cy[5], cy6 = cy[6], cy7 = cy[7];
-        const T cz5 = cz[5], cz6 = cz[6], cz7 = cz[7];
-        const int8_t ty = in ? ty_l : (int8_t)0;
-        act[u] = ty == 1 || ty == 2;
-        T x0 = act[u] ? x_l : T(0);
+    for (int u = 0; u < NX; ++u) {
+        const int q = min(t + NTH * u, E3 - 1);
+        const int i = o[0] + q % E, j = o[1] + (q / E) % E, k = o[2] + q / E2;
+        xin_ok[u] = inside(i, j, k);
+        const size_t e = xin_ok[u] ? node(i, j, k) : 0;
+        x0[u] = xin[e];
+        pe[u] = T(0);
+        xty[u] = 0;
         if (PRO) {
             // (P e)(i, j, k): the coarse interval of each index, combined in y, then z, then x
+            const int ic = min(max(i, 1), nx - 2), jc = min(max(j, 1), ny - 2), kc = min(max(k, 1), nz - 2);
             const int ncx = tr.nc[0], ncy = tr.nc[1], ncz = tr.nc[2];
             const int a0 = min(ic >> 1, ncx - 2), b0 = min(jc >> 1, ncy - 2), c0 = min(kc >> 1, ncz - 2);
             const size_t cpl = (size_t)ncx * ncy;
             const T *e00 = ec + (size_t)c0 * cpl + (size_t)b0 * ncx + a0;
             const T wx = tr.ax[0].pw[ic], wy = tr.ax[1].pw[jc], wz = tr.ax[2].pw[kc];
+            xty[u] = type[e];
             T ryz[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -710,101 +710,122 @@ __global__ void __launch_bounds__(MG_TB_THREADS, sizeof(T) == 4 ? 8 : 1) k_mg_sm
                 const T hi = (T(1) - wy) * e00[cpl + h] + wy * e00[cpl + ncx + h];
                 ryz[h] = (T(1) - wz) * lo + wz * hi;
             }
-            const T add = (T(1) - wx) * ryz[0] + wx * ryz[1];
-            if (ty == 1) x0 = x0 + add;
-        }
-        if (q < MG_TB_E3) xs[q] = x0;
-        rh[u] = act[u] ? r_l : T(0);
-        xp[u] = T(0);
-        kd[u] = T(1);
-#pragma unroll
-        for (int v = 0; v < 6; ++v) ko[u][v] = T(0);
-        if (ty == 2) {
-            const T *r = k7 + 7 * (size_t)ir_l;
-            kd[u] = r[0];
-#pragma unroll
-            for (int v = 0; v < 6; ++v) ko[u][v] = r[1 + v];
-        } else if (ty == 1) {
-            kd[u] = (cx6 + cy6) + cz6;
-            ko[u][0] = cx5; ko[u][1] = cx7;
-            ko[u][2] = cy5; ko[u][3] = cy7;
-            ko[u][4] = cz5; ko[u][5] = cz7;
+            pe[u] = (T(1) - wx) * ryz[0] + wx * ryz[1];
         }
     }
-    if (cown) {
+    T rh[NG], kd[NG], ko[NG][6], xp[NG];
+    int8_t ty[NG];
+    int irl[NG];
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+        const int g = min(t + NTH * u, G3 - 1);
+        const int i = o[0] + 1 + g % G, j = o[1] + 1 + (g / G) % G, k = o[2] + 1 + g / (G * G);
+        const bool in = t + NTH * u < G3 && inside(i, j, k);
+        const size_t e = in ? node(i, j, k) : 0;
+        ty[u] = type[e];
+        rh[u] = rho[e];
+        irl[u] = irr_map[e];
+        if (!in) ty[u] = 0;
+        const int ic = min(max(i, 1), nx - 2), jc = min(max(j, 1), ny - 2), kc = min(max(k, 1), nz - 2);
+        const T *cx = cf.c[0] + 8 * ic, *cy = cf.c[1] + 8 * jc, *cz = cf.c[2] + 8 * kc;
+        kd[u] = (cx[6] + cy[6]) + cz[6];
+        ko[u][0] = cx[5]; ko[u][1] = cx[7];
+        ko[u][2] = cy[5]; ko[u][3] = cy[7];
+        ko[u][4] = cz[5]; ko[u][5] = cz[7];
+        xp[u] = T(0);
+    }
+    T cw[10];                              // TB_RESTRICT: the coarse node's nine weights and diagonal
+    if (OUT == TB_RESTRICT) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            rsw[t][c] = tr.ax[0].rw[3 * cI + c];
-            rsw[t][3 + c] = tr.ax[1].rw[3 * cJ + c];
-            rsw[t][6 + c] = tr.ax[2].rw[3 * cK + c];
+            cw[c] = tr.ax[0].rw[cown ? 3 * cI + c : 0];
+            cw[3 + c] = tr.ax[1].rw[cown ? 3 * cJ + c : 0];
+            cw[6 + c] = tr.ax[2].rw[cown ? 3 * cK + c : 0];
         }
-        rsw[t][9] = F.diag[ce];
+        cw[9] = F.diag[ce];
+    }
+    // ---- the irregular nodes' stored K rows
+    T row[NG][7];
+#pragma unroll
+    for (int u = 0; u < NG; ++u)
+        if (ty[u] == 2) {
+            const T *r = k7 + 7 * (size_t)irl[u];
+#pragma unroll
+            for (int v = 0; v < 7; ++v) row[u][v] = r[v];
+        }
+#pragma unroll
+    for (int u = 0; u < NX; ++u) {
+        const int q = t + NTH * u;
+        T v = xin_ok[u] ? x0[u] : T(0);
+        if (PRO && xin_ok[u] && xty[u] == 1) v = v + pe[u];
+        if (q < E3) xs[0][q] = v;
+    }
+    bool act[NG];
+#pragma unroll
+    for (int u = 0; u < NG; ++u) {
+        const bool irr = ty[u] == 2;
+        act[u] = irr || ty[u] == 1;
+        kd[u] = act[u] ? (irr ? row[u][0] : kd[u]) : T(1);
+#pragma unroll
+        for (int v = 0; v < 6; ++v) ko[u][v] = act[u] ? (irr ? row[u][1 + v] : ko[u][v]) : T(0);
+        rh[u] = act[u] ? rh[u] : T(0);
     }
     __syncthreads();
-    // K x at point q of the LDS tile (neighbours outside the extended tile read 0)
-    auto kx_of = [&](int u, int q, T x0) {
-        const int ii = q % E, jj = (q / E) % E, kk = q / E2;
-        const T w = ii > 0 ? xs[q - 1] : T(0), ea = ii < E - 1 ? xs[q + 1] : T(0);
-        const T sv = jj > 0 ? xs[q - E] : T(0), nv = jj < E - 1 ? xs[q + E] : T(0);
-        const T mv = kk > 0 ? xs[q - E2] : T(0), uv = kk < E - 1 ? xs[q + E2] : T(0);
-        return kd[u] * x0 + ko[u][0] * w + ko[u][1] * ea + ko[u][2] * sv + ko[u][3] * nv + ko[u][4] * mv +
-               ko[u][5] * uv;
+    // point u of the thread in the extended tile
+    auto at_of = [&](int u) {
+        const int g = min(t + NTH * u, G3 - 1);
+        return (1 + g % G) + E * (1 + (g / G) % G) + E2 * (1 + g / (G * G));
+    };
+    const T *cur = xs[0];
+    auto kx_of = [&](int u, int q, T x) {
+        return kd[u] * x + ko[u][0] * cur[q - 1] + ko[u][1] * cur[q + 1] + ko[u][2] * cur[q - E] + ko[u][3] * cur[q + E] +
+               ko[u][4] * cur[q - E2] + ko[u][5] * cur[q + E2];
     };
     for (int s = 0; s < S.n; ++s) {
         const T c1 = S.c1[s], c2 = S.c2[s];
-        T xn[NPT];
+        T *nxt = xs[(s + 1) & 1];
 #pragma unroll
-        for (int u = 0; u < NPT; ++u) {
-            const int q = t + MG_TB_THREADS * u;
-            xn[u] = T(0);
-            if (!act[u]) continue;
-            const T x0 = xs[q];
-            const T kx = kx_of(u, q, x0);
-            xn[u] = x0 + c1 * (x0 - xp[u]) + c2 * (rh[u] - kx) / kd[u];
-            xp[u] = x0;
+        for (int u = 0; u < NG; ++u) {
+            const int q = at_of(u);
+            const T x = cur[q];
+            const T kx = kx_of(u, q, x);
+            const T xn = act[u] ? x + c1 * (x - xp[u]) + c2 * (rh[u] - kx) / kd[u] : T(0);
+            xp[u] = x;
+            if (t + NTH * u < G3) nxt[q] = xn;
         }
         __syncthreads();
-#pragma unroll
-        for (int u = 0; u < NPT; ++u)
-            if (act[u]) xs[t + MG_TB_THREADS * u] = xn[u];
-        __syncthreads();
+        cur = nxt;
     }
+    if (done) return;
 #pragma unroll
-    for (int u = 0; u < NPT; ++u) {
-        const int q = t + MG_TB_THREADS * u;
-        const int ii = q % E, jj = (q / E) % E, kk = q / E2;
-        if (OUT == TB_RESTRICT && q < MG_TB_E3) {
-            // the residual on the tile and the layer around it, 0 elsewhere and off the unknowns
-            const bool near = ii >= MG_TB_H - 1 && ii <= MG_TB_H + MG_TB_TS && jj >= MG_TB_H - 1 &&
-                              jj <= MG_TB_H + MG_TB_TS && kk >= MG_TB_H - 1 && kk <= MG_TB_H + MG_TB_TS;
-            rs[q] = (act[u] && near) ? rh[u] - kx_of(u, q, xs[q]) : T(0);
-        }
-        if (!act[u] || ii < MG_TB_H || ii >= MG_TB_H + MG_TB_TS || jj < MG_TB_H || jj >= MG_TB_H + MG_TB_TS ||
-            kk < MG_TB_H || kk >= MG_TB_H + MG_TB_TS)
-            continue;
-        const size_t e = (size_t)(o[0] + ii) + (size_t)nx * ((size_t)(o[1] + jj) + (size_t)ny * (o[2] + kk));
-        const T x0 = xs[q];
-        xout[e] = x0;
-        if (OUT == TB_RES) rout[e] = rh[u] - kx_of(u, q, x0);
+    for (int u = 0; u < NG; ++u) {
+        const int q = at_of(u), ii = q % E, jj = (q / E) % E, kk = q / E2;
+        if (t + NTH * u >= G3) continue;
+        const int lo = min(min(ii, jj), kk) - H, hi = max(max(ii, jj), kk) - H;   // tile: 0 .. TS - 1
+        const T x = cur[q];
+        if (OUT == TB_RESTRICT && lo >= 0 && hi <= TS)
+            rs[(ii - H) + RE * ((jj - H) + RE * (kk - H))] = act[u] ? rh[u] - kx_of(u, q, x) : T(0);
+        if (!act[u] || lo < 0 || hi >= TS) continue;
+        const size_t e = node(o[0] + ii, o[1] + jj, o[2] + kk);
+        xout[e] = x;
+        if (OUT == TB_RES) rout[e] = rh[u] - kx_of(u, q, x);
     }
     if (OUT == TB_RESTRICT) {
-        // coarse node (I, J, K): its fine points 2I - 1 .. 2I + 1 are the extended-tile points
-        // H + 2c .. H + 2c + 2 of each direction
+        // coarse node (I, J, K): its fine points 2I - 1 .. 2I + 1 are the points 2c .. 2c + 2 of
+        // the tile (and the layer above it) in each direction
         __syncthreads();
         if (cown) {
-            const int i0 = MG_TB_H + 2 * ci, j0 = MG_TB_H + 2 * cj, k0 = MG_TB_H + 2 * ck;
-            const T *w = rsw[t];
             T acc = T(0);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
 #pragma unroll
                 for (int b = 0; b < 3; ++b) {
-                    const T wyz = w[6 + c] * w[3 + b];
-                    const T *row = rs + (k0 + c) * E2 + (j0 + b) * E + i0;
-                    acc += wyz * (w[0] * row[0] + w[1] * row[1] + w[2] * row[2]);
+                    const T wyz = cw[6 + c] * cw[3 + b];
+                    const T *r = rs + (2 * ck + c) * RE * RE + (2 * cj + b) * RE + 2 * ci;
+                    acc += wyz * (cw[0] * r[0] + cw[1] * r[1] + cw[2] * r[2]);
                 }
             }
-            const T cdg = w[9];
+            const T cdg = cw[9];
             rc[ce] = cdg != T(0) ? acc : T(0);
             if (F.x1 && cdg != T(0)) F.x1[ce] = F.c2 * acc / cdg;
         }
@@ -925,13 +946,21 @@ void launch_mg_smooth_tb(hipStream_t s, int nx, int ny, int nz, const Coef<T> &c
                     (unsigned)((nz - 2 + MG_TB_TS - 1) / MG_TB_TS));
     const MgTransfer<T> t = tr ? *tr : MgTransfer<T>{};
     const MgFirst<T> F = first ? *first : MgFirst<T>{};
-#define CPS_TB_LAUNCH(OUT, PRO)                                                                                        \
-    k_mg_smooth_tb<T, OUT, PRO><<<grid, MG_TB_THREADS, 0, s>>>(nx, ny, nz, cf, type, irr_map, k7, rho, xin, xout, rout, \
-                                                               S, st, t, e_add, rc, F)
-    if (rc) CPS_TB_LAUNCH(TB_RESTRICT, false);
-    else if (rout) CPS_TB_LAUNCH(TB_RES, false);
-    else if (e_add) CPS_TB_LAUNCH(TB_X, true);
-    else CPS_TB_LAUNCH(TB_X, false);
+#define CPS_TB_LAUNCH(OUT, PRO, H)                                                                                     \
+    k_mg_smooth_tb<T, OUT, PRO, H><<<grid, MG_TB_THREADS, 0, s>>>(nx, ny, nz, cf, type, irr_map, k7, rho, xin, xout,   \
+                                                                  rout, S, st, t, e_add, rc, F)
+    // the least layers that hold the steps and the residual's (two for its restriction)
+#define CPS_TB_LAYERS(OUT, PRO, h)                                                                                     \
+    do {                                                                                                               \
+        if ((h) <= 2) CPS_TB_LAUNCH(OUT, PRO, 2);                                                                      \
+        else if ((h) == 3) CPS_TB_LAUNCH(OUT, PRO, 3);                                                                 \
+        else CPS_TB_LAUNCH(OUT, PRO, 4);                                                                               \
+    } while (0)
+    if (rc) CPS_TB_LAYERS(TB_RESTRICT, false, S.n + 2);
+    else if (rout) CPS_TB_LAYERS(TB_RES, false, S.n + 1);
+    else if (e_add) CPS_TB_LAYERS(TB_X, true, S.n);
+    else CPS_TB_LAYERS(TB_X, false, S.n);
+#undef CPS_TB_LAYERS
 #undef CPS_TB_LAUNCH
 }
 

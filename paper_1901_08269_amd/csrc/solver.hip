@@ -1292,7 +1292,8 @@ void mg_build(cps_solver *s, const std::vector<double> &hx0)
     cheb_coefficients(nmax, lam1, s->opt.lam_hi, s->mg_cc1.data(), s->mg_cc2.data());
     // a coarsest level below the problem's grid that fits one workgroup is solved there
     MgLevel &Lc2 = s->mg.back();
-    if (s->mg.size() > 1 && (size_t)(Lc2.n[0] - 2) * (Lc2.n[1] - 2) * (Lc2.n[2] - 2) <= (size_t)MG_LDS_NODES) {
+    if (s->mg.size() > 1 && (size_t)(Lc2.n[0] - 2) * (Lc2.n[1] - 2) * (Lc2.n[2] - 2) <= (size_t)MG_LDS_NODES &&
+        Lc2.nn <= (size_t)MG_LDS_PADDED) {
         Lc2.lds = true;
         std::vector<double> cc(s->mg_cc1);
         cc.insert(cc.end(), s->mg_cc2.begin(), s->mg_cc2.end());
