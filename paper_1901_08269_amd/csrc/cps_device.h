@@ -8,7 +8,8 @@
 //                  the irregular-row pass (irregular) or untouched (solid)
 //   1D tables      per direction d and index n, 8 coefficients at coef[d][8n + q]:
 //                  q = 0 a, 1 c, 2 ar, 3 br, 4 cr (compact scheme, Eq. app_xxx; b = 1),
-//                  5 ka, 6 kb, 7 kc (second-order scheme of K, Eq. 2ndorder_coef)
+//                  5 ka, 6 kb, 7 kc (second-order scheme of K, Eq. 2ndorder_coef); those of
+//                  the x axis also per coefficient (Coef)
 //   irregular rows CSR over node indices (rows in increasing node order): the full row of
 //                  B = A-bar + C (Eq. Bdec) at each irregular node, its 7-point K row and
 //                  the diagonal entry of B
@@ -55,16 +56,30 @@ struct Geom {
     Tiling tr2;                // 256 x (4 RPW2) tiles: RPW2 rows per wavefront (two-vector sweeps)
     Tiling tr2s;               // the same tiles in more z-chunks, for the FP32 two-vector sweeps
                                // (fewer registers: more of their wavefronts fit at once)
-    int lg;                    // coarse multigrid levels whose rows are at most 128 nodes
-                               // long: 2^lg lanes per row, 64 / 2^lg rows per wavefront
-                               // (tr then has (4 * 2^lg) x (4 * 64 / 2^lg) tiles); 6 otherwise
     int nflat;                 // blocks of the flat (vectorised) pointwise kernels
 };
 
+// The 1D tables, and the x axis's once more with each coefficient's values consecutive (xs + q
+// xp + n): a lane's four nodes then take one 4-vector per coefficient, and a wavefront's whole
+// lines, where the 8-value records put every lane on a line of its own (a marching wavefront
+// spent as long on its 12 to 20 table loads as on several plane steps).
 template <typename T>
 struct Coef {
     const T *c[3];
+    const T *xs;
+    int xp;
 };
+constexpr int COEF_PAD = 8;   // zeros after each coefficient's values
+__host__ __device__ __forceinline__ size_t coef_size(int nmax) { return (size_t)3 * 8 * nmax + 8 * (size_t)(nmax + COEF_PAD); }
+template <typename T>
+inline Coef<T> coef_of(const T *base, int nmax)
+{
+    Coef<T> c;
+    for (int d = 0; d < 3; ++d) c.c[d] = base + (size_t)d * 8 * nmax;
+    c.xs = base + (size_t)3 * 8 * nmax;
+    c.xp = nmax + COEF_PAD;
+    return c;
+}
 
 template <typename T>
 struct Irr {

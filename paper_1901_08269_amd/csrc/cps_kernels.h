@@ -21,9 +21,8 @@ struct Launch {
 template <typename T, typename TO>
 void launch_apply(int mode, const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, TO *y, const T *w,
                   const double *bvec, DevState *st);
-// rev: march down in z (consecutive sweeps alternate, see k_cheb4).  ev0/ev1 (optional, used
-// on a grid whose rows fill a wavefront): events that the launch itself stamps with the
-// kernel's start and end (hipExtLaunchKernelGGL)
+// rev: march down in z (consecutive sweeps alternate, see k_cheb4).  ev0/ev1 (optional): events
+// that the launch itself stamps with the kernel's start and end (hipExtLaunchKernelGGL)
 template <typename T>
 void launch_cheb(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *xc, const T *xm1, const T *rho, T *xn,
                  double c1, double c2, const DevState *st, int rev, hipEvent_t ev0 = nullptr,
@@ -172,7 +171,7 @@ struct SetupOut {
 };
 
 // 1D tables (FP64) from coordinates; t holds the three coordinate arrays
-// the 1D tables of all three axes (8 values per index; FP64 and FP32, 3 * 8 * nmax each)
+// the 1D tables of all three axes (FP64 and FP32, coef_size(nmax) values each, see Coef)
 void launch_coef(hipStream_t s, int nx, int ny, int nz, int nmax, const double *xyz, double *coef, float *coef32);
 // classify nodes; flags: bit0 invalid input (NaN/Inf), bit1 a wall node inside a body has a
 // fluid neighbour; with phi_out, g_out and f_out non-null the fields are also copied there

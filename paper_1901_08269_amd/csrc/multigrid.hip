@@ -223,13 +223,18 @@ __global__ void __launch_bounds__(256) k_mg_resid_restrict(Geom g, Tiling tl, Co
         }
     }
     T kax[5], kbx[5], kcx[5];
+    {
+        const T *x5 = cf.xs + (size_t)5 * cf.xp + ic, *x6 = x5 + cf.xp, *x7 = x6 + cf.xp;
+        const V va = *reinterpret_cast<const V *>(x5), vb = *reinterpret_cast<const V *>(x6),
+                vc = *reinterpret_cast<const V *>(x7);
+        const T a[5] = {va.x, va.y, va.z, va.w, x5[4]}, bb[5] = {vb.x, vb.y, vb.z, vb.w, x6[4]},
+                c[5] = {vc.x, vc.y, vc.z, vc.w, x7[4]};
 #pragma unroll
-    for (int u = 0; u < 5; ++u) {
-        const bool ok = u < 4 ? u < nv : need5;
-        const T *cx = cf.c[0] + 8 * (ok ? f0 + u : 1);
-        kax[u] = cx[5];
-        kbx[u] = cx[6];
-        kcx[u] = cx[7];
+        for (int u = 0; u < 5; ++u) {
+            kax[u] = a[u];
+            kbx[u] = bb[u];
+            kcx[u] = c[u];
+        }
     }
     // in-plane byte offsets of node ic on x rows 2 J0 - 2 .. 2 J0 + 2 CR (clamped to the wall
     // row, where x is 0); the residual rows 2 J0 - 1 .. 2 J0 + 2 CR - 1 are x rows 1 .. NR,
@@ -727,9 +732,9 @@ __global__ void __launch_bounds__(MG_TB_THREADS) k_mg_smooth_tb(int nx, int ny, 
         irl[u] = irr_map[e];
         if (!in) ty[u] = 0;
         const int ic = min(max(i, 1), nx - 2), jc = min(max(j, 1), ny - 2), kc = min(max(k, 1), nz - 2);
-        const T *cx = cf.c[0] + 8 * ic, *cy = cf.c[1] + 8 * jc, *cz = cf.c[2] + 8 * kc;
-        kd[u] = (cx[6] + cy[6]) + cz[6];
-        ko[u][0] = cx[5]; ko[u][1] = cx[7];
+        const T *cx = cf.xs + (size_t)5 * cf.xp + ic, *cy = cf.c[1] + 8 * jc, *cz = cf.c[2] + 8 * kc;
+        kd[u] = (cx[cf.xp] + cy[6]) + cz[6];
+        ko[u][0] = cx[0]; ko[u][1] = cx[2 * cf.xp];
         ko[u][2] = cy[5]; ko[u][3] = cy[7];
         ko[u][4] = cz[5]; ko[u][5] = cz[7];
         xp[u] = T(0);

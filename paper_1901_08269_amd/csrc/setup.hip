@@ -36,7 +36,7 @@ __global__ void k_coef(int nx, int ny, int nz, int nmax, const double *__restric
     const int n = d == 0 ? nx : (d == 1 ? ny : nz);
     const double *t = xyz + (d == 0 ? 0 : (d == 1 ? nx : nx + ny));
     const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= nmax) return;
+    if (i >= nmax + COEF_PAD) return;
     double o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (i == 0 || i == n - 1) {
         // wall indices: never used by a row; nonzero diagonals keep flat pointwise
@@ -58,16 +58,24 @@ __global__ void k_coef(int nx, int ny, int nz, int nmax, const double *__restric
         o[7] = 2.0 / (hf * (hf + hb));
     }
     const size_t at = 8 * ((size_t)d * nmax + i);
+    if (i < nmax)
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        coef[at + q] = o[q];
-        coef32[at + q] = (float)o[q];
-    }
+        for (int q = 0; q < 8; ++q) {
+            coef[at + q] = o[q];
+            coef32[at + q] = (float)o[q];
+        }
+    if (d == 0)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const size_t ax = (size_t)3 * 8 * nmax + (size_t)q * (nmax + COEF_PAD) + i;
+            coef[ax] = o[q];
+            coef32[ax] = (float)o[q];
+        }
 }
 
 void launch_coef(hipStream_t s, int nx, int ny, int nz, int nmax, const double *xyz, double *coef, float *coef32)
 {
-    k_coef<<<dim3((unsigned)((nmax + 255) / 256), 3), 256, 0, s>>>(nx, ny, nz, nmax, xyz, coef, coef32);
+    k_coef<<<dim3((unsigned)((nmax + COEF_PAD + 255) / 256), 3), 256, 0, s>>>(nx, ny, nz, nmax, xyz, coef, coef32);
 }
 
 // ---------------------------------------------------------------------------------------

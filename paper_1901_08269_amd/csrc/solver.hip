@@ -88,7 +88,7 @@ struct cps_solver {
     size_t nn = 0;
     // device data
     double *xyz = nullptr;        // x | y | z
-    double *coef64 = nullptr;     // 3 * 8 * nmax
+    double *coef64 = nullptr;     // coef_size(nmax)
     float *coef32 = nullptr;
     double *phi = nullptr, *gf = nullptr, *f = nullptr;
     int8_t *type = nullptr;
@@ -154,18 +154,8 @@ struct cps_solver {
     std::vector<Alloc> allocs;    // device blocks owned by this solver
 
     Launch launch() const { return Launch{g, stream, skip, partials}; }
-    Coef<double> cf64() const
-    {
-        Coef<double> c;
-        for (int d = 0; d < 3; ++d) c.c[d] = coef64 + (size_t)d * 8 * nmax;
-        return c;
-    }
-    Coef<float> cf32() const
-    {
-        Coef<float> c;
-        for (int d = 0; d < 3; ++d) c.c[d] = coef32 + (size_t)d * 8 * nmax;
-        return c;
-    }
+    Coef<double> cf64() const { return coef_of(coef64, nmax); }
+    Coef<float> cf32() const { return coef_of(coef32, nmax); }
     Irr<double> ir64() const
     {
         return Irr<double>{nirr, irr_node, irr_ptr, irr_col, irr_val64, irr_k64, irr_bd64, irr_bits, irr_wstart};
@@ -356,12 +346,7 @@ constexpr int APPLY_ZCHUNKS = 16;
 // grid-stride kernels over all nodes (fills, copies, restart) use at most this many blocks
 constexpr int FLAT_BLOCKS = 4096;
 
-// coarse = true (a coarse multigrid level): the sweep tiling aims at COARSE_TILES tiles
-// of at least one plane each, since a small grid's sweep is bound by the latency of its
-// z-march rather than by bandwidth (spheres8 256^3, mixed multigrid solve: 1024 tiles
-// 25.1 ms, 512 25.2 ms, 2048 25.6 ms)
-constexpr int COARSE_TILES = 1024;
-Geom make_geom(int nx, int ny, int nz, bool coarse = false)
+Geom make_geom(int nx, int ny, int nz)
 {
     Geom g{};
     g.nx = nx; g.ny = ny; g.nz = nz;
@@ -370,14 +355,9 @@ Geom make_geom(int nx, int ny, int nz, bool coarse = false)
         const int per_plane = ((nx - 2 + 4 * TX - 1) / (4 * TX)) * ((ny - 2 + TY - 1) / TY);
         g.ta = make_tiling(nx, ny, nz, 4 * TX, TY, per_plane * APPLY_ZCHUNKS, 4);
     }
-    // a coarse level whose rows need at most 32 lanes packs 64 / 2^lg rows into a wavefront
-    g.lg = 6;
-    if (coarse && RPW == 1)
-        while (g.lg > 3 && 4 * (1 << (g.lg - 1)) >= nx - 2) --g.lg;
     {
         const int per_plane = ((nx - 2 + 4 * TX - 1) / (4 * TX)) * ((ny - 2 + TY * RPW - 1) / (TY * RPW));
-        g.tr = coarse ? make_tiling(nx, ny, nz, 4 << g.lg, TY * RPW * (TX >> g.lg), COARSE_TILES, 1)
-                      : make_tiling(nx, ny, nz, 4 * TX, TY * RPW, per_plane * ROW_ZCHUNKS, 4);
+        g.tr = make_tiling(nx, ny, nz, 4 * TX, TY * RPW, per_plane * ROW_ZCHUNKS, 4);
         const int per_plane2 = ((nx - 2 + 4 * TX - 1) / (4 * TX)) * ((ny - 2 + TY * RPW2 - 1) / (TY * RPW2));
         g.tr2 = make_tiling(nx, ny, nz, 4 * TX, TY * RPW2, per_plane2 * ROW_ZCHUNKS, 4);
         g.tr2s = make_tiling(nx, ny, nz, 4 * TX, TY * RPW2, per_plane2 * ROW_ZCHUNKS_F32, 4);
@@ -500,12 +480,7 @@ void mg_alloc(cps_solver *s)
 template <typename T>
 Coef<T> mg_coef(const MgLevel &Lv)
 {
-    Coef<T> c;
-    for (int d = 0; d < 3; ++d) {
-        if constexpr (sizeof(T) == 8) c.c[d] = Lv.coef64 + (size_t)d * 8 * Lv.nmax;
-        else c.c[d] = Lv.coef32 + (size_t)d * 8 * Lv.nmax;
-    }
-    return c;
+    if constexpr (sizeof(T) == 8) return coef_of(Lv.coef64, Lv.nmax); else return coef_of(Lv.coef32, Lv.nmax);
 }
 
 // the K rows of a coarse level (the fields of B are not used by the K sweeps)
@@ -1240,14 +1215,14 @@ void mg_build(cps_solver *s, const std::vector<double> &hx0)
         const int cx = C.n[0], cy = C.n[1], cz = C.n[2];
         C.nmax = std::max({cx, cy, cz});
         C.nn = (size_t)cx * cy * cz;
-        C.g = make_geom(cx, cy, cz, true);
+        C.g = make_geom(cx, cy, cz);
         C.xyz = (double *)(dev + o_xyz);
         const int *dg = (const int *)(dev + o_g);
         double *phic = dalloc<double>(s, C.nn);
         temps.push_back(phic);
         launch_gather3(s->stream, cx, cy, cz, F.n[0], F.n[1], dg, dg + cx, dg + cx + cy, phi_f, phic);
-        C.coef64 = dalloc<double>(s, (size_t)3 * 8 * C.nmax);
-        C.coef32 = dalloc<float>(s, (size_t)3 * 8 * C.nmax);
+        C.coef64 = dalloc<double>(s, coef_size(C.nmax));
+        C.coef32 = dalloc<float>(s, coef_size(C.nmax));
         launch_coef(s->stream, cx, cy, cz, C.nmax, C.xyz, C.coef64, C.coef32);
         // node types from the coarse level set (it is also passed as g and f, which the
         // classification only checks for finiteness).  Its flags are not read: the coarse
@@ -1465,8 +1440,8 @@ int cps_setup(cps_solver **out, int32_t nx, int32_t ny, int32_t nz, const double
             to_device(s, s->f, f, s->nn * sizeof(double));
         }
         // 1D tables
-        s->coef64 = dalloc<double>(s, (size_t)3 * 8 * s->nmax);
-        s->coef32 = dalloc<float>(s, (size_t)3 * 8 * s->nmax);
+        s->coef64 = dalloc<double>(s, coef_size(s->nmax));
+        s->coef32 = dalloc<float>(s, coef_size(s->nmax));
         launch_coef(s->stream, nx, ny, nz, s->nmax, s->xyz, s->coef64, s->coef32);
         // classification
         s->type = dalloc<int8_t>(s, s->nn);

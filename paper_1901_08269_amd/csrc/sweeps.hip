@@ -189,6 +189,17 @@ __device__ __forceinline__ typename Vec4Of<T>::type load4(const T *__restrict__ 
     return v;
 }
 
+// coefficient q of the x axis at indices i .. i + 3
+template <typename T>
+__device__ __forceinline__ void coef_x4(const Coef<T> &cf, int q, int i, T (&o)[4])
+{
+    const typename Vec4Of<T>::type v = *reinterpret_cast<const typename Vec4Of<T>::type *>(cf.xs + (size_t)q * cf.xp + i);
+    o[0] = v.x;
+    o[1] = v.y;
+    o[2] = v.z;
+    o[3] = v.w;
+}
+
 // the four row-type bits of nodes i0 .. i0 + 3 (skip words are read in pairs; the array
 // carries two words of padding)
 __device__ __forceinline__ uint32_t skip4(const uint32_t *__restrict__ w, int i0)
@@ -208,22 +219,17 @@ __device__ __forceinline__ uint32_t skip4(const uint32_t *__restrict__ w, int i0
 // wavefront.  Wave-uniform y and z coefficients live in scalar registers.  Irregular rows
 // use their Shortley-Weller row in the leading blocks (one thread per row).  With RES the
 // same rows give the residual rho - K x_k instead (multigrid), with no x_{k-1}.
-// With MR (a coarse multigrid level whose rows fit in fewer than 64 lanes) each group of
-// 2^g.lg lanes owns one whole row, so a wavefront carries 64 / 2^g.lg rows and no lane idles;
-// the rows' y coefficients are then per lane.
-template <typename T, bool PREV0, bool RES, bool REV, bool MR = false, int R = RPW>
+template <typename T, bool PREV0, bool RES, bool REV, int R = RPW>
 __device__ __forceinline__ void cheb4_rows(const Geom &g, const Coef<T> &cf, const Irr<T> &ir,
                                            const uint32_t *__restrict__ skip, const T *__restrict__ xc,
                                            const T *xm1, const T *__restrict__ rho, T *xn, T c1, T c2,
                                            const DevState *st)
 {
     using V = typename Vec4Of<T>::type;
-    static_assert(!MR || R == 1, "multi-row wavefronts take one row per lane group");
     static_assert(R == RPW || R == RPW2, "the tilings hold these row counts");
     if (st && st->done) return;
     const int wv = threadIdx.y;
-    const int lw = MR ? 1 << g.lg : TX;                          // lanes per row
-    const int lane = MR ? (int)threadIdx.x & (lw - 1) : (int)threadIdx.x;
+    const int lane = (int)threadIdx.x;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t plane = (size_t)nx * ny;
     const int nib = irr_blocks(ir.n, NT);
@@ -243,29 +249,16 @@ __device__ __forceinline__ void cheb4_rows(const Geom &g, const Coef<T> &cf, con
     const Tiling &tl = (R == RPW) ? g.tr : tr2_of<T>(g);
     int bs, by, bz;
     if (!tile_of_block(tl, b, bs, by, bz)) return;
-    const int jw = 1 + (by * TY + wv) * (MR ? TX / lw : R);    // the wavefront's first row
-    if (jw > ny - 2) return;                                  // whole wavefront
-    // rows j0 .. j0 + R - 1 (MR: one row per lane group, clamped to the wall row)
-    const int j0 = MR ? min(jw + (int)threadIdx.x / lw, ny - 1) : jw;
-    Seg q;
-    if (MR) {
-        q.i0 = 1 + bs * (4 * lw) + 4 * lane;
-        q.nv = min(4, nx - 1 - q.i0);
-        q.full = q.nv == 4;
-    } else {
-        q = seg_of(nx, bs, lane);
-    }
+    const int j0 = 1 + (by * TY + wv) * R;                     // rows j0 .. j0 + R - 1
+    if (j0 > ny - 2) return;                                  // whole wavefront
+    const Seg q = seg_of(nx, bs, lane);
     const int k0 = 1 + bz * tl.TZ;
     const int k1 = min(k0 + tl.TZ, nz - 1);
     const int ic = q.nv > 0 ? q.i0 : 1;                        // lanes without nodes read valid memory
     T kax[4], kbx[4], kcx[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const T *cx = cf.c[0] + 8 * (u < q.nv ? q.i0 + u : 1);
-        kax[u] = cx[5];
-        kbx[u] = cx[6];
-        kcx[u] = cx[7];
-    }
+    coef_x4(cf, 5, ic, kax);
+    coef_x4(cf, 6, ic, kbx);
+    coef_x4(cf, 7, ic, kcx);
     // rows past ny - 2 read the wall row ny - 1 (zero in every iterate: the right y
     // neighbour of the last interior row) and are not stored
     bool rok[R];
@@ -278,16 +271,16 @@ __device__ __forceinline__ void cheb4_rows(const Geom &g, const Coef<T> &cf, con
         const int jc = rok[r] ? j : ny - 1;
         er[r] = (size_t)ic + (size_t)nx * jc;
         wr[r] = (size_t)jc * g.W + (ic >> 5);
-        kay[r] = MR ? cf.c[1][8 * jc + 5] : uniform(cf.c[1][8 * jc + 5]);
-        kby[r] = MR ? cf.c[1][8 * jc + 6] : uniform(cf.c[1][8 * jc + 6]);
-        kcy[r] = MR ? cf.c[1][8 * jc + 7] : uniform(cf.c[1][8 * jc + 7]);
+        kay[r] = uniform(cf.c[1][8 * jc + 5]);
+        kby[r] = uniform(cf.c[1][8 * jc + 6]);
+        kcy[r] = uniform(cf.c[1][8 * jc + 7]);
     }
     const size_t elo = (size_t)ic + (size_t)nx * (j0 - 1);                  // row j0 - 1 (>= 0)
     const size_t ehi = (size_t)ic + (size_t)nx * min(j0 + R, ny - 1);       // row j0 + R (<= ny - 1)
     // the segment's outer neighbours: node i0 - 1 for lane 0, node i0 + nv for the last lane
     // (both walls, hence zero in every iterate, when one segment spans the row)
-    const bool one_seg = nx - 2 <= 4 * lw;
-    const bool need_l = lane == 0, need_r = lane == lw - 1 || q.i0 + 4 >= nx - 1;
+    const bool one_seg = nx - 2 <= 4 * TX;
+    const bool need_l = lane == 0, need_r = lane == TX - 1 || q.i0 + 4 >= nx - 1;
     const int ir_off = q.nv > 0 ? q.nv : 0;
     const size_t wplane = (size_t)ny * g.W;
 
@@ -325,8 +318,8 @@ __device__ __forceinline__ void cheb4_rows(const Geom &g, const Coef<T> &cf, con
             const V &s4 = (r == 0) ? ylo : c0[r - 1];
             const V &n4 = (r == R - 1) ? yhi : c0[r + 1];
             const T cv[4] = {c0[r].x, c0[r].y, c0[r].z, c0[r].w};
-            T left = MR ? __shfl_up(cv[3], 1, lw) : __shfl_up(cv[3], 1, TX);
-            T right = MR ? __shfl_down(cv[0], 1, lw) : __shfl_down(cv[0], 1, TX);
+            T left = __shfl_up(cv[3], 1, TX);
+            T right = __shfl_down(cv[0], 1, TX);
             if (need_l) left = lft[r];
             if (need_r) right = rgt[r];
             const T sv[4] = {s4.x, s4.y, s4.z, s4.w};
@@ -373,8 +366,8 @@ __global__ void __launch_bounds__(NT) k_cheb4(Geom g, Coef<T> cf, Irr<T> ir, con
                                               const T *__restrict__ rho, T *xn, T c1, T c2,
                                               const DevState *st, int rev)
 {
-    if (rev) cheb4_rows<T, PREV0, false, true, false, R>(g, cf, ir, skip, xc, xm1, rho, xn, c1, c2, st);
-    else cheb4_rows<T, PREV0, false, false, false, R>(g, cf, ir, skip, xc, xm1, rho, xn, c1, c2, st);
+    if (rev) cheb4_rows<T, PREV0, false, true, R>(g, cf, ir, skip, xc, xm1, rho, xn, c1, c2, st);
+    else cheb4_rows<T, PREV0, false, false, R>(g, cf, ir, skip, xc, xm1, rho, xn, c1, c2, st);
 }
 
 // r = rho - K x at the unknown nodes (the residual of a multigrid level; same rows)
@@ -383,28 +376,145 @@ __global__ void __launch_bounds__(NT) k_resid4(Geom g, Coef<T> cf, Irr<T> ir, co
                                                const T *__restrict__ x, const T *__restrict__ rho, T *r,
                                                const DevState *st, int rev)
 {
-    if (rev) cheb4_rows<T, true, true, true, false, R>(g, cf, ir, skip, x, nullptr, rho, r, T(0), T(0), st);
-    else cheb4_rows<T, true, true, false, false, R>(g, cf, ir, skip, x, nullptr, rho, r, T(0), T(0), st);
+    if (rev) cheb4_rows<T, true, true, true, R>(g, cf, ir, skip, x, nullptr, rho, r, T(0), T(0), st);
+    else cheb4_rows<T, true, true, false, R>(g, cf, ir, skip, x, nullptr, rho, r, T(0), T(0), st);
 }
 
-// the same two kernels for coarse levels with several rows per wavefront (g.lg < 6)
-template <typename T, bool PREV0>
-__global__ void __launch_bounds__(NT) k_cheb4m(Geom g, Coef<T> cf, Irr<T> ir, const uint32_t *__restrict__ skip,
-                                               const T *__restrict__ xc, const T *xm1,
-                                               const T *__restrict__ rho, T *xn, T c1, T c2,
-                                               const DevState *st, int rev)
+// ---------------------------------------------------------------------------------------
+// Short sweeps: Chebyshev steps and residuals on grids whose sweep is bound by the latency of
+// its plane steps rather than by bandwidth (launch_sweep says where).  A thread computes four
+// consecutive nodes of a row in TZ planes and issues all of its loads before the first use, so
+// a sweep waits for memory once where the marching kernel (k_cheb4) waits at every plane.
+// Threads take the 4-node groups of a plane's rows in order, whatever the row length, so no
+// lane idles on rows shorter than 256 nodes; x neighbours come from the adjacent lanes, or from
+// memory at the ends of a wavefront and of a row.
+//   SW_FIRST     x_{k+1} from x_k, x_{k-1} = 0            (PREV0 of k_cheb4)
+//   SW_FULL      x_{k+1} from x_k and x_{k-1}
+//   SW_RESID     rho - K x_k
+// Measured (first step of a pass / full step), short against marching: 130^3 FP32 7.5 / 7.6
+// against 13.5 / 13.1 us, FP64 13.8 / 14.4 against 16.3 / 16.5 (marching with several rows per
+// wavefront); 202^3 FP32 20 / 22 against 26 / 26, FP64 42 / 48 against 45 / 57.  TZ = 4 is no
+// faster (130^3 8.0, 202^3 22 us), nor is forming the corrected iterate x + P e on load in place
+// of the prolongation pass (130^3 FP32: 30 + 12 us for the two steps of a pass against 6.5 + 7.5
+// + 7.6: 27 interpolations of neighbours per thread cost more than the pass).
+// ---------------------------------------------------------------------------------------
+struct ShortGrid {
+    int gpr;                   // 4-node groups per row
+    int items, nbx, nbz, nblk; // groups per plane, blocks per plane group, plane groups, blocks
+};
+template <int TZ>
+static ShortGrid short_grid(const Geom &g)
 {
-    if (rev) cheb4_rows<T, PREV0, false, true, true>(g, cf, ir, skip, xc, xm1, rho, xn, c1, c2, st);
-    else cheb4_rows<T, PREV0, false, false, true>(g, cf, ir, skip, xc, xm1, rho, xn, c1, c2, st);
+    ShortGrid q;
+    q.gpr = (g.nx - 2 + 3) / 4;
+    q.items = q.gpr * (g.ny - 2);
+    q.nbx = (q.items + NT - 1) / NT;
+    q.nbz = (g.nz - 2 + TZ - 1) / TZ;
+    q.nblk = (q.nbx * q.nbz + NXCD - 1) / NXCD * NXCD;
+    return q;
 }
+enum { SW_FIRST = 0, SW_FULL = 1, SW_RESID = 2 };
 
-template <typename T>
-__global__ void __launch_bounds__(NT) k_resid4m(Geom g, Coef<T> cf, Irr<T> ir, const uint32_t *__restrict__ skip,
-                                                const T *__restrict__ x, const T *__restrict__ rho, T *r,
-                                                const DevState *st, int rev)
+template <typename T, int KIND, int TZ>
+__global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T> cf, Irr<T> ir,
+                                                    const uint32_t *__restrict__ skip, const T *__restrict__ xc,
+                                                    const T *xm1, const T *__restrict__ rho, T *xn, T c1, T c2,
+                                                    const DevState *st)
 {
-    if (rev) cheb4_rows<T, true, true, true, true>(g, cf, ir, skip, x, nullptr, rho, r, T(0), T(0), st);
-    else cheb4_rows<T, true, true, false, true>(g, cf, ir, skip, x, nullptr, rho, r, T(0), T(0), st);
+    using V = typename Vec4Of<T>::type;
+    const int done = st ? st->done : 0;   // used before the stores: nothing waits for it
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const size_t plane = (size_t)nx * ny;
+    const int nib = irr_blocks(ir.n, NT);
+    const int b = (int)blockIdx.x - nib, tid = (int)threadIdx.x;
+    if (b < 0) {
+        const int row = (int)blockIdx.x * NT + tid;
+        if (row >= ir.n) return;
+        const int e = ir.node[row];
+        const T *k7 = ir.k7 + 7 * row;
+        const int off[6] = {-1, 1, -nx, nx, -(int)plane, (int)plane};
+        T kr[7], xv[6];
+#pragma unroll
+        for (int v = 0; v < 7; ++v) kr[v] = k7[v];
+#pragma unroll
+        for (int v = 0; v < 6; ++v) xv[v] = xc[e + off[v]];
+        const T z0 = xc[e], rh = rho[e];
+        const T kx = kr[0] * z0 + kr[1] * xv[0] + kr[2] * xv[1] + kr[3] * xv[2] + kr[4] * xv[3] + kr[5] * xv[4] +
+                     kr[6] * xv[5];
+        const T prev = KIND == SW_FULL ? xm1[e] : T(0);
+        if (!done) xn[e] = KIND == SW_RESID ? rh - kx : z0 + c1 * (z0 - prev) + c2 * (rh - kx) / kr[0];
+        return;
+    }
+    const int per = sg.nblk / NXCD, q = (b % NXCD) * per + b / NXCD;
+    if (q >= sg.nbx * sg.nbz) return;
+    const int bz = q / sg.nbx, bx = q - bz * sg.nbx;
+    const int item = bx * NT + tid, it = min(item, sg.items - 1);
+    const int row = it / sg.gpr, gx = it - row * sg.gpr;
+    const int j = 1 + row, i0 = 1 + 4 * gx, nv = min(4, nx - 1 - i0), k0 = 1 + bz * TZ;
+    const int lane = tid & 63;
+    const bool need_l = lane == 0 || gx == 0, need_r = lane == 63 || gx == sg.gpr - 1;
+    const size_t e0 = (size_t)i0 + (size_t)nx * j;           // at plane 0
+    int kp[TZ + 2];                                            // planes k0 - 1 .. k0 + TZ, inside the grid
+#pragma unroll
+    for (int p = 0; p < TZ + 2; ++p) kp[p] = min(k0 - 1 + p, nz - 1);
+    // ---- all loads
+    V xr[TZ + 2], ys[TZ], yn[TZ], rv[TZ], pv[TZ];
+    T lf[TZ], rt[TZ];
+    uint32_t sk[TZ];
+    const uint32_t *srow = skip + (size_t)j * g.W + (i0 >> 5);
+    const size_t wplane = (size_t)ny * g.W;
+#pragma unroll
+    for (int p = 0; p < TZ + 2; ++p) xr[p] = *reinterpret_cast<const V *>(xc + e0 + (size_t)kp[p] * plane);
+#pragma unroll
+    for (int t = 0; t < TZ; ++t) {
+        const size_t e = e0 + (size_t)kp[t + 1] * plane;
+        ys[t] = *reinterpret_cast<const V *>(xc + e - nx);
+        yn[t] = *reinterpret_cast<const V *>(xc + e + nx);
+        lf[t] = xc[need_l ? e - 1 : e];
+        rt[t] = xc[need_r ? e + nv : e];
+        rv[t] = *reinterpret_cast<const V *>(rho + e);
+        if (KIND == SW_FULL) pv[t] = *reinterpret_cast<const V *>(xm1 + e);
+        sk[t] = skip4(srow + (size_t)kp[t + 1] * wplane, i0);
+    }
+    T kax[4], kbx[4], kcx[4];
+    coef_x4(cf, 5, i0, kax);
+    coef_x4(cf, 6, i0, kbx);
+    coef_x4(cf, 7, i0, kcx);
+    const T *cy = cf.c[1] + 8 * j;
+    const T kay = cy[5], kby = cy[6], kcy = cy[7];
+#pragma unroll
+    for (int t = 0; t < TZ; ++t) {
+        const int k = k0 + t;
+        const T *cz = cf.c[2] + 8 * kp[t + 1];
+        const T za = cz[5], zb = cz[6], zcc = cz[7];
+        const T cv[4] = {xr[t + 1].x, xr[t + 1].y, xr[t + 1].z, xr[t + 1].w};
+        T left = __shfl_up(cv[3], 1, TX), right = __shfl_down(cv[0], 1, TX);
+        if (need_l) left = lf[t];
+        if (need_r) right = rt[t];
+        const T sv[4] = {ys[t].x, ys[t].y, ys[t].z, ys[t].w}, nvv[4] = {yn[t].x, yn[t].y, yn[t].z, yn[t].w};
+        const T mv[4] = {xr[t].x, xr[t].y, xr[t].z, xr[t].w}, uv[4] = {xr[t + 2].x, xr[t + 2].y, xr[t + 2].z, xr[t + 2].w};
+        const T rvv[4] = {rv[t].x, rv[t].y, rv[t].z, rv[t].w};
+        T pr[4] = {T(0), T(0), T(0), T(0)};
+        if (KIND == SW_FULL) { pr[0] = pv[t].x; pr[1] = pv[t].y; pr[2] = pv[t].z; pr[3] = pv[t].w; }
+        T out[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T w = (u == 0) ? left : cv[u - 1];
+            const T ea = (u + 1 < nv) ? cv[min(u + 1, 3)] : right;
+            const T kd = kbx[u] + kby + zb;
+            const T kx = kd * cv[u] + kax[u] * w + kcx[u] * ea + kay * sv[u] + kcy * nvv[u] + za * mv[u] + zcc * uv[u];
+            out[u] = KIND == SW_RESID ? rvv[u] - kx : cv[u] + c1 * (cv[u] - pr[u]) + c2 * (rvv[u] - kx) / kd;
+        }
+        if (done || item >= sg.items || k > nz - 2) continue;
+        T *o = xn + e0 + (size_t)k * plane;
+        if (nv == 4 && sk[t] == 0u) {
+            *reinterpret_cast<V *>(o) = V{out[0], out[1], out[2], out[3]};
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (u < nv && !((sk[t] >> u) & 1u)) o[u] = out[u];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -445,11 +555,11 @@ __global__ void __launch_bounds__(NT) k_apply4(Geom g, Coef<T> cf, Irr<T> ir, co
             const int k1 = min(k0 + tl.TZ, nz - 1);               // output planes [k0, k1)
             const int ic = q.nv > 0 ? q.i0 : 1;
             T ax[4], cxx[4], arx[4], brx[4], crx[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const T *cx = cf.c[0] + 8 * (u < q.nv ? q.i0 + u : 1);
-                ax[u] = cx[0]; cxx[u] = cx[1]; arx[u] = cx[2]; brx[u] = cx[3]; crx[u] = cx[4];
-            }
+            coef_x4(cf, 0, ic, ax);
+            coef_x4(cf, 1, ic, cxx);
+            coef_x4(cf, 2, ic, arx);
+            coef_x4(cf, 3, ic, brx);
+            coef_x4(cf, 4, ic, crx);
             const T *cy = cf.c[1] + 8 * jr;
             const T ay = uniform(cy[0]), cyy = uniform(cy[1]), ary = uniform(cy[2]), bry = uniform(cy[3]),
                     cry = uniform(cy[4]);
@@ -633,8 +743,7 @@ __global__ void __launch_bounds__(NT) k_first4(Geom g, Coef<T> cf, Irr<T> ir, co
     const int ic = q.nv > 0 ? q.i0 : 1;
     const int k0 = 1 + bz * tl.TZ, k1 = min(k0 + tl.TZ, nz - 1);
     T kbx[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) kbx[u] = cf.c[0][8 * (u < q.nv ? q.i0 + u : 1) + 6];
+    coef_x4(cf, 6, ic, kbx);
     const T kby = uniform(cf.c[1][8 * jr + 6]);
     const size_t e0 = (size_t)ic + (size_t)nx * jr, wr = (size_t)jr * g.W + (ic >> 5), wplane = (size_t)ny * g.W;
     for (int k = k0; k < k1; ++k) {
@@ -702,8 +811,7 @@ __global__ void __launch_bounds__(NT) k_update4(Geom g, Coef<T> cf, Irr<T> ir, c
             const int ic = q.nv > 0 ? q.i0 : 1;
             const int k0 = 1 + bz * tl.TZ, k1 = min(k0 + tl.TZ, nz - 1);
             T brx[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) brx[u] = cf.c[0][8 * (u < q.nv ? q.i0 + u : 1) + 3];
+            coef_x4(cf, 3, ic, brx);
             const T bry = uniform(cf.c[1][8 * jr + 3]);
             const size_t e0 = (size_t)ic + (size_t)nx * jr, wr = (size_t)jr * g.W + (ic >> 5),
                          wplane = (size_t)ny * g.W;
@@ -943,24 +1051,54 @@ void launch_apply(int mode, const Launch &L, const Coef<T> &cf, const Irr<T> &ir
 #undef CPS_APPLY_LAUNCH
 }
 
+// Which grids sweep with the short kernel: those whose vectors take at most SHORT_MAX_BYTES, so
+// that the three a sweep touches stay in the 256 MB Infinity Cache together; there its time is
+// its latency.  On larger grids the marching kernel's fewer loads per point win.  Measured (us,
+// first step of a pass / full step, short against marching): FP32 230^3 (47 MB) 27 / 30 against
+// 32 / 34, 256^3 (67 MB) 44 / 53 against 44 / 51; FP64 200^3 (64 MB) 42 / 48 against 45 / 57,
+// 228^3 (95 MB) 77 / 94 against 72 / 92.
+constexpr size_t SHORT_MAX_BYTES = 65000000;
+template <typename T>
+static bool sweeps_short(const Geom &g)
+{
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= SHORT_MAX_BYTES;
+}
+
+template <typename T, int KIND>
+static void launch_short(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *xc, const T *xm1, const T *rho,
+                         T *xn, double c1, double c2, const DevState *st, hipEvent_t ev0, hipEvent_t ev1)
+{
+    constexpr int TZ = 2;
+    const ShortGrid sg = short_grid<TZ>(L.g);
+    const dim3 grid(sg.nblk + irr_blocks(ir.n, NT));
+    if (ev0)
+        hipExtLaunchKernelGGL((k_sweep_short<T, KIND, TZ>), grid, dim3(NT), 0, L.stream, ev0, ev1, 0, L.g, sg, cf, ir,
+                              L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st);
+    else
+        k_sweep_short<T, KIND, TZ><<<grid, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st);
+}
+
 template <typename T>
 void launch_cheb(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *xc, const T *xm1, const T *rho, T *xn,
                  double c1, double c2, const DevState *st, int rev, hipEvent_t ev0, hipEvent_t ev1)
 {
-    dim3 grid(L.g.tr.nblk + irr_blocks(ir.n, NT)), blk = tile_block();
-    const bool mr = L.g.lg < 6;
+    if (sweeps_short<T>(L.g)) {
+        if (xm1) launch_short<T, SW_FULL>(L, cf, ir, xc, xm1, rho, xn, c1, c2, st, ev0, ev1);
+        else launch_short<T, SW_FIRST>(L, cf, ir, xc, xm1, rho, xn, c1, c2, st, ev0, ev1);
+        return;
+    }
+    const dim3 blk = tile_block();
     if (xm1 == nullptr) {
         // the sweep without an x_{k-1} moves less per plane step: RPW2 rows per wavefront
         dim3 grid2(tr2_of<T>(L.g).nblk + irr_blocks(ir.n, NT));
-        if (mr) k_cheb4m<T, true><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st, rev);
-        else if (ev0)
+        if (ev0)
             hipExtLaunchKernelGGL((k_cheb4<T, true, RPW2>), grid2, blk, 0, L.stream, ev0, ev1, 0, L.g, cf, ir, L.skip, xc,
                                   xm1, rho, xn, (T)c1, (T)c2, st, rev);
         else k_cheb4<T, true, RPW2><<<grid2, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st,
                                                                rev);
     } else {
-        if (mr) k_cheb4m<T, false><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st, rev);
-        else if (ev0)
+        dim3 grid(L.g.tr.nblk + irr_blocks(ir.n, NT));
+        if (ev0)
             hipExtLaunchKernelGGL((k_cheb4<T, false>), grid, blk, 0, L.stream, ev0, ev1, 0, L.g, cf, ir, L.skip, xc, xm1,
                                   rho, xn, (T)c1, (T)c2, st, rev);
         else k_cheb4<T, false><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st, rev);
@@ -971,10 +1109,12 @@ template <typename T>
 void launch_resid(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *r,
                   const DevState *st, int rev)
 {
-    dim3 grid(L.g.tr.nblk + irr_blocks(ir.n, NT)), blk = tile_block();
+    if (sweeps_short<T>(L.g)) {
+        launch_short<T, SW_RESID>(L, cf, ir, x, nullptr, rho, r, 0.0, 0.0, st, nullptr, nullptr);
+        return;
+    }
     dim3 grid2(tr2_of<T>(L.g).nblk + irr_blocks(ir.n, NT));
-    if (L.g.lg < 6) k_resid4m<T><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, x, rho, r, st, rev);
-    else k_resid4<T, RPW2><<<grid2, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, x, rho, r, st, rev);
+    k_resid4<T, RPW2><<<grid2, tile_block(), 0, L.stream>>>(L.g, cf, ir, L.skip, x, rho, r, st, rev);
 }
 
 template <typename T>

@@ -142,3 +142,26 @@ def test_spheres8_256_multigrid_vs_oracle_samples():
         print(f"{precision}: {st['iters']} iterations, max rel. difference vs oracle samples {rel:.2e}")
         assert rel <= 1e-9
         S.close()
+
+
+# Grids around the sweep kernels' edges.  Short sweeps: rows that are no multiple of four nodes,
+# rows longer than a wavefront's 256 nodes, an odd and an even number of planes, one plane.
+# Marching sweeps (16.4 M points: more bytes per vector than short sweeps take, in FP64 and in
+# FP32): two row segments, the second ragged.
+@pytest.mark.parametrize("shape,steps", [((19, 18, 20), (1, 2, 5)), ((262, 9, 8), (1, 2, 5)), ((31, 5, 3), (1, 2, 5)),
+                                         ((67, 20, 21), (1, 2, 5)), ((283, 243, 245), (3,))])
+def test_sweeps_match_oracle_on_ragged_grids(shape, steps):
+    grids = tuple(W.tanh_grid(n, 0.9) for n in shape)
+    bodies = [W.Sphere((0.5, 0.5, 0.5), 0.21)] if min(shape) >= 18 else []
+    w = W.polynomial_case(0, bodies, rng_seed=13, grids=grids)
+    print(f"[case] sweeps {shape}", flush=True)
+    P = oracle.Problem.from_workload(w)
+    rho = _random_rho(w.phi.shape, P.types(), 17)
+    for m in steps:
+        lo = 0.01
+        ref = P.precond(rho, m, lo, 2.0)
+        S = cps.Solver.from_workload(w, precond="chebyshev", inner_iters=m, lam_lo=lo)
+        for prec, bar in (("fp64", 1e-11), ("fp32", 1e-5)):
+            got = _np(S.precond(rho, prec))
+            assert np.max(np.abs(got - ref)) <= bar * np.max(np.abs(ref)), (m, prec)
+        S.close()
