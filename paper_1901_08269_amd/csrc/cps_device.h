@@ -114,6 +114,28 @@ struct DevState {
     int iters;                 // completed iterations
 };
 
+// The blocks of the short kernels (sweeps.hip): a thread takes four nodes of a row, SHORT_TZ
+// planes of them; with OVERLAP (stencils) a wavefront computes the inner 62 of the 64 4-node
+// groups it loads.
+constexpr int SHORT_TZ = 2;
+template <bool OVERLAP>
+struct ShortGrid {
+    static constexpr int wave = OVERLAP ? TX - 2 : TX, block = NT / TX * wave;   // groups computed per wave, block
+    int gpr;                   // 4-node groups per row
+    int items, nbx, nbz, nblk; // groups per plane, blocks per SHORT_TZ planes, plane groups, blocks
+};
+template <bool OVERLAP>
+inline ShortGrid<OVERLAP> short_grid(const Geom &g)
+{
+    ShortGrid<OVERLAP> q;
+    q.gpr = (g.nx - 2 + 3) / 4;
+    q.items = q.gpr * (g.ny - 2);
+    q.nbx = (q.items + q.block - 1) / q.block;
+    q.nbz = (g.nz - 2 + SHORT_TZ - 1) / SHORT_TZ;
+    q.nblk = (q.nbx * q.nbz + NXCD - 1) / NXCD * NXCD;
+    return q;
+}
+
 // the tiling of the two-vector sweeps in precision T
 template <typename T>
 __host__ __device__ __forceinline__ const Tiling &tr2_of(const Geom &g)
@@ -146,9 +168,9 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Deterministic block reduction of NV values over NT threads; result valid in thread 0.
-template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double (*sh)[NT / 64])
+// Deterministic block reduction of NV values over NW wavefronts; result valid in thread 0.
+template <int NV, int NW>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double (&sh)[NV][NW])
 {
     int tid = threadIdx.x + threadIdx.y * blockDim.x;
     int lane = tid & 63, wv = tid >> 6;
@@ -162,7 +184,7 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double (*sh)[NT / 64]
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             double s = 0.0;
-            for (int w = 0; w < NT / 64; ++w) s += sh[q][w];
+            for (int w = 0; w < NW; ++w) s += sh[q][w];
             v[q] = s;
         }
     }
@@ -175,7 +197,7 @@ template <int NV>
 __device__ __forceinline__ void write_partials(double (&v)[NV], double *partials)
 {
     __shared__ double sh[NV][NT / 64];
-    block_sum<NV>(v, sh);
+    block_sum(v, sh);
     int tid = threadIdx.x + threadIdx.y * blockDim.x;
     if (tid == 0) {
 #pragma unroll
@@ -183,19 +205,32 @@ __device__ __forceinline__ void write_partials(double (&v)[NV], double *partials
     }
 }
 
-// Fixed-order totals of the NV partial columns over nblocks blocks; valid in thread 0.
+// Fixed-order totals of the NV partial columns over nblocks blocks; valid in thread 0.  One block
+// of FIN_NT threads reads them all, so its time is the memory round trips in a row: a thread loads
+// FIN_AHEAD rows at once, then adds them in order (512 / 4100 / 16400 / 65800 rows: 3.7 / 4.6 / 7.0 /
+// 20 us; 256 threads with one load in flight 4.5 / 7.3 / 24 us for the first three).
+constexpr int FIN_NT = 1024, FIN_AHEAD = 4;
 template <int NV>
 __device__ __forceinline__ void total_partials(double (&tot)[NV], const double *partials, int nblocks)
 {
-    __shared__ double sh[NV][NT / 64];
-    int tid = threadIdx.x + threadIdx.y * blockDim.x;
+    __shared__ double sh[NV][FIN_NT / 64];
+    const int tid = (int)threadIdx.x;
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        double s = 0.0;
-        for (int b = tid; b < nblocks; b += NT) s += partials[(size_t)b * NV + q];
-        tot[q] = s;
+    for (int q = 0; q < NV; ++q) tot[q] = 0.0;
+    for (int b = tid; b < nblocks; b += FIN_AHEAD * FIN_NT) {
+        double v[FIN_AHEAD][NV];
+#pragma unroll
+        for (int u = 0; u < FIN_AHEAD; ++u)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) v[u][q] = partials[(size_t)min(b + u * FIN_NT, nblocks - 1) * NV + q];
+#pragma unroll
+        for (int u = 0; u < FIN_AHEAD; ++u)
+            if (b + u * FIN_NT < nblocks) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) tot[q] += v[u][q];
+            }
     }
-    block_sum<NV>(tot, sh);
+    block_sum(tot, sh);
 }
 
 }  // namespace cps

@@ -3,10 +3,11 @@
 // sweeps of the preconditioner K, and the BiCGSTAB vector updates with their dot products
 // reduced in the same launch (Alg. 1 with the split of Eq. Bdec).
 //
-// Launch shape: the stencil and update kernels run on vectorised rows -- a wavefront owns a
-// 256-node segment of an x-row, four nodes per lane -- in blocks of four wavefronts that
-// march over z-chunks of the interior (XCD-aware tile order); blocks before (or, for the B
-// apply, after) the tiles process the irregular rows; the restart kernel strides over all
+// Launch shape: the stencil and update kernels give a lane four nodes of an x-row.  On large
+// grids the stencils' wavefronts own a 256-node segment of a row and march over z-chunks of the
+// interior; on smaller ones, and in the vector updates everywhere, a thread takes two planes at
+// a time (XCD-aware block order in both); blocks before (or, for the B apply, after) the tiles
+// process the irregular rows; the restart kernel strides over all
 // nodes with 16-byte vectors.  Kernels that reduce write one partial per block; a one-block finalize
 // kernel that follows sums them in a fixed order (deterministic) and updates the
 // device-resident BiCGSTAB scalars, so the host never waits inside an iteration.
@@ -80,13 +81,13 @@ __device__ __forceinline__ AuxT<T, MODE> load_aux(size_t e, const T *__restrict_
 //   FIN_RES     true residual norms ||r||^2, ||D^-1 r||^2
 //   FIN_RESTART rho = r0n2 = (r, r); alpha = beta = 0, omega = 1
 template <int KIND>
-__global__ void __launch_bounds__(NT) k_finalize(const double *partials, int nblocks, DevState *st)
+__global__ void __launch_bounds__(FIN_NT) k_finalize(const double *partials, int nblocks, DevState *st)
 {
     constexpr int NV = (KIND == FIN_RESTART) ? 1 : 2;
     if ((KIND == FIN_V || KIND == FIN_T || KIND == FIN_UPDATE) && st->done) return;
     double tot[NV];
     total_partials<NV>(tot, partials, nblocks);
-    if (threadIdx.x + threadIdx.y * blockDim.x != 0) return;
+    if (threadIdx.x != 0) return;
     if (KIND == FIN_V) {
         double sig = tot[0];
         if (!(sig == sig) || !(tot[NV - 1] == tot[NV - 1])) st->done = 3;
@@ -386,8 +387,9 @@ __global__ void __launch_bounds__(NT) k_resid4(Geom g, Coef<T> cf, Irr<T> ir, co
 // consecutive nodes of a row in TZ planes and issues all of its loads before the first use, so
 // a sweep waits for memory once where the marching kernel (k_cheb4) waits at every plane.
 // Threads take the 4-node groups of a plane's rows in order, whatever the row length, so no
-// lane idles on rows shorter than 256 nodes; x neighbours come from the adjacent lanes, or from
-// memory at the ends of a wavefront and of a row.
+// lane idles on rows shorter than 256 nodes.  A wavefront loads 64 groups and computes the inner
+// 62: x neighbours then always come from the adjacent lanes (beyond a row's ends lie the walls,
+// 0 in every iterate), and no end of a wavefront loads them apart.
 //   SW_FIRST     x_{k+1} from x_k, x_{k-1} = 0            (PREV0 of k_cheb4)
 //   SW_FULL      x_{k+1} from x_k and x_{k-1}
 //   SW_RESID     rho - K x_k
@@ -398,30 +400,43 @@ __global__ void __launch_bounds__(NT) k_resid4(Geom g, Coef<T> cf, Irr<T> ir, co
 // of the prolongation pass (130^3 FP32: 30 + 12 us for the two steps of a pass against 6.5 + 7.5
 // + 7.6: 27 interpolations of neighbours per thread cost more than the pass).
 // ---------------------------------------------------------------------------------------
-struct ShortGrid {
-    int gpr;                   // 4-node groups per row
-    int items, nbx, nbz, nblk; // groups per plane, blocks per plane group, plane groups, blocks
-};
-template <int TZ>
-static ShortGrid short_grid(const Geom &g)
-{
-    ShortGrid q;
-    q.gpr = (g.nx - 2 + 3) / 4;
-    q.items = q.gpr * (g.ny - 2);
-    q.nbx = (q.items + NT - 1) / NT;
-    q.nbz = (g.nz - 2 + TZ - 1) / TZ;
-    q.nblk = (q.nbx * q.nbz + NXCD - 1) / NXCD * NXCD;
-    return q;
-}
 enum { SW_FIRST = 0, SW_FULL = 1, SW_RESID = 2 };
 
-template <typename T, int KIND, int TZ>
-__global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T> cf, Irr<T> ir,
+// The 4-node group and the first of the TZ planes of a thread of a tile block b.
+struct ShortItem {
+    int i0, nv, j, k0;         // first node, valid nodes, row, first plane
+    bool first, last;          // first, last group of its row
+    bool live;                 // computes (not one of a wavefront's two outer lanes)
+    bool ok;                   // the block has work
+};
+template <bool OVERLAP>
+__device__ __forceinline__ ShortItem short_item(const Geom &g, const ShortGrid<OVERLAP> &sg, int b)
+{
+    ShortItem m;
+    const int per = sg.nblk / NXCD, q = (b % NXCD) * per + b / NXCD;
+    m.ok = q < sg.nbx * sg.nbz;
+    const int bz = q / sg.nbx, bx = q - bz * sg.nbx, tid = (int)threadIdx.x, lane = tid & 63;
+    const int item = bx * sg.block + (tid >> 6) * sg.wave + lane - (OVERLAP ? 1 : 0);
+    m.live = (!OVERLAP || (lane >= 1 && lane <= sg.wave)) && item < sg.items;
+    const int it = min(max(item, 0), sg.items - 1);
+    const int row = it / sg.gpr, gx = it - row * sg.gpr;
+    m.j = 1 + row;
+    m.i0 = 1 + 4 * gx;
+    m.nv = min(4, g.nx - 1 - m.i0);
+    m.first = gx == 0;
+    m.last = gx == sg.gpr - 1;
+    m.k0 = 1 + bz * SHORT_TZ;
+    return m;
+}
+
+template <typename T, int KIND>
+__global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid<true> sg, Coef<T> cf, Irr<T> ir,
                                                     const uint32_t *__restrict__ skip, const T *__restrict__ xc,
                                                     const T *xm1, const T *__restrict__ rho, T *xn, T c1, T c2,
                                                     const DevState *st)
 {
     using V = typename Vec4Of<T>::type;
+    constexpr int TZ = SHORT_TZ;
     const int done = st ? st->done : 0;   // used before the stores: nothing waits for it
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t plane = (size_t)nx * ny;
@@ -445,21 +460,15 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T
         if (!done) xn[e] = KIND == SW_RESID ? rh - kx : z0 + c1 * (z0 - prev) + c2 * (rh - kx) / kr[0];
         return;
     }
-    const int per = sg.nblk / NXCD, q = (b % NXCD) * per + b / NXCD;
-    if (q >= sg.nbx * sg.nbz) return;
-    const int bz = q / sg.nbx, bx = q - bz * sg.nbx;
-    const int item = bx * NT + tid, it = min(item, sg.items - 1);
-    const int row = it / sg.gpr, gx = it - row * sg.gpr;
-    const int j = 1 + row, i0 = 1 + 4 * gx, nv = min(4, nx - 1 - i0), k0 = 1 + bz * TZ;
-    const int lane = tid & 63;
-    const bool need_l = lane == 0 || gx == 0, need_r = lane == 63 || gx == sg.gpr - 1;
+    const ShortItem m = short_item(g, sg, b);
+    if (!m.ok) return;
+    const int j = m.j, i0 = m.i0, nv = m.nv, k0 = m.k0;
     const size_t e0 = (size_t)i0 + (size_t)nx * j;           // at plane 0
     int kp[TZ + 2];                                            // planes k0 - 1 .. k0 + TZ, inside the grid
 #pragma unroll
     for (int p = 0; p < TZ + 2; ++p) kp[p] = min(k0 - 1 + p, nz - 1);
     // ---- all loads
     V xr[TZ + 2], ys[TZ], yn[TZ], rv[TZ], pv[TZ];
-    T lf[TZ], rt[TZ];
     uint32_t sk[TZ];
     const uint32_t *srow = skip + (size_t)j * g.W + (i0 >> 5);
     const size_t wplane = (size_t)ny * g.W;
@@ -470,8 +479,6 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T
         const size_t e = e0 + (size_t)kp[t + 1] * plane;
         ys[t] = *reinterpret_cast<const V *>(xc + e - nx);
         yn[t] = *reinterpret_cast<const V *>(xc + e + nx);
-        lf[t] = xc[need_l ? e - 1 : e];
-        rt[t] = xc[need_r ? e + nv : e];
         rv[t] = *reinterpret_cast<const V *>(rho + e);
         if (KIND == SW_FULL) pv[t] = *reinterpret_cast<const V *>(xm1 + e);
         sk[t] = skip4(srow + (size_t)kp[t + 1] * wplane, i0);
@@ -489,8 +496,8 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T
         const T za = cz[5], zb = cz[6], zcc = cz[7];
         const T cv[4] = {xr[t + 1].x, xr[t + 1].y, xr[t + 1].z, xr[t + 1].w};
         T left = __shfl_up(cv[3], 1, TX), right = __shfl_down(cv[0], 1, TX);
-        if (need_l) left = lf[t];
-        if (need_r) right = rt[t];
+        if (m.first) left = T(0);
+        if (m.last) right = T(0);
         const T sv[4] = {ys[t].x, ys[t].y, ys[t].z, ys[t].w}, nvv[4] = {yn[t].x, yn[t].y, yn[t].z, yn[t].w};
         const T mv[4] = {xr[t].x, xr[t].y, xr[t].z, xr[t].w}, uv[4] = {xr[t + 2].x, xr[t + 2].y, xr[t + 2].z, xr[t + 2].w};
         const T rvv[4] = {rv[t].x, rv[t].y, rv[t].z, rv[t].w};
@@ -505,7 +512,7 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T
             const T kx = kd * cv[u] + kax[u] * w + kcx[u] * ea + kay * sv[u] + kcy * nvv[u] + za * mv[u] + zcc * uv[u];
             out[u] = KIND == SW_RESID ? rvv[u] - kx : cv[u] + c1 * (cv[u] - pr[u]) + c2 * (rvv[u] - kx) / kd;
         }
-        if (done || item >= sg.items || k > nz - 2) continue;
+        if (done || !m.live || k > nz - 2) continue;
         T *o = xn + e0 + (size_t)k * plane;
         if (nv == 4 && sk[t] == 0u) {
             *reinterpret_cast<V *>(o) = V{out[0], out[1], out[2], out[3]};
@@ -528,6 +535,44 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid sg, Coef<T
 // per plane measured no faster).  Irregular rows gather their stored full row of B in the
 // blocks after the tiles, IRR_LANES lanes per row.
 // ---------------------------------------------------------------------------------------
+// One block of the B apply's irregular rows: IRR_LANES lanes per row gather the full row of B,
+// four entries per lane at a time (their column and value loads, then their x loads, are issued
+// together: three dependent memory round trips for a row of up to 64 entries).
+template <typename T, typename TO, int MODE>
+__device__ __forceinline__ void irregular_rows(const Irr<T> &ir, int irr_block, int tid, const T *__restrict__ x,
+                                               TO *__restrict__ y, const T *__restrict__ w,
+                                               const double *__restrict__ bvec, double (&acc)[2], bool done)
+{
+    const int row = irr_block * (NT / IRR_LANES) + tid / IRR_LANES;
+    const int il = tid % IRR_LANES;
+    double sacc = 0.0;
+    if (row < ir.n) {
+        const int p0 = ir.ptr[row], p1 = ir.ptr[row + 1];
+        for (int e = p0 + il; e < p1; e += 4 * IRR_LANES) {
+            int c[4];
+            T v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int ee = e + t * IRR_LANES;
+                const int ec = ee < p1 ? ee : p0;       // entries past the row end read entry p0
+                c[t] = ir.col[ec];
+                const T vv = ir.val[ec];
+                v[t] = ee < p1 ? vv : T(0);
+            }
+            T xv[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) xv[t] = x[c[t]];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sacc += (double)v[t] * (double)xv[t];
+        }
+    }
+    for (int o = IRR_LANES / 2; o > 0; o >>= 1) sacc += __shfl_xor(sacc, o, IRR_LANES);
+    if (row < ir.n && il == 0 && !done) {
+        const size_t e = (size_t)ir.node[row];
+        emit<T, TO, MODE>(e, (T)sacc, (double)ir.bdiag[row], load_aux<T, MODE>(e, w, bvec), y, acc);
+    }
+}
+
 template <typename T, typename TO, int MODE>
 __global__ void __launch_bounds__(NT) k_apply4(Geom g, Coef<T> cf, Irr<T> ir, const uint32_t *__restrict__ skip,
                                                const T *__restrict__ x, TO *__restrict__ y, const T *__restrict__ w,
@@ -661,113 +706,218 @@ __global__ void __launch_bounds__(NT) k_apply4(Geom g, Coef<T> cf, Irr<T> ir, co
             }
         }
     } else {
-        // irregular rows: IRR_LANES lanes per row gather the full row of B, four entries per
-        // lane at a time (their column and value loads, then their x loads, are issued
-        // together: three dependent memory round trips for a row of up to 64 entries)
-        const int rows_per_block = NT / IRR_LANES;
-        const int row = irr_block * rows_per_block + tid / IRR_LANES;
-        const int il = tid % IRR_LANES;
-        double sacc = 0.0;
-        if (row < ir.n) {
-            const int p0 = ir.ptr[row], p1 = ir.ptr[row + 1];
-            for (int e = p0 + il; e < p1; e += 4 * IRR_LANES) {
-                int c[4];
-                T v[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int ee = e + t * IRR_LANES;
-                    const int ec = ee < p1 ? ee : p0;       // entries past the row end read entry p0
-                    c[t] = ir.col[ec];
-                    const T vv = ir.val[ec];
-                    v[t] = ee < p1 ? vv : T(0);
-                }
-                T xv[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) xv[t] = x[c[t]];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) sacc += (double)v[t] * (double)xv[t];
-            }
-        }
-        for (int o = IRR_LANES / 2; o > 0; o >>= 1) sacc += __shfl_xor(sacc, o, IRR_LANES);
-        if (row < ir.n && il == 0) {
-            const size_t e = (size_t)ir.node[row];
-            emit<T, TO, MODE>(e, (T)sacc, (double)ir.bdiag[row], load_aux<T, MODE>(e, w, bvec), y, acc);
-        }
+        irregular_rows<T, TO, MODE>(ir, irr_block, tid, x, y, w, bvec, acc, false);
     }
     if constexpr (NV > 0) write_partials<2>(acc, partials);
 }
 
 // ---------------------------------------------------------------------------------------
-// Vector updates of Alg. 1 on vectorised rows:
-//   k_first4 FIRST_P  p = r + beta (p - omega v)   (search direction; p = r after a (re)start:
-//                                                  beta = 0)
-//            FIRST_S  s = r - alpha v              (intermediate residual)
-//            then x_1 = c2 * (p or s) / diag(K), the first Chebyshev step from x_0 = 0
-//   k_update4         u += alpha p^ + omega s^, r = s - omega t, partials of (r0, r) and of
-//                     ||D^-1 r||^2 (D = diag B); the finalize kernel forms beta and tests
-//                     convergence
-// A wavefront owns one row of a 256-node segment, four nodes per lane, and walks its
-// z-chunk.  The diagonals of K and B are formed from the 1D tables with the x coefficients
-// held per lane and the y and z coefficients wave-uniform, so no node index is ever
-// decoded.  Walls are not touched (zero in every vector); irregular rows (their own
-// diagonals) run in the leading blocks, one thread per row.
+// The B apply in the short form (k_sweep_short says what that is), on small grids: a thread
+// loads its group on rows j - 1 .. j + 1 of planes k0 - 1 .. k0 + TZ at once and forms the same
+// x, y and z filters as k_apply4.  It filters every row twice as often, which is what bounds it
+// (apply_short says where that pays).
 // ---------------------------------------------------------------------------------------
-template <typename T, int KIND>
-__global__ void __launch_bounds__(NT) k_first4(Geom g, Coef<T> cf, Irr<T> ir, const uint32_t *__restrict__ skip,
-                                               const T *__restrict__ r, T *__restrict__ ps, const T *__restrict__ v,
-                                               T *__restrict__ x1, T c2, const DevState *st)
+template <typename T, typename TO, int MODE>
+__global__ void __launch_bounds__(NT) k_apply_short(Geom g, ShortGrid<true> sg, Coef<T> cf, Irr<T> ir,
+                                                    const uint32_t *__restrict__ skip, const T *__restrict__ x,
+                                                    TO *__restrict__ y, const T *__restrict__ w,
+                                                    const double *__restrict__ bvec, DevState *st, double *partials)
 {
     using V = typename Vec4Of<T>::type;
-    if (st->done) return;
-    const T alpha = (T)st->alpha, beta = (T)st->beta, omega = (T)st->omega;
-    const int lane = threadIdx.x, wv = threadIdx.y;
+    constexpr int NV = (MODE == MODE_PLAIN) ? 0 : 2, TZ = SHORT_TZ;
+    const int done = (MODE != MODE_PLAIN && MODE != MODE_RES) ? st->done : 0;   // used before the stores
+    double acc[2] = {0.0, 0.0};
+    const int tid = (int)threadIdx.x;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t plane = (size_t)nx * ny;
-    const int nib = irr_blocks(ir.n, NT);
-    const int b = (int)blockIdx.x - nib;
+    if ((int)blockIdx.x < sg.nblk) {
+        const ShortItem m = short_item(g, sg, (int)blockIdx.x);
+        if (m.ok) {
+            const int j = m.j, i0 = m.i0, nv = m.nv;
+            const size_t e0 = (size_t)i0 + (size_t)nx * j;
+            V xr[3][TZ + 2];
+            int kp[TZ + 2];
+#pragma unroll
+            for (int p = 0; p < TZ + 2; ++p) {
+                kp[p] = min(m.k0 - 1 + p, nz - 1);
+                const T *c = x + e0 + (size_t)kp[p] * plane;
+                xr[0][p] = *reinterpret_cast<const V *>(c - nx);
+                xr[1][p] = *reinterpret_cast<const V *>(c);
+                xr[2][p] = *reinterpret_cast<const V *>(c + nx);
+            }
+            uint32_t sk[TZ];
+            AuxT<T, MODE> aux[TZ][4];
+            const uint32_t *srow = skip + (size_t)j * g.W + (i0 >> 5);
+#pragma unroll
+            for (int t = 0; t < TZ; ++t) {
+                const size_t e = e0 + (size_t)kp[t + 1] * plane;
+                sk[t] = skip4(srow + (size_t)kp[t + 1] * ny * g.W, i0);
+                if (MODE == MODE_RES) {
+                    const typename Vec4Of<double>::type b4 = *reinterpret_cast<const typename Vec4Of<double>::type *>(bvec + e);
+                    aux[t][0] = b4.x; aux[t][1] = b4.y; aux[t][2] = b4.z; aux[t][3] = b4.w;
+                } else if (MODE == MODE_V || MODE == MODE_T) {
+                    const V a4 = *reinterpret_cast<const V *>(w + e);
+                    aux[t][0] = a4.x; aux[t][1] = a4.y; aux[t][2] = a4.z; aux[t][3] = a4.w;
+                }
+            }
+            T ax[4], cxx[4], arx[4], brx[4], crx[4];
+            coef_x4(cf, 0, i0, ax);
+            coef_x4(cf, 1, i0, cxx);
+            coef_x4(cf, 2, i0, arx);
+            coef_x4(cf, 3, i0, brx);
+            coef_x4(cf, 4, i0, crx);
+            const T *cy = cf.c[1] + 8 * j;
+            const T ay = cy[0], cyy = cy[1], ary = cy[2], bry = cy[3], cry = cy[4];
+            T LL[TZ + 2][4], LR[TZ + 2][4];
+#pragma unroll
+            for (int p = 0; p < TZ + 2; ++p) {
+                T uL[3][4], uR[3][4];
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    const T cv[4] = {xr[r][p].x, xr[r][p].y, xr[r][p].z, xr[r][p].w};
+                    T left = __shfl_up(cv[3], 1, TX), right = __shfl_down(cv[0], 1, TX);
+                    if (m.first) left = T(0);
+                    if (m.last) right = T(0);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const T wm = (u == 0) ? left : cv[u - 1];
+                        const T ep = (u + 1 < nv) ? cv[min(u + 1, 3)] : right;
+                        uL[r][u] = ax[u] * wm + cv[u] + cxx[u] * ep;
+                        uR[r][u] = arx[u] * wm + brx[u] * cv[u] + crx[u] * ep;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    LL[p][u] = ay * uL[0][u] + uL[1][u] + cyy * uL[2][u];
+                    LR[p][u] = (ay * uR[0][u] + uR[1][u] + cyy * uR[2][u]) +
+                               (ary * uL[0][u] + bry * uL[1][u] + cry * uL[2][u]);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < TZ; ++t) {
+                const int k = m.k0 + t;
+                const T *cz = cf.c[2] + 8 * kp[t + 1];
+                const T az = cz[0], ccz = cz[1], arz = cz[2], brz = cz[3], crz = cz[4];
+                if (done || !m.live || k > nz - 2) continue;
+                TO o[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const T v = az * LR[t][u] + LR[t + 1][u] + ccz * LR[t + 2][u] + arz * LL[t][u] + brz * LL[t + 1][u] +
+                                crz * LL[t + 2][u];
+                    const bool on = u < nv && !((sk[t] >> u) & 1u);
+                    if (MODE == MODE_RES) {
+                        const double r = (double)aux[t][u] - (double)v, rd = r / (double)(brx[u] + bry + brz);
+                        o[u] = (TO)r;
+                        if (on) { acc[0] += r * r; acc[1] += rd * rd; }
+                    } else {
+                        o[u] = (TO)v;
+                        if ((MODE == MODE_V || MODE == MODE_T) && on) {
+                            acc[0] += (double)aux[t][u] * (double)v;
+                            acc[1] += (double)v * (double)v;
+                        }
+                    }
+                }
+                TO *yo = y + e0 + (size_t)k * plane;
+                if (nv == 4 && sk[t] == 0u) {
+                    *reinterpret_cast<typename Vec4Of<TO>::type *>(yo) = typename Vec4Of<TO>::type{o[0], o[1], o[2], o[3]};
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (u < nv && !((sk[t] >> u) & 1u)) yo[u] = o[u];
+                }
+            }
+        }
+    } else {
+        irregular_rows<T, TO, MODE>(ir, (int)blockIdx.x - sg.nblk, tid, x, y, w, bvec, acc, done != 0);
+    }
+    if (done) return;
+    if constexpr (NV > 0) write_partials<2>(acc, partials);
+}
+
+// ---------------------------------------------------------------------------------------
+// Vector updates of Alg. 1:
+//   k_first4 FIRST_P  p = r + beta (p - omega v)   (search direction; p = r after a (re)start:
+//                                                 beta = 0)
+//           FIRST_S  s = r - alpha v              (intermediate residual)
+//           then x_1 = c2 * (p or s) / diag(K), the first Chebyshev step from x_0 = 0
+//   k_update4         u += alpha p^ + omega s^, r = s - omega t, partials of (r0, r) and of
+//                    ||D^-1 r||^2 (D = diag B); the finalize kernel forms beta and tests
+//                    convergence
+// A thread takes four nodes of a row in SHORT_TZ planes, all loads issued at once; blocks follow
+// each other in memory, which the HBM rewards on large grids.  The diagonals of K and B are
+// formed from the 1D tables.  Walls are not touched (zero in every
+// vector); irregular rows (their own diagonals) run in the leading blocks, one thread per row.
+// Bound by HBM once the vectors leave the caches.  FP32, against the version that gave a row
+// segment of 256 nodes a wavefront and walked a 16th of the planes one by one (us, k_update4 /
+// FIRST_P / FIRST_S): 202^3 40 / 28 / 24 against 51 / 34 / 28; 256^3 91 / 62 / 47 against 92 / 64 / 49;
+// 512^3 858 / 580 / 455 (5.0 TB/s) against 980 / 650 / 549; FP64 202^3 92 / 71 / 55 against 112 / 79 /
+// 65.  Walking more than one such group per block, along the planes or within one, gives the
+// 512^3 gain back (930 .. 970), for fewer partials.
+// ---------------------------------------------------------------------------------------
+template <typename T, int KIND>
+__global__ void __launch_bounds__(NT) k_first4(Geom g, ShortGrid<false> sg, Coef<T> cf, Irr<T> ir,
+                                              const uint32_t *__restrict__ skip, const T *__restrict__ r,
+                                              T *__restrict__ ps, const T *__restrict__ v, T *__restrict__ x1, T c2,
+                                              const DevState *st)
+{
+    using V = typename Vec4Of<T>::type;
+    constexpr int TZ = SHORT_TZ;
+    const int done = st->done;            // used before the stores: nothing waits for it
+    const T alpha = (T)st->alpha, beta = (T)st->beta, omega = (T)st->omega;
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const size_t plane = (size_t)nx * ny;
+    const int nib = irr_blocks(ir.n, NT), b = (int)blockIdx.x - nib;
     if (b < 0) {
-        const int row = (int)blockIdx.x * NT + (int)threadIdx.x + wv * TX;
-        if (row >= ir.n) return;
+        const int row = (int)blockIdx.x * NT + (int)threadIdx.x;
+        if (row >= ir.n || done) return;
         const int e = ir.node[row];
         const T val = (KIND == FIRST_P) ? r[e] + beta * (ps[e] - omega * v[e]) : r[e] - alpha * v[e];
         ps[e] = val;
         x1[e] = c2 * val / ir.k7[7 * row];
         return;
     }
-    const Tiling &tl = g.ta;
-    int bs, by, bz;
-    if (!tile_of_block(tl, b, bs, by, bz)) return;
-    const int jr = 1 + by * TY + wv;
-    if (jr > ny - 2) return;
-    const Seg q = seg_of(nx, bs, lane);
-    const int ic = q.nv > 0 ? q.i0 : 1;
-    const int k0 = 1 + bz * tl.TZ, k1 = min(k0 + tl.TZ, nz - 1);
+    const ShortItem m = short_item(g, sg, b);
+    if (!m.ok) return;
+    const size_t e0 = (size_t)m.i0 + (size_t)nx * m.j;
+    const uint32_t *srow = skip + (size_t)m.j * g.W + (m.i0 >> 5);
     T kbx[4];
-    coef_x4(cf, 6, ic, kbx);
-    const T kby = uniform(cf.c[1][8 * jr + 6]);
-    const size_t e0 = (size_t)ic + (size_t)nx * jr, wr = (size_t)jr * g.W + (ic >> 5), wplane = (size_t)ny * g.W;
-    for (int k = k0; k < k1; ++k) {
+    coef_x4(cf, 6, m.i0, kbx);
+    const T kby = cf.c[1][8 * m.j + 6];
+    V r4[TZ], v4[TZ], p4[TZ];
+    uint32_t sk[TZ];
+    T kz[TZ];
+#pragma unroll
+    for (int t = 0; t < TZ; ++t) {
+        const int k = min(m.k0 + t, nz - 1);
         const size_t e = e0 + (size_t)k * plane;
-        const V r4 = load4(r, e, q), v4 = load4(v, e, q);
-        V p4 = {T(0), T(0), T(0), T(0)};
-        if (KIND == FIRST_P) p4 = load4(ps, e, q);
-        const uint32_t sk = skip4(skip + (size_t)k * wplane + wr, ic);
-        const T kz = uniform(cf.c[2][8 * k + 6]);
-        const T rv[4] = {r4.x, r4.y, r4.z, r4.w}, vv[4] = {v4.x, v4.y, v4.z, v4.w}, pv[4] = {p4.x, p4.y, p4.z, p4.w};
+        r4[t] = *reinterpret_cast<const V *>(r + e);
+        v4[t] = *reinterpret_cast<const V *>(v + e);
+        if (KIND == FIRST_P) p4[t] = *reinterpret_cast<const V *>(ps + e);
+        sk[t] = skip4(srow + (size_t)k * ny * g.W, m.i0);
+        kz[t] = cf.c[2][8 * k + 6];
+    }
+    if (done || !m.live) return;
+#pragma unroll
+    for (int t = 0; t < TZ; ++t) {
+        const int k = m.k0 + t;
+        if (k > nz - 2) break;
+        const T rv[4] = {r4[t].x, r4[t].y, r4[t].z, r4[t].w}, vv[4] = {v4[t].x, v4[t].y, v4[t].z, v4[t].w};
+        T pv[4] = {T(0), T(0), T(0), T(0)};
+        if (KIND == FIRST_P) { pv[0] = p4[t].x; pv[1] = p4[t].y; pv[2] = p4[t].z; pv[3] = p4[t].w; }
         T out[4], xo[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             out[u] = (KIND == FIRST_P) ? rv[u] + beta * (pv[u] - omega * vv[u]) : rv[u] - alpha * vv[u];
-            xo[u] = c2 * out[u] / (kbx[u] + kby + kz);
+            xo[u] = c2 * out[u] / (kbx[u] + kby + kz[t]);
         }
-        if (q.full && sk == 0u) {
-            V o = {out[0], out[1], out[2], out[3]}, xq = {xo[0], xo[1], xo[2], xo[3]};
-            *reinterpret_cast<V *>(ps + e) = o;
-            *reinterpret_cast<V *>(x1 + e) = xq;
+        const size_t e = e0 + (size_t)k * plane;
+        if (m.nv == 4 && sk[t] == 0u) {
+            *reinterpret_cast<V *>(ps + e) = V{out[0], out[1], out[2], out[3]};
+            *reinterpret_cast<V *>(x1 + e) = V{xo[0], xo[1], xo[2], xo[3]};
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (u < q.nv && !((sk >> u) & 1u)) {
+                if (u < m.nv && !((sk[t] >> u) & 1u)) {
                     ps[e + u] = out[u];
                     x1[e + u] = xo[u];
                 }
@@ -776,75 +926,84 @@ __global__ void __launch_bounds__(NT) k_first4(Geom g, Coef<T> cf, Irr<T> ir, co
 }
 
 template <typename T>
-__global__ void __launch_bounds__(NT) k_update4(Geom g, Coef<T> cf, Irr<T> ir, const uint32_t *__restrict__ skip,
-                                                T *__restrict__ xs, const T *__restrict__ ph, const T *__restrict__ sh,
-                                                const T *__restrict__ s, const T *__restrict__ t,
-                                                const T *__restrict__ r0, T *__restrict__ r, DevState *st,
-                                                double *partials)
+__global__ void __launch_bounds__(NT) k_update4(Geom g, ShortGrid<false> sg, Coef<T> cf, Irr<T> ir,
+                                               const uint32_t *__restrict__ skip, T *__restrict__ xs,
+                                               const T *__restrict__ ph, const T *__restrict__ sh,
+                                               const T *__restrict__ s, const T *__restrict__ t_,
+                                               const T *__restrict__ r0, T *__restrict__ r, DevState *st,
+                                               double *partials)
 {
     using V = typename Vec4Of<T>::type;
-    if (st->done) return;
+    constexpr int TZ = SHORT_TZ;
+    const int done = st->done;            // used before the stores: nothing waits for it
     const T alphaT = (T)st->alpha, omegaT = (T)st->omega;
     double acc[2] = {0.0, 0.0};
-    const int lane = threadIdx.x, wv = threadIdx.y;
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t plane = (size_t)nx * ny;
-    const int nib = irr_blocks(ir.n, NT);
-    const int b = (int)blockIdx.x - nib;
+    const int nib = irr_blocks(ir.n, NT), b = (int)blockIdx.x - nib;
     if (b < 0) {
         // irregular rows: x and r are updated by the tiles like every node; here only the
         // Jacobi-weighted norm with the row's own diagonal
-        const int row = (int)blockIdx.x * NT + (int)threadIdx.x + wv * TX;
+        const int row = (int)blockIdx.x * NT + (int)threadIdx.x;
         if (row < ir.n) {
             const int e = ir.node[row];
-            const T rv = s[e] - omegaT * t[e];
+            const T rv = s[e] - omegaT * t_[e];
             const double rd = (double)rv / (double)ir.bdiag[row];
             acc[1] += rd * rd;
         }
     } else {
-        const Tiling &tl = g.ta;
-        int bs, by, bz;
-        const bool tile = tile_of_block(tl, b, bs, by, bz);
-        const int jr = tile ? 1 + by * TY + wv : ny;
-        if (jr <= ny - 2) {
-            const Seg q = seg_of(nx, bs, lane);
-            const int ic = q.nv > 0 ? q.i0 : 1;
-            const int k0 = 1 + bz * tl.TZ, k1 = min(k0 + tl.TZ, nz - 1);
+        const ShortItem m = short_item(g, sg, b);
+        if (m.ok) {
+            const int k0 = m.k0;
+            const size_t e0 = (size_t)m.i0 + (size_t)nx * m.j;
+            const uint32_t *srow = skip + (size_t)m.j * g.W + (m.i0 >> 5);
             T brx[4];
-            coef_x4(cf, 3, ic, brx);
-            const T bry = uniform(cf.c[1][8 * jr + 3]);
-            const size_t e0 = (size_t)ic + (size_t)nx * jr, wr = (size_t)jr * g.W + (ic >> 5),
-                         wplane = (size_t)ny * g.W;
-            for (int k = k0; k < k1; ++k) {
+            coef_x4(cf, 3, m.i0, brx);
+            const T bry = cf.c[1][8 * m.j + 3];
+            V x4[TZ], p4[TZ], h4[TZ], s4[TZ], t4[TZ], z4[TZ];
+            uint32_t sk[TZ];
+            T bz[TZ];
+#pragma unroll
+            for (int t = 0; t < TZ; ++t) {
+                const int k = min(k0 + t, nz - 1);
                 const size_t e = e0 + (size_t)k * plane;
-                const V x4 = load4(xs, e, q), p4 = load4(ph, e, q), h4 = load4(sh, e, q), s4 = load4(s, e, q),
-                        t4 = load4(t, e, q), z4 = load4(r0, e, q);
-                const uint32_t sk = skip4(skip + (size_t)k * wplane + wr, ic);
-                const T brz = uniform(cf.c[2][8 * k + 3]);
-                const T xv[4] = {x4.x, x4.y, x4.z, x4.w}, pv[4] = {p4.x, p4.y, p4.z, p4.w},
-                        hv[4] = {h4.x, h4.y, h4.z, h4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w},
-                        tv[4] = {t4.x, t4.y, t4.z, t4.w}, zv[4] = {z4.x, z4.y, z4.z, z4.w};
+                x4[t] = *reinterpret_cast<const V *>(xs + e);
+                p4[t] = *reinterpret_cast<const V *>(ph + e);
+                h4[t] = *reinterpret_cast<const V *>(sh + e);
+                s4[t] = *reinterpret_cast<const V *>(s + e);
+                t4[t] = *reinterpret_cast<const V *>(t_ + e);
+                z4[t] = *reinterpret_cast<const V *>(r0 + e);
+                sk[t] = skip4(srow + (size_t)k * ny * g.W, m.i0);
+                bz[t] = cf.c[2][8 * k + 3];
+            }
+#pragma unroll
+            for (int t = 0; t < TZ; ++t) {
+                const int k = k0 + t;
+                if (done || !m.live || k > nz - 2) continue;
+                const T xv[4] = {x4[t].x, x4[t].y, x4[t].z, x4[t].w}, pv[4] = {p4[t].x, p4[t].y, p4[t].z, p4[t].w},
+                        hv[4] = {h4[t].x, h4[t].y, h4[t].z, h4[t].w}, sv[4] = {s4[t].x, s4[t].y, s4[t].z, s4[t].w},
+                        tv[4] = {t4[t].x, t4[t].y, t4[t].z, t4[t].w}, zv[4] = {z4[t].x, z4[t].y, z4[t].z, z4[t].w};
                 T xo[4], ro[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     xo[u] = xv[u] + (alphaT * pv[u] + omegaT * hv[u]);
                     ro[u] = sv[u] - omegaT * tv[u];
-                    if (u < q.nv) {
+                    if (u < m.nv) {
                         acc[0] += (double)zv[u] * (double)ro[u];
-                        if (!((sk >> u) & 1u)) {
-                            const double rd = (double)ro[u] / ((double)brx[u] + (double)bry + (double)brz);
+                        if (!((sk[t] >> u) & 1u)) {
+                            const double rd = (double)ro[u] / ((double)brx[u] + (double)bry + (double)bz[t]);
                             acc[1] += rd * rd;
                         }
                     }
                 }
-                if (q.full) {
-                    V xq = {xo[0], xo[1], xo[2], xo[3]}, rq = {ro[0], ro[1], ro[2], ro[3]};
-                    *reinterpret_cast<V *>(xs + e) = xq;
-                    *reinterpret_cast<V *>(r + e) = rq;
+                const size_t e = e0 + (size_t)k * plane;
+                if (m.nv == 4) {
+                    *reinterpret_cast<V *>(xs + e) = V{xo[0], xo[1], xo[2], xo[3]};
+                    *reinterpret_cast<V *>(r + e) = V{ro[0], ro[1], ro[2], ro[3]};
                 } else {
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
-                        if (u < q.nv) {
+                        if (u < m.nv) {
                             xs[e + u] = xo[u];
                             r[e + u] = ro[u];
                         }
@@ -852,6 +1011,7 @@ __global__ void __launch_bounds__(NT) k_update4(Geom g, Coef<T> cf, Irr<T> ir, c
             }
         }
     }
+    if (done) return;
     write_partials<2>(acc, partials);
 }
 
@@ -1017,20 +1177,49 @@ __global__ void k_scale(size_t n, double *__restrict__ x, double alpha)
 // ---------------------------------------------------------------------------------------
 static inline dim3 tile_block() { return dim3(TX, TY, 1); }
 
+// Which grids sweep with the short kernel: those whose vectors take at most SHORT_MAX_BYTES, so
+// that the three a sweep touches stay in the 256 MB Infinity Cache together; there its time is
+// its latency.  On larger grids the marching kernel's fewer loads per point win.  Measured (us,
+// first step of a pass / full step, short against marching): FP32 230^3 (47 MB) 27 / 30 against
+// 32 / 34, 256^3 (67 MB) 44 / 53 against 44 / 51; FP64 200^3 (64 MB) 42 / 48 against 45 / 57,
+// 228^3 (95 MB) 77 / 94 against 72 / 92.
+constexpr size_t SHORT_MAX_BYTES = 65000000;
+template <typename T>
+static bool sweeps_short(const Geom &g)
+{
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= SHORT_MAX_BYTES;
+}
+
+// The B apply in the short form up to APPLY_SHORT_BYTES per vector.  Measured (us, short against
+// marching): 32^3 FP64 6.0 against 9.1; 130^3 FP32 13.6 against 15.2, FP64 17.9 against 21.6; 202^3
+// FP32 (32 MB) 40 against 34, FP64 (64 MB) 73 against 65.
+constexpr size_t APPLY_SHORT_BYTES = 20000000;
+template <typename T>
+static bool apply_short(const Geom &g)
+{
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= APPLY_SHORT_BYTES;
+}
+
 template <int KIND>
 static void finalize(const Launch &L, int nb, DevState *st)
 {
-    k_finalize<KIND><<<1, tile_block(), 0, L.stream>>>(L.partials, nb, st);
+    k_finalize<KIND><<<1, FIN_NT, 0, L.stream>>>(L.partials, nb, st);
 }
 
 template <typename T, typename TO>
 void launch_apply(int mode, const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, TO *y, const T *w,
                   const double *bvec, DevState *st)
 {
-    int nb = L.g.ta.nblk + irr_blocks(ir.n, NT / IRR_LANES);
-    dim3 grid(nb), blk = tile_block();
-#define CPS_APPLY_LAUNCH(M) \
-    k_apply4<T, TO, M><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, x, y, w, bvec, st, L.partials)
+    const bool shrt = apply_short<T>(L.g);
+    const ShortGrid<true> sg = short_grid<true>(L.g);
+    const int nb = (shrt ? sg.nblk : L.g.ta.nblk) + irr_blocks(ir.n, NT / IRR_LANES);
+#define CPS_APPLY_LAUNCH(M)                                                                                            \
+    do {                                                                                                               \
+        if (shrt)                                                                                                      \
+            k_apply_short<T, TO, M><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, x, y, w, bvec, st, L.partials);  \
+        else                                                                                                           \
+            k_apply4<T, TO, M><<<nb, tile_block(), 0, L.stream>>>(L.g, cf, ir, L.skip, x, y, w, bvec, st, L.partials); \
+    } while (0)
     switch (mode) {
     case MODE_PLAIN:
         CPS_APPLY_LAUNCH(MODE_PLAIN);
@@ -1051,31 +1240,17 @@ void launch_apply(int mode, const Launch &L, const Coef<T> &cf, const Irr<T> &ir
 #undef CPS_APPLY_LAUNCH
 }
 
-// Which grids sweep with the short kernel: those whose vectors take at most SHORT_MAX_BYTES, so
-// that the three a sweep touches stay in the 256 MB Infinity Cache together; there its time is
-// its latency.  On larger grids the marching kernel's fewer loads per point win.  Measured (us,
-// first step of a pass / full step, short against marching): FP32 230^3 (47 MB) 27 / 30 against
-// 32 / 34, 256^3 (67 MB) 44 / 53 against 44 / 51; FP64 200^3 (64 MB) 42 / 48 against 45 / 57,
-// 228^3 (95 MB) 77 / 94 against 72 / 92.
-constexpr size_t SHORT_MAX_BYTES = 65000000;
-template <typename T>
-static bool sweeps_short(const Geom &g)
-{
-    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= SHORT_MAX_BYTES;
-}
-
 template <typename T, int KIND>
 static void launch_short(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *xc, const T *xm1, const T *rho,
                          T *xn, double c1, double c2, const DevState *st, hipEvent_t ev0, hipEvent_t ev1)
 {
-    constexpr int TZ = 2;
-    const ShortGrid sg = short_grid<TZ>(L.g);
+    const ShortGrid<true> sg = short_grid<true>(L.g);
     const dim3 grid(sg.nblk + irr_blocks(ir.n, NT));
     if (ev0)
-        hipExtLaunchKernelGGL((k_sweep_short<T, KIND, TZ>), grid, dim3(NT), 0, L.stream, ev0, ev1, 0, L.g, sg, cf, ir,
+        hipExtLaunchKernelGGL((k_sweep_short<T, KIND>), grid, dim3(NT), 0, L.stream, ev0, ev1, 0, L.g, sg, cf, ir,
                               L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st);
     else
-        k_sweep_short<T, KIND, TZ><<<grid, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st);
+        k_sweep_short<T, KIND><<<grid, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, xc, xm1, rho, xn, (T)c1, (T)c2, st);
 }
 
 template <typename T>
@@ -1130,11 +1305,12 @@ template <typename T>
 void launch_first(int kind, const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *r, T *ps, const T *v, T *x1,
                   double c2, const DevState *st)
 {
-    dim3 grid(L.g.ta.nblk + irr_blocks(ir.n, NT)), blk = tile_block();
+    const ShortGrid<false> sg = short_grid<false>(L.g);
+    const int nb = sg.nblk + irr_blocks(ir.n, NT);
     if (kind == FIRST_P)
-        k_first4<T, FIRST_P><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
+        k_first4<T, FIRST_P><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
     else
-        k_first4<T, FIRST_S><<<grid, blk, 0, L.stream>>>(L.g, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
+        k_first4<T, FIRST_S><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
 }
 
 template <typename T, typename TX_>
@@ -1142,9 +1318,9 @@ void launch_update(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, TX_ *xs
                    const T *t, const T *r0, T *r, DevState *st)
 {
     static_assert(sizeof(T) == sizeof(TX_), "solution and Krylov vectors share a precision");
-    int nb = L.g.ta.nblk + irr_blocks(ir.n, NT);
-    k_update4<T><<<dim3(nb), tile_block(), 0, L.stream>>>(L.g, cf, ir, L.skip, (T *)xs, ph, sh, s, t, r0, r, st,
-                                                          L.partials);
+    const ShortGrid<false> sg = short_grid<false>(L.g);
+    const int nb = sg.nblk + irr_blocks(ir.n, NT);
+    k_update4<T><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, (T *)xs, ph, sh, s, t, r0, r, st, L.partials);
     finalize<FIN_UPDATE>(L, nb, st);
 }
 

@@ -5,6 +5,7 @@ import os
 
 import numpy as np
 import pytest
+import scipy.sparse
 
 import oracle
 import paper_1901_08269_amd as cps
@@ -174,6 +175,35 @@ def test_apply_fp64_and_fp32(name):
     ratio32 = np.max(np.abs(y32 - y_ref) / np.maximum(scale, 1e-300))
     print(f"fp32 max error / (eps32 * scale) = {ratio32 / 2.0 ** -23:.2f}")
     assert ratio32 <= 32 * 2.0 ** -23
+
+
+class _NoIrregularRows:
+    """A problem without bodies, for _rounding_scale: its irregular rows' matrix is empty."""
+
+    def __init__(self, P):
+        self.shape, self.types = P.shape, P.types
+
+    def csr(self):
+        return scipy.sparse.csr_matrix((0, 0)), np.zeros(0, dtype=np.int64)
+
+
+# Grids around the edges of the apply kernels: rows that are no multiple of four nodes, a group
+# of rows per wavefront, rows longer than a wavefront's 248 and 256 nodes, one plane; the last
+# two take the marching kernel in FP64, and in both precisions.
+@pytest.mark.parametrize("shape", [(19, 18, 20), (262, 9, 8), (31, 5, 3), (67, 20, 21), (5, 5, 5), (259, 103, 101),
+                                   (263, 161, 129)])
+def test_apply_on_ragged_grids(shape):
+    grids = tuple(W.tanh_grid(n, 0.9) for n in shape)
+    w = W.polynomial_case(0, [], rng_seed=13, grids=grids)
+    print(f"[case] apply {shape}", flush=True)
+    P = oracle.Problem.from_workload(w)
+    S = cps.Solver.from_workload(w)
+    x = _random_field(P, 19)
+    y_ref = P.apply(x)
+    scale = _rounding_scale(_NoIrregularRows(P), x, grids)
+    for prec, eps in (("fp64", 2.0 ** -52), ("fp32", 2.0 ** -23)):
+        assert np.all(np.abs(_np(S.apply(x, prec)) - y_ref) <= 32 * eps * scale), prec
+    S.close()
 
 
 @pytest.mark.parametrize("name", CASES)
