@@ -888,9 +888,11 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
                               const T *rho, const T *ri, const MgTransfer<T> &t, T *rc, const MgFirst<T> &first,
                               const DevState *st)
 {
-    // the fifth-node path (more registers) only where a further segment exists
+    // the fifth-node path (more registers) only where some lane 63 owns its second coarse node
+    // (128) and that node's last fine point (257) is interior; with an odd nx that is so from
+    // nx = 259, where one segment still covers the coarse row
     const int ncx = t.nc[0], ncy = t.nc[1], ncz = t.nc[2];
-    const bool fifth = (ncx - 2 + 127) / 128 > 1;
+    const bool fifth = g.nx - 2 >= 257;
     const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true, RR_ROWS>)
                            : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false, RR_ROWS>);
     // The march is bound by the latency of its plane steps: all blocks run in one round,

@@ -81,6 +81,21 @@ def test_vcycle_matches_oracle(name):
     assert np.max(np.abs(got2 - 2.0 * got)) <= 1e-12 * scale
 
 
+# rows around one 128-node segment of coarse nodes: up to 257 fine points the last lane needs no
+# node beyond its four; at 259 it does, with one segment still; 261 starts a second segment
+@pytest.mark.parametrize("nx", [257, 258, 259, 260, 261])
+def test_vcycle_at_the_first_segment_end_matches_oracle(nx):
+    grids = (W.tanh_grid(nx, 1.1), W.uniform_grid(24), W.uniform_grid(21))
+    w = W.polynomial_case(0, [W.Sphere((0.5, 0.5, 0.5), 0.2)], rng_seed=11, grids=grids)
+    M = mg.Multigrid(w.x, w.y, w.z, w.phi)
+    rho = _random_rho(w.phi.shape, M.lv[0]["P"].types(), 31)
+    ref = M.apply(rho)
+    S = cps.Solver.from_workload(w, precond="multigrid")
+    for prec, bar in (("fp64", 1e-11), ("fp32", 2e-5)):
+        assert np.max(np.abs(_np(S.precond(rho, prec)) - ref)) <= bar * np.max(np.abs(ref)), prec
+    S.close()
+
+
 def test_vcycle_options_match_oracle():
     """Two levels, one smoothing step each side, 8 coarse steps, smoother interval [0.3, 2]."""
     w = _case("sphere_stretched")
