@@ -119,22 +119,32 @@ __device__ __forceinline__ T mg_reg_resid(T rh, T c, T w, T e, T s, T n, T m, T 
 }
 
 // Residual and restriction in one pass on the problem's grid: rc = R (rho - K x) at the
-// unknown coarse nodes, 0 at the other interior ones (the sums of k_mg_restrict, in its
-// order), with no fine residual stored.  A wavefront owns coarse row J of a 128-node coarse
-// segment bs and the coarse planes K0 .. K1 - 1 of a chunk.  Lane l takes coarse nodes
-// I0 = 1 + 128 bs + 2 l and I0 + 1, whose fine points are f0 = 2 I0 - 1 .. f0 + 4: it forms
-// the residual at f0 .. f0 + 3 (the four-node layout of the vectorised sweeps) and takes
-// the one at f0 + 4 from the next lane; the last lane forms its own fifth node when its
-// segment owns I0 + 1 and f0 + 4 is interior.  The wavefront marches over the fine planes
-// 2 K0 - 1 .. 2 K1 - 1: at each it forms the residual of fine rows 2J - 1 .. 2J + 1 from x
-// on rows 2J - 2 .. 2J + 2 (the planes below and above carried in registers), combines it
-// in x and y, and adds it to the coarse planes that the fine plane belongs to; coarse plane
-// K is complete, and stored, after fine plane 2K + 1.  Fine rows 2J - 1 and 2J + 1 are formed
-// by both wavefronts that need them, the first fine plane of a chunk by both chunks.
+// unknown coarse nodes, 0 at the other interior ones (the sums of k_mg_restrict), with no fine
+// residual stored.  A block owns RR_ROWS coarse rows of a 128-node coarse segment bs and the
+// coarse planes K0 .. K1 - 1 of a chunk, and has a wavefront more than rows: wavefront w forms
+// the residual of fine rows 2J - 1 and 2J, J = J0 + w, so that no wavefront forms a row twice.
+// Both belong to coarse row J; row 2J - 1 is also the last of coarse row J - 1, whose wavefront
+// gets that share, summed over the three fine planes of a coarse plane, through LDS (the
+// wavefront beyond the block's rows works for that share alone).
+// Lane l takes coarse nodes I0 = 1 + 128 bs + 2 l and I0 + 1, whose fine points are
+// f0 = 2 I0 - 1 .. f0 + 4: it forms the residual at f0 .. f0 + 3 (the four-node layout of the
+// vectorised sweeps) and takes the one at f0 + 4 from the next lane; the last lane forms its own
+// fifth node when its segment owns I0 + 1 and f0 + 4 is interior (FIFTH).  One load per row and
+// plane brings both ends of a segment what they need beyond it: nodes f0 + 4 and f0 + 5 in lane 63,
+// f0 - 1 in lane 0.
+// The wavefronts march over the fine planes 2 K0 - 1 .. 2 K1 - 1, x of the planes below and above
+// carried in registers; coarse plane K is complete, and stored, after fine plane 2K + 1.  The
+// first fine plane of a chunk is formed by both chunks.
 // Irregular and solid fine nodes (skip bits) take their residual from ri, which holds it
 // at the irregular nodes (the irregular rows of the residual kernel, run before) and 0 at
 // the solid ones; walls give 0.  With a first step F (F.x1 non-null) the coarse level's first Chebyshev
 // step from zero is written too, as k_mg_restrict does.
+// Bound by its loads (instructions and round trips per plane).  Against one coarse row per
+// wavefront with its three fine rows, four wavefronts a block (us): 512^3 FP32 363 against 505; 256^3
+// FP32 40.5 against 49.6; 200^3 FP32 24 against 31; 128^3 FP32 14.8 against 14.5.  Seven rows: with 3 /
+// 4 / 8 rows 256^3 FP32 takes 44 / 61 / 42 and FP64 104 / 98 / 115 against 40.5 and 88 (eight
+// wavefronts fill a CU's registers evenly).  Loading a plane ahead is slower (48 at 256^3: the
+// registers cost a quarter of the wavefronts).
 // Loads through a buffer resource based at a wave-uniform address (one plane of an
 // array): the 32-bit byte offset of each lane goes in a vector register and the base in
 // scalar registers, so an address costs no 64-bit vector arithmetic (this kernel issues
@@ -178,27 +188,45 @@ __device__ __forceinline__ double bload1<double>(__amdgpu_buffer_rsrc_t r, uint3
 {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
 }
-__device__ __forceinline__ uint32_t bload_u32(__amdgpu_buffer_rsrc_t r, uint32_t off)
+template <typename T>
+struct MgPair {
+    T a, b;
+};
+template <typename T>
+__device__ __forceinline__ MgPair<T> bload2(__amdgpu_buffer_rsrc_t r, uint32_t off);
+template <>
+__device__ __forceinline__ MgPair<float> bload2<float>(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
-    return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+    return __builtin_bit_cast(MgPair<float>, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+}
+template <>
+__device__ __forceinline__ MgPair<double> bload2<double>(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(MgPair<double>, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+__device__ __forceinline__ uint64_t bload_u64(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
 }
 
-template <typename T, bool FIFTH, int CR>
-__global__ void __launch_bounds__(256) k_mg_resid_restrict(Geom g, Tiling tl, Coef<T> cf,
+// coarse rows of a block
+constexpr int RR_ROWS = 7;
+
+template <typename T, bool FIFTH>
+__global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g, Tiling tl, Coef<T> cf,
                                                            const uint32_t *__restrict__ skip,
                                                            const T *__restrict__ x, const T *__restrict__ rho,
                                                            const T *__restrict__ ri, int ncx, int ncy, int ncz,
                                                            MgAxis<T> ax, MgAxis<T> ay, MgAxis<T> az,
                                                            T *__restrict__ rc, MgFirst<T> F, const DevState *st)
 {
-    constexpr int NR = 2 * CR + 1;                            // fine residual rows of a wavefront
     using V = typename MgVec4<T>::type;
+    __shared__ T sh[2][RR_ROWS + 1][2][64];                   // row 2J - 1's share of coarse row J - 1
     if (st && st->done) return;
     int bs, by, bz;
     if (!tile_of_block(tl, (int)blockIdx.x, bs, by, bz)) return;
-    const int J0 = 1 + (by * 4 + (int)threadIdx.y) * CR;     // the wavefront's first coarse row
-    if (J0 > ncy - 2) return;                                  // whole wavefront
-    const int lane = (int)threadIdx.x;
+    const int wv = (int)threadIdx.y, lane = (int)threadIdx.x;
+    const int J = 1 + by * RR_ROWS + wv;                       // the wavefront's coarse row (up to ncy - 2 + RR_ROWS)
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t plane = (size_t)nx * ny, wplane = (size_t)ny * g.W;
     const int I0 = 1 + 128 * bs + 2 * lane;
@@ -210,7 +238,9 @@ __global__ void __launch_bounds__(256) k_mg_resid_restrict(Geom g, Tiling tl, Co
     // the +x neighbour of the last interior node is the wall node (0 in every vector).
     const int ic = min(f0, nx - 1);
     const bool need5 = FIFTH && lane == 63 && own1 && f0 + 4 <= nx - 2;
-    const bool needl = lane == 0 && bs > 0;                   // node f0 - 1 is interior
+    const bool needl = FIFTH && lane == 0 && bs > 0;          // node f0 - 1 is interior
+    const bool edge = need5 || needl;
+    const uint32_t eoff = (uint32_t)((need5 ? 4 : -1) * (int)sizeof(T));   // from node ic to the edge pair
     // the skip bits that matter: the lane's interior nodes, and the fifth node where formed
     const uint32_t smask = ((1u << max(nv, 0)) - 1u) | (need5 ? 0x10u : 0u);
     T w0[3], w1[3];
@@ -236,17 +266,17 @@ __global__ void __launch_bounds__(256) k_mg_resid_restrict(Geom g, Tiling tl, Co
             kcx[u] = c[u];
         }
     }
-    // in-plane byte offsets of node ic on x rows 2 J0 - 2 .. 2 J0 + 2 CR (clamped to the wall
-    // row, where x is 0); the residual rows 2 J0 - 1 .. 2 J0 + 2 CR - 1 are x rows 1 .. NR,
-    // those past the last interior row zeroed; ow: byte offsets of their skip words
-    uint32_t ox[NR + 2], ow[NR];
+    // in-plane byte offsets of node ic on x rows 2J - 2 .. 2J + 1 (clamped to the wall row, where
+    // x is 0); the residual rows 2J - 1 and 2J are x rows 1 and 2, those past the last interior
+    // row zeroed; ow: byte offsets of their skip words
+    uint32_t ox[4], ow[2];
 #pragma unroll
-    for (int c = 0; c < NR + 2; ++c) ox[c] = (uint32_t)((ic + nx * min(2 * J0 - 2 + c, ny - 1)) * sizeof(T));
-    bool rok[NR];
-    T kay[NR], kby[NR], kcy[NR];
+    for (int c = 0; c < 4; ++c) ox[c] = (uint32_t)((ic + nx * min(2 * J - 2 + c, ny - 1)) * sizeof(T));
+    bool rok[2];
+    T kay[2], kby[2], kcy[2];
 #pragma unroll
-    for (int b = 0; b < NR; ++b) {
-        const int j = 2 * J0 - 1 + b;
+    for (int b = 0; b < 2; ++b) {
+        const int j = 2 * J - 1 + b;
         rok[b] = j <= ny - 2;
         const int jc = min(j, ny - 1);
         ow[b] = (uint32_t)((jc * g.W + (ic >> 5)) * sizeof(uint32_t));
@@ -254,96 +284,81 @@ __global__ void __launch_bounds__(256) k_mg_resid_restrict(Geom g, Tiling tl, Co
         kby[b] = wave_uniform(cf.c[1][8 * jc + 6]);
         kcy[b] = wave_uniform(cf.c[1][8 * jc + 7]);
     }
-    // the coarse rows J0 .. J0 + CR - 1 (those past the last interior one are not stored)
-    // and their y weights on fine rows 2J - 1 .. 2J + 1
-    bool jok[CR];
-    T wy[CR][3];
-#pragma unroll
-    for (int c = 0; c < CR; ++c) {
-        jok[c] = J0 + c <= ncy - 2;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) wy[c][q] = jok[c] ? wave_uniform(ay.rw[3 * (J0 + c) + q]) : T(0);
-    }
+    // the y weights of rows 2J - 1 and 2J in coarse row J, and of row 2J - 1 in coarse row J - 1
+    const bool jok = wv < RR_ROWS && J <= ncy - 2;             // the wavefront stores coarse row J
+    const int Jc = min(J, ncy - 2), Jp = min(J - 1, ncy - 2);
+    const T wy0 = wave_uniform(ay.rw[3 * Jc]), wy1 = wave_uniform(ay.rw[3 * Jc + 1]);
+    const T wyp = (wv > 0 && J - 1 <= ncy - 2) ? wave_uniform(ay.rw[3 * Jp + 2]) : T(0);
 
     const int K0 = 1 + bz * tl.TZ, K1 = min(K0 + tl.TZ, ncz - 1);
     const int p0 = 2 * K0 - 1, p1 = 2 * K1 - 1;
-    // x of the residual rows at the plane below (m) and at the current one (c); the fifth
-    // node's in m5, c5
-    V xm[NR], xc[NR];
-    T m5[NR], c5[NR];
+    // x of the residual rows at the plane below (m) and at the current one (c); their edge pairs
+    V xm[2], xc[2];
+    MgPair<T> em[2], ec[2];
     {
         const __amdgpu_buffer_rsrc_t xb = plane_rsrc(x + (size_t)(p0 - 1) * plane), x0 = plane_rsrc(x + (size_t)p0 * plane);
 #pragma unroll
-        for (int b = 0; b < NR; ++b) {
+        for (int b = 0; b < 2; ++b) {
             xm[b] = bload4<T>(xb, ox[b + 1]);
             xc[b] = bload4<T>(x0, ox[b + 1]);
-            m5[b] = need5 ? bload1<T>(xb, ox[b + 1] + 4 * sizeof(T)) : T(0);
-            c5[b] = need5 ? bload1<T>(x0, ox[b + 1] + 4 * sizeof(T)) : T(0);
+            em[b] = edge ? bload2<T>(xb, ox[b + 1] + eoff) : MgPair<T>{T(0), T(0)};
+            ec[b] = edge ? bload2<T>(x0, ox[b + 1] + eoff) : MgPair<T>{T(0), T(0)};
         }
     }
     // the coarse plane being summed: the diagonals of its nodes (0 where not an unknown),
-    // loaded when the plane opens and used when it is stored two fine planes later
-    T acc0[CR], acc1[CR], dg0[CR], dg1[CR];
-#pragma unroll
-    for (int c = 0; c < CR; ++c) acc0[c] = acc1[c] = dg0[c] = dg1[c] = T(0);
-    auto coarse_at = [&](int c, int K) -> size_t {
-        return (size_t)(own0 ? I0 : 1) + (size_t)ncx * (min(J0 + c, ncy - 2) + (size_t)ncy * K);
-    };
+    // loaded when the plane opens and used when it is stored two fine planes later; prv: the
+    // share of coarse row J - 1
+    T acc[2] = {T(0), T(0)}, prv[2] = {T(0), T(0)}, dg[2] = {T(0), T(0)};
+    const size_t erow = (size_t)(own0 ? I0 : 1) + (size_t)ncx * Jc, cplane = (size_t)ncx * ncy;
     auto open = [&](int K) {
-#pragma unroll
-        for (int c = 0; c < CR; ++c) {
-            acc0[c] = T(0);
-            acc1[c] = T(0);
-            const size_t ec = coarse_at(c, K);
-            dg0[c] = (own0 && jok[c]) ? F.diag[ec] : T(0);
-            dg1[c] = (own1 && jok[c]) ? F.diag[ec + 1] : T(0);
-        }
+        const size_t e = erow + cplane * K;
+        acc[0] = acc[1] = prv[0] = prv[1] = T(0);
+        dg[0] = (own0 && jok) ? F.diag[e] : T(0);
+        dg[1] = (own1 && jok) ? F.diag[e + 1] : T(0);
     };
     auto emit = [&](int K) {
-#pragma unroll
-        for (int c = 0; c < CR; ++c) {
-            if (!jok[c]) continue;
-            const size_t ec = coarse_at(c, K);
-            if (own0) rc[ec] = dg0[c] != T(0) ? acc0[c] : T(0);
-            if (own1) rc[ec + 1] = dg1[c] != T(0) ? acc1[c] : T(0);
-            if (F.x1) {
-                if (dg0[c] != T(0)) F.x1[ec] = F.c2 * acc0[c] / dg0[c];
-                if (dg1[c] != T(0)) F.x1[ec + 1] = F.c2 * acc1[c] / dg1[c];
-            }
+        sh[K & 1][wv][0][lane] = prv[0];
+        sh[K & 1][wv][1][lane] = prv[1];
+        __syncthreads();
+        if (!jok) return;
+        const T a0 = acc[0] + sh[K & 1][wv + 1][0][lane], a1 = acc[1] + sh[K & 1][wv + 1][1][lane];
+        const size_t e = erow + cplane * K;
+        if (own0) rc[e] = dg[0] != T(0) ? a0 : T(0);
+        if (own1) rc[e + 1] = dg[1] != T(0) ? a1 : T(0);
+        if (F.x1) {
+            if (dg[0] != T(0)) F.x1[e] = F.c2 * a0 / dg[0];
+            if (dg[1] != T(0)) F.x1[e + 1] = F.c2 * a1 / dg[1];
         }
     };
     // coarse plane K += its z weight q times the fine plane's rows, restricted in y
-    auto add_plane = [&](int K, int q, const T *xr0, const T *xr1) {
+    auto add_plane = [&](int K, int q, const T (&xr)[2][2]) {
         const T wz = wave_uniform(az.rw[3 * K + q]);
+        const T c0 = wz * wy0, c1 = wz * wy1, cp = wz * wyp;
 #pragma unroll
-        for (int c = 0; c < CR; ++c)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const T wyz = wz * wy[c][b];
-                acc0[c] += wyz * xr0[2 * c + b];
-                acc1[c] += wyz * xr1[2 * c + b];
-            }
+        for (int o = 0; o < 2; ++o) {
+            acc[o] += c0 * xr[0][o] + c1 * xr[1][o];
+            prv[o] += cp * xr[0][o];
+        }
     };
     // skip bits of nodes ic .. ic + 4 on the residual rows of plane q (words read in pairs;
     // the array carries two words of padding), loaded one plane ahead
     auto skip_bits = [&](int q, int b) -> uint32_t {
-        const __amdgpu_buffer_rsrc_t sq = plane_rsrc(skip + (size_t)q * wplane);
-        const uint64_t pair = (uint64_t)bload_u32(sq, ow[b]) | ((uint64_t)bload_u32(sq, ow[b] + 4) << 32);
-        return (uint32_t)(pair >> (ic & 31)) & smask;
+        return (uint32_t)(bload_u64(plane_rsrc(skip + (size_t)q * wplane), ow[b]) >> (ic & 31)) & smask;
     };
-    uint32_t skn[NR];
+    uint32_t skn[2];
 #pragma unroll
-    for (int b = 0; b < NR; ++b) skn[b] = skip_bits(p0, b);
+    for (int b = 0; b < 2; ++b) skn[b] = skip_bits(p0, b);
     for (int p = p0; p <= p1; ++p) {
         const bool pv = p <= nz - 2;                          // fine plane p is interior
         const size_t kp = (size_t)p * plane;
         const __amdgpu_buffer_rsrc_t xk = plane_rsrc(x + kp), xn = plane_rsrc(x + (size_t)min(p + 1, nz - 1) * plane);
         const __amdgpu_buffer_rsrc_t rk = plane_rsrc(rho + kp), rik = plane_rsrc(ri + kp);
-        V xp[NR], rh[NR], ri4[NR];
-        uint32_t sk[NR];
-        T lf[NR], p5[NR], q5[NR], h5[NR], ri5[NR];
+        V xp[2], rh[2], ri4[2];
+        MgPair<T> ep[2];
+        uint32_t sk[2];
+        T h5[2], ri5[2];
 #pragma unroll
-        for (int b = 0; b < NR; ++b) {
+        for (int b = 0; b < 2; ++b) {
             const uint32_t o = ox[b + 1];
             sk[b] = skn[b];
             skn[b] = skip_bits(min(p + 1, nz - 1), b);
@@ -353,72 +368,191 @@ __global__ void __launch_bounds__(256) k_mg_resid_restrict(Geom g, Tiling tl, Co
             if (sk[b]) ri4[b] = bload4<T>(rik, o);
             else ri4[b] = V{T(0), T(0), T(0), T(0)};
             ri5[b] = (FIFTH && ((sk[b] >> 4) & 1u)) ? bload1<T>(rik, o + 4 * sizeof(T)) : T(0);
-            lf[b] = needl ? bload1<T>(xk, o - sizeof(T)) : T(0);
-            p5[b] = need5 ? bload1<T>(xn, o + 4 * sizeof(T)) : T(0);
-            q5[b] = need5 ? bload1<T>(xk, o + 5 * sizeof(T)) : T(0);
+            ep[b] = edge ? bload2<T>(xn, o + eoff) : MgPair<T>{T(0), T(0)};
             h5[b] = need5 ? bload1<T>(rk, o + 4 * sizeof(T)) : T(0);
         }
-        // the outer y neighbours: x rows 0 and NR + 1
-        const V ylo = bload4<T>(xk, ox[0]), yhi = bload4<T>(xk, ox[NR + 1]);
+        // the outer y neighbours: x rows 0 and 3
+        const V ylo = bload4<T>(xk, ox[0]), yhi = bload4<T>(xk, ox[3]);
         const T ylo5 = need5 ? bload1<T>(xk, ox[0] + 4 * sizeof(T)) : T(0);
-        const T yhi5 = need5 ? bload1<T>(xk, ox[NR + 1] + 4 * sizeof(T)) : T(0);
+        const T yhi5 = need5 ? bload1<T>(xk, ox[3] + 4 * sizeof(T)) : T(0);
         const T *cz = cf.c[2] + 8 * p;
         const T za = wave_uniform(cz[5]), zb = wave_uniform(cz[6]), zc = wave_uniform(cz[7]);
-        T xr0[NR], xr1[NR];
+        T xr[2][2];
 #pragma unroll
-        for (int b = 0; b < NR; ++b) {
-            const V &s4 = b == 0 ? ylo : xc[b - 1];
-            const V &n4 = b == NR - 1 ? yhi : xc[b + 1];
-            const T cv[5] = {xc[b].x, xc[b].y, xc[b].z, xc[b].w, c5[b]};
-            const T sv[5] = {s4.x, s4.y, s4.z, s4.w, b == 0 ? ylo5 : c5[b - 1]};
-            const T nw[5] = {n4.x, n4.y, n4.z, n4.w, b == NR - 1 ? yhi5 : c5[b + 1]};
-            const T mv[5] = {xm[b].x, xm[b].y, xm[b].z, xm[b].w, m5[b]};
-            const T uv[5] = {xp[b].x, xp[b].y, xp[b].z, xp[b].w, p5[b]};
+        for (int b = 0; b < 2; ++b) {
+            const V &s4 = b == 0 ? ylo : xc[0];
+            const V &n4 = b == 0 ? xc[1] : yhi;
+            const T cv[5] = {xc[b].x, xc[b].y, xc[b].z, xc[b].w, ec[b].a};
+            const T sv[5] = {s4.x, s4.y, s4.z, s4.w, b == 0 ? ylo5 : ec[0].a};
+            const T nw[5] = {n4.x, n4.y, n4.z, n4.w, b == 0 ? ec[1].a : yhi5};
+            const T mv[5] = {xm[b].x, xm[b].y, xm[b].z, xm[b].w, em[b].a};
+            const T uv[5] = {xp[b].x, xp[b].y, xp[b].z, xp[b].w, ep[b].a};
             const T rv[5] = {rh[b].x, rh[b].y, rh[b].z, rh[b].w, h5[b]};
             T left = __shfl_up(cv[3], 1, 64), right = __shfl_down(cv[0], 1, 64);
-            if (lane == 0) left = lf[b];
-            if (lane == 63) right = c5[b];
+            if (lane == 0) left = ec[b].a;                    // 0 at the wall (no edge pair)
+            if (lane == 63) right = ec[b].a;
             // x neighbours of the five nodes: node u's -x one is wxn[u], its +x one exn[u]
             const T wxn[5] = {left, cv[0], cv[1], cv[2], cv[3]};
-            const T exn[5] = {cv[1], cv[2], cv[3], right, q5[b]};
+            const T exn[5] = {cv[1], cv[2], cv[3], right, ec[b].b};
             T r[5];
 #pragma unroll
-            for (int u = 0; u < 5; ++u)
+            for (int u = 0; u < (FIFTH ? 5 : 4); ++u)
                 r[u] = mg_reg_resid(rv[u], cv[u], wxn[u], exn[u], sv[u], nw[u], mv[u], uv[u], kax[u], kbx[u],
                                     kcx[u], kay[b], kby[b], kcy[b], za, zb, zc);
             // solid or irregular nodes: their residual from ri (0 at a solid node)
             const T qv[5] = {ri4[b].x, ri4[b].y, ri4[b].z, ri4[b].w, ri5[b]};
 #pragma unroll
-            for (int u = 0; u < 5; ++u) r[u] = ((sk[b] >> u) & 1u) ? qv[u] : r[u];
+            for (int u = 0; u < (FIFTH ? 5 : 4); ++u) r[u] = ((sk[b] >> u) & 1u) ? qv[u] : r[u];
             const bool live = pv && rok[b];
 #pragma unroll
             for (int u = 0; u < 4; ++u) r[u] = (live && u < nv) ? r[u] : T(0);
             T v4 = __shfl_down(r[0], 1, 64);
-            if (lane == 63) v4 = (live && need5) ? r[4] : T(0);
-            xr0[b] = w0[0] * r[0] + w0[1] * r[1] + w0[2] * r[2];
-            xr1[b] = w1[0] * r[2] + w1[1] * r[3] + w1[2] * v4;
+            if (lane == 63) v4 = (FIFTH && live && need5) ? r[4] : T(0);
+            xr[b][0] = w0[0] * r[0] + w0[1] * r[1] + w0[2] * r[2];
+            xr[b][1] = w1[0] * r[2] + w1[1] * r[3] + w1[2] * v4;
         }
         if (p & 1) {
             // fine plane 2K + 1: the last of coarse plane K, the first of K + 1
             const int K = (p - 1) >> 1;
             if (K >= K0) {
-                add_plane(K, 2, xr0, xr1);
+                add_plane(K, 2, xr);
                 emit(K);
             }
             if (K + 1 < K1) {
                 open(K + 1);
-                add_plane(K + 1, 0, xr0, xr1);
+                add_plane(K + 1, 0, xr);
             }
         } else {
-            add_plane(p >> 1, 1, xr0, xr1);
+            add_plane(p >> 1, 1, xr);
         }
 #pragma unroll
-        for (int b = 0; b < NR; ++b) {
+        for (int b = 0; b < 2; ++b) {
             xm[b] = xc[b];
             xc[b] = xp[b];
-            m5[b] = c5[b];
-            c5[b] = p5[b];
+            em[b] = ec[b];
+            ec[b] = ep[b];
         }
+    }
+}
+
+// The same on small grids, whose march is bound by the round trips of its planes: a wavefront forms
+// the residual of one fine plane p = 2K - 1 + q for coarse plane K, all its loads issued at once,
+// and the three wavefronts of a coarse plane sum their shares through LDS.  Lanes take the groups
+// of four fine nodes of a plane's coarse rows in order, whatever the row length; of a wavefront's
+// 64 groups the inner 62 are summed, so that both x neighbours and the fifth fine point always
+// come from the adjacent lanes.  Fine rows and planes shared by two coarse ones are formed twice.
+constexpr int RRS_WAVE = 62, RRS_WAVES = 2;                    // groups of a wavefront, wavefronts per plane
+template <typename T>
+__global__ void __launch_bounds__(64 * 3 * RRS_WAVES)
+    k_mg_resid_restrict_short(Geom g, Coef<T> cf, const uint32_t *__restrict__ skip, const T *__restrict__ x,
+                              const T *__restrict__ rho, const T *__restrict__ ri, int ncx, int ncy, int ncz,
+                              MgAxis<T> ax, MgAxis<T> ay, MgAxis<T> az, int gpr, int nbx, T *__restrict__ rc,
+                              MgFirst<T> F, const DevState *st)
+{
+    using V = typename MgVec4<T>::type;
+    __shared__ T sh[RRS_WAVES][2][2][64];                      // the shares of planes q = 1, 2
+    const int done = st ? st->done : 0;                        // used before the stores: nothing waits for it
+    const int per = (int)gridDim.x / NXCD, blk = ((int)blockIdx.x % NXCD) * per + (int)blockIdx.x / NXCD;
+    const int K = 1 + blk / nbx;
+    if (K > ncz - 2) return;                                   // whole block
+    const int lane = (int)threadIdx.x, q = (int)threadIdx.y, w = (int)threadIdx.z;
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const int item = ((blk % nbx) * RRS_WAVES + w) * RRS_WAVE + lane - 1;
+    const int items = gpr * (ncy - 2), it = min(max(item, 0), items - 1);
+    const int J = 1 + it / gpr, gx = it % gpr, I0 = 1 + 2 * gx, f0 = 4 * gx + 1;
+    const bool live = lane >= 1 && lane <= RRS_WAVE && item < items;
+    const bool own0 = live && I0 <= ncx - 2, own1 = live && I0 + 1 <= ncx - 2;
+    const int nv = min(4, nx - 1 - f0);                        // interior fine nodes of the group
+    const int p = 2 * K - 1 + q, pc = min(p, nz - 1);
+    const size_t plane = (size_t)nx * ny;
+    int row[5];                                                // fine rows 2J - 2 .. 2J + 2 (the wall row beyond)
+#pragma unroll
+    for (int c = 0; c < 5; ++c) row[c] = f0 + nx * min(2 * J - 2 + c, ny - 1);
+    uint64_t pair[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+        __builtin_memcpy(&pair[b], skip + ((size_t)min(2 * J - 1 + b, ny - 1) + (size_t)ny * pc) * g.W + (f0 >> 5), 8);
+    const T *xk = x + plane * pc, *xm = x + plane * (p - 1), *xu = x + plane * min(p + 1, nz - 1);
+    V c4[5], m4[3], u4[3], r4[3], i4[3];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) c4[c] = *reinterpret_cast<const V *>(xk + row[c]);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        m4[b] = *reinterpret_cast<const V *>(xm + row[b + 1]);
+        u4[b] = *reinterpret_cast<const V *>(xu + row[b + 1]);
+        r4[b] = *reinterpret_cast<const V *>(rho + plane * pc + row[b + 1]);
+    }
+    T ka[4], kb[4], kc[4], ky[3][3], wx0[3], wx1[3], wy[3];
+    {
+        const T *x5 = cf.xs + (size_t)5 * cf.xp + f0, *x6 = x5 + cf.xp, *x7 = x6 + cf.xp;
+        const V va = *reinterpret_cast<const V *>(x5), vb = *reinterpret_cast<const V *>(x6),
+                vc = *reinterpret_cast<const V *>(x7);
+        const T a[4] = {va.x, va.y, va.z, va.w}, bb[4] = {vb.x, vb.y, vb.z, vb.w}, c[4] = {vc.x, vc.y, vc.z, vc.w};
+        const int a0 = own0 ? I0 : 1, a1 = own1 ? I0 + 1 : a0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { ka[u] = a[u]; kb[u] = bb[u]; kc[u] = c[u]; }
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) ky[b][d] = cf.c[1][8 * min(2 * J - 1 + b, ny - 1) + 5 + d];
+            wx0[b] = ax.rw[3 * a0 + b];
+            wx1[b] = ax.rw[3 * a1 + b];
+            wy[b] = ay.rw[3 * J + b];
+        }
+    }
+    const T za = cf.c[2][8 * pc + 5], zb = cf.c[2][8 * pc + 6], zc = cf.c[2][8 * pc + 7], wz = az.rw[3 * K + q];
+    T dg[2] = {T(0), T(0)};
+    const size_t e = (size_t)I0 + (size_t)ncx * (J + (size_t)ncy * K);
+    if (q == 0) {
+        if (own0) dg[0] = F.diag[e];
+        if (own1) dg[1] = F.diag[e + 1];
+    }
+    uint32_t sk[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        sk[b] = (uint32_t)(pair[b] >> (f0 & 31)) & ((1u << nv) - 1u);
+        i4[b] = V{T(0), T(0), T(0), T(0)};
+        if (sk[b]) i4[b] = *reinterpret_cast<const V *>(ri + plane * pc + row[b + 1]);
+    }
+    T s0 = T(0), s1 = T(0);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const bool ok = p <= nz - 2 && 2 * J - 1 + b <= ny - 2;
+        const T cv[4] = {c4[b + 1].x, c4[b + 1].y, c4[b + 1].z, c4[b + 1].w};
+        const T sv[4] = {c4[b].x, c4[b].y, c4[b].z, c4[b].w}, nw[4] = {c4[b + 2].x, c4[b + 2].y, c4[b + 2].z, c4[b + 2].w};
+        const T mv[4] = {m4[b].x, m4[b].y, m4[b].z, m4[b].w}, uv[4] = {u4[b].x, u4[b].y, u4[b].z, u4[b].w};
+        const T rv[4] = {r4[b].x, r4[b].y, r4[b].z, r4[b].w}, iv[4] = {i4[b].x, i4[b].y, i4[b].z, i4[b].w};
+        T left = __shfl_up(cv[3], 1, 64), right = __shfl_down(cv[0], 1, 64);
+        if (gx == 0) left = T(0);                              // the walls
+        if (gx == gpr - 1) right = T(0);
+        T r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T wv = u == 0 ? left : cv[u - 1], ev = u == 3 ? right : cv[u + 1];
+            r[u] = mg_reg_resid(rv[u], cv[u], wv, ev, sv[u], nw[u], mv[u], uv[u], ka[u], kb[u], kc[u], ky[b][0],
+                                ky[b][1], ky[b][2], za, zb, zc);
+            if ((sk[b] >> u) & 1u) r[u] = iv[u];
+            if (!ok || u >= nv) r[u] = T(0);
+        }
+        T v4 = __shfl_down(r[0], 1, 64);
+        if (gx == gpr - 1) v4 = T(0);
+        const T wyz = wz * wy[b];
+        s0 += wyz * (wx0[0] * r[0] + wx0[1] * r[1] + wx0[2] * r[2]);
+        s1 += wyz * (wx1[0] * r[2] + wx1[1] * r[3] + wx1[2] * v4);
+    }
+    if (q > 0) {
+        sh[w][q - 1][0][lane] = s0;
+        sh[w][q - 1][1][lane] = s1;
+    }
+    __syncthreads();
+    if (q > 0 || done) return;
+    s0 += sh[w][0][0][lane] + sh[w][1][0][lane];
+    s1 += sh[w][0][1][lane] + sh[w][1][1][lane];
+    if (own0) rc[e] = dg[0] != T(0) ? s0 : T(0);
+    if (own1) rc[e + 1] = dg[1] != T(0) ? s1 : T(0);
+    if (F.x1) {
+        if (dg[0] != T(0)) F.x1[e] = F.c2 * s0 / dg[0];
+        if (dg[1] != T(0)) F.x1[e + 1] = F.c2 * s1 / dg[1];
     }
 }
 
@@ -880,27 +1014,44 @@ void launch_mg_restrict(hipStream_t s, const MgTransfer<T> &t, const T *r, T *rc
                                                   rc, first);
 }
 
-// coarse rows per wavefront of the fused residual and restriction
-constexpr int RR_ROWS = 1;
+// Which grids restrict with the short kernel: up to RRS_MAX_BYTES per vector.  Its twice-formed rows
+// and planes lose where the march has planes enough to overlap.  Measured (us, short against
+// march): FP32 48^3 5.6 / 9.9, 66^3 5.6 / 11.2, 98^3 8.5 / 12.6, 130^3 16.5 / 14.8; FP64 32^3 6.6 / 13.7,
+// 66^3 7.2 / 14.0, 98^3 (7 MB) 12.7 / 13.2, 211x147x99 31 / 20.
+constexpr size_t RRS_MAX_BYTES = 6000000;
+template <typename T>
+static bool resid_restrict_short(const Geom &g)
+{
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= RRS_MAX_BYTES;
+}
 
 template <typename T>
 void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, const uint32_t *skip, const T *x,
                               const T *rho, const T *ri, const MgTransfer<T> &t, T *rc, const MgFirst<T> &first,
                               const DevState *st)
 {
+    if (resid_restrict_short<T>(g)) {
+        const int gpr = (g.nx - 2 + 3) / 4;
+        const int nbx = (gpr * (t.nc[1] - 2) + RRS_WAVE * RRS_WAVES - 1) / (RRS_WAVE * RRS_WAVES);
+        const int nb = (nbx * (t.nc[2] - 2) + NXCD - 1) / NXCD * NXCD;
+        k_mg_resid_restrict_short<T><<<nb, dim3(64, 3, RRS_WAVES), 0, s>>>(g, cf, skip, x, rho, ri, t.nc[0], t.nc[1],
+                                                                          t.nc[2], t.ax[0], t.ax[1], t.ax[2], gpr, nbx,
+                                                                          rc, first, st);
+        return;
+    }
     // the fifth-node path (more registers) only where some lane 63 owns its second coarse node
     // (128) and that node's last fine point (257) is interior; with an odd nx that is so from
     // nx = 259, where one segment still covers the coarse row
     const int ncx = t.nc[0], ncy = t.nc[1], ncz = t.nc[2];
     const bool fifth = g.nx - 2 >= 257;
-    const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true, RR_ROWS>)
-                           : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false, RR_ROWS>);
+    const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true>)
+                           : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false>);
     // The march is bound by the latency of its plane steps: all blocks run in one round,
     // as many as fit on the device at once (z-chunks of at least two coarse planes).
     static int per_cu[2] = {0, 0};
     if (!per_cu[fifth]) {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 256, 0) != hipSuccess || nb < 1) nb = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 64 * (RR_ROWS + 1), 0) != hipSuccess || nb < 1) nb = 1;
         per_cu[fifth] = nb;
     }
     int dev = 0, ncu = 0;
@@ -909,7 +1060,7 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
         ncu = 256;
     Tiling tl{};
     tl.tw = 128;
-    tl.ty = 4 * RR_ROWS;
+    tl.ty = RR_ROWS;
     tl.tiles_x = (ncx - 2 + 127) / 128;
     tl.tiles_y = (ncy - 2 + tl.ty - 1) / tl.ty;
     const int nzi = ncz - 2, per_plane = tl.tiles_x * tl.tiles_y;
@@ -919,10 +1070,10 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
     tl.ntiles = per_plane * tl.zchunks;
     tl.nblk = (tl.ntiles + NXCD - 1) / NXCD * NXCD;
     if (fifth)
-        k_mg_resid_restrict<T, true, RR_ROWS><<<tl.nblk, dim3(64, 4), 0, s>>>(
+        k_mg_resid_restrict<T, true><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(
             g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st);
     else
-        k_mg_resid_restrict<T, false, RR_ROWS><<<tl.nblk, dim3(64, 4), 0, s>>>(
+        k_mg_resid_restrict<T, false><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(
             g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st);
 }
 

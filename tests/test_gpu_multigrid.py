@@ -81,11 +81,14 @@ def test_vcycle_matches_oracle(name):
     assert np.max(np.abs(got2 - 2.0 * got)) <= 1e-12 * scale
 
 
-# rows around one 128-node segment of coarse nodes: up to 257 fine points the last lane needs no
-# node beyond its four; at 259 it does, with one segment still; 261 starts a second segment
-@pytest.mark.parametrize("nx", [257, 258, 259, 260, 261])
-def test_vcycle_at_the_first_segment_end_matches_oracle(nx):
-    grids = (W.tanh_grid(nx, 1.1), W.uniform_grid(24), W.uniform_grid(21))
+# The fused residual and restriction.  Small grids: rows around one 128-node segment of coarse
+# nodes (up to 257 fine points the last lane of a segment needs no node beyond its four; at 259 it
+# does, with one segment still; 261 starts a second), coarse rows of one and two nodes.  Grids
+# beyond the small kernel's size: the same row ends, coarse rows that fill a block's seven or not.
+@pytest.mark.parametrize("shape", [(257, 24, 21), (258, 24, 21), (259, 24, 21), (260, 24, 21), (261, 24, 21),
+                                   (19, 22, 33), (257, 103, 61), (259, 103, 61), (263, 101, 62), (131, 115, 106)])
+def test_residual_restriction_edges_match_oracle(shape):
+    grids = (W.tanh_grid(shape[0], 1.1), W.uniform_grid(shape[1]), W.uniform_grid(shape[2]))
     w = W.polynomial_case(0, [W.Sphere((0.5, 0.5, 0.5), 0.2)], rng_seed=11, grids=grids)
     M = mg.Multigrid(w.x, w.y, w.z, w.phi)
     rho = _random_rho(w.phi.shape, M.lv[0]["P"].types(), 31)
