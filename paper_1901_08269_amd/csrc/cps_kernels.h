@@ -105,6 +105,14 @@ template <typename T>
 void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, const uint32_t *skip, const T *x,
                               const T *rho, const T *ri, const MgTransfer<T> &t, T *rc, const MgFirst<T> &first,
                               const DevState *st);
+// Two smoothing steps on the problem's grid in one pass: y = x + c2a (rho - K x) / diag K, then
+// out = y + c1 (y - x) + c2 (rho - K y) / diag K.  yi (0 at the solid nodes) takes y at the
+// irregular nodes; y is stored nowhere else.  mg_pair_pays: the grids where this is the faster way.
+template <typename T>
+bool mg_pair_pays(const Geom &g);
+template <typename T>
+void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
+                    double c2a, double c1, double c2, const DevState *st);
 // The coarsest level's `steps` Chebyshev steps (coefficients c1, c2) from 0 in one workgroup
 // of MG_LDS_THREADS threads; the level has at most MG_LDS_NODES interior nodes, at most
 // MG_LDS_PADDED nodes with its walls (6885 for the 9 x 9 x 85 points that the coarsening rule

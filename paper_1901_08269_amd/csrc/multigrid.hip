@@ -435,6 +435,280 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
     }
 }
 
+// Two smoothing steps from x_0 in one pass over memory (a post-smoothing pass of nu = 2):
+//   y = x_0 + c2a (rho - K x_0) / diag K,  z = y + c1 (y - x_0) + c2 (rho - K y) / diag K
+// with y never stored: x_0 and rho in, z out, 3 vectors instead of 7.  A block marches in z over
+// 2 Pair::waves rows of a 256-node segment: wavefront w forms y of its two rows at plane k (four
+// nodes per lane, x of the planes k - 1 .. k + 1 in registers), then z at plane k - 1 from the y
+// of planes k - 2 .. k; the rows of the neighbouring wavefronts come through LDS, one barrier a
+// plane.  The block's first and last row and a chunk's outer planes are formed for y alone.
+// Where a row has more segments (SEG), the outer lanes form y at the node beyond theirs as well.
+// Irregular nodes: y is read from yi (0 at the solid nodes), z is not written; k_mg_pair_irregular
+// forms both, before.
+// A block's waves fill a CU's registers: 12 in FP32, 8 in FP64; 1 / diag K is formed once for both
+// steps.  Bound by registers (8 to 12 wavefronts a CU) and the vector instructions of the two
+// steps.  Measured with k_mg_pair_irregular, against the two sweeps (us): 256^3 FP32 52 + 7 against
+// 41 + 48, FP64 109 + 10 against 90 + 119; 512^3 FP32 493 + 24 against 393 + 491.
+template <typename T>
+struct Pair {
+    static constexpr int waves = sizeof(T) == 4 ? 12 : 8, rows = 2 * waves - 2;   // rows stored by a block
+};
+template <typename T, bool SEG>
+__global__ void __launch_bounds__(64 * Pair<T>::waves)
+    k_mg_pair(Geom g, Tiling tl, Coef<T> cf, const uint32_t *__restrict__ skip, const T *__restrict__ x,
+              const T *__restrict__ rho, const T *__restrict__ yi, T *__restrict__ out, T c2a, T c1, T c2,
+              const DevState *st)
+{
+    using V = typename MgVec4<T>::type;
+    constexpr int PAIR_WAVES = Pair<T>::waves, PAIR_ROWS = Pair<T>::rows;
+    __shared__ V sh[2][PAIR_WAVES][2][64];                    // y of a plane's rows
+    if (st && st->done) return;
+    int bs, by, bz;
+    if (!tile_of_block(tl, (int)blockIdx.x, bs, by, bz)) return;
+    const int wv = (int)threadIdx.y, lane = (int)threadIdx.x;
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const size_t plane = (size_t)nx * ny, wplane = (size_t)ny * g.W;
+    const int i0 = 1 + 256 * bs + 4 * lane;
+    const int nv = min(4, nx - 1 - i0);                       // interior nodes of the lane
+    const int ic = min(i0, nx - 1);                           // lanes past the row end: the wall node
+    const bool needr = SEG && lane == 63 && i0 + 4 <= nx - 2; // the node beyond the lane's is interior
+    const bool needl = SEG && lane == 0 && bs > 0;
+    const bool edge = needr || needl;
+    const int ie = needr ? i0 + 4 : (needl ? i0 - 1 : ic);    // that node
+    const uint32_t past = 0xFu & ~((1u << max(nv, 0)) - 1u);  // the lane's places past the row end
+    const uint32_t eoff = (uint32_t)((needr ? 4 : -2) * (int)sizeof(T)), hoff = (uint32_t)((ie - ic) * (int)sizeof(T));
+    T kax[5], kbx[5], kcx[5];
+    {
+        const T *x5 = cf.xs + (size_t)5 * cf.xp, *x6 = x5 + cf.xp, *x7 = x6 + cf.xp;
+        const V va = *reinterpret_cast<const V *>(x5 + ic), vb = *reinterpret_cast<const V *>(x6 + ic),
+                vc = *reinterpret_cast<const V *>(x7 + ic);
+        const T a[5] = {va.x, va.y, va.z, va.w, SEG ? x5[ie] : T(0)}, bb[5] = {vb.x, vb.y, vb.z, vb.w, SEG ? x6[ie] : T(1)},
+                c[5] = {vc.x, vc.y, vc.z, vc.w, SEG ? x7[ie] : T(0)};
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            kax[u] = a[u];
+            kbx[u] = bb[u];
+            kcx[u] = c[u];
+        }
+    }
+    // the wavefront's rows j0, j0 + 1, and byte offsets of node ic on x rows j0 - 1 .. j0 + 2
+    // (clamped to the wall rows, where x is 0); rows outside the interior have y = 0
+    const int j0 = PAIR_ROWS * by + 2 * wv;
+    uint32_t ox[4], ow[2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ox[c] = (uint32_t)((ic + nx * min(max(j0 - 1 + c, 0), ny - 1)) * sizeof(T));
+    bool rok[2], own[2];
+    T kay[2], kby[2], kcy[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int j = j0 + b, jc = min(j, ny - 1);
+        rok[b] = j >= 1 && j <= ny - 2;
+        own[b] = rok[b] && 2 * wv + b >= 1 && 2 * wv + b <= PAIR_ROWS;
+        ow[b] = (uint32_t)((jc * g.W + (ic >> 5)) * sizeof(uint32_t));
+        kay[b] = wave_uniform(cf.c[1][8 * jc + 5]);
+        kby[b] = wave_uniform(cf.c[1][8 * jc + 6]);
+        kcy[b] = wave_uniform(cf.c[1][8 * jc + 7]);
+    }
+    const int K0 = 1 + bz * tl.TZ, K1 = min(K0 + tl.TZ, nz - 1);
+    // x at the plane behind (m) and the current one (c) with the edge pairs; y of the two planes
+    // behind (0, 1), at the edge node too; rho, 1 / diag K and the skip bits of the plane behind
+    V xm[2], xc[2], y0[2], y1[2], rp[2], dp[2];
+    MgPair<T> em[2], ec[2];
+    T ye1[2] = {T(0), T(0)};
+    uint32_t skp[2] = {0u, 0u}, skn[2];
+    const V zero4 = V{T(0), T(0), T(0), T(0)};
+    auto skip_bits = [&](int q, int b) -> uint32_t {
+        const uint64_t pair = bload_u64(plane_rsrc(skip + (size_t)q * wplane), ow[b]);
+        const uint32_t m = (uint32_t)(pair >> (ic & 31)) & ((1u << max(nv, 0)) - 1u);
+        if (!SEG || !edge) return m;
+        return m | (needr ? ((uint32_t)(pair >> (ic & 31)) & 0x10u) : (((uint32_t)(pair >> ((ic & 31) - 1)) & 1u) << 4));
+    };
+    {
+        const __amdgpu_buffer_rsrc_t xb = plane_rsrc(x + (size_t)max(K0 - 2, 0) * plane),
+                                     xk = plane_rsrc(x + (size_t)(K0 - 1) * plane);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            skn[b] = skip_bits(K0 - 1, b);
+            xm[b] = bload4<T>(xb, ox[b + 1]);
+            xc[b] = bload4<T>(xk, ox[b + 1]);
+            em[b] = edge ? bload2<T>(xb, ox[b + 1] + eoff) : MgPair<T>{T(0), T(0)};
+            ec[b] = edge ? bload2<T>(xk, ox[b + 1] + eoff) : MgPair<T>{T(0), T(0)};
+            y0[b] = y1[b] = rp[b] = dp[b] = zero4;
+        }
+    }
+    for (int k = K0 - 1; k <= K1; ++k) {
+        const size_t kp = (size_t)k * plane;
+        const __amdgpu_buffer_rsrc_t xk = plane_rsrc(x + kp), xn = plane_rsrc(x + (size_t)min(k + 1, nz - 1) * plane);
+        const __amdgpu_buffer_rsrc_t rk = plane_rsrc(rho + kp), yk = plane_rsrc(yi + kp);
+        V xp[2], rh[2], yi4[2];
+        MgPair<T> ep[2];
+        uint32_t sk[2];
+        T h5[2], yi5[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const uint32_t o = ox[b + 1];
+            sk[b] = skn[b];
+            skn[b] = skip_bits(min(k + 1, nz - 1), b);
+            xp[b] = bload4<T>(xn, o);
+            rh[b] = bload4<T>(rk, o);
+            // y at the lane's solid and irregular nodes (issued with the other loads)
+            if (sk[b]) yi4[b] = bload4<T>(yk, o);
+            else yi4[b] = zero4;
+            yi5[b] = (SEG && (sk[b] & 0x10u)) ? bload1<T>(yk, o + hoff) : T(0);
+            ep[b] = edge ? bload2<T>(xn, o + eoff) : MgPair<T>{T(0), T(0)};
+            h5[b] = edge ? bload1<T>(rk, o + hoff) : T(0);
+        }
+        // the outer y neighbours: x rows j0 - 1 and j0 + 2
+        const V xlo = bload4<T>(xk, ox[0]), xhi = bload4<T>(xk, ox[3]);
+        const T xlo5 = edge ? bload1<T>(xk, ox[0] + hoff) : T(0), xhi5 = edge ? bload1<T>(xk, ox[3] + hoff) : T(0);
+        V y2[2], dk[2];
+        T ye2[2];
+        {
+            const T *cz = cf.c[2] + 8 * k;
+            const T za = wave_uniform(cz[5]), zb = wave_uniform(cz[6]), zc = wave_uniform(cz[7]);
+            const bool pv = k >= 1 && k <= nz - 2;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const T ce = needr ? ec[b].a : ec[b].b, co = needr ? ec[b].b : ec[b].a;   // edge node, the one beyond
+                const T me = needr ? em[b].a : em[b].b, pe = needr ? ep[b].a : ep[b].b;
+                const V &s4 = b == 0 ? xlo : xc[0];
+                const V &n4 = b == 0 ? xc[1] : xhi;
+                const T se = b == 0 ? xlo5 : (needr ? ec[0].a : ec[0].b);
+                const T ne = b == 0 ? (needr ? ec[1].a : ec[1].b) : xhi5;
+                const T cv[4] = {xc[b].x, xc[b].y, xc[b].z, xc[b].w};
+                const T sv[4] = {s4.x, s4.y, s4.z, s4.w}, nw[4] = {n4.x, n4.y, n4.z, n4.w};
+                const T mv[4] = {xm[b].x, xm[b].y, xm[b].z, xm[b].w}, uv[4] = {xp[b].x, xp[b].y, xp[b].z, xp[b].w};
+                const T rv[4] = {rh[b].x, rh[b].y, rh[b].z, rh[b].w}, iv[4] = {yi4[b].x, yi4[b].y, yi4[b].z, yi4[b].w};
+                T left = __shfl_up(cv[3], 1, 64), right = __shfl_down(cv[0], 1, 64);
+                if (lane == 0) left = needl ? ce : T(0);
+                if (lane == 63) right = needr ? ce : T(0);
+                const bool live = pv && rok[b];               // uniform
+                T yv[4], dv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const T r = mg_reg_resid(rv[u], cv[u], u == 0 ? left : cv[u - 1], u == 3 ? right : cv[u + 1], sv[u],
+                                             nw[u], mv[u], uv[u], kax[u], kbx[u], kcx[u], kay[b], kby[b], kcy[b], za, zb, zc);
+                    dv[u] = T(1) / (kbx[u] + kby[b] + zb);
+                    yv[u] = cv[u] + c2a * r * dv[u];
+                }
+                if (__any(sk[b] | past)) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if ((sk[b] >> u) & 1u) yv[u] = iv[u];
+                        if ((past >> u) & 1u) yv[u] = T(0);
+                    }
+                }
+                y2[b] = live ? V{yv[0], yv[1], yv[2], yv[3]} : zero4;
+                dk[b] = V{dv[0], dv[1], dv[2], dv[3]};
+                ye2[b] = T(0);
+                if (SEG) {
+                    const T r = mg_reg_resid(h5[b], ce, needr ? cv[3] : co, needr ? co : cv[0], se, ne, me, pe, kax[4], kbx[4],
+                                             kcx[4], kay[b], kby[b], kcy[b], za, zb, zc);
+                    ye2[b] = ce + c2a * r / (kbx[4] + kby[b] + zb);
+                    if (sk[b] & 0x10u) ye2[b] = yi5[b];
+                    if (!live || !edge) ye2[b] = T(0);
+                }
+            }
+        }
+        if (k >= K0 + 1) {
+            const int q = k - 1;
+            const T *cz = cf.c[2] + 8 * q;
+            const T za = wave_uniform(cz[5]), zb = wave_uniform(cz[6]), zc = wave_uniform(cz[7]);
+            const V ylo = wv > 0 ? sh[q & 1][wv - 1][1][lane] : zero4;
+            const V yhi = wv < PAIR_WAVES - 1 ? sh[q & 1][wv + 1][0][lane] : zero4;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const V &s4 = b == 0 ? ylo : y1[0];
+                const V &n4 = b == 0 ? y1[1] : yhi;
+                const T cv[4] = {y1[b].x, y1[b].y, y1[b].z, y1[b].w};
+                const T sv[4] = {s4.x, s4.y, s4.z, s4.w}, nw[4] = {n4.x, n4.y, n4.z, n4.w};
+                const T mv[4] = {y0[b].x, y0[b].y, y0[b].z, y0[b].w}, uv[4] = {y2[b].x, y2[b].y, y2[b].z, y2[b].w};
+                const T dv[4] = {dp[b].x, dp[b].y, dp[b].z, dp[b].w};
+                const T rv[4] = {rp[b].x, rp[b].y, rp[b].z, rp[b].w}, xv[4] = {xm[b].x, xm[b].y, xm[b].z, xm[b].w};
+                T left = __shfl_up(cv[3], 1, 64), right = __shfl_down(cv[0], 1, 64);
+                if (lane == 0) left = ye1[b];                  // 0 at a wall
+                if (lane == 63) right = ye1[b];
+                T zv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const T r = mg_reg_resid(rv[u], cv[u], u == 0 ? left : cv[u - 1], u == 3 ? right : cv[u + 1], sv[u],
+                                             nw[u], mv[u], uv[u], kax[u], kbx[u], kcx[u], kay[b], kby[b], kcy[b], za, zb, zc);
+                    zv[u] = cv[u] + c1 * (cv[u] - xv[u]) + c2 * r * dv[u];
+                }
+                if (own[b]) {
+                    T *o = out + (size_t)q * plane + (ox[b + 1] / (uint32_t)sizeof(T));
+                    if (nv == 4 && (skp[b] & 0xFu) == 0u) {
+                        *reinterpret_cast<V *>(o) = V{zv[0], zv[1], zv[2], zv[3]};
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (u < nv && !((skp[b] >> u) & 1u)) o[u] = zv[u];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            sh[k & 1][wv][b][lane] = y2[b];
+            xm[b] = xc[b];
+            xc[b] = xp[b];
+            em[b] = ec[b];
+            ec[b] = ep[b];
+            y0[b] = y1[b];
+            y1[b] = y2[b];
+            ye1[b] = ye2[b];
+            rp[b] = rh[b];
+            dp[b] = dk[b];
+            skp[b] = sk[b];
+        }
+        __syncthreads();
+    }
+}
+
+// The irregular rows of k_mg_pair: y and z at the irregular nodes, yi and out.  Eight lanes take
+// a row: lane q forms y at the row's q-th node (its own, then the -x, +x, -y, +y, -z, +z
+// neighbours) from x_0.  Bound by its gathers.
+template <typename T>
+__global__ void __launch_bounds__(NT) k_mg_pair_irregular(Geom g, Coef<T> cf, Irr<T> ir,
+                                                          const uint32_t *__restrict__ skip, const T *__restrict__ x,
+                                                          const T *__restrict__ rho, T *__restrict__ yi,
+                                                          T *__restrict__ out, T c2a, T c1, T c2, const DevState *st)
+{
+    const int done = st ? st->done : 0;
+    const int t = (int)(blockIdx.x * NT + threadIdx.x), q = t & 7;
+    const bool live = (t >> 3) < ir.n;
+    const int row = min(t >> 3, ir.n - 1);
+    const int nx = g.nx, ny = g.ny, nz = g.nz, plane = nx * ny;
+    const int e = ir.node[row];
+    const T kq = ir.k7[7 * (size_t)row + min(q, 6)], kd0 = ir.k7[7 * (size_t)row], x0 = x[e], rho0 = rho[e];
+    const int k0 = e / plane, r0 = e - k0 * plane, j0 = r0 / nx, i0 = r0 - j0 * nx;
+    const int i = i0 + (q == 2) - (q == 1), j = j0 + (q == 4) - (q == 3), k = k0 + (q == 6) - (q == 5);
+    T y = T(0);
+    const bool wall = i == 0 || i == nx - 1 || j == 0 || j == ny - 1 || k == 0 || k == nz - 1;
+    if (!wall && q < 7) {
+        const size_t w = ((size_t)j + (size_t)ny * k) * g.W + (i >> 5);
+        const bool sb = (skip[w] >> (i & 31)) & 1u, ib = (ir.bits[w] >> (i & 31)) & 1u;
+        const size_t eq = (size_t)i + (size_t)nx * j + (size_t)plane * k;
+        const T c = x[eq], xw = x[eq - 1], xe = x[eq + 1], xs = x[eq - nx], xn = x[eq + nx], xd = x[eq - plane],
+                xu = x[eq + plane], rq = rho[eq];
+        T a[7] = {cf.c[0][8 * i + 6] + cf.c[1][8 * j + 6] + cf.c[2][8 * k + 6], cf.c[0][8 * i + 5], cf.c[0][8 * i + 7],
+                  cf.c[1][8 * j + 5], cf.c[1][8 * j + 7], cf.c[2][8 * k + 5], cf.c[2][8 * k + 7]};
+        if (ib) {
+            const T *k7 = ir.k7 + 7 * (size_t)irr_row_of(ir, w, i);
+#pragma unroll
+            for (int v = 0; v < 7; ++v) a[v] = k7[v];
+        }
+        const T kx = a[0] * c + a[1] * xw + a[2] * xe + a[3] * xs + a[4] * xn + a[5] * xd + a[6] * xu;
+        if (!sb || ib) y = c + c2a * (rq - kx) / a[0];
+    }
+    T sum = q < 7 ? kq * y : T(0);
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) sum += __shfl_xor(sum, o, 64);
+    if (q != 0 || !live || done) return;
+    yi[e] = y;
+    out[e] = y + c1 * (y - x0) + c2 * (rho0 - sum) / kd0;
+}
+
 // The same on small grids, whose march is bound by the round trips of its planes: a wavefront forms
 // the residual of one fine plane p = 2K - 1 + q for coarse plane K, all its loads issued at once,
 // and the three wavefronts of a coarse plane sum their shares through LDS.  Lanes take the groups
@@ -1014,6 +1288,32 @@ void launch_mg_restrict(hipStream_t s, const MgTransfer<T> &t, const T *r, T *rc
                                                   rc, first);
 }
 
+// Tiles of a kernel whose blocks march over tiles_x x tiles_y columns of nzi planes.  The march is
+// bound by the latency of its plane steps: all blocks run in one round, as many as fit on the
+// device at once (z-chunks of at least two planes).  per_cu: the kernel's blocks per CU, 0 before
+// its first launch.
+static Tiling march_tiling(int &per_cu, const void *fn, int threads, int tiles_x, int tiles_y, int nzi)
+{
+    if (!per_cu) {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, 0) != hipSuccess || nb < 1) nb = 1;
+        per_cu = nb;
+    }
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+        ncu = 256;
+    Tiling tl{};
+    tl.tiles_x = tiles_x;
+    tl.tiles_y = tiles_y;
+    const int per_plane = tiles_x * tiles_y, want = std::max(1, per_cu * ncu / per_plane);
+    tl.TZ = std::max(std::min(2, nzi), (nzi + want - 1) / want);
+    tl.zchunks = (nzi + tl.TZ - 1) / tl.TZ;
+    tl.ntiles = per_plane * tl.zchunks;
+    tl.nblk = (tl.ntiles + NXCD - 1) / NXCD * NXCD;
+    return tl;
+}
+
 // Which grids restrict with the short kernel: up to RRS_MAX_BYTES per vector.  Its twice-formed rows
 // and planes lose where the march has planes enough to overlap.  Measured (us, short against
 // march): FP32 48^3 5.6 / 9.9, 66^3 5.6 / 11.2, 98^3 8.5 / 12.6, 130^3 16.5 / 14.8; FP64 32^3 6.6 / 13.7,
@@ -1046,35 +1346,48 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
     const bool fifth = g.nx - 2 >= 257;
     const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true>)
                            : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false>);
-    // The march is bound by the latency of its plane steps: all blocks run in one round,
-    // as many as fit on the device at once (z-chunks of at least two coarse planes).
     static int per_cu[2] = {0, 0};
-    if (!per_cu[fifth]) {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 64 * (RR_ROWS + 1), 0) != hipSuccess || nb < 1) nb = 1;
-        per_cu[fifth] = nb;
-    }
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
-        ncu = 256;
-    Tiling tl{};
-    tl.tw = 128;
-    tl.ty = RR_ROWS;
-    tl.tiles_x = (ncx - 2 + 127) / 128;
-    tl.tiles_y = (ncy - 2 + tl.ty - 1) / tl.ty;
-    const int nzi = ncz - 2, per_plane = tl.tiles_x * tl.tiles_y;
-    const int want = std::max(1, per_cu[fifth] * ncu / per_plane);
-    tl.TZ = std::max(std::min(2, nzi), (nzi + want - 1) / want);
-    tl.zchunks = (nzi + tl.TZ - 1) / tl.TZ;
-    tl.ntiles = per_plane * tl.zchunks;
-    tl.nblk = (tl.ntiles + NXCD - 1) / NXCD * NXCD;
+    const Tiling tl = march_tiling(per_cu[fifth], fn, 64 * (RR_ROWS + 1), (ncx - 2 + 127) / 128, (ncy - 2 + RR_ROWS - 1) / RR_ROWS,
+                                   ncz - 2);
     if (fifth)
         k_mg_resid_restrict<T, true><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(
             g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st);
     else
         k_mg_resid_restrict<T, false><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(
             g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st);
+}
+
+// Which grids take the pair: those with more than PAIR_MIN_BYTES per vector.  On smaller ones the
+// sweeps run from the Infinity Cache and their launches cost less than the pair's few wavefronts.
+// Measured (us, pair with its irregular rows against two sweeps): FP32 130^3 23 / 15, 202^3 (32 MB)
+// 41 / 38; FP64 162^3 (33 MB) 42 / 42.
+constexpr size_t PAIR_MIN_BYTES = 40000000;
+template <typename T>
+bool mg_pair_pays(const Geom &g)
+{
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > PAIR_MIN_BYTES;
+}
+
+template <typename T>
+void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
+                    double c2a, double c1, double c2, const DevState *st)
+{
+    const Geom &g = L.g;
+    if (ir.n > 0)
+        k_mg_pair_irregular<T><<<(8 * ir.n + NT - 1) / NT, NT, 0, L.stream>>>(g, cf, ir, L.skip, x, rho, yi, out, (T)c2a,
+                                                                            (T)c1, (T)c2, st);
+    const bool seg = g.nx - 2 > 256;
+    const void *fn = seg ? reinterpret_cast<const void *>(&k_mg_pair<T, true>)
+                         : reinterpret_cast<const void *>(&k_mg_pair<T, false>);
+    static int per_cu[2] = {0, 0};
+    const Tiling tl = march_tiling(per_cu[seg], fn, 64 * Pair<T>::waves, (g.nx - 2 + 255) / 256,
+                                   (g.ny - 2 + Pair<T>::rows - 1) / Pair<T>::rows, g.nz - 2);
+    if (seg)
+        k_mg_pair<T, true><<<tl.nblk, dim3(64, Pair<T>::waves), 0, L.stream>>>(g, tl, cf, L.skip, x, rho, yi, out, (T)c2a, (T)c1,
+                                                                         (T)c2, st);
+    else
+        k_mg_pair<T, false><<<tl.nblk, dim3(64, Pair<T>::waves), 0, L.stream>>>(g, tl, cf, L.skip, x, rho, yi, out, (T)c2a,
+                                                                          (T)c1, (T)c2, st);
 }
 
 template <typename T>
@@ -1160,5 +1473,12 @@ template void launch_mg_prolong_add<double>(hipStream_t, const MgTransfer<double
                                             const double *, double *);
 template void launch_mg_prolong_add<float>(hipStream_t, const MgTransfer<float> &, const uint32_t *, int, const float *,
                                            float *);
+
+template bool mg_pair_pays<double>(const Geom &);
+template bool mg_pair_pays<float>(const Geom &);
+template void launch_mg_pair<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *, const double *,
+                                     double *, double *, double, double, double, const DevState *);
+template void launch_mg_pair<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *, const float *,
+                                    float *, float *, double, double, double, const DevState *);
 
 }  // namespace cps

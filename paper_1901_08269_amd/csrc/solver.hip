@@ -658,7 +658,11 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
                                 mg_vecs<T>(s->mg[1])[0], mg_first<T>(s, 1), st);
     T *e = mg_level<T>(s, 1, st);
     launch_mg_prolong_add<T>(s->stream, mg_transfer<T>(s->mg[0]), s->skip, s->g.W, e, x);
-    mg_smooth<T>(s, 0, L, cf, ir, ps, x, nullptr, x, res, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
+    // a sampled cycle smooths sweep by sweep, each with its own stamps
+    if (nu == 2 && !samp && mg_pair_pays<T>(s->g))
+        launch_mg_pair<T>(L, cf, ir, x, ps, res, dst, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st);
+    else
+        mg_smooth<T>(s, 0, L, cf, ir, ps, x, nullptr, x, res, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
 }
 
 // phi (dst) = sip_iters iterations of the strongly implicit procedure on K phi = ps from 0

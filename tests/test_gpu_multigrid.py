@@ -99,6 +99,24 @@ def test_residual_restriction_edges_match_oracle(shape):
     S.close()
 
 
+# Grids above 40 MB per vector in both precisions, where the two post-smoothing steps run as one
+# pass: one segment of 256 nodes per row and two, rows and planes that do not fill the last tiles
+# (22 rows in FP32, 14 in FP64), bodies across a segment's end.
+@pytest.mark.parametrize("shape", [(258, 203, 200), (283, 191, 196)])
+def test_large_vcycle_matches_oracle(shape):
+    grids = tuple(W.tanh_grid(n, 1.1) for n in shape)
+    bodies = [W.Sphere((0.55, 0.5, 0.48), 0.21), W.Sphere((0.93, 0.2, 0.31), 0.05)]
+    w = W.polynomial_case(0, bodies, rng_seed=13, grids=grids)
+    print(f"[case] multigrid large {shape}", flush=True)
+    M = mg.Multigrid(w.x, w.y, w.z, w.phi)
+    rho = _random_rho(w.phi.shape, M.lv[0]["P"].types(), 31)
+    ref = M.apply(rho)
+    S = cps.Solver.from_workload(w, precond="multigrid")
+    for prec, bar in (("fp64", 1e-11), ("fp32", 2e-5)):
+        assert np.max(np.abs(_np(S.precond(rho, prec)) - ref)) <= bar * np.max(np.abs(ref)), prec
+    S.close()
+
+
 def test_vcycle_options_match_oracle():
     """Two levels, one smoothing step each side, 8 coarse steps, smoother interval [0.3, 2]."""
     w = _case("sphere_stretched")
