@@ -1037,6 +1037,146 @@ __global__ void __launch_bounds__(MG_LDS_THREADS) k_mg_coarsest(int nx, int ny, 
         if (act[u]) out[at[u]] = x[u];
 }
 
+// The value of the lane before / after within 16 lanes (0 beyond them).
+__device__ __forceinline__ float lane_before(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_after(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x101, 0xf, 0xf, true));
+}
+template <typename F>
+__device__ __forceinline__ double both_halves(double v, F f)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__float_as_int(f(__int_as_float((int)(b & 0xffffffffll))));
+    const uint32_t hi = (uint32_t)__float_as_int(f(__int_as_float((int)(b >> 32))));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double lane_before(double v)
+{
+    return both_halves(v, [](float h) { return lane_before(h); });
+}
+__device__ __forceinline__ double lane_after(double v)
+{
+    return both_halves(v, [](float h) { return lane_after(h); });
+}
+
+// The same iteration on a level of at most 16 interior nodes per axis (every cube's coarsest
+// level): 16 lanes take a row of x, a thread four nodes along z, z fastest in LDS.  The x
+// neighbours come from the adjacent lanes' registers, three quarters of the z neighbours from the
+// thread's own, and the y neighbours of all four nodes in one read: 5 LDS instructions a step
+// instead of 28 (FP32), and a third of the loads before the steps.  Lanes, rows and planes past
+// the interior hold 0.  Solve of 16^3 nodes, 8 steps (us): FP32 8.6 against 13.1,
+// FP64 11.2 against 16.6.
+constexpr int MG_C16 = 16;
+template <typename T>
+__global__ void __launch_bounds__(MG_LDS_THREADS) k_mg_coarsest16(int nx, int ny, int nz, Coef<T> cf,
+                                                                  const int8_t *__restrict__ type,
+                                                                  const int *__restrict__ irr_map,
+                                                                  const T *__restrict__ k7, const T *__restrict__ rho,
+                                                                  T *__restrict__ out, int steps,
+                                                                  const T *__restrict__ c1, const T *__restrict__ c2,
+                                                                  const DevState *st)
+{
+    // z column of LDS: KO places before k = 0 (so that four nodes start at 16 bytes), a pitch that
+    // spreads 8 lanes' 16-byte reads over all banks
+    constexpr int KO = 16 / (int)sizeof(T), LZ = sizeof(T) == 4 ? 24 : 22, LY = LZ * MG_C16;
+    struct alignas(16) Four {
+        T v[4];
+    };
+    __shared__ alignas(16) T xs[2][(MG_C16 + 2) * LY];
+    __shared__ T cs[2 * MG_MAX_COARSE_STEPS];
+    const int done = st ? st->done : 0;   // used at the end: nothing waits for it
+    const int t = (int)threadIdx.x, wv = t >> 6, i = t & 15, j = 4 * (wv & 3) + ((t >> 4) & 3), k0 = 4 * (wv >> 2);
+    const int ni = nx - 2, nj = ny - 2, nk = nz - 2, nxy = nx * ny;
+    const bool col = i < ni && j < nj;
+    const int ic = min(i, ni - 1) + 1, jc = min(j, nj - 1) + 1;
+    // all nodes' loads at once, then those of the irregular rows' stored K rows
+    int node[4], irl[4];
+    int8_t ty[4];
+    T rh[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int kc = min(k0 + u, nk - 1) + 1;
+        node[u] = ic + nx * jc + nxy * kc;
+        ty[u] = type[node[u]];
+        rh[u] = rho[node[u]];
+        irl[u] = irr_map[node[u]];
+    }
+    const T *cx = cf.c[0] + 8 * ic, *cy = cf.c[1] + 8 * jc;
+    const T kx5 = cx[5], kx6 = cx[6], kx7 = cx[7], ky5 = cy[5], ky6 = cy[6], ky7 = cy[7];
+    if (t < steps) {
+        cs[t] = c1[t];
+        cs[MG_MAX_COARSE_STEPS + t] = c2[t];
+    }
+    {
+        Four *z = reinterpret_cast<Four *>(xs);
+        for (int q = t; q < 2 * (MG_C16 + 2) * LY / 4; q += MG_LDS_THREADS) z[q] = Four{{T(0), T(0), T(0), T(0)}};
+    }
+    T ko[4][6], x[4], xp[4];
+    bool act[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int kc = min(k0 + u, nk - 1) + 1;
+        const T *cz = cf.c[2] + 8 * kc;
+        T row[7] = {kx6 + ky6 + cz[6], kx5, kx7, ky5, ky7, cz[5], cz[7]};
+        const bool in = col && k0 + u < nk, irr = in && ty[u] == 2;
+        if (irr) {
+            const T *p = k7 + 7 * (size_t)irl[u];
+#pragma unroll
+            for (int v = 0; v < 7; ++v) row[v] = p[v];
+        }
+        act[u] = irr || (in && ty[u] == 1);
+        // rows scaled by 1 / diag K: (rho - K x) / diag = rho' - x - sum_v ko'_v x_v
+        const T rd = act[u] ? T(1) / row[0] : T(0);
+        rh[u] *= rd;
+#pragma unroll
+        for (int v = 0; v < 6; ++v) ko[u][v] = row[1 + v] * rd;
+        if (!act[u]) rh[u] = T(0);
+        x[u] = T(0);
+        xp[u] = T(0);
+    }
+    const int at = (j + 1) * LY + i * LZ + KO + k0;
+    __syncthreads();
+    auto step = [&](const T *cur, T *nxt, int s) __attribute__((always_inline)) {
+        const T a1 = cs[s], a2 = cs[MG_MAX_COARSE_STEPS + s];
+        const Four lo = *reinterpret_cast<const Four *>(cur + at - LY), hi = *reinterpret_cast<const Four *>(cur + at + LY);
+        const T zlo = cur[at - 1], zhi = cur[at + 4];
+        Four xn;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            T kx = x[u];
+            kx += ko[u][0] * lane_before(x[u]);
+            kx += ko[u][1] * lane_after(x[u]);
+            kx += ko[u][2] * lo.v[u];
+            kx += ko[u][3] * hi.v[u];
+            kx += ko[u][4] * (u == 0 ? zlo : x[u == 0 ? 0 : u - 1]);
+            kx += ko[u][5] * (u == 3 ? zhi : x[u == 3 ? 3 : u + 1]);
+            xn.v[u] = x[u] + a1 * (x[u] - xp[u]) + a2 * (rh[u] - kx);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            xp[u] = x[u];
+            x[u] = act[u] ? xn.v[u] : T(0);
+            xn.v[u] = x[u];
+        }
+        *reinterpret_cast<Four *>(nxt + at) = xn;
+        __syncthreads();
+    };
+    int s = 0;
+    for (; s + 1 < steps; s += 2) {
+        step(xs[0], xs[1], s);
+        step(xs[1], xs[0], s + 1);
+    }
+    if (s < steps) step(xs[0], xs[1], s);
+    if (done) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (act[u]) out[node[u]] = x[u];
+}
+
 // Temporally blocked Chebyshev-Jacobi steps on a coarse level (launch_mg_smooth_tb).  The
 // block owns a tile of MG_TB_TS^3 nodes.  x_0 is loaded on the tile and H layers around it
 // (edge E, 0 at nodes that are not unknowns and outside the grid's interior) into LDS; the
@@ -1404,7 +1544,12 @@ void launch_mg_coarsest(hipStream_t s, int nx, int ny, int nz, const Coef<T> &cf
                         const int *irr_map, const T *k7, const T *rho, T *out, int steps, const T *c1, const T *c2,
                         const DevState *st)
 {
-    k_mg_coarsest<T><<<1, MG_LDS_THREADS, 0, s>>>(nx, ny, nz, cf, type, irr_map, k7, rho, out, steps, c1, c2, st);
+    // at most 16 interior nodes per axis: a thread's z column and its x row fit the layout
+    // (k_mg_coarsest16 has both times)
+    if (std::max(nx, std::max(ny, nz)) - 2 <= MG_C16)
+        k_mg_coarsest16<T><<<1, MG_LDS_THREADS, 0, s>>>(nx, ny, nz, cf, type, irr_map, k7, rho, out, steps, c1, c2, st);
+    else
+        k_mg_coarsest<T><<<1, MG_LDS_THREADS, 0, s>>>(nx, ny, nz, cf, type, irr_map, k7, rho, out, steps, c1, c2, st);
 }
 
 template <typename T>

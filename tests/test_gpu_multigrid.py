@@ -117,6 +117,22 @@ def test_large_vcycle_matches_oracle(shape):
     S.close()
 
 
+# Coarsest levels in one workgroup: interiors of 16 x 15 x 15 and 16 x 9 x 8 nodes (a row of 16
+# lanes full, columns of four not), 8 x 16 x 9, and 17 x 9 x 9 (more than 16 along one axis).
+@pytest.mark.parametrize("shape", [(34, 33, 32), (34, 20, 19), (18, 34, 21), (36, 20, 20)])
+def test_coarsest_level_shapes_match_oracle(shape):
+    grids = tuple(W.tanh_grid(n, 0.9) for n in shape)
+    w = W.polynomial_case(0, [W.Sphere((0.5, 0.52, 0.47), 0.24)], rng_seed=4, grids=grids)
+    for steps in (1, 7, 8):
+        M = mg.Multigrid(w.x, w.y, w.z, w.phi, levels=2, coarse_steps=steps)
+        rho = _random_rho(w.phi.shape, M.lv[0]["P"].types(), 3)
+        ref = M.apply(rho)
+        S = cps.Solver.from_workload(w, precond="multigrid", mg_levels=2, mg_coarse_steps=steps)
+        for prec, bar in (("fp64", 1e-11), ("fp32", 2e-5)):
+            assert np.max(np.abs(_np(S.precond(rho, prec)) - ref)) <= bar * np.max(np.abs(ref)), (steps, prec)
+        S.close()
+
+
 def test_vcycle_options_match_oracle():
     """Two levels, one smoothing step each side, 8 coarse steps, smoother interval [0.3, 2]."""
     w = _case("sphere_stretched")
