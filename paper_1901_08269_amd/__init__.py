@@ -246,7 +246,7 @@ class Solver:
     def residual(self, u):
         torch = _torch()
         uu = _dev64(u, self.shape)
-        r = torch.zeros(self.shape, dtype=torch.float64, device="cuda")
+        r = torch.empty(self.shape, dtype=torch.float64, device="cuda")
         rel = (C.c_double * 2)()
         self._check(self.L.cps_residual(self.h, _ptr(uu), _ptr(r), C.cast(rel, C.c_void_p)), "cps_residual")
         return r, rel[0], rel[1]
@@ -254,7 +254,7 @@ class Solver:
     def apply(self, x, precision="fp64"):
         torch = _torch()
         xx = _dev64(x, self.shape)
-        y = torch.zeros(self.shape, dtype=torch.float64, device="cuda")
+        y = torch.empty(self.shape, dtype=torch.float64, device="cuda")
         p = CPS_MIXED if precision in ("fp32", "mixed") else CPS_FP64
         self._check(self.L.cps_apply(self.h, _ptr(xx), _ptr(y), p), "cps_apply")
         return y
@@ -262,7 +262,7 @@ class Solver:
     def precond(self, rho, precision="fp64"):
         torch = _torch()
         rr = _dev64(rho, self.shape)
-        y = torch.zeros(self.shape, dtype=torch.float64, device="cuda")
+        y = torch.empty(self.shape, dtype=torch.float64, device="cuda")
         p = CPS_MIXED if precision in ("fp32", "mixed") else CPS_FP64
         self._check(self.L.cps_precond(self.h, _ptr(rr), _ptr(y), p), "cps_precond")
         return y

@@ -57,7 +57,7 @@ struct VecList {
 template <typename T>
 void launch_zero_off_unknowns(hipStream_t s, size_t nn, size_t pad, const int8_t *type, const VecList<T> &v);
 template <typename TI, typename TO>
-void launch_masked_copy(hipStream_t s, size_t n, const int8_t *type, const TI *src, TO *dst);
+void launch_masked_copy(hipStream_t s, size_t n, const int8_t *type, const TI *src, TO *dst, TO *zero = nullptr);
 void launch_output(hipStream_t s, size_t n, const int8_t *type, const double *x, const double *gv, double *u);
 void launch_check_finite(hipStream_t s, size_t n, const int8_t *type, const double *x, int *flag);
 constexpr int DOT_BLOCKS = 1024;

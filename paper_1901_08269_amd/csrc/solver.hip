@@ -278,12 +278,12 @@ T *dalloc(cps_solver *s, size_t n)
     return (T *)p;
 }
 
-void dfree(cps_solver *s, void *p)
+void dfree(cps_solver *s, void *p, bool synced = false)
 {
     if (!p) return;
     auto it = std::find_if(s->allocs.begin(), s->allocs.end(), [&](const cps_solver::Alloc &a) { return a.p == p; });
     if (it == s->allocs.end()) return;
-    (void)hipStreamSynchronize(s->stream);
+    if (!synced) (void)hipStreamSynchronize(s->stream);   // synced: the caller has waited for the stream
     cache_release(it->p, it->bytes);
     s->allocs.erase(it);
 }
@@ -292,6 +292,14 @@ void dfree(cps_solver *s, void *p)
 void to_device(cps_solver *s, void *dst, const void *src, size_t bytes)
 {
     ck(hipMemcpyAsync(dst, src, bytes, s->opt.device_ptrs ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s->stream));
+}
+
+// A single operator (residual, apply, precond) reads its device input and writes its device output
+// in place of staging copies of them, unless the two arrays share memory.
+bool direct_io(const cps_solver *s, const double *in, const double *out)
+{
+    const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out, n = s->nn * sizeof(double);
+    return s->opt.device_ptrs && (a + n <= b || b + n <= a);
 }
 
 void from_device(cps_solver *s, void *dst, const void *src, size_t bytes)
@@ -853,7 +861,7 @@ void free_solver(cps_solver *s)
 double scale_warm_start(cps_solver *s, double *x64)
 {
     const Launch L = s->launch();
-    if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn);
+    if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
     double *y = s->tmp64;    // B u0 at the unknown rows
     launch_apply<double, double>(MODE_PLAIN, L, s->cf64(), s->ir64(), x64, y, nullptr, nullptr, nullptr);
     if (!s->dot_partials) s->dot_partials = dalloc<double>(s, 2 * DOT_BLOCKS);
@@ -1288,23 +1296,25 @@ void precond_standalone(cps_solver *s, const double *rho_dev, double *out_dev)
 {
     Vecs<T> V;
     T *all[5];
+    VecList<T> list{};
     for (auto &p : all) {
         p = dalloc<T>(s, s->nn + VEC_PAD);
-        launch_fill<T>(s->stream, s->nn + VEC_PAD, p, T(0));
+        list.p[list.n++] = p;
     }
+    // as for the solve's vectors: the unknowns are written before they are read
+    launch_zero_off_unknowns<T>(s->stream, s->nn, VEC_PAD, s->type, list);
     V.c[0] = all[0]; V.c[1] = all[1];
     T *rin = all[2], *ps = all[3], *dst = all[4];
     launch_masked_copy<double, T>(s->stream, s->nn, s->type, rho_dev, rin);
-    // state: alpha = 0 so that the fused first step computes x1 from rho itself
-    DevState zero{};
-    ck(hipMemcpyAsync(s->st, &zero, sizeof(DevState), hipMemcpyHostToDevice, s->stream));
-    sync(s);
+    // state: all 0 (alpha = 0, so that the fused first step computes x1 from rho itself)
+    static_assert(sizeof(DevState) % sizeof(double) == 0, "the state is cleared as doubles");
+    launch_fill<double>(s->stream, sizeof(DevState) / sizeof(double), reinterpret_cast<double *>(s->st), 0.0);
     double c1[MAX_INNER], c2[MAX_INNER];
     cheb_coefficients(s->opt.inner_iters, s->opt.lam_lo, s->opt.lam_hi, c1, c2);
     precond_apply<T>(s, V, FIRST_S, rin, ps, rin, dst, c1, c2, s->st);
     launch_masked_copy<T, double>(s->stream, s->nn, s->type, dst, out_dev);
     sync(s);
-    for (auto p : all) dfree(s, p);
+    for (auto p : all) dfree(s, p, true);
 }
 
 }  // namespace
@@ -1599,7 +1609,7 @@ int cps_solve(cps_solver *s, double tol, double *u, int32_t warm_start, cps_stat
             // a device array is read in place; a host one is staged first
             const double *u_dev = u;
             if (!s->opt.device_ptrs) {
-                if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn);
+                if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
                 to_device(s, s->tmp64, u, s->nn * sizeof(double));
                 u_dev = s->tmp64;
             }
@@ -1706,7 +1716,7 @@ int cps_solve(cps_solver *s, double tol, double *u, int32_t warm_start, cps_stat
         if (s->opt.device_ptrs) {
             launch_output(s->stream, s->nn, s->type, x64, s->gf, u);
         } else {
-            if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn);
+            if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
             launch_output(s->stream, s->nn, s->type, x64, s->gf, s->tmp64);
             from_device(s, u, s->tmp64, s->nn * sizeof(double));
         }
@@ -1726,21 +1736,21 @@ int cps_residual(cps_solver *s, const double *u, double *r, double *rel)
 {
     if (!s || !u) return CPS_EINVAL;
     try {
-        if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn);
-        double *xin = dalloc<double>(s, s->nn + VEC_PAD);
-        double *rout = dalloc<double>(s, s->nn);
-        to_device(s, s->tmp64, u, s->nn * sizeof(double));
-        launch_masked_copy<double, double>(s->stream, s->nn, s->type, s->tmp64, xin);
-        launch_fill<double>(s->stream, s->nn, rout, 0.0);
+        if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
+        const bool direct = r ? direct_io(s, u, r) : (bool)s->opt.device_ptrs;
+        double *xin = direct ? s->tmp64 : dalloc<double>(s, s->nn + VEC_PAD);
+        double *rout = direct && r ? r : dalloc<double>(s, s->nn);
+        if (!direct) to_device(s, s->tmp64, u, s->nn * sizeof(double));
+        launch_masked_copy<double, double>(s->stream, s->nn, s->type, direct ? u : s->tmp64, xin, rout);
         launch_apply<double, double>(MODE_RES, s->launch(), s->cf64(), s->ir64(), xin, rout, nullptr, s->rhs, s->st);
-        if (r) from_device(s, r, rout, s->nn * sizeof(double));
+        if (r && !direct) from_device(s, r, rout, s->nn * sizeof(double));
         DevState ds = read_state(s);
         if (rel) {
             rel[0] = std::sqrt(ds.res2 / (s->bn2 > 0 ? s->bn2 : 1.0));
             rel[1] = std::sqrt(ds.res2s / (s->bs2 > 0 ? s->bs2 : 1.0));
         }
-        dfree(s, xin);
-        dfree(s, rout);
+        if (xin != s->tmp64) dfree(s, xin, true);
+        if (rout != r) dfree(s, rout, true);
     } catch (HipFail &) {
         return CPS_EDEVICE;
     } catch (std::bad_alloc &) {
@@ -1753,27 +1763,28 @@ int cps_apply(cps_solver *s, const double *x, double *y, int32_t precision)
 {
     if (!s || !x || !y || (precision != CPS_FP64 && precision != CPS_MIXED)) return CPS_EINVAL;
     try {
-        if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn);
-        to_device(s, s->tmp64, x, s->nn * sizeof(double));
+        if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
+        const bool direct = direct_io(s, x, y);
+        if (!direct) to_device(s, s->tmp64, x, s->nn * sizeof(double));
         if (precision == CPS_FP64) {
-            double *xin = dalloc<double>(s, s->nn + VEC_PAD), *yo = dalloc<double>(s, s->nn);
-            launch_masked_copy<double, double>(s->stream, s->nn, s->type, s->tmp64, xin);
-            launch_fill<double>(s->stream, s->nn, yo, 0.0);
+            double *xin = direct ? s->tmp64 : dalloc<double>(s, s->nn + VEC_PAD), *yo = direct ? y : dalloc<double>(s, s->nn);
+            launch_masked_copy<double, double>(s->stream, s->nn, s->type, direct ? x : s->tmp64, xin, yo);
             launch_apply<double, double>(MODE_PLAIN, s->launch(), s->cf64(), s->ir64(), xin, yo, nullptr, nullptr, nullptr);
-            from_device(s, y, yo, s->nn * sizeof(double));
+            if (!direct) from_device(s, y, yo, s->nn * sizeof(double));
             sync(s);
-            dfree(s, xin);
-            dfree(s, yo);
+            if (!direct) {
+                dfree(s, xin, true);
+                dfree(s, yo, true);
+            }
         } else {
             float *xin = dalloc<float>(s, s->nn + VEC_PAD), *yo = dalloc<float>(s, s->nn);
-            launch_masked_copy<double, float>(s->stream, s->nn, s->type, s->tmp64, xin);
-            launch_fill<float>(s->stream, s->nn, yo, 0.0f);
+            launch_masked_copy<double, float>(s->stream, s->nn, s->type, direct ? x : s->tmp64, xin);
             launch_apply<float, float>(MODE_PLAIN, s->launch(), s->cf32(), s->ir32(), xin, yo, nullptr, nullptr, nullptr);
-            launch_masked_copy<float, double>(s->stream, s->nn, s->type, yo, s->tmp64);
-            from_device(s, y, s->tmp64, s->nn * sizeof(double));
+            launch_masked_copy<float, double>(s->stream, s->nn, s->type, yo, direct ? y : s->tmp64);
+            if (!direct) from_device(s, y, s->tmp64, s->nn * sizeof(double));
             sync(s);
-            dfree(s, xin);
-            dfree(s, yo);
+            dfree(s, xin, true);
+            dfree(s, yo, true);
         }
     } catch (HipFail &) {
         return CPS_EDEVICE;
@@ -1787,17 +1798,20 @@ int cps_precond(cps_solver *s, const double *rho, double *phi, int32_t precision
 {
     if (!s || !rho || !phi || (precision != CPS_FP64 && precision != CPS_MIXED)) return CPS_EINVAL;
     try {
-        if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn);
-        double *out = dalloc<double>(s, s->nn);
-        to_device(s, s->tmp64, rho, s->nn * sizeof(double));
+        if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
+        const bool direct = direct_io(s, rho, phi);
+        if (!direct) to_device(s, s->tmp64, rho, s->nn * sizeof(double));
+        const double *in = direct ? rho : s->tmp64;
+        double *out = direct ? phi : s->tmp64;               // written after the last read of the input
         const int timing = s->opt.kernel_timing;
         s->opt.kernel_timing = 0;
-        if (precision == CPS_FP64) precond_standalone<double>(s, s->tmp64, out);
-        else precond_standalone<float>(s, s->tmp64, out);
+        if (precision == CPS_FP64) precond_standalone<double>(s, in, out);
+        else precond_standalone<float>(s, in, out);
         s->opt.kernel_timing = timing;
-        from_device(s, phi, out, s->nn * sizeof(double));
-        sync(s);
-        dfree(s, out);
+        if (!direct) {
+            from_device(s, phi, out, s->nn * sizeof(double));
+            sync(s);
+        }
     } catch (HipFail &) {
         return CPS_EDEVICE;
     } catch (std::bad_alloc &) {

@@ -1107,14 +1107,19 @@ __global__ void k_zero_off_unknowns(size_t nn, size_t pad, const int8_t *__restr
     }
 }
 
-// dst = src at unknown nodes (types 1, 2), 0 elsewhere; converts precision
+// dst = src at unknown nodes (types 1, 2), 0 elsewhere; converts precision.  zero (or null): an
+// array set to 0 at the other nodes.
 template <typename TI, typename TO>
-__global__ void k_masked_copy(size_t n, const int8_t *__restrict__ type, const TI *__restrict__ src, TO *__restrict__ dst)
+__global__ void k_masked_copy(size_t n, const int8_t *__restrict__ type, const TI *__restrict__ src, TO *__restrict__ dst,
+                              TO *__restrict__ zero)
 {
     size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (; e < n; e += (size_t)gridDim.x * blockDim.x) {
-        int8_t t = type[e];
-        dst[e] = (t == 1 || t == 2) ? (TO)src[e] : TO(0);
+        const int8_t t = type[e];
+        const TI v = src[e];
+        const bool unk = t == 1 || t == 2;
+        dst[e] = unk ? (TO)v : TO(0);
+        if (zero && !unk) zero[e] = TO(0);
     }
 }
 
@@ -1352,9 +1357,9 @@ void launch_fill(hipStream_t s, size_t n, T *a, T val)
 }
 
 template <typename TI, typename TO>
-void launch_masked_copy(hipStream_t s, size_t n, const int8_t *type, const TI *src, TO *dst)
+void launch_masked_copy(hipStream_t s, size_t n, const int8_t *type, const TI *src, TO *dst, TO *zero)
 {
-    k_masked_copy<TI, TO><<<flat_grid(n), 256, 0, s>>>(n, type, src, dst);
+    k_masked_copy<TI, TO><<<flat_grid(n), 256, 0, s>>>(n, type, src, dst, zero);
 }
 
 void launch_output(hipStream_t s, size_t n, const int8_t *type, const double *x, const double *gv, double *u)
@@ -1417,8 +1422,8 @@ template void launch_zero_off_unknowns<float>(hipStream_t, size_t, size_t, const
 template void launch_fill<double>(hipStream_t, size_t, double *, double);
 template void launch_fill<float>(hipStream_t, size_t, float *, float);
 template void launch_fill<unsigned>(hipStream_t, size_t, unsigned *, unsigned);
-template void launch_masked_copy<double, double>(hipStream_t, size_t, const int8_t *, const double *, double *);
-template void launch_masked_copy<double, float>(hipStream_t, size_t, const int8_t *, const double *, float *);
-template void launch_masked_copy<float, double>(hipStream_t, size_t, const int8_t *, const float *, double *);
+template void launch_masked_copy<double, double>(hipStream_t, size_t, const int8_t *, const double *, double *, double *);
+template void launch_masked_copy<double, float>(hipStream_t, size_t, const int8_t *, const double *, float *, float *);
+template void launch_masked_copy<float, double>(hipStream_t, size_t, const int8_t *, const float *, double *, double *);
 
 }  // namespace cps

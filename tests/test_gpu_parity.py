@@ -264,6 +264,47 @@ def test_residual_matches_oracle():
     assert abs(rel - rel_ref) <= 1e-12 * rel_ref
 
 
+@pytest.mark.parametrize("precond", ["multigrid", "chebyshev", "sip"])
+def test_operators_write_whole_arrays_and_work_in_place(precond):
+    """residual, apply and precond through the C-ABI: an output full of NaN is written at every
+    node (0 off the unknowns, the walls and the solid nodes), an output that is the input array
+    or overlaps it gets the same values, and arrays need only the alignment of a double."""
+    import ctypes as C
+    import torch
+    x, y, z, phi, g, f, _ = _case("sphere_stretched")
+    print(f"[case] operator arrays {precond}", flush=True)
+    S = cps.Solver(x, y, z, phi, g, f, precond=precond)
+    nn = phi.size
+    off = torch.as_tensor(~np.isin(_np(S.rhs_and_types()[1]), (1, 2))).reshape(-1).cuda()
+    v = torch.as_tensor(np.random.default_rng(3).standard_normal(nn)).cuda()
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+
+    def residual(i, o, _):
+        rel = (C.c_double * 2)()
+        return S.L.cps_residual(S.h, ptr(i), ptr(o), C.cast(rel, C.c_void_p))
+
+    ops = {"residual": residual, "apply": lambda i, o, p: S.L.cps_apply(S.h, ptr(i), ptr(o), p),
+           "precond": lambda i, o, p: S.L.cps_precond(S.h, ptr(i), ptr(o), p)}
+    for name, op in ops.items():
+        for p in (cps.CPS_FP64, cps.CPS_MIXED):
+            out = torch.full((nn,), float("nan"), dtype=torch.float64, device="cuda")
+            torch.cuda.synchronize()
+            assert op(v, out, p) == 0
+            assert bool(torch.isfinite(out).all()) and bool((out[off] == 0).all())
+            for shift_in, shift_out in ((0, 0), (0, 1), (3, 0)):      # the same array, overlapping ones
+                buf = torch.zeros(nn + 3, dtype=torch.float64, device="cuda")
+                buf[shift_in:shift_in + nn] = v
+                torch.cuda.synchronize()
+                assert op(buf[shift_in:], buf[shift_out:], p) == 0
+                assert torch.equal(buf[shift_out:shift_out + nn], out), (name, p, shift_in, shift_out)
+            a, b = torch.zeros(nn + 1, dtype=torch.float64, device="cuda"), torch.zeros(nn + 1, dtype=torch.float64,
+                                                                                          device="cuda")
+            a[1:] = v
+            torch.cuda.synchronize()
+            assert op(a[1:], b[1:], p) == 0 and torch.equal(b[1:], out)
+    S.close()
+
+
 def test_determinism_bitwise():
     _, S, _ = _both("sphere_stretched")
     u1, s1 = S.solve(1e-10)
