@@ -168,6 +168,30 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// The arithmetic of a smoothing step, written with explicit fused operations where several
+// kernels form the same value (a small problem's pass in one launch, or sweep by sweep when its
+// sweeps are timed) and have to agree to the last bit.
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// (K x)_i from the row d, cw .. cu and its nodes' values (centre, -x, +x, -y, +y, -z, +z)
+template <typename T>
+__device__ __forceinline__ T row7(T d, T x, T cw, T w, T ce, T e, T cs, T s, T cn, T n, T cd, T dn, T cu, T up)
+{
+    return fma_(cu, up, fma_(cd, dn, fma_(cn, n, fma_(cs, s, fma_(ce, e, fma_(cw, w, d * x))))));
+}
+// x_{k+1} of a Chebyshev step: x + c1 (x - x_{k-1}) + c2 r / d
+template <typename T>
+__device__ __forceinline__ T cheb_next(T x, T xm1, T c1, T c2, T r, T d)
+{
+    return fma_(c1, x - xm1, x) + c2 * r / d;
+}
+// (1 - w) a + w b
+template <typename T>
+__device__ __forceinline__ T lerp_(T w, T a, T b)
+{
+    return fma_(w, b, (T(1) - w) * a);
+}
+
 // Deterministic block reduction of NV values over NW wavefronts; result valid in thread 0.
 template <int NV, int NW>
 __device__ __forceinline__ void block_sum(double (&v)[NV], double (&sh)[NV][NW])

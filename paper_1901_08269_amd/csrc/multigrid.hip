@@ -881,14 +881,15 @@ __global__ void __launch_bounds__(256) k_mg_prolong_add(int nfx, int nfy, int nf
     const V q11 = *reinterpret_cast<const V *>(e00 + cplane + ncx);
     const V wxv = *reinterpret_cast<const V *>(ax.pw + i0);
     const T wy = ay.pw[j];
-    const V lo = (T(1) - wy) * q00 + wy * q10, hi = (T(1) - wy) * q01 + wy * q11;   // y, coarse planes c, c + 1
+    const T lo[4] = {lerp_(wy, q00.x, q10.x), lerp_(wy, q00.y, q10.y), lerp_(wy, q00.z, q10.z), lerp_(wy, q00.w, q10.w)};
+    const T hi[4] = {lerp_(wy, q01.x, q11.x), lerp_(wy, q01.y, q11.y), lerp_(wy, q01.z, q11.z), lerp_(wy, q01.w, q11.w)};
+    // (y, on the coarse planes c, c + 1)
     const T wx[4] = {wxv.x, wxv.y, wxv.z, wxv.w};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         if (!ok[h]) continue;
         const T wz = az.pw[kp + h];
-        const V r4 = (T(1) - wz) * lo + wz * hi;
-        const T ryz[4] = {r4.x, r4.y, r4.z, r4.w};
+        const T ryz[4] = {lerp_(wz, lo[0], hi[0]), lerp_(wz, lo[1], hi[1]), lerp_(wz, lo[2], hi[2]), lerp_(wz, lo[3], hi[3])};
         T add[4];
         bool m[4];
         bool all = nv == 4;
@@ -897,7 +898,7 @@ __global__ void __launch_bounds__(256) k_mg_prolong_add(int nfx, int nfy, int nf
             const int d = min((i0 + u) >> 1, ncx - 2) - a0;   // 0 .. 2
             const T l = d == 0 ? ryz[0] : (d == 1 ? ryz[1] : ryz[2]);
             const T r = d == 0 ? ryz[1] : (d == 1 ? ryz[2] : ryz[3]);
-            add[u] = (T(1) - wx[u]) * l + wx[u] * r;
+            add[u] = lerp_(wx[u], l, r);
             m[u] = u < nv && !((sk[h] >> u) & 1u);   // regular unknowns only (interior, no skip bit)
             all = all && m[u];
         }
@@ -1259,11 +1260,10 @@ __global__ void __launch_bounds__(MG_TB_THREADS) k_mg_smooth_tb(int nx, int ny, 
             T ryz[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const T lo = (T(1) - wy) * e00[h] + wy * e00[ncx + h];
-                const T hi = (T(1) - wy) * e00[cpl + h] + wy * e00[cpl + ncx + h];
-                ryz[h] = (T(1) - wz) * lo + wz * hi;
+                const T lo = lerp_(wy, e00[h], e00[ncx + h]), hi = lerp_(wy, e00[cpl + h], e00[cpl + ncx + h]);
+                ryz[h] = lerp_(wz, lo, hi);
             }
-            pe[u] = (T(1) - wx) * ryz[0] + wx * ryz[1];
+            pe[u] = lerp_(wx, ryz[0], ryz[1]);
         }
     }
     T rh[NG], kd[NG], ko[NG][6], xp[NG];
@@ -1331,8 +1331,8 @@ __global__ void __launch_bounds__(MG_TB_THREADS) k_mg_smooth_tb(int nx, int ny, 
     };
     const T *cur = xs[0];
     auto kx_of = [&](int u, int q, T x) {
-        return kd[u] * x + ko[u][0] * cur[q - 1] + ko[u][1] * cur[q + 1] + ko[u][2] * cur[q - E] + ko[u][3] * cur[q + E] +
-               ko[u][4] * cur[q - E2] + ko[u][5] * cur[q + E2];
+        return row7(kd[u], x, ko[u][0], cur[q - 1], ko[u][1], cur[q + 1], ko[u][2], cur[q - E], ko[u][3], cur[q + E],
+                    ko[u][4], cur[q - E2], ko[u][5], cur[q + E2]);
     };
     for (int s = 0; s < S.n; ++s) {
         const T c1 = S.c1[s], c2 = S.c2[s];
@@ -1342,7 +1342,7 @@ __global__ void __launch_bounds__(MG_TB_THREADS) k_mg_smooth_tb(int nx, int ny, 
             const int q = at_of(u);
             const T x = cur[q];
             const T kx = kx_of(u, q, x);
-            const T xn = act[u] ? x + c1 * (x - xp[u]) + c2 * (rh[u] - kx) / kd[u] : T(0);
+            const T xn = act[u] ? cheb_next(x, xp[u], c1, c2, rh[u] - kx, kd[u]) : T(0);
             xp[u] = x;
             if (t + NTH * u < G3) nxt[q] = xn;
         }

@@ -95,6 +95,7 @@ struct cps_solver {
     uint32_t *skip = nullptr;
     double *dot_partials = nullptr;  // warm-start scaling: per-block partial dots
     uint32_t *irr_bits = nullptr;  // irregular-node bits (skip-word layout)
+    int *irr_map = nullptr;        // node -> irregular row, on small grids with the multigrid preconditioner
     int *irr_wstart = nullptr;     // irregular rows before each bit word
     int nirr = 0;
     int *irr_node = nullptr, *irr_ptr = nullptr, *irr_col = nullptr;
@@ -655,6 +656,26 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
     }
     const int nu = s->opt.mg_nu;
     launch_first<T>(kind, L, cf, ir, r, ps, v, a, s->mg_c2[0], st);
+    if (s->irr_map && nu >= 2 && nu - 1 <= MG_TB_H - 2) {
+        // a small problem (irr_map is there up to MG_TB_MAX_POINTS): its passes temporally blocked
+        // like a small coarse level's (mg_level), two launches for six.  Their times, with the
+        // residual's restriction and the prolongation (us, blocked against sweep by sweep): 32^3
+        // FP64 16.3 / 27.7, 48^3 FP32 12.4 / 24.0, 66^3 FP32 19.2 / 23.7, FP64 29.6 / 29.8.  A sampled
+        // cycle smooths sweep by sweep after the coarse correction, with the same result.
+        const MgTransfer<T> &tr = mg_transfer<T>(s->mg[0]);
+        const MgFirst<T> first = mg_first<T>(s, 1);
+        launch_mg_smooth_tb<T>(s->stream, s->nx, s->ny, s->nz, cf, s->type, s->irr_map, ir.k7, ps, a, b, nullptr,
+                               mg_steps<T>(s, 1, nu), st, &tr, nullptr, mg_vecs<T>(s->mg[1])[0], &first);
+        T *e = mg_level<T>(s, 1, st);
+        if (samp) {
+            launch_mg_prolong_add<T>(s->stream, tr, s->skip, s->g.W, e, b);
+            mg_smooth<T>(s, 0, L, cf, ir, ps, b, nullptr, b, a, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
+        } else {
+            launch_mg_smooth_tb<T>(s->stream, s->nx, s->ny, s->nz, cf, s->type, s->irr_map, ir.k7, ps, b, dst, nullptr,
+                                   mg_steps<T>(s, 0, nu), st, &tr, e);
+        }
+        return;
+    }
     T *x = mg_smooth<T>(s, 0, L, cf, ir, ps, nullptr, nullptr, a, b, nullptr, 1, nu, s->mg_c1.data(), s->mg_c2.data(), st,
                         samp);
     // the residual goes straight into the coarse right-hand side; the other buffer (0 at
@@ -1504,6 +1525,10 @@ int cps_setup(cps_solver **out, int32_t nx, int32_t ny, int32_t nz, const double
         s->irr_bits = dalloc<uint32_t>(s, (size_t)s->g.W * ny * nz);
         s->irr_wstart = dalloc<int>(s, (size_t)s->g.W * ny * nz);
         launch_irr_words(s->stream, s->g, s->type, s->irr_node, s->nirr, s->irr_bits, s->irr_wstart);
+        if (o.precond == CPS_PRECOND_MULTIGRID && (long long)(nx - 2) * (ny - 2) * (nz - 2) <= MG_TB_MAX_POINTS) {
+            s->irr_map = dalloc<int>(s, s->nn);
+            launch_mg_irr_map(s->stream, s->nirr, s->irr_node, s->irr_map);
+        }
         // reduction scratch: enough for the largest launch
         size_t maxblk = (size_t)std::max({s->g.ta.nblk, s->g.tr.nblk, s->g.tr2.nblk, s->g.tr2s.nblk, s->g.nflat,
                                           short_grid<true>(s->g).nblk}) +

@@ -454,10 +454,9 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid<true> sg, 
 #pragma unroll
         for (int v = 0; v < 6; ++v) xv[v] = xc[e + off[v]];
         const T z0 = xc[e], rh = rho[e];
-        const T kx = kr[0] * z0 + kr[1] * xv[0] + kr[2] * xv[1] + kr[3] * xv[2] + kr[4] * xv[3] + kr[5] * xv[4] +
-                     kr[6] * xv[5];
+        const T kx = row7(kr[0], z0, kr[1], xv[0], kr[2], xv[1], kr[3], xv[2], kr[4], xv[3], kr[5], xv[4], kr[6], xv[5]);
         const T prev = KIND == SW_FULL ? xm1[e] : T(0);
-        if (!done) xn[e] = KIND == SW_RESID ? rh - kx : z0 + c1 * (z0 - prev) + c2 * (rh - kx) / kr[0];
+        if (!done) xn[e] = KIND == SW_RESID ? rh - kx : cheb_next(z0, prev, c1, c2, rh - kx, kr[0]);
         return;
     }
     const ShortItem m = short_item(g, sg, b);
@@ -509,8 +508,8 @@ __global__ void __launch_bounds__(NT) k_sweep_short(Geom g, ShortGrid<true> sg, 
             const T w = (u == 0) ? left : cv[u - 1];
             const T ea = (u + 1 < nv) ? cv[min(u + 1, 3)] : right;
             const T kd = kbx[u] + kby + zb;
-            const T kx = kd * cv[u] + kax[u] * w + kcx[u] * ea + kay * sv[u] + kcy * nvv[u] + za * mv[u] + zcc * uv[u];
-            out[u] = KIND == SW_RESID ? rvv[u] - kx : cv[u] + c1 * (cv[u] - pr[u]) + c2 * (rvv[u] - kx) / kd;
+            const T kx = row7(kd, cv[u], kax[u], w, kcx[u], ea, kay, sv[u], kcy, nvv[u], za, mv[u], zcc, uv[u]);
+            out[u] = KIND == SW_RESID ? rvv[u] - kx : cheb_next(cv[u], pr[u], c1, c2, rvv[u] - kx, kd);
         }
         if (done || !m.live || k > nz - 2) continue;
         T *o = xn + e0 + (size_t)k * plane;
