@@ -37,7 +37,7 @@ void launch_resid_irregular(const Launch &L, const Coef<T> &cf, const Irr<T> &ir
                             const DevState *st);
 template <typename T>
 void launch_first(int kind, const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *r, T *ps, const T *v, T *x1,
-                  double c2, const DevState *st);
+                  double c2, const DevState *st, bool all_x1 = true);
 template <typename T, typename TX_>
 void launch_update(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, TX_ *xs, const T *ph, const T *sh, const T *s,
                    const T *t, const T *r0, T *r, DevState *st);
@@ -113,6 +113,11 @@ bool mg_pair_pays(const Geom &g);
 template <typename T>
 void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
                     double c2a, double c1, double c2, const DevState *st);
+// out = x_1 + c1 x_1 + c2 (rho - K x_1) / diag K with x_1 = c2a rho / diag K, which is read at the
+// irregular nodes alone (launch_first with all_x1 = false) and is 0 at the solid ones.
+template <typename T>
+void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
+                      double c1, double c2, const DevState *st);
 // The coarsest level's `steps` Chebyshev steps (coefficients c1, c2) from 0 in one workgroup
 // of MG_LDS_THREADS threads; the level has at most MG_LDS_NODES interior nodes, at most
 // MG_LDS_PADDED nodes with its walls (6885 for the 9 x 9 x 85 points that the coarsening rule

@@ -435,6 +435,16 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
     }
 }
 
+// 1 / d of a positive diagonal (far from the ends of the exponent range): the hardware's reciprocal
+// and a Newton step in FP32, a third of the instructions of a division (V-cycles of 256^3 .. 513 x 190
+// x 180 nodes differ from FP64 by the same 2.2e-7 .. 3.2e-7, digit for digit).
+__device__ __forceinline__ float recip(float d)
+{
+    const float r = __builtin_amdgcn_rcpf(d);
+    return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double recip(double d) { return 1.0 / d; }
+
 // Two smoothing steps from x_0 in one pass over memory (a post-smoothing pass of nu = 2):
 //   y = x_0 + c2a (rho - K x_0) / diag K,  z = y + c1 (y - x_0) + c2 (rho - K y) / diag K
 // with y never stored: x_0 and rho in, z out, 3 vectors instead of 7.  A block marches in z over
@@ -447,8 +457,8 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
 // forms both, before.
 // A block's waves fill a CU's registers: 12 in FP32, 8 in FP64; 1 / diag K is formed once for both
 // steps.  Bound by registers (8 to 12 wavefronts a CU) and the vector instructions of the two
-// steps.  Measured with k_mg_pair_irregular, against the two sweeps (us): 256^3 FP32 52 + 7 against
-// 41 + 48, FP64 109 + 10 against 90 + 119; 512^3 FP32 493 + 24 against 393 + 491.
+// steps.  Measured with k_mg_pair_irregular, against the two sweeps (us): 256^3 FP32 48 + 8 against
+// 41 + 48, FP64 109 + 9 against 90 + 119; 512^3 FP32 473 + 25 against 393 + 491.
 template <typename T>
 struct Pair {
     static constexpr int waves = sizeof(T) == 4 ? 12 : 8, rows = 2 * waves - 2;   // rows stored by a block
@@ -588,7 +598,7 @@ __global__ void __launch_bounds__(64 * Pair<T>::waves)
                 for (int u = 0; u < 4; ++u) {
                     const T r = mg_reg_resid(rv[u], cv[u], u == 0 ? left : cv[u - 1], u == 3 ? right : cv[u + 1], sv[u],
                                              nw[u], mv[u], uv[u], kax[u], kbx[u], kcx[u], kay[b], kby[b], kcy[b], za, zb, zc);
-                    dv[u] = T(1) / (kbx[u] + kby[b] + zb);
+                    dv[u] = recip(kbx[u] + kby[b] + zb);
                     yv[u] = cv[u] + c2a * r * dv[u];
                 }
                 if (__any(sk[b] | past)) {
@@ -654,6 +664,202 @@ __global__ void __launch_bounds__(64 * Pair<T>::waves)
             xc[b] = xp[b];
             em[b] = ec[b];
             ec[b] = ep[b];
+            y0[b] = y1[b];
+            y1[b] = y2[b];
+            ye1[b] = ye2[b];
+            rp[b] = rh[b];
+            dp[b] = dk[b];
+            skp[b] = sk[b];
+        }
+        __syncthreads();
+    }
+}
+
+// The second smoothing step from zero, x_2 = x_1 + c1 x_1 + c2 (rho - K x_1) / diag K, with
+// x_1 = c2a rho / diag K formed here instead of stored and read: rho in, x_2 out, 2 vectors instead
+// of 3, and the vector update before it writes one less.  The march of k_mg_pair, with x_1 of a
+// plane's rows in place of y.  x_1 holds the step at the irregular nodes and 0 at the solid ones;
+// the irregular rows run in the blocks after the tiles, eight lanes a row.
+// Measured against the stored x_1 (us, this step / the two vector updates before it): 256^3 FP32
+// 41 / 50 + 34 against 45 / 63 + 48, FP64 88 / 113 + 80 against 100 / 145 + 109; 512^3 FP32
+// 352 / 440 + 321 against 393 / 576 + 452.  Loading a plane ahead costs 5 to 15 %, as in the other
+// marches: registers.
+template <typename T>
+struct Second {
+    static constexpr int waves = 8, rows = 2 * waves - 2;     // rows stored by a block
+};
+template <typename T, bool SEG>
+__global__ void __launch_bounds__(64 * Second<T>::waves)
+    k_mg_second(Geom g, Tiling tl, Coef<T> cf, Irr<T> ir, const uint32_t *__restrict__ skip, const T *__restrict__ x1,
+                const T *__restrict__ rho, T *__restrict__ out, T c2a, T c1, T c2, const DevState *st)
+{
+    using V = typename MgVec4<T>::type;
+    constexpr int WAVES = Second<T>::waves, ROWS = Second<T>::rows;
+    __shared__ V sh[2][WAVES][2][64];                         // x_1 of a plane's rows
+    if (st && st->done) return;
+    const int wv = (int)threadIdx.y, lane = (int)threadIdx.x;
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const size_t plane = (size_t)nx * ny, wplane = (size_t)ny * g.W;
+    if ((int)blockIdx.x >= tl.nblk) {
+        const int t = ((int)blockIdx.x - tl.nblk) * 64 * WAVES + 64 * wv + lane, q = t & 7, row = t >> 3;
+        const int rc = min(row, ir.n - 1), e = ir.node[rc];
+        const T kq = ir.k7[7 * (size_t)rc + min(q, 6)], kd0 = ir.k7[7 * (size_t)rc], rho0 = rho[e];
+        const int k0 = e / (int)plane, r0 = e - k0 * (int)plane, j0 = r0 / nx, i0 = r0 - j0 * nx;
+        const int i = i0 + (q == 2) - (q == 1), j = j0 + (q == 4) - (q == 3), k = k0 + (q == 6) - (q == 5);
+        const bool wall = i == 0 || i == nx - 1 || j == 0 || j == ny - 1 || k == 0 || k == nz - 1;
+        const size_t eq = (size_t)i + (size_t)nx * j + plane * k;
+        const bool sb = (skip[((size_t)j + (size_t)ny * k) * g.W + (i >> 5)] >> (i & 31)) & 1u;
+        const T a = x1[eq], b = rho[eq], d = cf.c[0][8 * i + 6] + cf.c[1][8 * j + 6] + cf.c[2][8 * k + 6];
+        const T y = wall ? T(0) : (sb ? a : c2a * b / d);
+        T sum = q < 7 ? kq * y : T(0);
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) sum += __shfl_xor(sum, o, 64);
+        if (q == 0 && row < ir.n) out[e] = y + c1 * y + c2 * (rho0 - sum) / kd0;
+        return;
+    }
+    int bs, by, bz;
+    if (!tile_of_block(tl, (int)blockIdx.x, bs, by, bz)) return;
+    const int i0 = 1 + 256 * bs + 4 * lane;
+    const int nv = min(4, nx - 1 - i0);                       // interior nodes of the lane
+    const int ic = min(i0, nx - 1);                           // lanes past the row end: the wall node
+    const bool needr = SEG && lane == 63 && i0 + 4 <= nx - 2; // the node beyond the lane's is interior
+    const bool needl = SEG && lane == 0 && bs > 0;
+    const bool edge = needr || needl;
+    const int ie = needr ? i0 + 4 : (needl ? i0 - 1 : ic);    // that node
+    const uint32_t past = 0xFu & ~((1u << max(nv, 0)) - 1u);  // the lane's places past the row end
+    const uint32_t hoff = (uint32_t)((ie - ic) * (int)sizeof(T));
+    T kax[4], kbx[5], kcx[4];
+    {
+        const T *x5 = cf.xs + (size_t)5 * cf.xp, *x6 = x5 + cf.xp, *x7 = x6 + cf.xp;
+        const V va = *reinterpret_cast<const V *>(x5 + ic), vb = *reinterpret_cast<const V *>(x6 + ic),
+                vc = *reinterpret_cast<const V *>(x7 + ic);
+        const T a[4] = {va.x, va.y, va.z, va.w}, bb[5] = {vb.x, vb.y, vb.z, vb.w, SEG ? x6[ie] : T(1)},
+                c[4] = {vc.x, vc.y, vc.z, vc.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            kax[u] = a[u];
+            kcx[u] = c[u];
+        }
+#pragma unroll
+        for (int u = 0; u < 5; ++u) kbx[u] = bb[u];
+    }
+    // the wavefront's rows j0, j0 + 1 (rows outside the interior have x_1 = 0)
+    const int j0 = ROWS * by + 2 * wv;
+    uint32_t ox[2], ow[2];
+    bool rok[2], own[2];
+    T kay[2], kby[2], kcy[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int j = j0 + b, jc = min(j, ny - 1);
+        rok[b] = j >= 1 && j <= ny - 2;
+        own[b] = rok[b] && 2 * wv + b >= 1 && 2 * wv + b <= ROWS;
+        ox[b] = (uint32_t)((ic + nx * jc) * sizeof(T));
+        ow[b] = (uint32_t)((jc * g.W + (ic >> 5)) * sizeof(uint32_t));
+        kay[b] = wave_uniform(cf.c[1][8 * jc + 5]);
+        kby[b] = wave_uniform(cf.c[1][8 * jc + 6]);
+        kcy[b] = wave_uniform(cf.c[1][8 * jc + 7]);
+    }
+    const int K0 = 1 + bz * tl.TZ, K1 = min(K0 + tl.TZ, nz - 1);
+    // x_1 of the two planes behind (0, 1), at the edge node too; rho, 1 / diag K and the skip bits
+    // of the plane behind
+    V y0[2], y1[2], rp[2], dp[2];
+    T ye1[2] = {T(0), T(0)};
+    uint32_t skp[2] = {0u, 0u}, skn[2];
+    const V zero4 = V{T(0), T(0), T(0), T(0)};
+    auto skip_bits = [&](int q, int b) -> uint32_t {
+        const uint64_t pair = bload_u64(plane_rsrc(skip + (size_t)q * wplane), ow[b]);
+        const uint32_t m = (uint32_t)(pair >> (ic & 31)) & ((1u << max(nv, 0)) - 1u);
+        if (!SEG || !edge) return m;
+        return m | (needr ? ((uint32_t)(pair >> (ic & 31)) & 0x10u) : (((uint32_t)(pair >> ((ic & 31) - 1)) & 1u) << 4));
+    };
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        y0[b] = y1[b] = rp[b] = dp[b] = zero4;
+        skn[b] = skip_bits(K0 - 1, b);
+    }
+    for (int k = K0 - 1; k <= K1; ++k) {
+        const __amdgpu_buffer_rsrc_t rk = plane_rsrc(rho + (size_t)k * plane), yk = plane_rsrc(x1 + (size_t)k * plane);
+        V rh[2], yi4[2];
+        uint32_t sk[2];
+        T h5[2], yi5[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            sk[b] = skn[b];
+            skn[b] = skip_bits(min(k + 1, nz - 1), b);
+            rh[b] = bload4<T>(rk, ox[b]);
+            h5[b] = edge ? bload1<T>(rk, ox[b] + hoff) : T(0);
+            // x_1 at the lane's solid and irregular nodes
+            if (sk[b]) yi4[b] = bload4<T>(yk, ox[b]);
+            else yi4[b] = zero4;
+            yi5[b] = (SEG && (sk[b] & 0x10u)) ? bload1<T>(yk, ox[b] + hoff) : T(0);
+        }
+        V y2[2], dk[2];
+        T ye2[2];
+        {
+            const T zb = wave_uniform(cf.c[2][8 * k + 6]);
+            const bool pv = k >= 1 && k <= nz - 2;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const T rv[4] = {rh[b].x, rh[b].y, rh[b].z, rh[b].w}, iv[4] = {yi4[b].x, yi4[b].y, yi4[b].z, yi4[b].w};
+                const bool live = pv && rok[b];               // uniform
+                T yv[4], dv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    dv[u] = recip(kbx[u] + kby[b] + zb);
+                    yv[u] = c2a * rv[u] * dv[u];
+                }
+                if (__any(sk[b] | past)) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if ((sk[b] >> u) & 1u) yv[u] = iv[u];
+                        if ((past >> u) & 1u) yv[u] = T(0);
+                    }
+                }
+                y2[b] = live ? V{yv[0], yv[1], yv[2], yv[3]} : zero4;
+                dk[b] = V{dv[0], dv[1], dv[2], dv[3]};
+                ye2[b] = T(0);
+                if (SEG && live && edge) ye2[b] = (sk[b] & 0x10u) ? yi5[b] : c2a * h5[b] / (kbx[4] + kby[b] + zb);
+            }
+        }
+        if (k >= K0 + 1) {
+            const int q = k - 1;
+            const T *cz = cf.c[2] + 8 * q;
+            const T za = wave_uniform(cz[5]), zb = wave_uniform(cz[6]), zc = wave_uniform(cz[7]);
+            const V ylo = wv > 0 ? sh[q & 1][wv - 1][1][lane] : zero4;
+            const V yhi = wv < WAVES - 1 ? sh[q & 1][wv + 1][0][lane] : zero4;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const V &s4 = b == 0 ? ylo : y1[0];
+                const V &n4 = b == 0 ? y1[1] : yhi;
+                const T cv[4] = {y1[b].x, y1[b].y, y1[b].z, y1[b].w}, dv[4] = {dp[b].x, dp[b].y, dp[b].z, dp[b].w};
+                const T sv[4] = {s4.x, s4.y, s4.z, s4.w}, nw[4] = {n4.x, n4.y, n4.z, n4.w};
+                const T mv[4] = {y0[b].x, y0[b].y, y0[b].z, y0[b].w}, uv[4] = {y2[b].x, y2[b].y, y2[b].z, y2[b].w};
+                const T rv[4] = {rp[b].x, rp[b].y, rp[b].z, rp[b].w};
+                T left = __shfl_up(cv[3], 1, 64), right = __shfl_down(cv[0], 1, 64);
+                if (lane == 0) left = ye1[b];                  // 0 at a wall
+                if (lane == 63) right = ye1[b];
+                T zv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const T r = mg_reg_resid(rv[u], cv[u], u == 0 ? left : cv[u - 1], u == 3 ? right : cv[u + 1], sv[u],
+                                             nw[u], mv[u], uv[u], kax[u], kbx[u], kcx[u], kay[b], kby[b], kcy[b], za, zb, zc);
+                    zv[u] = cv[u] + c1 * cv[u] + c2 * r * dv[u];
+                }
+                if (own[b]) {
+                    T *o = out + (size_t)q * plane + (ox[b] / (uint32_t)sizeof(T));
+                    if (nv == 4 && (skp[b] & 0xFu) == 0u) {
+                        *reinterpret_cast<V *>(o) = V{zv[0], zv[1], zv[2], zv[3]};
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (u < nv && !((skp[b] >> u) & 1u)) o[u] = zv[u];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            sh[k & 1][wv][b][lane] = y2[b];
             y0[b] = y1[b];
             y1[b] = y2[b];
             ye1[b] = ye2[b];
@@ -1531,6 +1737,27 @@ void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const 
 }
 
 template <typename T>
+void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
+                      double c1, double c2, const DevState *st)
+{
+    const Geom &g = L.g;
+    constexpr int NTH = 64 * Second<T>::waves;
+    const bool seg = g.nx - 2 > 256;
+    const void *fn = seg ? reinterpret_cast<const void *>(&k_mg_second<T, true>)
+                         : reinterpret_cast<const void *>(&k_mg_second<T, false>);
+    static int per_cu[2] = {0, 0};
+    const Tiling tl = march_tiling(per_cu[seg], fn, NTH, (g.nx - 2 + 255) / 256,
+                                   (g.ny - 2 + Second<T>::rows - 1) / Second<T>::rows, g.nz - 2);
+    const int nb = tl.nblk + (8 * ir.n + NTH - 1) / NTH;
+    if (seg)
+        k_mg_second<T, true><<<nb, dim3(64, Second<T>::waves), 0, L.stream>>>(g, tl, cf, ir, L.skip, x1, rho, out, (T)c2a,
+                                                                            (T)c1, (T)c2, st);
+    else
+        k_mg_second<T, false><<<nb, dim3(64, Second<T>::waves), 0, L.stream>>>(g, tl, cf, ir, L.skip, x1, rho, out, (T)c2a,
+                                                                             (T)c1, (T)c2, st);
+}
+
+template <typename T>
 void launch_mg_prolong_add(hipStream_t s, const MgTransfer<T> &t, const uint32_t *skip_f, int W, const T *e, T *x)
 {
     // blockIdx.z = p covers fine planes 2p and 2p + 1 (interior planes 1 .. nf[2] - 2)
@@ -1625,5 +1852,10 @@ template void launch_mg_pair<double>(const Launch &, const Coef<double> &, const
                                      double *, double *, double, double, double, const DevState *);
 template void launch_mg_pair<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *, const float *,
                                     float *, float *, double, double, double, const DevState *);
+
+template void launch_mg_second<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *,
+                                       const double *, double *, double, double, double, const DevState *);
+template void launch_mg_second<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *,
+                                      const float *, float *, double, double, double, const DevState *);
 
 }  // namespace cps

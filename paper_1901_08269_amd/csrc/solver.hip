@@ -655,7 +655,9 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
         return;
     }
     const int nu = s->opt.mg_nu;
-    launch_first<T>(kind, L, cf, ir, r, ps, v, a, s->mg_c2[0], st);
+    // on large grids the second step forms x_1 itself, in a cycle that is not timed sweep by sweep
+    const bool second = nu == 2 && !samp && mg_pair_pays<T>(s->g);
+    launch_first<T>(kind, L, cf, ir, r, ps, v, a, s->mg_c2[0], st, !second);
     if (s->irr_map && nu >= 2 && nu - 1 <= MG_TB_H - 2) {
         // a small problem (irr_map is there up to MG_TB_MAX_POINTS): its passes temporally blocked
         // like a small coarse level's (mg_level), two launches for six.  Their times, with the
@@ -676,8 +678,14 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
         }
         return;
     }
-    T *x = mg_smooth<T>(s, 0, L, cf, ir, ps, nullptr, nullptr, a, b, nullptr, 1, nu, s->mg_c1.data(), s->mg_c2.data(), st,
-                        samp);
+    T *x;
+    if (second) {
+        launch_mg_second<T>(L, cf, ir, a, ps, b, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st);
+        x = b;
+    } else {
+        x = mg_smooth<T>(s, 0, L, cf, ir, ps, nullptr, nullptr, a, b, nullptr, 1, nu, s->mg_c1.data(), s->mg_c2.data(), st,
+                         samp);
+    }
     // the residual goes straight into the coarse right-hand side; the other buffer (0 at
     // the solid nodes, like every iterate) first takes the residual at the irregular nodes,
     // then serves as the post-smoothing's second iterate

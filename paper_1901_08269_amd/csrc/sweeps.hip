@@ -853,7 +853,7 @@ __global__ void __launch_bounds__(NT) k_apply_short(Geom g, ShortGrid<true> sg, 
 // 65.  Walking more than one such group per block, along the planes or within one, gives the
 // 512^3 gain back (930 .. 970), for fewer partials.
 // ---------------------------------------------------------------------------------------
-template <typename T, int KIND>
+template <typename T, int KIND, bool X1 = true>
 __global__ void __launch_bounds__(NT) k_first4(Geom g, ShortGrid<false> sg, Coef<T> cf, Irr<T> ir,
                                               const uint32_t *__restrict__ skip, const T *__restrict__ r,
                                               T *__restrict__ ps, const T *__restrict__ v, T *__restrict__ x1, T c2,
@@ -912,13 +912,13 @@ __global__ void __launch_bounds__(NT) k_first4(Geom g, ShortGrid<false> sg, Coef
         const size_t e = e0 + (size_t)k * plane;
         if (m.nv == 4 && sk[t] == 0u) {
             *reinterpret_cast<V *>(ps + e) = V{out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<V *>(x1 + e) = V{xo[0], xo[1], xo[2], xo[3]};
+            if (X1) *reinterpret_cast<V *>(x1 + e) = V{xo[0], xo[1], xo[2], xo[3]};
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (u < m.nv && !((sk[t] >> u) & 1u)) {
                     ps[e + u] = out[u];
-                    x1[e + u] = xo[u];
+                    if (X1) x1[e + u] = xo[u];
                 }
         }
     }
@@ -1307,11 +1307,15 @@ void launch_resid_irregular(const Launch &L, const Coef<T> &cf, const Irr<T> &ir
 
 template <typename T>
 void launch_first(int kind, const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *r, T *ps, const T *v, T *x1,
-                  double c2, const DevState *st)
+                  double c2, const DevState *st, bool all_x1)
 {
     const ShortGrid<false> sg = short_grid<false>(L.g);
     const int nb = sg.nblk + irr_blocks(ir.n, NT);
-    if (kind == FIRST_P)
+    if (kind == FIRST_P && !all_x1)
+        k_first4<T, FIRST_P, false><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
+    else if (!all_x1)
+        k_first4<T, FIRST_S, false><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
+    else if (kind == FIRST_P)
         k_first4<T, FIRST_P><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
     else
         k_first4<T, FIRST_S><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, r, ps, v, x1, (T)c2, st);
@@ -1403,9 +1407,9 @@ template void launch_resid<double>(const Launch &, const Coef<double> &, const I
 template void launch_resid<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *, const float *,
                                   float *, const DevState *, int);
 template void launch_first<double>(int, const Launch &, const Coef<double> &, const Irr<double> &, const double *,
-                                   double *, const double *, double *, double, const DevState *);
+                                   double *, const double *, double *, double, const DevState *, bool);
 template void launch_first<float>(int, const Launch &, const Coef<float> &, const Irr<float> &, const float *, float *,
-                                  const float *, float *, double, const DevState *);
+                                  const float *, float *, double, const DevState *, bool);
 template void launch_update<double, double>(const Launch &, const Coef<double> &, const Irr<double> &, double *,
                                             const double *, const double *, const double *, const double *,
                                             const double *, double *, DevState *);
