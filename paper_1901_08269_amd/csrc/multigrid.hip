@@ -139,9 +139,12 @@ __device__ __forceinline__ T mg_reg_resid(T rh, T c, T w, T e, T s, T n, T m, T 
 // at the irregular nodes (the irregular rows of the residual kernel, run before) and 0 at
 // the solid ones; walls give 0.  With a first step F (F.x1 non-null) the coarse level's first Chebyshev
 // step from zero is written too, as k_mg_restrict does.
+// Where a fine row has at most 128 interior nodes (HALF), a wavefront takes two coarse rows, half of
+// its lanes each: no lane idles, and a block's 15 rows leave room for chunks of one plane (128^3
+// FP32 11.3 us against 14.8, 12.3 with chunks of two; 98^3 FP64 9.8 against 13.2).
 // Bound by its loads (instructions and round trips per plane).  Against one coarse row per
 // wavefront with its three fine rows, four wavefronts a block (us): 512^3 FP32 363 against 505; 256^3
-// FP32 40.5 against 49.6; 200^3 FP32 24 against 31; 128^3 FP32 14.8 against 14.5.  Seven rows: with 3 /
+// FP32 40.5 against 49.6; 200^3 FP32 24 against 31.  Seven rows: with 3 /
 // 4 / 8 rows 256^3 FP32 takes 44 / 61 / 42 and FP64 104 / 98 / 115 against 40.5 and 88 (eight
 // wavefronts fill a CU's registers evenly).  Loading a plane ahead is slower (48 at 256^3: the
 // registers cost a quarter of the wavefronts).
@@ -212,7 +215,7 @@ __device__ __forceinline__ uint64_t bload_u64(__amdgpu_buffer_rsrc_t r, uint32_t
 // coarse rows of a block
 constexpr int RR_ROWS = 7;
 
-template <typename T, bool FIFTH>
+template <typename T, bool FIFTH, bool HALF>
 __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g, Tiling tl, Coef<T> cf,
                                                            const uint32_t *__restrict__ skip,
                                                            const T *__restrict__ x, const T *__restrict__ rho,
@@ -221,12 +224,14 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
                                                            T *__restrict__ rc, MgFirst<T> F, const DevState *st)
 {
     using V = typename MgVec4<T>::type;
-    __shared__ T sh[2][RR_ROWS + 1][2][64];                   // row 2J - 1's share of coarse row J - 1
+    constexpr int LANES = HALF ? 32 : 64, SLOTS = 64 / LANES * (RR_ROWS + 1), ROWS = SLOTS - 1;
+    __shared__ T sh[2][SLOTS][2][LANES];                      // row 2J - 1's share of coarse row J - 1
+    auto uni = [](T v) { return HALF ? v : wave_uniform(v); };   // a value of the coarse row
     if (st && st->done) return;
     int bs, by, bz;
     if (!tile_of_block(tl, (int)blockIdx.x, bs, by, bz)) return;
-    const int wv = (int)threadIdx.y, lane = (int)threadIdx.x;
-    const int J = 1 + by * RR_ROWS + wv;                       // the wavefront's coarse row (up to ncy - 2 + RR_ROWS)
+    const int lane = (int)threadIdx.x % LANES, wv = ((int)threadIdx.x + 64 * (int)threadIdx.y) / LANES;
+    const int J = 1 + by * ROWS + wv;                          // the lanes' coarse row (up to ncy - 2 + ROWS)
     const int nx = g.nx, ny = g.ny, nz = g.nz;
     const size_t plane = (size_t)nx * ny, wplane = (size_t)ny * g.W;
     const int I0 = 1 + 128 * bs + 2 * lane;
@@ -237,7 +242,7 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
     // Values past the lane's valid nodes are never used: their residuals are zeroed, and
     // the +x neighbour of the last interior node is the wall node (0 in every vector).
     const int ic = min(f0, nx - 1);
-    const bool need5 = FIFTH && lane == 63 && own1 && f0 + 4 <= nx - 2;
+    const bool need5 = FIFTH && lane == LANES - 1 && own1 && f0 + 4 <= nx - 2;
     const bool needl = FIFTH && lane == 0 && bs > 0;          // node f0 - 1 is interior
     const bool edge = need5 || needl;
     const uint32_t eoff = (uint32_t)((need5 ? 4 : -1) * (int)sizeof(T));   // from node ic to the edge pair
@@ -280,15 +285,15 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
         rok[b] = j <= ny - 2;
         const int jc = min(j, ny - 1);
         ow[b] = (uint32_t)((jc * g.W + (ic >> 5)) * sizeof(uint32_t));
-        kay[b] = wave_uniform(cf.c[1][8 * jc + 5]);
-        kby[b] = wave_uniform(cf.c[1][8 * jc + 6]);
-        kcy[b] = wave_uniform(cf.c[1][8 * jc + 7]);
+        kay[b] = uni(cf.c[1][8 * jc + 5]);
+        kby[b] = uni(cf.c[1][8 * jc + 6]);
+        kcy[b] = uni(cf.c[1][8 * jc + 7]);
     }
     // the y weights of rows 2J - 1 and 2J in coarse row J, and of row 2J - 1 in coarse row J - 1
-    const bool jok = wv < RR_ROWS && J <= ncy - 2;             // the wavefront stores coarse row J
+    const bool jok = wv < ROWS && J <= ncy - 2;             // the wavefront stores coarse row J
     const int Jc = min(J, ncy - 2), Jp = min(J - 1, ncy - 2);
-    const T wy0 = wave_uniform(ay.rw[3 * Jc]), wy1 = wave_uniform(ay.rw[3 * Jc + 1]);
-    const T wyp = (wv > 0 && J - 1 <= ncy - 2) ? wave_uniform(ay.rw[3 * Jp + 2]) : T(0);
+    const T wy0 = uni(ay.rw[3 * Jc]), wy1 = uni(ay.rw[3 * Jc + 1]);
+    const T wyp = (wv > 0 && J - 1 <= ncy - 2) ? uni(ay.rw[3 * Jp + 2]) : T(0);
 
     const int K0 = 1 + bz * tl.TZ, K1 = min(K0 + tl.TZ, ncz - 1);
     const int p0 = 2 * K0 - 1, p1 = 2 * K1 - 1;
@@ -388,9 +393,9 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
             const T mv[5] = {xm[b].x, xm[b].y, xm[b].z, xm[b].w, em[b].a};
             const T uv[5] = {xp[b].x, xp[b].y, xp[b].z, xp[b].w, ep[b].a};
             const T rv[5] = {rh[b].x, rh[b].y, rh[b].z, rh[b].w, h5[b]};
-            T left = __shfl_up(cv[3], 1, 64), right = __shfl_down(cv[0], 1, 64);
+            T left = __shfl_up(cv[3], 1, LANES), right = __shfl_down(cv[0], 1, LANES);
             if (lane == 0) left = ec[b].a;                    // 0 at the wall (no edge pair)
-            if (lane == 63) right = ec[b].a;
+            if (lane == LANES - 1) right = ec[b].a;
             // x neighbours of the five nodes: node u's -x one is wxn[u], its +x one exn[u]
             const T wxn[5] = {left, cv[0], cv[1], cv[2], cv[3]};
             const T exn[5] = {cv[1], cv[2], cv[3], right, ec[b].b};
@@ -406,8 +411,8 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
             const bool live = pv && rok[b];
 #pragma unroll
             for (int u = 0; u < 4; ++u) r[u] = (live && u < nv) ? r[u] : T(0);
-            T v4 = __shfl_down(r[0], 1, 64);
-            if (lane == 63) v4 = (FIFTH && live && need5) ? r[4] : T(0);
+            T v4 = __shfl_down(r[0], 1, LANES);
+            if (lane == LANES - 1) v4 = (FIFTH && live && need5) ? r[4] : T(0);
             xr[b][0] = w0[0] * r[0] + w0[1] * r[1] + w0[2] * r[2];
             xr[b][1] = w1[0] * r[2] + w1[1] * r[3] + w1[2] * v4;
         }
@@ -1058,9 +1063,11 @@ __global__ void __launch_bounds__(256) k_mg_prolong_add(int nfx, int nfy, int nf
                                                         const T *__restrict__ e, T *__restrict__ x)
 {
     using V = typename MgVec4<T>::type;
-    const int j = 1 + (int)(blockIdx.y * 4 + threadIdx.y), kp = 2 * (int)blockIdx.z;
-    const int i0 = 1 + (int)(blockIdx.x * 256 + 4 * threadIdx.x);
-    if (j > nfy - 2 || i0 > nfx - 2) return;
+    // threads take the 4-node groups of a plane's rows in order: no lane idles on short rows (130^3
+    // FP32 5.3 us against 7.0 with a row segment per wavefront, 512^3 210 against 219)
+    const int gpr = (nfx - 2 + 3) / 4, it = (int)(blockIdx.x * 256 + threadIdx.x), row = it / gpr;
+    const int j = 1 + row, kp = 2 * (int)blockIdx.z, i0 = 1 + 4 * (it - row * gpr);
+    if (j > nfy - 2) return;
     const int nv = min(4, nfx - 1 - i0);
     const int a0 = min(i0 >> 1, ncx - 2), b = min(j >> 1, ncy - 2), c = min(kp >> 1, ncz - 2);
     const size_t cplane = (size_t)ncx * ncy, fplane = (size_t)nfx * nfy;
@@ -1636,9 +1643,9 @@ void launch_mg_restrict(hipStream_t s, const MgTransfer<T> &t, const T *r, T *rc
 
 // Tiles of a kernel whose blocks march over tiles_x x tiles_y columns of nzi planes.  The march is
 // bound by the latency of its plane steps: all blocks run in one round, as many as fit on the
-// device at once (z-chunks of at least two planes).  per_cu: the kernel's blocks per CU, 0 before
+// device at once (z-chunks of at least min_tz planes).  per_cu: the kernel's blocks per CU, 0 before
 // its first launch.
-static Tiling march_tiling(int &per_cu, const void *fn, int threads, int tiles_x, int tiles_y, int nzi)
+static Tiling march_tiling(int &per_cu, const void *fn, int threads, int tiles_x, int tiles_y, int nzi, int min_tz = 2)
 {
     if (!per_cu) {
         int nb = 0;
@@ -1653,7 +1660,7 @@ static Tiling march_tiling(int &per_cu, const void *fn, int threads, int tiles_x
     tl.tiles_x = tiles_x;
     tl.tiles_y = tiles_y;
     const int per_plane = tiles_x * tiles_y, want = std::max(1, per_cu * ncu / per_plane);
-    tl.TZ = std::max(std::min(2, nzi), (nzi + want - 1) / want);
+    tl.TZ = std::max(std::min(min_tz, nzi), (nzi + want - 1) / want);
     tl.zchunks = (nzi + tl.TZ - 1) / tl.TZ;
     tl.ntiles = per_plane * tl.zchunks;
     tl.nblk = (tl.ntiles + NXCD - 1) / NXCD * NXCD;
@@ -1662,9 +1669,9 @@ static Tiling march_tiling(int &per_cu, const void *fn, int threads, int tiles_x
 
 // Which grids restrict with the short kernel: up to RRS_MAX_BYTES per vector.  Its twice-formed rows
 // and planes lose where the march has planes enough to overlap.  Measured (us, short against
-// march): FP32 48^3 5.6 / 9.9, 66^3 5.6 / 11.2, 98^3 8.5 / 12.6, 130^3 16.5 / 14.8; FP64 32^3 6.6 / 13.7,
-// 66^3 7.2 / 14.0, 98^3 (7 MB) 12.7 / 13.2, 211x147x99 31 / 20.
-constexpr size_t RRS_MAX_BYTES = 6000000;
+// march): FP32 66^3 5.6 / 11.2, 82^3 8.3 / 8.8, 98^3 (3.5 MB) 8.5 / 8.6, 130^3 16.5 / 11.3; FP64 32^3
+// 6.6 / 13.7, 70^3 (2.5 MB) 7.5 / 10.7, 82^3 (4.1 MB) 11.7 / 10.7, 211x147x99 31 / 20.
+constexpr size_t RRS_MAX_BYTES = 3300000;
 template <typename T>
 static bool resid_restrict_short(const Geom &g)
 {
@@ -1689,18 +1696,21 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
     // (128) and that node's last fine point (257) is interior; with an odd nx that is so from
     // nx = 259, where one segment still covers the coarse row
     const int ncx = t.nc[0], ncy = t.nc[1], ncz = t.nc[2];
-    const bool fifth = g.nx - 2 >= 257;
-    const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true>)
-                           : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false>);
-    static int per_cu[2] = {0, 0};
-    const Tiling tl = march_tiling(per_cu[fifth], fn, 64 * (RR_ROWS + 1), (ncx - 2 + 127) / 128, (ncy - 2 + RR_ROWS - 1) / RR_ROWS,
-                                   ncz - 2);
-    if (fifth)
-        k_mg_resid_restrict<T, true><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(
-            g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st);
-    else
-        k_mg_resid_restrict<T, false><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(
-            g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st);
+    const bool fifth = g.nx - 2 >= 257, half = g.nx - 2 <= 128;
+    const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true, false>)
+                     : half ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false, true>)
+                            : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false, false>);
+    static int per_cu[3] = {0, 0, 0};
+    const int rows = half ? 2 * RR_ROWS + 1 : RR_ROWS;
+    const Tiling tl = march_tiling(per_cu[fifth ? 0 : half ? 1 : 2], fn, 64 * (RR_ROWS + 1), (ncx - 2 + 127) / 128,
+                                   (ncy - 2 + rows - 1) / rows, ncz - 2, half ? 1 : 2);
+#define CPS_RR_LAUNCH(FIFTH, HALF)                                                                                     \
+    k_mg_resid_restrict<T, FIFTH, HALF><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(                                     \
+        g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st)
+    if (fifth) CPS_RR_LAUNCH(true, false);
+    else if (half) CPS_RR_LAUNCH(false, true);
+    else CPS_RR_LAUNCH(false, false);
+#undef CPS_RR_LAUNCH
 }
 
 // Which grids take the pair: those with more than PAIR_MIN_BYTES per vector.  On smaller ones the
@@ -1761,8 +1771,9 @@ template <typename T>
 void launch_mg_prolong_add(hipStream_t s, const MgTransfer<T> &t, const uint32_t *skip_f, int W, const T *e, T *x)
 {
     // blockIdx.z = p covers fine planes 2p and 2p + 1 (interior planes 1 .. nf[2] - 2)
-    dim3 grid((unsigned)((t.nf[0] - 2 + 255) / 256), (unsigned)((t.nf[1] - 2 + 3) / 4), (unsigned)((t.nf[2] - 2) / 2 + 1));
-    k_mg_prolong_add<T><<<grid, dim3(64, 4), 0, s>>>(t.nf[0], t.nf[1], t.nf[2], t.nc[0], t.nc[1], t.nc[2], t.ax[0],
+    const int groups = (t.nf[0] - 2 + 3) / 4 * (t.nf[1] - 2);
+    dim3 grid((unsigned)((groups + 255) / 256), 1, (unsigned)((t.nf[2] - 2) / 2 + 1));
+    k_mg_prolong_add<T><<<grid, 256, 0, s>>>(t.nf[0], t.nf[1], t.nf[2], t.nc[0], t.nc[1], t.nc[2], t.ax[0],
                                                      t.ax[1], t.ax[2], skip_f, W, e, x);
 }
 

@@ -81,12 +81,15 @@ def test_vcycle_matches_oracle(name):
     assert np.max(np.abs(got2 - 2.0 * got)) <= 1e-12 * scale
 
 
-# The fused residual and restriction.  Small grids: rows around one 128-node segment of coarse
-# nodes (up to 257 fine points the last lane of a segment needs no node beyond its four; at 259 it
-# does, with one segment still; 261 starts a second), coarse rows of one and two nodes.  Grids
-# beyond the small kernel's size: the same row ends, coarse rows that fill a block's seven or not.
-@pytest.mark.parametrize("shape", [(257, 24, 21), (258, 24, 21), (259, 24, 21), (260, 24, 21), (261, 24, 21),
-                                   (19, 22, 33), (257, 103, 61), (259, 103, 61), (263, 101, 62), (131, 115, 106)])
+# The way from the problem's grid to the first coarse one.  Grids smoothed in blocked launches (up
+# to 300,000 interior points); the fused residual and restriction on small vectors (259 x 62 x 41 in
+# FP32, 131 x 71 x 43 in both precisions) and by marching: rows of at most 128 nodes, two coarse rows
+# a wavefront; rows around one 128-node segment of coarse nodes (up to 257 fine points the last lane
+# of a segment needs no node beyond its four; at 259 it does, with one segment still; 261 starts a
+# second); coarse rows that fill a block's 7 or 15 or not.
+@pytest.mark.parametrize("shape", [(257, 24, 21), (259, 24, 21), (261, 24, 21), (19, 22, 33), (259, 62, 41),
+                                   (131, 71, 43), (94, 90, 77), (101, 99, 97), (130, 115, 106), (131, 115, 106),
+                                   (257, 103, 61), (258, 103, 61), (259, 103, 61), (260, 101, 62), (263, 101, 62)])
 def test_residual_restriction_edges_match_oracle(shape):
     grids = (W.tanh_grid(shape[0], 1.1), W.uniform_grid(shape[1]), W.uniform_grid(shape[2]))
     w = W.polynomial_case(0, [W.Sphere((0.5, 0.5, 0.5), 0.2)], rng_seed=11, grids=grids)
