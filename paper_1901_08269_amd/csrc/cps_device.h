@@ -114,24 +114,26 @@ struct DevState {
     int iters;                 // completed iterations
 };
 
-// The blocks of the short kernels (sweeps.hip): a thread takes four nodes of a row, SHORT_TZ
-// planes of them; with OVERLAP (stencils) a wavefront computes the inner 62 of the 64 4-node
+// The blocks of the short kernels (sweeps.hip): a thread takes four nodes of a row, tz planes of
+// them (SHORT_TZ, or more in the apply); with OVERLAP (stencils) a wavefront computes the inner 62 of the 64 4-node
 // groups it loads.
 constexpr int SHORT_TZ = 2;
 template <bool OVERLAP>
 struct ShortGrid {
     static constexpr int wave = OVERLAP ? TX - 2 : TX, block = NT / TX * wave;   // groups computed per wave, block
     int gpr;                   // 4-node groups per row
-    int items, nbx, nbz, nblk; // groups per plane, blocks per SHORT_TZ planes, plane groups, blocks
+    int tz;                    // planes of a thread
+    int items, nbx, nbz, nblk; // groups per plane, blocks per tz planes, plane groups, blocks
 };
 template <bool OVERLAP>
-inline ShortGrid<OVERLAP> short_grid(const Geom &g)
+inline ShortGrid<OVERLAP> short_grid(const Geom &g, int tz = SHORT_TZ)
 {
     ShortGrid<OVERLAP> q;
     q.gpr = (g.nx - 2 + 3) / 4;
     q.items = q.gpr * (g.ny - 2);
     q.nbx = (q.items + q.block - 1) / q.block;
-    q.nbz = (g.nz - 2 + SHORT_TZ - 1) / SHORT_TZ;
+    q.tz = tz;
+    q.nbz = (g.nz - 2 + tz - 1) / tz;
     q.nblk = (q.nbx * q.nbz + NXCD - 1) / NXCD * NXCD;
     return q;
 }

@@ -425,7 +425,7 @@ __device__ __forceinline__ ShortItem short_item(const Geom &g, const ShortGrid<O
     m.nv = min(4, g.nx - 1 - m.i0);
     m.first = gx == 0;
     m.last = gx == sg.gpr - 1;
-    m.k0 = 1 + bz * SHORT_TZ;
+    m.k0 = 1 + bz * sg.tz;
     return m;
 }
 
@@ -716,14 +716,14 @@ __global__ void __launch_bounds__(NT) k_apply4(Geom g, Coef<T> cf, Irr<T> ir, co
 // x, y and z filters as k_apply4.  It filters every row twice as often, which is what bounds it
 // (apply_short says where that pays).
 // ---------------------------------------------------------------------------------------
-template <typename T, typename TO, int MODE>
+template <typename T, typename TO, int MODE, int TZ>
 __global__ void __launch_bounds__(NT) k_apply_short(Geom g, ShortGrid<true> sg, Coef<T> cf, Irr<T> ir,
                                                     const uint32_t *__restrict__ skip, const T *__restrict__ x,
                                                     TO *__restrict__ y, const T *__restrict__ w,
                                                     const double *__restrict__ bvec, DevState *st, double *partials)
 {
     using V = typename Vec4Of<T>::type;
-    constexpr int NV = (MODE == MODE_PLAIN) ? 0 : 2, TZ = SHORT_TZ;
+    constexpr int NV = (MODE == MODE_PLAIN) ? 0 : 2;
     const int done = (MODE != MODE_PLAIN && MODE != MODE_RES) ? st->done : 0;   // used before the stores
     double acc[2] = {0.0, 0.0};
     const int tid = (int)threadIdx.x;
@@ -1195,9 +1195,9 @@ static bool sweeps_short(const Geom &g)
 }
 
 // The B apply in the short form up to APPLY_SHORT_BYTES per vector.  Measured (us, short against
-// marching): 32^3 FP64 6.0 against 9.1; 130^3 FP32 13.6 against 15.2, FP64 17.9 against 21.6; 202^3
-// FP32 (32 MB) 40 against 34, FP64 (64 MB) 73 against 65.
-constexpr size_t APPLY_SHORT_BYTES = 20000000;
+// marching): 32^3 FP64 6.0 against 9.1; 130^3 FP32 11.2 against 15.2, FP64 17.9 against 21.6; 202^3
+// FP32 (32 MB) 34 against 34, 256^3 65 against 47, FP64 202^3 (64 MB) 73 against 65.
+constexpr size_t APPLY_SHORT_BYTES = 20000000, APPLY_FOUR_POINTS = 1100000;
 template <typename T>
 static bool apply_short(const Geom &g)
 {
@@ -1215,12 +1215,21 @@ void launch_apply(int mode, const Launch &L, const Coef<T> &cf, const Irr<T> &ir
                   const double *bvec, DevState *st)
 {
     const bool shrt = apply_short<T>(L.g);
-    const ShortGrid<true> sg = short_grid<true>(L.g);
+    // four planes of a thread on larger FP32 grids: 18 filtered rows for four outputs against 12 for
+    // two; where that leaves too few threads, and in FP64 (registers), two.  Measured (us, four
+    // against two): FP32 66^3 6.3 / 5.1, 98^3 7.9 / 6.9, 110^3 8.8 / 9.2, 128^3 11.7 / 14.3, 162^3 16.3 / 18.4; FP64 130^3
+    // 24.2 / 18.0.
+    const bool four = sizeof(T) == 4 && (size_t)(L.g.nx - 2) * (L.g.ny - 2) * (L.g.nz - 2) > APPLY_FOUR_POINTS;
+    const ShortGrid<true> sg = short_grid<true>(L.g, four ? 4 : SHORT_TZ);
     const int nb = (shrt ? sg.nblk : L.g.ta.nblk) + irr_blocks(ir.n, NT / IRR_LANES);
 #define CPS_APPLY_LAUNCH(M)                                                                                            \
     do {                                                                                                               \
-        if (shrt)                                                                                                      \
-            k_apply_short<T, TO, M><<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, x, y, w, bvec, st, L.partials);  \
+        if (shrt && four)                                                                                              \
+            k_apply_short<T, TO, M, sizeof(T) == 4 ? 4 : SHORT_TZ>                                                     \
+                <<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, x, y, w, bvec, st, L.partials);                     \
+        else if (shrt)                                                                                                 \
+            k_apply_short<T, TO, M, SHORT_TZ>                                                                          \
+                <<<nb, NT, 0, L.stream>>>(L.g, sg, cf, ir, L.skip, x, y, w, bvec, st, L.partials);                     \
         else                                                                                                           \
             k_apply4<T, TO, M><<<nb, tile_block(), 0, L.stream>>>(L.g, cf, ir, L.skip, x, y, w, bvec, st, L.partials); \
     } while (0)
