@@ -493,7 +493,7 @@ __global__ void __launch_bounds__(256) k_ibi_table(Ctx C, int nirr, const int *_
     const int d = arm >> 1, side = arm & 1;
     const size_t rownode = (size_t)nodes[row];
     const int nx = C.n[0], ny = C.n[1];
-    const int idx[3] = {(int)(rownode % nx), (int)((rownode / nx) % ny), (int)(rownode / ((size_t)nx * ny))};
+    const int rn = (int)rownode, idx[3] = {rn % nx, (rn / nx) % ny, rn / (nx * ny)};
     const size_t nb = side ? rownode + C.stride[d] : rownode - C.stride[d];
     if (C.type[nb] != 3) return;
     const size_t line0 = rownode - (size_t)idx[d] * C.stride[d];
@@ -598,7 +598,7 @@ __device__ __forceinline__ bool onesided_weights(const double *pt, const double 
 // coefficient on an unknown, (-1, value) for a term moved to the right-hand side.  A window
 // makes at most 2 runs x 5 points (F-S-F) or 6 points (one run); 12 leaves room.
 constexpr int WIN_CAP = 12;
-struct WinList {
+struct alignas(16) WinList {
     double v[WIN_CAP];
     int16_t slot[WIN_CAP];
     int n;
@@ -613,13 +613,12 @@ struct WinList {
     __device__ __forceinline__ void rhs_add(double c) { add(-1, c); }
 };
 
-// coefficient c on the node at offset o (from the row node): unknown -> slot; wall -> RHS
-__device__ __forceinline__ void put(const Ctx &C, WinList &R, size_t rownode, const int o[3], double c)
+// coefficient c on the node at offset o (from the row node) of type ty: unknown -> slot; wall -> RHS
+__device__ __forceinline__ void put(const Ctx &C, WinList &R, size_t rownode, const int o[3], int8_t ty, double c)
 {
-    size_t node = rownode + (ptrdiff_t)o[0] * (ptrdiff_t)C.stride[0] + (ptrdiff_t)o[1] * (ptrdiff_t)C.stride[1] +
-                  (ptrdiff_t)o[2] * (ptrdiff_t)C.stride[2];
-    int8_t ty = C.type[node];
     if (ty == 0) {
+        size_t node = rownode + (ptrdiff_t)o[0] * (ptrdiff_t)C.stride[0] + (ptrdiff_t)o[1] * (ptrdiff_t)C.stride[1] +
+                      (ptrdiff_t)o[2] * (ptrdiff_t)C.stride[2];
         R.rhs_add(-c * C.g[node]);
         return;
     }
@@ -629,20 +628,20 @@ __device__ __forceinline__ void put(const Ctx &C, WinList &R, size_t rownode, co
 }
 
 // Working storage of one lane's one-sided operator: its points (coordinate, offset along
-// the line from the window centre, IBI or grid node, g at an IBI) and weights.  It lives
+// the line from the window centre, kind: the type of a grid node or PT_IBI, g at an IBI) and weights.  It lives
 // in LDS: the point list grows in a data-dependent order, and as a private array it would
 // sit in scratch memory.
 constexpr int PT_CAP = 6;   // one run: <= 2 nodes + IBI + march to 6 points; S-F-S: 3
+constexpr signed char PT_IBI = 4;
 struct PtBuf {
     double *t, *g, *w;
-    signed char *off;
-    bool *ibi;
+    signed char *off, *kind;
 };
 
 // one fluid run [plo, phi_] (positions -1..1 along d of the window centred at `wc` = row
 // offset) of a window meeting the body
 __device__ __forceinline__ void run_operator(const Ctx &C, WinList &R, size_t rownode, const int rowidx[3], int d, const int wc[3],
-                             int plo, int phi_, const bool sol[3], int nruns, const D3 Ld, double W, int &fb,
+                             int plo, int phi_, const int8_t wty[3], int nruns, const D3 Ld, double W, int &fb,
                              double &minhb, int *bad, PtBuf P)
 {
     const int n = C.n[d];
@@ -650,14 +649,14 @@ __device__ __forceinline__ void run_operator(const Ctx &C, WinList &R, size_t ro
     int base[3] = {rowidx[0] + wc[0], rowidx[1] + wc[1], rowidx[2] + wc[2]};
     base[d] = 0;
     size_t line0 = (size_t)base[0] * C.stride[0] + (size_t)base[1] * C.stride[1] + (size_t)base[2] * C.stride[2];
-    bool sl = plo > -1 && sol[plo - 1 + 1];
-    bool sr = phi_ < 1 && sol[phi_ + 1 + 1];
+    bool sl = plo > -1 && wty[plo - 1 + 1] == 3;
+    bool sr = phi_ < 1 && wty[phi_ + 1 + 1] == 3;
     int np = 0;
-    auto push = [&](double t, int off, bool ibi, double gv) {
+    auto push = [&](double t, int off, signed char kind, double gv) {
         if (np >= PT_CAP) return;
         P.t[np] = t;
         P.off[np] = (signed char)off;
-        P.ibi[np] = ibi;
+        P.kind[np] = kind;
         P.g[np] = gv;
         ++np;
     };
@@ -666,37 +665,49 @@ __device__ __forceinline__ void run_operator(const Ctx &C, WinList &R, size_t ro
     if (sl && sr) {
         double tl = ibi_cached(C, d, base, line0, cidx + plo, cidx + plo - 1, &gv, &fr);
         minhb = fmin(minhb, fr);
-        push(tl, 0, true, gv);
-        for (int p = plo; p <= phi_; ++p) push(C.t[d][cidx + p], p, false, 0.0);
+        push(tl, 0, PT_IBI, gv);
+        for (int p = plo; p <= phi_; ++p) push(C.t[d][cidx + p], p, wty[p + 1], 0.0);
         double th = ibi_cached(C, d, base, line0, cidx + phi_, cidx + phi_ + 1, &gv, &fr);
         minhb = fmin(minhb, fr);
-        push(th, 0, true, gv);
+        push(th, 0, PT_IBI, gv);
         shortened = true;
     } else {
         const int want = (nruns == 2) ? 5 : 6;
-        for (int p = plo; p <= phi_; ++p) push(C.t[d][cidx + p], p, false, 0.0);
         int near = sr ? phi_ : plo;                 // run node next to the interface
         int step = sr ? -1 : 1;                     // march away from the interface
+        int pos = sr ? plo : phi_;
+        // the nodes of the march, all loaded before the first is looked at (indices past the grid
+        // read its last node)
+        int8_t mty[PT_CAP - 2];
+        double mt[PT_CAP - 2];
+#pragma unroll
+        for (int q = 0; q < PT_CAP - 2; ++q) {
+            const int gi = min(max(cidx + pos + step * (q + 1), 0), n - 1);
+            mty[q] = C.type[line0 + (size_t)gi * C.stride[d]];
+            mt[q] = C.t[d][gi];
+        }
+        for (int p = plo; p <= phi_; ++p) push(C.t[d][cidx + p], p, wty[p + 1], 0.0);
         double tb = ibi_cached(C, d, base, line0, cidx + near, cidx + near - step, &gv, &fr);
         minhb = fmin(minhb, fr);
-        push(tb, 0, true, gv);
-        int pos = sr ? plo : phi_;
-        while (np < want) {
+        push(tb, 0, PT_IBI, gv);
+        bool end = false;
+#pragma unroll
+        for (int q = 0; q < PT_CAP - 2; ++q) {
+            if (end || np >= want) continue;
             int nxt = pos + step;
             int gi = cidx + nxt;
-            if (gi < 0 || gi >= n) { shortened = true; break; }
-            size_t node = line0 + (size_t)gi * C.stride[d];
-            int8_t ty = C.type[node];
-            if (ty == 3) {
+            if (gi < 0 || gi >= n) { shortened = true; end = true; continue; }
+            if (mty[q] == 3) {
                 double te = ibi_cached(C, d, base, line0, cidx + pos, gi, &gv, &fr);
                 minhb = fmin(minhb, fr);
-                push(te, 0, true, gv);
+                push(te, 0, PT_IBI, gv);
                 shortened = true;
-                break;
+                end = true;
+                continue;
             }
-            push(C.t[d][gi], nxt, false, 0.0);
+            push(mt[q], nxt, mty[q], 0.0);
             pos = nxt;
-            if (ty == 0) break;   // a wall node: known value, nothing beyond it
+            if (mty[q] == 0) end = true;   // a wall node: known value, nothing beyond it
         }
         if (np < want) shortened = true;
     }
@@ -721,38 +732,38 @@ __device__ __forceinline__ void run_operator(const Ctx &C, WinList &R, size_t ro
     }
     for (int q = 0; q < np; ++q) {
         double c = W * P.w[q];
-        if (P.ibi[q]) {
+        if (P.kind[q] == PT_IBI) {
             R.rhs_add(-c * P.g[q]);
         } else {
             int o[3] = {wc[0], wc[1], wc[2]};
             o[d] = P.off[q];
-            put(C, R, rownode, o, c);
+            put(C, R, rownode, o, P.kind[q], c);
         }
     }
 }
 
 // Shortley-Weller K row at the node `rownode` = (idx): Eqs. 2ndorder_coef_mod, A7_mod.  Output
 // [diag, -x, +x, -y, +y, -z, +z]; a neighbour that is not an unknown gets 0 (zero Dirichlet
-// data), a solid neighbour moves the arm to the interface intersection.
-__device__ void sw_krow(const Ctx &C, size_t rownode, const int idx[3], double *out)
+// data), a solid neighbour moves the arm to the interface intersection.  Three consecutive lanes
+// take the directions d = 0, 1, 2; the first adds their diagonal terms in that order.
+__device__ __forceinline__ void sw_krow(const Ctx &C, size_t rownode, const int idx[3], int d, double *out)
 {
-    double kr[7];
-    kr[0] = 0.0;
-    for (int d = 0; d < 3; ++d) {
-        int b0[3] = {idx[0], idx[1], idx[2]};
-        b0[d] = 0;
-        size_t line0 = (size_t)b0[0] * C.stride[0] + (size_t)b0[1] * C.stride[1] + (size_t)b0[2] * C.stride[2];
-        size_t nm = rownode - C.stride[d], npl = rownode + C.stride[d];
-        double hb = C.t[d][idx[d]] - C.t[d][idx[d] - 1], hf = C.t[d][idx[d] + 1] - C.t[d][idx[d]];
-        double gv, fr;
-        if (C.type[nm] == 3) hb = C.t[d][idx[d]] - ibi_cached(C, d, b0, line0, idx[d], idx[d] - 1, &gv, &fr);
-        if (C.type[npl] == 3) hf = ibi_cached(C, d, b0, line0, idx[d], idx[d] + 1, &gv, &fr) - C.t[d][idx[d]];
-        kr[0] += -2.0 / (hb * hf);
-        int8_t tm = C.type[nm], tp = C.type[npl];
-        kr[1 + 2 * d] = (tm == 1 || tm == 2) ? 2.0 / (hb * (hf + hb)) : 0.0;
-        kr[2 + 2 * d] = (tp == 1 || tp == 2) ? 2.0 / (hf * (hf + hb)) : 0.0;
-    }
-    for (int q = 0; q < 7; ++q) out[q] = kr[q];
+    const int i = d == 0 ? idx[0] : (d == 1 ? idx[1] : idx[2]);
+    const size_t sd = d == 0 ? C.stride[0] : (d == 1 ? C.stride[1] : C.stride[2]);
+    const double *t = d == 0 ? C.t[0] : (d == 1 ? C.t[1] : C.t[2]);
+    const int b0[3] = {d == 0 ? 0 : idx[0], d == 1 ? 0 : idx[1], d == 2 ? 0 : idx[2]};
+    const size_t line0 = rownode - (size_t)i * sd;
+    const int8_t tm = C.type[rownode - sd], tp = C.type[rownode + sd];
+    const double t0 = t[i], tl = t[i - 1], tr = t[i + 1];
+    double hb = t0 - tl, hf = tr - t0;
+    double gv, fr;
+    if (tm == 3) hb = t0 - ibi_cached(C, d, b0, line0, i, i - 1, &gv, &fr);
+    if (tp == 3) hf = ibi_cached(C, d, b0, line0, i, i + 1, &gv, &fr) - t0;
+    const double diag = -2.0 / (hb * hf);
+    out[1 + 2 * d] = (tm == 1 || tm == 2) ? 2.0 / (hb * (hf + hb)) : 0.0;
+    out[2 + 2 * d] = (tp == 1 || tp == 2) ? 2.0 / (hf * (hf + hb)) : 0.0;
+    const double d1 = __shfl_down(diag, 1, 64), d2 = __shfl_down(diag, 2, 64);
+    if (d == 0) out[0] = ((0.0 + diag) + d1) + d2;
 }
 
 // K rows only (a coarse level of the multigrid preconditioner), the arithmetic of sw_krow
@@ -771,7 +782,7 @@ __global__ void __launch_bounds__(256) k_krows(Ctx C, int nirr, const int *__res
     if (live) {
         const size_t rownode = (size_t)nodes[row];
         const int nx = C.n[0], ny = C.n[1];
-        const int idx[3] = {(int)(rownode % nx), (int)((rownode / nx) % ny), (int)(rownode / ((size_t)nx * ny))};
+        const int rn = (int)rownode, idx[3] = {rn % nx, (rn / nx) % ny, rn / (nx * ny)};
         const int id = d == 0 ? idx[0] : (d == 1 ? idx[1] : idx[2]);
         const size_t sd = d == 0 ? C.stride[0] : (d == 1 ? C.stride[1] : C.stride[2]);
         const double *td = d == 0 ? C.t[0] : (d == 1 ? C.t[1] : C.t[2]);
@@ -809,9 +820,13 @@ __global__ void k_gather3(int ncx, int ncy, int ncz, int nfx, int nfy, const int
 
 // One irregular row per 32-lane group (four rows per 128-thread block).  Lanes 0..26 take
 // the 27 windows of Eq. lhsrhs_xxyyzz_mod (direction d = lane / 9, cross offsets from
-// lane % 9) and list their contributions in LDS; lane 27 forms the row's Q-bar term and its
-// Shortley-Weller K row.  The row's lanes then sum the lists in window order into the row's
+// lane % 9) and list their contributions in LDS, with a node of the row's Q-bar term each; lanes 27
+// to 29 form a direction each of the Shortley-Weller K row.  The row's lanes then sum the lists in window order into the row's
 // slots (a fixed order: reruns are bitwise equal) and emit the row in slot order.
+// Bound by a block's own chain (two wavefronts a SIMD: 215 registers for the 6 x 6 solves in place):
+// loads one after another and divergent lanes.  The nodes of a window, of a march and of Q-bar
+// are loaded at once, and no lane takes a row's 27 f values or its whole K row by itself (us, against
+// that): 256^3 with 8 spheres 397 against 537, 128^3 star 130 against 166, 32^3 43 against 53.
 constexpr int BR_ROWS = 4;          // rows per block
 constexpr int BR_LANES = 32;        // lanes per row
 __global__ void __launch_bounds__(BR_ROWS * BR_LANES) k_build_rows(
@@ -820,11 +835,12 @@ __global__ void __launch_bounds__(BR_ROWS * BR_LANES) k_build_rows(
     double *__restrict__ minhb_row, int *__restrict__ fb_row, int *__restrict__ bad)
 {
     __shared__ WinList wl[BR_ROWS][27];
-    __shared__ double pt_t[BR_ROWS * 27][PT_CAP], pt_g[BR_ROWS * 27][PT_CAP], pt_w[BR_ROWS * 27][PT_CAP];
-    __shared__ signed char pt_off[BR_ROWS * 27][PT_CAP];
-    __shared__ bool pt_ibi[BR_ROWS * 27][PT_CAP];
-    __shared__ double qbar[BR_ROWS];
-    __shared__ double slot_sum[BR_ROWS][NSLOT];
+    // the windows' points, then (they are done with) the rows' slot sums
+    constexpr int PT_N = BR_ROWS * 27 * PT_CAP;
+    static_assert(BR_ROWS * NSLOT <= 3 * PT_N, "the sums fit where the points were");
+    __shared__ double pt_buf[3 * PT_N];
+    __shared__ signed char pt_off[BR_ROWS * 27][PT_CAP], pt_kind[BR_ROWS * 27][PT_CAP];
+    __shared__ double qw[BR_ROWS][27], qf[BR_ROWS][27];         // Q-bar: weight (0 on solid) and f of each node
     __shared__ int wfb[BR_ROWS][27];
     __shared__ double wminhb[BR_ROWS][27];
     const int grp = threadIdx.x / BR_LANES, lane = threadIdx.x % BR_LANES;
@@ -832,7 +848,7 @@ __global__ void __launch_bounds__(BR_ROWS * BR_LANES) k_build_rows(
     const bool live = row < nirr;
     const size_t rownode = live ? (size_t)nodes[row] : 0;
     const int nx = C.n[0], ny = C.n[1];
-    const int idx[3] = {(int)(rownode % nx), (int)((rownode / nx) % ny), (int)(rownode / ((size_t)nx * ny))};
+    const int rn = (int)rownode, idx[3] = {rn % nx, (rn / nx) % ny, rn / (nx * ny)};
     // the row's compact weights along x, y, z: L (left-hand side) and R (second derivative)
     D3 Lx{0, 1, 0}, Ly{0, 1, 0}, Lz{0, 1, 0}, Rx{0, 0, 0}, Ry{0, 0, 0}, Rz{0, 0, 0};
     if (live) {
@@ -854,84 +870,119 @@ __global__ void __launch_bounds__(BR_ROWS * BR_LANES) k_build_rows(
         int wc[3] = {0, 0, 0};
         wc[d1] = s1;
         wc[d2] = s2;
-        bool sol[3];
-        int nsol = 0;
+        int8_t wty[3];                                         // types along the window
+#pragma unroll
         for (int p = -1; p <= 1; ++p) {
             int o[3] = {wc[0], wc[1], wc[2]};
             o[d] = p;
-            size_t node = rownode + (ptrdiff_t)o[0] + (ptrdiff_t)o[1] * nx + (ptrdiff_t)o[2] * (ptrdiff_t)C.stride[2];
-            sol[p + 1] = C.type[node] == 3;
-            nsol += sol[p + 1];
+            wty[p + 1] = C.type[rownode + (ptrdiff_t)o[0] + (ptrdiff_t)o[1] * nx + (ptrdiff_t)o[2] * (ptrdiff_t)C.stride[2]];
         }
+        {
+            // this lane's node of the 3x3x3 box: the row's L_x L_y L_z weights on f at every
+            // non-solid node make Q-bar
+            const int bx = lane % 3 - 1, by = (lane / 3) % 3 - 1, bz = lane / 9 - 1;
+            const size_t node = rownode + bx + (ptrdiff_t)by * nx + (ptrdiff_t)bz * (ptrdiff_t)C.stride[2];
+            const int8_t bt = C.type[node];
+            const double bf = C.f[node];
+            qw[grp][lane] = bt != 3 ? Lx[bx + 1] * Ly[by + 1] * Lz[bz + 1] : 0.0;
+            qf[grp][lane] = bt != 3 ? bf : 0.0;
+        }
+        const int nsol = (wty[0] == 3) + (wty[1] == 3) + (wty[2] == 3);
         if (nsol == 0) {
             for (int p = -1; p <= 1; ++p) {
                 int o[3] = {wc[0], wc[1], wc[2]};
                 o[d] = p;
-                put(C, R, rownode, o, W * Rd[p + 1]);
+                put(C, R, rownode, o, wty[p + 1], W * Rd[p + 1]);
             }
         } else if (nsol < 3) {      // a window inside the body is dropped
             int lo[2], hi[2], nr = 0;
             for (int p = -1; p <= 1;) {
-                if (sol[p + 1]) { ++p; continue; }
+                if (wty[p + 1] == 3) { ++p; continue; }
                 int a = p;
-                while (p < 1 && !sol[p + 2]) ++p;
+                while (p < 1 && wty[p + 2] != 3) ++p;
                 lo[nr] = a;
                 hi[nr] = p;
                 ++nr;
                 ++p;
             }
             const int pw = grp * 27 + lane;
-            const PtBuf pb{pt_t[pw], pt_g[pw], pt_w[pw], pt_off[pw], pt_ibi[pw]};
+            double *pt = pt_buf + pw * PT_CAP;
+            const PtBuf pb{pt, pt + PT_N, pt + 2 * PT_N, pt_off[pw], pt_kind[pw]};
             for (int q = 0; q < nr; ++q)
-                run_operator(C, R, rownode, idx, d, wc, lo[q], hi[q], sol, nr, Ld, W, fb, minhb, bad, pb);
+                run_operator(C, R, rownode, idx, d, wc, lo[q], hi[q], wty, nr, Ld, W, fb, minhb, bad, pb);
         }
         if (R.n > WIN_CAP) atomicOr(bad, 2);
         wfb[grp][lane] = fb;
         wminhb[grp][lane] = minhb;
-    } else if (live && lane == 27) {
-        // Q-bar: the row's L_x L_y L_z weights on f at every non-solid node of the 3x3x3 box
-        double q = 0.0;
-#pragma unroll
-        for (int dz = -1; dz <= 1; ++dz)
-#pragma unroll
-            for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-                for (int dx = -1; dx <= 1; ++dx) {
-                    size_t node = rownode + dx + (ptrdiff_t)dy * nx + (ptrdiff_t)dz * (ptrdiff_t)C.stride[2];
-                    if (C.type[node] != 3) q += Lx[dx + 1] * Ly[dy + 1] * Lz[dz + 1] * C.f[node];
-                }
-        qbar[grp] = q;
-        sw_krow(C, rownode, idx, k7 + 7 * (size_t)row);
+    } else if (live && lane < 30) {
+        sw_krow(C, rownode, idx, lane - 27, k7 + 7 * (size_t)row);
     }
     __syncthreads();
     if (!live) return;
     // Sum the windows' lists in window order: lane l owns the slots l, l + 32, ... and adds
-    // the entries for them in list order (the same order for every run) into its slots of
-    // the row's LDS sums (a lane reads every entry's slot and only its own entries' values),
-    // lane 0 the right-hand side, which starts from Q-bar.
+    // the entries for them in list order (the same order for every run): its first slot's (the 27
+    // nodes around the row, most entries) in a register, the others' into the row's LDS sums
+    // (a lane reads every entry's slot); lane 0 the right-hand side, which starts from Q-bar.
+    // The loop is a chain of LDS round trips: entries are read four at a time, and the next
+    // window's first four before the current ones are added.
     constexpr int SPL = (NSLOT + BR_LANES - 1) / BR_LANES;   // slots per lane
-    double *sums = slot_sum[grp];
+    double *sums = pt_buf + grp * NSLOT;
     uint32_t mused = 0u;
 #pragma unroll
-    for (int q = 0; q < SPL; ++q)
+    for (int q = 1; q < SPL; ++q)
         if (lane + BR_LANES * q < NSLOT) sums[lane + BR_LANES * q] = 0.0;
-    double rhs = qbar[grp];
-    for (int w = 0; w < 27; ++w) {
+    struct alignas(16) Two {
+        double a, b;
+    };
+    struct Entries {
+        Two lo, hi;
+        short4 slot;
+    };
+    static_assert(WIN_CAP % 4 == 0, "entries are read four at a time");
+    auto entries = [&](int w, int e) {
         const WinList &R = wl[grp][w];
-        const int n = min(R.n, WIN_CAP);
-        for (int e = 0; e < n; ++e) {
-            const int sl = R.slot[e];
-            if (sl < 0) {
-                if (lane == 0) rhs += R.v[e];
-            } else if ((sl & (BR_LANES - 1)) == lane) {
-                sums[sl] += R.v[e];
-                mused |= 1u << (sl / BR_LANES);
+        return Entries{*reinterpret_cast<const Two *>(R.v + e), *reinterpret_cast<const Two *>(R.v + e + 2),
+                       *reinterpret_cast<const short4 *>(R.slot + e)};
+    };
+    double rhs = 0.0, mine0 = 0.0;
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < 27; ++q) rhs += qw[grp][q] * qf[grp][q];
+    }
+    Entries next = entries(0, 0);
+    int nnext = min(wl[grp][0].n, WIN_CAP);
+    for (int w = 0; w < 27; ++w) {
+        Entries E = next;
+        const int n = nnext;
+        if (w < 26) {
+            next = entries(w + 1, 0);
+            nnext = min(wl[grp][w + 1].n, WIN_CAP);
+        }
+        for (int e = 0; e < n; e += 4) {
+            if (e > 0) E = entries(w, e);
+            const int sl[4] = {E.slot.x, E.slot.y, E.slot.z, E.slot.w};
+            const double v[4] = {E.lo.a, E.lo.b, E.hi.a, E.hi.b};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (e + u >= n) continue;
+                if (sl[u] < 0) {
+                    if (lane == 0) rhs += v[u];
+                } else if (sl[u] < BR_LANES) {
+                    if (sl[u] == lane) {
+                        mine0 += v[u];
+                        mused |= 1u;
+                    }
+                } else if ((sl[u] & (BR_LANES - 1)) == lane) {
+                    sums[sl[u]] += v[u];
+                    mused |= 1u << (sl[u] / BR_LANES);
+                }
             }
         }
     }
     double mine[SPL];
 #pragma unroll
-    for (int q = 0; q < SPL; ++q) mine[q] = lane + BR_LANES * q < NSLOT ? sums[lane + BR_LANES * q] : 0.0;
+    for (int q = 1; q < SPL; ++q) mine[q] = lane + BR_LANES * q < NSLOT ? sums[lane + BR_LANES * q] : 0.0;
+    mine[0] = mine0;
     // emit in slot order: slot sl = lane + 32 q; its output position is the number of used
     // slots before it (prefix over q, then over lanes)
     int cnt_total = 0, base_q = 0;
