@@ -107,7 +107,8 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
                               const DevState *st);
 // Two smoothing steps on the problem's grid in one pass: y = x + c2a (rho - K x) / diag K, then
 // out = y + c1 (y - x) + c2 (rho - K y) / diag K.  yi (0 at the solid nodes) takes y at the
-// irregular nodes; y is stored nowhere else.  mg_pair_pays: the grids where this is the faster way.
+// irregular nodes; y is stored nowhere else.  mg_pair_pays: the grids where this is the faster way
+// (no others are accepted).
 template <typename T>
 bool mg_pair_pays(const Geom &g);
 template <typename T>
@@ -115,6 +116,9 @@ void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const 
                     double c2a, double c1, double c2, const DevState *st);
 // out = x_1 + c1 x_1 + c2 (rho - K x_1) / diag K with x_1 = c2a rho / diag K, which is read at the
 // irregular nodes alone (launch_first with all_x1 = false) and is 0 at the solid ones.
+// mg_second_pays: the grids where this is the faster way.
+template <typename T>
+bool mg_second_pays(const Geom &g);
 template <typename T>
 void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
                       double c1, double c2, const DevState *st);

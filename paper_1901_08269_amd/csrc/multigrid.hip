@@ -1713,15 +1713,22 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
 #undef CPS_RR_LAUNCH
 }
 
-// Which grids take the pair: those with more than PAIR_MIN_BYTES per vector.  On smaller ones the
-// sweeps run from the Infinity Cache and their launches cost less than the pair's few wavefronts.
-// Measured (us, pair with its irregular rows against two sweeps): FP32 130^3 23 / 15, 202^3 (32 MB)
-// 41 / 38; FP64 162^3 (33 MB) 42 / 42.
-constexpr size_t PAIR_MIN_BYTES = 40000000;
+// Which grids take these marches: those with more than MARCH_MIN_BYTES per vector.  On smaller ones
+// the sweeps run from the Infinity Cache and their launches cost less than the marches' few
+// wavefronts.  Measured (us, pair with its irregular rows against two sweeps): FP32 130^3 23 / 15,
+// 202^3 (32 MB) 41 / 38; FP64 162^3 (33 MB) 42 / 42.  The FP64 pair with the edge nodes of rows
+// beyond 256 interior nodes spills its registers (300^3: 717 us against 242 + 294), so those grids
+// sweep twice.
+constexpr size_t MARCH_MIN_BYTES = 40000000;
+template <typename T>
+bool mg_second_pays(const Geom &g)
+{
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > MARCH_MIN_BYTES;
+}
 template <typename T>
 bool mg_pair_pays(const Geom &g)
 {
-    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > PAIR_MIN_BYTES;
+    return mg_second_pays<T>(g) && (sizeof(T) == 4 || g.nx - 2 <= 256);
 }
 
 template <typename T>
@@ -1732,18 +1739,20 @@ void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const 
     if (ir.n > 0)
         k_mg_pair_irregular<T><<<(8 * ir.n + NT - 1) / NT, NT, 0, L.stream>>>(g, cf, ir, L.skip, x, rho, yi, out, (T)c2a,
                                                                             (T)c1, (T)c2, st);
-    const bool seg = g.nx - 2 > 256;
-    const void *fn = seg ? reinterpret_cast<const void *>(&k_mg_pair<T, true>)
-                         : reinterpret_cast<const void *>(&k_mg_pair<T, false>);
+    const auto launch = [&](auto kernel, int &per_cu) {
+        const Tiling tl = march_tiling(per_cu, reinterpret_cast<const void *>(kernel), 64 * Pair<T>::waves,
+                                       (g.nx - 2 + 255) / 256, (g.ny - 2 + Pair<T>::rows - 1) / Pair<T>::rows, g.nz - 2);
+        kernel<<<tl.nblk, dim3(64, Pair<T>::waves), 0, L.stream>>>(g, tl, cf, L.skip, x, rho, yi, out, (T)c2a, (T)c1, (T)c2,
+                                                                 st);
+    };
     static int per_cu[2] = {0, 0};
-    const Tiling tl = march_tiling(per_cu[seg], fn, 64 * Pair<T>::waves, (g.nx - 2 + 255) / 256,
-                                   (g.ny - 2 + Pair<T>::rows - 1) / Pair<T>::rows, g.nz - 2);
-    if (seg)
-        k_mg_pair<T, true><<<tl.nblk, dim3(64, Pair<T>::waves), 0, L.stream>>>(g, tl, cf, L.skip, x, rho, yi, out, (T)c2a, (T)c1,
-                                                                         (T)c2, st);
-    else
-        k_mg_pair<T, false><<<tl.nblk, dim3(64, Pair<T>::waves), 0, L.stream>>>(g, tl, cf, L.skip, x, rho, yi, out, (T)c2a,
-                                                                          (T)c1, (T)c2, st);
+    if constexpr (sizeof(T) == 4) {
+        if (g.nx - 2 > 256) {
+            launch(k_mg_pair<T, true>, per_cu[1]);
+            return;
+        }
+    }
+    launch(k_mg_pair<T, false>, per_cu[0]);
 }
 
 template <typename T>
@@ -1859,6 +1868,8 @@ template void launch_mg_prolong_add<float>(hipStream_t, const MgTransfer<float> 
 
 template bool mg_pair_pays<double>(const Geom &);
 template bool mg_pair_pays<float>(const Geom &);
+template bool mg_second_pays<double>(const Geom &);
+template bool mg_second_pays<float>(const Geom &);
 template void launch_mg_pair<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *, const double *,
                                      double *, double *, double, double, double, const DevState *);
 template void launch_mg_pair<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *, const float *,

@@ -656,7 +656,7 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
     }
     const int nu = s->opt.mg_nu;
     // on large grids the second step forms x_1 itself, in a cycle that is not timed sweep by sweep
-    const bool second = nu == 2 && !samp && mg_pair_pays<T>(s->g);
+    const bool second = nu == 2 && !samp && mg_second_pays<T>(s->g);
     launch_first<T>(kind, L, cf, ir, r, ps, v, a, s->mg_c2[0], st, !second);
     if (s->irr_map && nu >= 2 && nu - 1 <= MG_TB_H - 2) {
         // a small problem (irr_map is there up to MG_TB_MAX_POINTS): its passes temporally blocked

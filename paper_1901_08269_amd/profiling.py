@@ -123,7 +123,10 @@ def algorithmic_bytes(name):
     """Bytes per interior point that a solve kernel must move (each operand once), or None.
 
     k_cheb4       one Chebyshev step: x_k, x_{k-1}, rho in, x_{k+1} out (no x_{k-1}: first step)
-    k_first4      p = r + beta (p - omega v) (P) or s = r - alpha v (S), and x_1 = c p / diag K
+    k_first4      p = r + beta (p - omega v) (P) or s = r - alpha v (S), and x_1 = c p / diag K (not
+                  stored with the third argument false)
+    k_mg_second   the second smoothing step from rho: rho in, x_2 out
+    k_mg_pair     two smoothing steps: x, rho in, x_2 out
     k_apply4      y = B x with a second operand (V, T), y = B x (plain), r = b - B x (residual)
     k_update4     x += alpha p^ + omega s^, r = s - omega t, with (r0, r)
     k_resid4      r = rho - K x (multigrid): x, rho in, r out
@@ -134,7 +137,7 @@ def algorithmic_bytes(name):
     """
     n = short_name(name)
     m = re.match(r"cps::(k_cheb4|k_first4|k_apply4|k_update4|k_resid4|k_mg_restrict|k_mg_resid_restrict"
-                 r"|k_mg_prolong_add)<(.*)>$", n)
+                 r"|k_mg_prolong_add|k_mg_second|k_mg_pair)<(.*)>$", n)
     if not m:
         return None
     kern, args = m.group(1), [a.strip() for a in m.group(2).split(",")]
@@ -152,7 +155,11 @@ def algorithmic_bytes(name):
     if kern == "k_mg_prolong_add":
         return 2 * t + t / 8
     if kern == "k_first4":
-        return (5 if args[1] == "0" else 4) * t
+        return ((5 if args[1] == "0" else 4) - (args[2:3] == ["false"])) * t
+    if kern == "k_mg_second":
+        return 2 * t
+    if kern == "k_mg_pair":
+        return 3 * t
     if kern == "k_update4":
         return 8 * t
     to, mode = _SIZE[args[1]], int(args[2])
