@@ -180,9 +180,9 @@ def main():
     t0 = time.perf_counter()
     stats = []
     for q in range(args.steps):
-        # the full-traffic preconditioner sweeps on the problem's grid in every 8th run of them
-        # are timed by events that each sweep's launch stamps with the kernel's own start and
-        # end; sweeps queued after convergence are left out
+        # every 8th V-cycle smooths the problem's grid sweep by sweep, timed by events that each
+        # sweep's launch stamps with the kernel's own start and end; sweeps queued after
+        # convergence are left out
         u, st = step("mixed", 8, overlap=True)
         stats.append(st)
         print(f"# step {q}: {st['iters']} iters, {st['refine_steps']} refinements, "
@@ -275,9 +275,10 @@ def main():
             got = u.reshape(-1)[samples[0]]
             parity["headline_solution_vs_oracle_rel_maxdiff"] = float(torch.max(torch.abs(got - samples[1])) / samples[2])
 
-    # roofline of the dominant kernel, k_cheb4: every Chebyshev sweep of the multigrid smoother
-    # on the problem's grid (first steps of a pass: 3 vectors per point; the others: 4), timed
-    # live by the library with events that each sweep's launch stamps
+    # roofline of the smoother's sweep, k_cheb4: every Chebyshev sweep of the multigrid smoother
+    # on the problem's grid (first steps of a pass: 3 vectors per point; the others: 4) in the
+    # sampled cycles, timed live by the library with events that each sweep's launch stamps; the
+    # other cycles form the same steps in k_mg_second and k_mg_pair
     sweeps = sum(s_["sweep_launches"] for s_ in stats)
     sweep_ms = sum(s_["sweep_ms"] for s_ in stats)
     sweep_bytes = sum(s_["sweep_bytes"] for s_ in stats)
@@ -299,8 +300,8 @@ def main():
             traffic_note = f"profiles/k_cheb4_{tag}_traffic.md (FETCH_SIZE+WRITE_SIZE, copy-calibrated)"
         else:
             traffic_note = "kernel sources changed since the counters were taken"
-    roofline = {"kernel": "k_cheb4<float, *> (every smoother sweep on the problem's grid: first steps of a pass "
-                          "<float, true, 2> and the others <float, false, 1>; per-launch averages)",
+    roofline = {"kernel": "k_cheb4<float, *> (every smoother sweep on the problem's grid in the sampled cycles: first "
+                          "steps of a pass <float, true, 2> and the others <float, false, 1>; per-launch averages)",
                 "bound": "hbm", "achieved": achieved, "peak": metrics.MI355X_HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": (achieved / metrics.MI355X_HBM_PEAK_GBS) if achieved else None, "traffic": traffic,
                 "traffic_source": traffic_note,

@@ -76,7 +76,9 @@ typedef struct cps_options {
                             * grid (multigrid: every smoothing step there but the pointwise first
                             * step of a pre-smoothing pass; Chebyshev: steps 1 .. inner_iters - 1)
                             * in every n-th preconditioner apply, each by a pair of HIP events that
-                            * its launch stamps with the kernel's start and end (stats); sweeps
+                            * its launch stamps with the kernel's start and end (stats); a
+                            * timed multigrid apply runs the steps that others fuse one by
+                            * one (equal to rounding, on small grids bit for bit); sweeps
                             * queued after convergence are left out; 0: off */
     double inner_tol;      /* CPS_MIXED: residual reduction asked of each FP32 inner solve */
     double lam_lo, lam_hi; /* Chebyshev interval for the spectrum of diag(K)^-1 K (default
@@ -103,8 +105,9 @@ typedef struct cps_options {
      * (the two stencil neighbours it lies between minus the centre); sip_alpha = 0 is the
      * incomplete factorisation without fill), sip_iters iterations from phi = 0 per apply
      * (the paper runs 8 inner iterations of its modified strongly implicit procedure,
-     * Sec. 4).  The substitutions run hyperplane by hyperplane (i + j + k = const), one
-     * launch each: far slower on a GPU than the parallel inner solvers. */
+     * Sec. 4).  The substitutions run hyperplane by hyperplane (i + j + k = const) in tiles of
+     * 16^3 nodes, one launch per hyperplane of tiles: slower on a GPU than the parallel inner
+     * solvers. */
     int32_t sip_iters;       /* 1..64 (default 8) */
     int32_t fp64_finish;     /* CPS_MIXED, 1 (default): when a refinement step reduces
                               * ||D^-1 r||_2 by less than sqrt(2) (the FP32 solve no longer

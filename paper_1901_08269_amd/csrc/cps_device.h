@@ -49,8 +49,7 @@ struct Tiling {
 struct Geom {
     int nx, ny, nz;
     int W;                     // skip-bit words per x-line
-    Tiling ta;                 // 256 x 4 tiles, one row per wavefront: the B apply and the
-                               // vector updates
+    Tiling ta;                 // 256 x 4 tiles, one row per wavefront: the marching B apply
     Tiling tr;                 // 256 x 4 tiles: one x-row segment of 256 nodes per wavefront,
                                // four nodes per lane (vectorised Chebyshev sweeps)
     Tiling tr2;                // 256 x (4 RPW2) tiles: RPW2 rows per wavefront (two-vector sweeps)

@@ -1400,7 +1400,7 @@ __global__ void __launch_bounds__(MG_LDS_THREADS) k_mg_coarsest16(int nx, int ny
 // others have read stale neighbours, which move inwards one layer per step).  H is the least
 // that the pass needs: the steps, and one layer more for the residual on the tile, two for its
 // restriction.  x_k and x_{k+1} live in two LDS arrays that swap roles, one barrier per step.
-// The arithmetic is that of the single sweep (k_cheb4m).
+// The arithmetic is that of the single sweep (row7, cheb_next), bit for bit k_sweep_short's.
 //
 // The levels this runs on are bound by latency: the kernel waits for memory twice (all loads
 // that depend on indices only, then the irregular nodes' stored K rows into registers of

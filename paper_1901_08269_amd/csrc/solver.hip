@@ -349,7 +349,7 @@ constexpr int ROW_ZCHUNKS = 16;
 // The FP32 two-vector sweeps (113 VGPRs, four wavefronts per SIMD, against 180 and two in
 // FP64) fill the GPU with more z-chunks: 24 instead of 16 (768 instead of 512 blocks at 256^3).
 constexpr int ROW_ZCHUNKS_F32 = 24;
-// z-chunks of the vectorised B apply and vector updates (each at least 4 planes; 8 and 32
+// z-chunks of the marching B apply (each at least 4 planes; 8 and 32
 // measured the same at 256^3)
 constexpr int APPLY_ZCHUNKS = 16;
 // grid-stride kernels over all nodes (fills, copies, restart) use at most this many blocks
@@ -663,17 +663,23 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
         // like a small coarse level's (mg_level), two launches for six.  Their times, with the
         // residual's restriction and the prolongation (us, blocked against sweep by sweep): 32^3
         // FP64 16.3 / 27.7, 48^3 FP32 12.4 / 24.0, 66^3 FP32 19.2 / 23.7, FP64 29.6 / 29.8.  A sampled
-        // cycle smooths sweep by sweep after the coarse correction, with the same result.
+        // cycle smooths sweep by sweep (its residual restricted by the same kernel, with no steps
+        // left to do), with the same result.
         const MgTransfer<T> &tr = mg_transfer<T>(s->mg[0]);
         const MgFirst<T> first = mg_first<T>(s, 1);
-        launch_mg_smooth_tb<T>(s->stream, s->nx, s->ny, s->nz, cf, s->type, s->irr_map, ir.k7, ps, a, b, nullptr,
-                               mg_steps<T>(s, 1, nu), st, &tr, nullptr, mg_vecs<T>(s->mg[1])[0], &first);
+        const int done_steps = samp ? nu : 1;
+        T *in = samp ? mg_smooth<T>(s, 0, L, cf, ir, ps, nullptr, nullptr, a, b, nullptr, 1, nu, s->mg_c1.data(),
+                                    s->mg_c2.data(), st, samp)
+                     : a;
+        T *x = in == a ? b : a;
+        launch_mg_smooth_tb<T>(s->stream, s->nx, s->ny, s->nz, cf, s->type, s->irr_map, ir.k7, ps, in, x, nullptr,
+                               mg_steps<T>(s, done_steps, nu), st, &tr, nullptr, mg_vecs<T>(s->mg[1])[0], &first);
         T *e = mg_level<T>(s, 1, st);
         if (samp) {
-            launch_mg_prolong_add<T>(s->stream, tr, s->skip, s->g.W, e, b);
-            mg_smooth<T>(s, 0, L, cf, ir, ps, b, nullptr, b, a, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
+            launch_mg_prolong_add<T>(s->stream, tr, s->skip, s->g.W, e, x);
+            mg_smooth<T>(s, 0, L, cf, ir, ps, x, nullptr, x, in, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
         } else {
-            launch_mg_smooth_tb<T>(s->stream, s->nx, s->ny, s->nz, cf, s->type, s->irr_map, ir.k7, ps, b, dst, nullptr,
+            launch_mg_smooth_tb<T>(s->stream, s->nx, s->ny, s->nz, cf, s->type, s->irr_map, ir.k7, ps, x, dst, nullptr,
                                    mg_steps<T>(s, 0, nu), st, &tr, e);
         }
         return;
