@@ -399,12 +399,12 @@ __global__ void __launch_bounds__(768, SPLIT ? 6 : 1) k_wgrad(int n, int V, int 
 // sum over chunks (fixed order) into the canonical gradient W[co][ci][tap] (ci < ci_real).
 // The order is sequential per output and the outputs are few, so the loads of 32 chunks are
 // issued before their additions (one memory round trip for 32 chunks instead of one for each).
-__device__ __forceinline__ void wgrad_reduce(int nchunk, int Cin, int Cout, int ci_real, const float *__restrict__ P,
-                                             float *__restrict__ gW)
+__device__ __forceinline__ void wgrad_reduce(int block, int nchunk, int Cin, int Cout, int ci_real,
+                                             const float *__restrict__ P, float *__restrict__ gW)
 {
     constexpr int NB = 32;
     // thread order (co, tap, ci): consecutive threads read consecutive partials of a chunk
-    int q = blockIdx.x * blockDim.x + threadIdx.x;
+    int q = block * (int)blockDim.x + (int)threadIdx.x;
     int total = Cout * ci_real * 27;
     if (q >= total) return;
     int ci = q % ci_real, tap = (q / ci_real) % 27, co = q / (27 * ci_real);
@@ -469,19 +469,34 @@ __global__ void __launch_bounds__(64) k_colsum_part(int V, int C, const bf16 *__
     }
 }
 
-// The layer's gradients from their partials, one launch: blocks below wblocks sum the weight
-// gradient over chunks (wgrad_reduce), the C blocks after them one channel's bias gradient each
-// (thread t adds parts t, t + 256, ...; then a tree in LDS).
-__global__ void __launch_bounds__(256) k_grad_final(int wblocks, int nchunk, int Cin, int Cout, int ci_real,
-                                                    const float *__restrict__ P, const float *__restrict__ part,
-                                                    float *__restrict__ gW, float *__restrict__ gb)
+// All layers' gradients from their partials in one launch: a layer's first wblocks blocks sum its
+// weight gradient over chunks (wgrad_reduce), the C blocks after them one channel's bias gradient
+// each (thread t adds parts t, t + 256, ...; then a tree in LDS).  Every layer's partials are kept
+// until here: a launch per layer was bound by its own latency (us for the 14 layers: 16^3, batch 4
+// 11 against 57; 64^3, batch 8 71 against 152).
+struct GradLayer {
+    int block0, wblocks, nchunk, cip, co, ci;   // block0: the layer's first block
+    const float *P, *part;
+    float *gW, *gb;
+};
+struct GradList {
+    GradLayer l[NLAYER];
+};
+__global__ void __launch_bounds__(256) k_grad_final(GradList list)
 {
     __shared__ float sh[256];
-    if ((int)blockIdx.x < wblocks) {
-        wgrad_reduce(nchunk, Cin, Cout, ci_real, P, gW);
+    int q = 0;
+#pragma unroll
+    for (int i = 1; i < NLAYER; ++i) q = (int)blockIdx.x >= list.l[i].block0 ? i : q;
+    const GradLayer L = list.l[q];
+    const int block = (int)blockIdx.x - L.block0;
+    if (block < L.wblocks) {
+        wgrad_reduce(block, L.nchunk, L.cip, L.co, L.ci, L.P, L.gW);
         return;
     }
-    const int c = (int)blockIdx.x - wblocks, t = (int)threadIdx.x;
+    const float *__restrict__ part = L.part;
+    float *__restrict__ gb = L.gb;
+    const int c = block - L.wblocks, t = (int)threadIdx.x, Cout = L.co;
     float acc = 0.f;
     for (int b = t; b < COLSUM_PARTS; b += 256) acc += part[(size_t)b * Cout + c];
     sh[t] = acc;
@@ -919,7 +934,8 @@ extern "C++" int cps_internal_fields(cps_solver *s, const double **phi, const do
 
 struct LayerInfo {
     int ci, co, cip, lvl;
-    long off;   // offset of W in the flat parameters (bias follows)
+    long off;    // offset of W in the flat parameters (bias follows)
+    size_t part; // offset of the weight gradient's chunk partials
 };
 
 struct cps_model {
@@ -934,12 +950,12 @@ struct cps_model {
     float *gskip[NLAYER] = {};  // gradient through the skip connections (layers 1, 3, 5), FP32
     float *gtmp = nullptr;      // data gradient of a pooled or upsampled input, FP32
     bf16 *gb = nullptr, *gb2 = nullptr;   // gradients entering two consecutive layers (BF16, masked)
-    float *wpart = nullptr;    // weight-gradient chunk partials
+    float *wpart = nullptr;    // weight-gradient chunk partials, layer by layer
     size_t wpart_n = 0;
     float *pred = nullptr, *inp = nullptr;
     double *lpart = nullptr, *lossv = nullptr, *sig = nullptr;
     float *hpart = nullptr;
-    float *cpart = nullptr;    // bias-gradient column-sum partials (COLSUM_PARTS x channels)
+    float *cpart = nullptr;    // bias-gradient column-sum partials (COLSUM_PARTS x 64 per layer)
     int adam_t = 0;
     int device = 0;             // the device current at creation (its stream's device)
     std::vector<void *> allocs;
@@ -1073,7 +1089,8 @@ void launch_conv(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, c
 #undef CONV
 }
 
-void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int nchunk, const bf16 *G, const bf16 *X)
+void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int nchunk, const bf16 *G, const bf16 *X,
+                  float *part)
 {
     const int tco = Cout / 16, tci = Cin / 16;
     const bool split = tco * tci < 4;
@@ -1085,9 +1102,9 @@ void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int
     // more than 64 KB of LDS (grids of more than about 128 cells per axis) has to be asked for
     if (lds > 65536) nck(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     if (split)
-        k_wgrad<true><<<run_blocks(nchunk, tco * tci), 768, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
+        k_wgrad<true><<<run_blocks(nchunk, tco * tci), 768, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, part);
     else
-        k_wgrad<false><<<run_blocks(nchunk, tci), 192 * tco, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, m->wpart);
+        k_wgrad<false><<<run_blocks(nchunk, tci), 192 * tco, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, part);
 }
 
 void repack(cps_model *m)
@@ -1142,17 +1159,18 @@ void backward(cps_model *m, int B, const float *tgt, const float *msk)
     k_head_bwd_final<<<HEAD_C + 1, 256, 0, m->stream>>>(nhb, HEAD_C, m->hpart, m->g + m->head_off);
     // gb: the gradient entering layer q (BF16, masked by its ReLU), made by the layer after it
     bf16 *gb = m->gb, *gnext = m->gb2;
+    GradList grads{};
     for (int q = NLAYER - 1; q >= 0; --q, std::swap(gb, gnext)) {
         const LayerInfo &l = m->L[q];
         const int n = nc >> l.lvl;
         const int V = B * n * n * n;
         // weight and bias gradients
         const int wchunk = wgrad_chunk(V), nchunk = (V + wchunk - 1) / wchunk;
-        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, gb, m->in[q]);
-        k_colsum_part<<<COLSUM_PARTS / 2, 64, 0, m->stream>>>(V, l.co, gb, m->cpart);
-        const int wblocks = (int)nblk((size_t)l.co * l.ci * 27);
-        k_grad_final<<<wblocks + l.co, 256, 0, m->stream>>>(wblocks, nchunk, l.cip, l.co, l.ci, m->wpart, m->cpart,
-                                                            m->g + l.off, m->g + l.off + (long)l.co * l.ci * 27);
+        float *wpart = m->wpart + l.part, *cpart = m->cpart + (size_t)q * COLSUM_PARTS * 64;
+        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, gb, m->in[q], wpart);
+        k_colsum_part<<<COLSUM_PARTS / 2, 64, 0, m->stream>>>(V, l.co, gb, cpart);
+        grads.l[q] = GradLayer{0, (int)nblk((size_t)l.co * l.ci * 27), nchunk, l.cip, l.co, l.ci, wpart, cpart, m->g + l.off,
+                               m->g + l.off + (long)l.co * l.ci * 27};
         if (q == 0) break;
         // data gradient, turned into the gradient entering layer q - 1
         ConvOut O{};
@@ -1175,6 +1193,12 @@ void backward(cps_model *m, int B, const float *tgt, const float *msk)
             launch_conv<CONV_GATE>(m, n, V, l.co, l.cip, gb, m->Wf[q], O);
         }
     }
+    int blocks = 0;
+    for (GradLayer &l : grads.l) {
+        l.block0 = blocks;
+        blocks += l.wblocks + l.co;
+    }
+    k_grad_final<<<blocks, 256, 0, m->stream>>>(grads);
 }
 
 void free_model(cps_model *m)
@@ -1232,11 +1256,14 @@ int cps_model_create(cps_model **out, const cps_model_spec *spec, void *stream)
             if (q == 8 || q == 10 || q == 12) maxci = std::max(maxci, V * m->L[q - 1].co);
             maxco = std::max(maxco, V * l.co);
             // the chunk count for every batch size up to B (the chunk size depends on V)
+            size_t part = 0;
             for (int bb = 1; bb <= B; ++bb) {
                 const size_t Vb = (size_t)bb * n * n * n;
                 const size_t wchunk = wgrad_chunk((int)Vb), nchunk = (Vb + wchunk - 1) / wchunk;
-                m->wpart_n = std::max(m->wpart_n, nchunk * l.co * 27 * l.cip);
+                part = std::max(part, nchunk * l.co * 27 * l.cip);
             }
+            l.part = m->wpart_n;
+            m->wpart_n += part;
         }
         for (int q = 0; q < NLAYER; ++q) {
             LayerInfo &l = m->L[q];
@@ -1260,7 +1287,7 @@ int cps_model_create(cps_model **out, const cps_model_spec *spec, void *stream)
         m->lossv = nalloc<double>(m, 2);
         m->sig = nalloc<double>(m, 1);
         m->hpart = nalloc<float>(m, HEAD_BLOCKS * 17);
-        m->cpart = nalloc<float>(m, (size_t)COLSUM_PARTS * 64);   // channels are at most 64
+        m->cpart = nalloc<float>(m, (size_t)NLAYER * COLSUM_PARTS * 64);   // channels are at most 64
         // He-normal initialisation from the spec's seed (host, deterministic)
         std::vector<float> h(m->nparam, 0.f);
         uint64_t st = spec->seed * 6364136223846793005ULL + 1442695040888963407ULL;
