@@ -269,6 +269,54 @@ inline int wgrad_chunk(int V)
     const int c = (int)std::min<long>(4096, std::max<long>(256, (long)V * 27 / 2048));
     return (c + 63) / 64 * 64;
 }
+// db[c] = sum_v G[v][c] in two fixed-order passes.  Pass 1: COLSUM_PARTS parts; lane vl of a
+// part adds every lanes-th voxel of the part's stride per channel (lanes = 256 / C), and the
+// part's lanes are added per channel in lane order.  A thread takes eight channels of one lane
+// (16-byte loads, eight of them in flight), a wavefront two parts.  The parts run in blocks of
+// their own after the weight gradient's, in its launch, whose wavefronts leave the memory idle
+// (us of a training step for the 14 layers in launches of their own: 137 at 64^3, batch 8, 42 at
+// 16^3, batch 4).  Pass 2 (k_grad_final) adds the part sums.
+constexpr int COLSUM_PARTS = 512;
+constexpr int COLSUM_LDS = 256;          // floats per part of a block
+__device__ __forceinline__ void colsum_part(int p, int V, int C, const bf16 *__restrict__ G, float *__restrict__ part,
+                                            float *sh)
+{
+    const int lanes = 256 / C, c8 = C / 8;                 // C <= 64: at most 32 threads per part
+    const int t = (int)threadIdx.x & 31, vl = t / c8, c = 8 * (t - vl * c8);
+    if (vl < lanes && p < COLSUM_PARTS) {
+        float s[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] = 0.f;
+        const size_t step = (size_t)COLSUM_PARTS * lanes;
+        auto add = [&](uint4 w) {
+            const unsigned u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s[2 * j] += __uint_as_float(u[j] << 16);
+                s[2 * j + 1] += __uint_as_float(u[j] & 0xFFFF0000u);
+            }
+        };
+        size_t v = (size_t)p * lanes + vl;
+        for (; v + 7 * step < (size_t)V; v += 8 * step) {
+            uint4 w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = *reinterpret_cast<const uint4 *>(G + (v + k * step) * C + c);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) add(w[k]);
+        }
+        for (; v < (size_t)V; v += step) add(*reinterpret_cast<const uint4 *>(G + v * C + c));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sh[vl * C + c + j] = s[j];
+    }
+    __syncthreads();
+    if (p >= COLSUM_PARTS) return;
+    for (int q = t; q < C; q += 32) {
+        float acc = 0.f;
+        for (int l = 0; l < lanes; ++l) acc += sh[l * C + q];
+        part[(size_t)p * C + q] = acc;
+    }
+}
+
 constexpr int WG_VS = 256;       // voxels staged in LDS per round: sixteen 16-voxel MFMA steps
 constexpr int WG_RED_TAPS = 3;   // taps per dz whose wave sums are exchanged at a time (SPLIT)
 
@@ -306,9 +354,14 @@ __device__ __forceinline__ bf16x4 mask4(bf16x4 a, uint2 k)
 template <bool SPLIT>
 __global__ void __launch_bounds__(768, SPLIT ? 6 : 1) k_wgrad(int n, int V, int Cin, int Cout, int wchunk, TapRows tr,
                                                const bf16 *__restrict__ G, const bf16 *__restrict__ X,
-                                               float *__restrict__ P)
+                                               float *__restrict__ P, int nblocks, float *__restrict__ bpart)
 {
     extern __shared__ uint4 lds[];
+    if ((int)blockIdx.x >= nblocks) {                          // the blocks after: the bias gradient's parts
+        const int h = (int)threadIdx.x >> 5, p = ((int)blockIdx.x - nblocks) * ((int)blockDim.x >> 5) + h;
+        colsum_part(p, V, Cout, G, bpart, reinterpret_cast<float *>(lds) + COLSUM_LDS * h);
+        return;
+    }
     const int tci = Cin / 16, tco = SPLIT ? 1 : Cout / 16;    // tco: co groups of the block
     const int zrows = tr.nseg * tr.seg;                        // rows of X per dz
     uint4 *xs = lds, *gs = lds + 2 * 3 * zrows;                // [3][zrows], [tco][WG_VS] rows
@@ -421,52 +474,6 @@ __device__ __forceinline__ void wgrad_reduce(int block, int nchunk, int Cin, int
     }
     for (; c < nchunk; ++c) s += p[(size_t)c * pitch];
     gW[((size_t)co * ci_real + ci) * 27 + tap] = s;
-}
-
-// db[c] = sum_v G[v][c] in two fixed-order passes.  Pass 1: COLSUM_PARTS parts; lane vl of a
-// part adds every lanes-th voxel of the part's stride per channel (lanes = 256 / C), and the
-// part's lanes are added per channel in lane order.  A thread takes eight channels of one lane
-// (16-byte loads, eight of them in flight), a wavefront two parts.  Pass 2 (k_grad_final) adds
-// the part sums.  (One channel per thread and 2-byte loads took 27 us per layer at 64^3, batch
-// 8, this 9 us.)
-constexpr int COLSUM_PARTS = 512;
-__global__ void __launch_bounds__(64) k_colsum_part(int V, int C, const bf16 *__restrict__ G, float *__restrict__ part)
-{
-    __shared__ float sh[2][256];
-    const int lanes = 256 / C, c8 = C / 8;                 // C <= 64: at most 32 threads per part
-    const int h = (int)threadIdx.x >> 5, t = (int)threadIdx.x & 31;
-    const int p = 2 * (int)blockIdx.x + h, vl = t / c8, c = 8 * (t - vl * c8);
-    if (vl < lanes) {
-        float s[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s[j] = 0.f;
-        const size_t step = (size_t)COLSUM_PARTS * lanes;
-        auto add = [&](uint4 w) {
-            const unsigned u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                s[2 * j] += __uint_as_float(u[j] << 16);
-                s[2 * j + 1] += __uint_as_float(u[j] & 0xFFFF0000u);
-            }
-        };
-        size_t v = (size_t)p * lanes + vl;
-        for (; v + 7 * step < (size_t)V; v += 8 * step) {
-            uint4 w[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = *reinterpret_cast<const uint4 *>(G + (v + k * step) * C + c);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) add(w[k]);
-        }
-        for (; v < (size_t)V; v += step) add(*reinterpret_cast<const uint4 *>(G + v * C + c));
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sh[h][vl * C + c + j] = s[j];
-    }
-    __syncthreads();
-    for (int q = t; q < C; q += 32) {
-        float acc = 0.f;
-        for (int l = 0; l < lanes; ++l) acc += sh[h][l * C + q];
-        part[(size_t)p * C + q] = acc;
-    }
 }
 
 // All layers' gradients from their partials in one launch: a layer's first wblocks blocks sum its
@@ -1090,21 +1097,24 @@ void launch_conv(cps_model *m, int n, int V, int Cin, int Cout, const bf16 *X, c
 }
 
 void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int nchunk, const bf16 *G, const bf16 *X,
-                  float *part)
+                  float *part, float *bpart)
 {
     const int tco = Cout / 16, tci = Cin / 16;
     const bool split = tco * tci < 4;
     const TapRows tr = tap_rows(n, WG_VS);
     const size_t rows = 3 * (size_t)tr.nseg * tr.seg + (split ? 1 : tco) * WG_VS;
     const size_t red = split ? sizeof(f32x4) * 9 * WG_RED_TAPS * 64 : 0;
-    const size_t lds = std::max(rows * 32 + 6 * WG_VS * sizeof(uint16_t), red);
+    const int nt = split ? 768 : 192 * tco, groups = nt / 32;
+    const size_t lds = std::max(std::max(rows * 32 + 6 * WG_VS * sizeof(uint16_t), red),
+                                groups * COLSUM_LDS * sizeof(float));
     const void *fn = split ? reinterpret_cast<const void *>(&k_wgrad<true>) : reinterpret_cast<const void *>(&k_wgrad<false>);
     // more than 64 KB of LDS (grids of more than about 128 cells per axis) has to be asked for
     if (lds > 65536) nck(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const int nblocks = (int)run_blocks(nchunk, split ? tco * tci : tci), grid = nblocks + (COLSUM_PARTS + groups - 1) / groups;
     if (split)
-        k_wgrad<true><<<run_blocks(nchunk, tco * tci), 768, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, part);
+        k_wgrad<true><<<grid, nt, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, part, nblocks, bpart);
     else
-        k_wgrad<false><<<run_blocks(nchunk, tci), 192 * tco, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, part);
+        k_wgrad<false><<<grid, nt, lds, m->stream>>>(n, V, Cin, Cout, wchunk, tr, G, X, part, nblocks, bpart);
 }
 
 void repack(cps_model *m)
@@ -1167,8 +1177,7 @@ void backward(cps_model *m, int B, const float *tgt, const float *msk)
         // weight and bias gradients
         const int wchunk = wgrad_chunk(V), nchunk = (V + wchunk - 1) / wchunk;
         float *wpart = m->wpart + l.part, *cpart = m->cpart + (size_t)q * COLSUM_PARTS * 64;
-        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, gb, m->in[q], wpart);
-        k_colsum_part<<<COLSUM_PARTS / 2, 64, 0, m->stream>>>(V, l.co, gb, cpart);
+        launch_wgrad(m, n, V, l.cip, l.co, wchunk, nchunk, gb, m->in[q], wpart, cpart);
         grads.l[q] = GradLayer{0, (int)nblk((size_t)l.co * l.ci * 27), nchunk, l.cip, l.co, l.ci, wpart, cpart, m->g + l.off,
                                m->g + l.off + (long)l.co * l.ci * 27};
         if (q == 0) break;
