@@ -561,22 +561,34 @@ __global__ void k_pack_input(int V, int n3, int cin, const float *__restrict__ i
     store16(out + (size_t)v * 16, o);
 }
 
-// 2x2x2 average pooling, [V][C] at n -> [V/8][C] at n/2
-__global__ void k_pool(int B, int n, int C, const bf16 *__restrict__ in, bf16 *__restrict__ out)
+// 2x2x2 average pooling, [V][C] at n -> [V/8][C] at n/2; eight channels per thread, its eight voxels'
+// 16-byte loads at once (us per level on average, against a channel per thread and 2-byte loads: 64^3,
+// batch 8 7.4 / 15.6, 32^3, batch 8 3.4 / 4.4)
+__global__ void __launch_bounds__(256) k_pool(int B, int n, int C, const bf16 *__restrict__ in, bf16 *__restrict__ out)
 {
-    int m = n / 2;
-    size_t total = (size_t)B * m * m * m * C;
-    size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= total) return;
-    int c = (int)(q % C);
-    size_t v = q / C;
-    int x = (int)(v % m), y = (int)((v / m) % m), z = (int)((v / ((size_t)m * m)) % m), b = (int)(v / ((size_t)m * m * m));
-    float s = 0.f;
+    const int m = n / 2, c8 = C / 8;
+    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= (size_t)B * m * m * m * c8) return;
+    const size_t vq = q / c8;
+    const unsigned c = 8 * (unsigned)(q - vq * c8), v = (unsigned)vq, um = (unsigned)m;
+    const unsigned vy = v / um, vz = vy / um, b = vz / um, x = v - vy * um, y = vy - vz * um, z = vz - b * um;
+    union Eight {
+        uint4 w;
+        bf16 h[8];
+    } ch[8], o8;
+#pragma unroll
     for (int o = 0; o < 8; ++o) {
-        int zz = 2 * z + (o >> 2), yy = 2 * y + ((o >> 1) & 1), xx = 2 * x + (o & 1);
-        s += bf2f(in[((((size_t)b * n + zz) * n + yy) * n + xx) * C + c]);
+        const unsigned zz = 2 * z + (o >> 2), yy = 2 * y + ((o >> 1) & 1), xx = 2 * x + (o & 1);
+        ch[o].w = *reinterpret_cast<const uint4 *>(in + ((((size_t)b * n + zz) * n + yy) * n + xx) * C + c);
     }
-    out[q] = f2bf(s * 0.125f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float s = 0.f;
+#pragma unroll
+        for (int o = 0; o < 8; ++o) s += bf2f(ch[o].h[j]);
+        o8.h[j] = f2bf(s * 0.125f);
+    }
+    *reinterpret_cast<uint4 *>(out + vq * C + c) = o8.w;
 }
 
 // gradient entering the 3x3x3 layer before a pooling (its output act at n, [V][C]): the skip
@@ -1141,7 +1153,7 @@ void forward(cps_model *m, int B, const float *inp, float *pred)
         const int n = nc >> l.lvl;
         const int V = B * n * n * n;
         if (q == 2 || q == 4 || q == 6) {
-            k_pool<<<nblk((size_t)V * l.cip), 256, 0, m->stream>>>(B, 2 * n, l.cip, m->out[q - 1], m->in[q]);
+            k_pool<<<nblk((size_t)V * l.cip / 8), 256, 0, m->stream>>>(B, 2 * n, l.cip, m->out[q - 1], m->in[q]);
         } else if (q == 8 || q == 10 || q == 12) {
             int sk = skip_of(q);
             k_upcat<<<nblk((size_t)V * l.cip / 8), 256, 0, m->stream>>>(B, n / 2, m->L[q - 1].co, m->L[sk].co,
