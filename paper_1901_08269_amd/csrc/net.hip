@@ -28,6 +28,7 @@
 
 #include "cps.h"
 #include "cps_device.h"
+#include "cps_host.h"
 
 namespace cpsnet {
 
@@ -972,6 +973,7 @@ struct cps_model {
     float *wpart = nullptr;    // weight-gradient chunk partials, layer by layer
     size_t wpart_n = 0;
     float *pred = nullptr, *inp = nullptr;
+    float *arg[3] = {};         // copies of a call's inputs, targets and masks that are not in this device's memory
     double *lpart = nullptr, *lossv = nullptr, *sig = nullptr;
     float *hpart = nullptr;
     float *cpart = nullptr;    // bias-gradient column-sum partials (COLSUM_PARTS x 64 per layer)
@@ -1055,6 +1057,16 @@ T *nalloc(cps_model *m, size_t n)
     m->allocs.push_back(p);
     nck(hipMemsetAsync(p, 0, (n ? n : 1) * sizeof(T), m->stream));
     return (T *)p;
+}
+
+// an array of n values that a call reads: in place, or copied into the model's buffer q (of `most`
+// values, made on first use) where the kernels cannot read it
+const float *readable(cps_model *m, const float *p, size_t n, int q, size_t most)
+{
+    if (!p || cps::device_array(p, n * sizeof(float), m->device)) return p;
+    if (!m->arg[q]) m->arg[q] = nalloc<float>(m, most);
+    nck(hipMemcpyAsync(m->arg[q], p, n * sizeof(float), hipMemcpyDefault, m->stream));
+    return m->arg[q];
 }
 
 void layer_table(const int ch[4], int cin, LayerInfo L[NLAYER])
@@ -1368,8 +1380,11 @@ int cps_model_forward(cps_model *m, const float *inputs, int32_t batch, float *p
 {
     if (!m || !inputs || !pred || batch < 1 || batch > m->spec.batch) return CPS_EINVAL;
     try {
-        forward(m, batch, inputs, pred);
+        const size_t n3 = (size_t)m->spec.nc * m->spec.nc * m->spec.nc, ci = m->spec.in_ch;
+        const bool in_place = cps::device_array(pred, batch * n3 * sizeof(float), m->device);
+        forward(m, batch, readable(m, inputs, batch * n3 * ci, 0, m->spec.batch * n3 * ci), in_place ? pred : m->pred);
         nck(hipGetLastError());
+        if (!in_place) nck(hipMemcpyAsync(pred, m->pred, batch * n3 * sizeof(float), hipMemcpyDefault, m->stream));
         nck(hipStreamSynchronize(m->stream));
     } catch (NetFail &f) {
         return f.code;
@@ -1382,8 +1397,9 @@ int cps_model_train_step(cps_model *m, const float *inputs, const float *target,
 {
     if (!m || !inputs || !target || batch < 1 || batch > m->spec.batch) return CPS_EINVAL;
     try {
-        forward(m, batch, inputs, m->pred);
-        backward(m, batch, target, mask);
+        const size_t n3 = (size_t)m->spec.nc * m->spec.nc * m->spec.nc, ci = m->spec.in_ch, most = m->spec.batch * n3;
+        forward(m, batch, readable(m, inputs, batch * n3 * ci, 0, most * ci), m->pred);
+        backward(m, batch, readable(m, target, batch * n3, 1, most), readable(m, mask, batch * n3, 2, most));
         if (update) {
             m->adam_t++;
             const float b1 = 0.9f, b2 = 0.999f;

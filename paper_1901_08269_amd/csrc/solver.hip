@@ -18,6 +18,7 @@
 
 #include "cps.h"
 #include "cps_device.h"
+#include "cps_host.h"
 #include "cps_kernels.h"
 
 using namespace cps;
@@ -83,6 +84,7 @@ struct MgLevel {
 struct cps_solver {
     cps_options opt;
     hipStream_t stream = nullptr;
+    int device = 0;               // the device current at setup
     Geom g{};
     int nx = 0, ny = 0, nz = 0, nmax = 0;
     size_t nn = 0;
@@ -296,11 +298,14 @@ void to_device(cps_solver *s, void *dst, const void *src, size_t bytes)
 }
 
 // A single operator (residual, apply, precond) reads its device input and writes its device output
-// in place of staging copies of them, unless the two arrays share memory.
+// (or none) in place of staging copies of them, unless the two arrays share memory or one is not
+// wholly in this device's memory.
 bool direct_io(const cps_solver *s, const double *in, const double *out)
 {
-    const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out, n = s->nn * sizeof(double);
-    return s->opt.device_ptrs && (a + n <= b || b + n <= a);
+    const size_t n = s->nn * sizeof(double);
+    if (!s->opt.device_ptrs || !device_array(in, n, s->device)) return false;
+    const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
+    return !out || ((a + n <= b || b + n <= a) && device_array(out, n, s->device));
 }
 
 void from_device(cps_solver *s, void *dst, const void *src, size_t bytes)
@@ -1459,6 +1464,7 @@ int cps_setup(cps_solver **out, int32_t nx, int32_t ny, int32_t nz, const double
     s->g = make_geom(nx, ny, nz);
     int rc = CPS_OK;
     try {
+        ck(hipGetDevice(&s->device));
         static_assert(2 * sizeof(DevState) <= PINNED_BLOCK / 2, "state copies fit half a pinned block");
         void *blk = pinned_get();
         s->hst = (DevState *)blk;
@@ -1776,7 +1782,7 @@ int cps_residual(cps_solver *s, const double *u, double *r, double *rel)
     if (!s || !u) return CPS_EINVAL;
     try {
         if (!s->tmp64) s->tmp64 = dalloc<double>(s, s->nn + VEC_PAD);
-        const bool direct = r ? direct_io(s, u, r) : (bool)s->opt.device_ptrs;
+        const bool direct = direct_io(s, u, r);
         double *xin = direct ? s->tmp64 : dalloc<double>(s, s->nn + VEC_PAD);
         double *rout = direct && r ? r : dalloc<double>(s, s->nn);
         if (!direct) to_device(s, s->tmp64, u, s->nn * sizeof(double));

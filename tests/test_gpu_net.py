@@ -62,6 +62,31 @@ def test_forward_backward_vs_oracle(nc, B):
     print(f"worst tensor {worst:.2e}")
 
 
+def test_arrays_outside_device_memory():
+    """Inputs, targets and masks in host memory give the results of the same arrays on the device,
+    bit for bit, and a prediction can be written to host memory: such arrays are copied, where a
+    kernel working on them in place would fault."""
+    import ctypes as C
+    import torch
+    print("[case] network arrays in host memory", flush=True)
+    nc, B = 8, 3
+    inp, tgt, msk = _batch(nc, B, 6)
+    res = []
+    for host in (False, True):
+        a = [t.cpu() if host else t for t in (inp, tgt, msk)]
+        m = learned.Model(nc, batch=B, channels=CH, seed=4)
+        pred = m.forward(a[0][:2])
+        out = torch.zeros((2, nc, nc, nc), dtype=torch.float32, device="cpu" if host else "cuda")
+        assert m.L.cps_model_forward(m.h, C.c_void_p(a[0].data_ptr()), 2, C.c_void_p(out.data_ptr())) == 0
+        assert bool((out.cuda() == pred).all())
+        loss = m.train_step(*a)
+        w, g = m.params(grads=True)
+        res.append((pred.cpu().numpy(), loss, w, g))
+        m.close()
+    for x, y in zip(*res):
+        assert np.array_equal(x, y)
+
+
 def test_adam_steps_vs_oracle():
     """Two training steps with the Adam update: the parameters after each step against the
     oracle's Adam (Kingma & Ba, Algorithm 1) applied to the same starting parameters and the
