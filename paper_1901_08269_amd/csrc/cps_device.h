@@ -56,6 +56,7 @@ struct Geom {
     Tiling tr2s;               // the same tiles in more z-chunks, for the FP32 two-vector sweeps
                                // (fewer registers: more of their wavefronts fit at once)
     int nflat;                 // blocks of the flat (vectorised) pointwise kernels
+    double kd_min, kd_max;     // the problem's grid: bounds of |diag K| over its regular rows
 };
 
 // The 1D tables, and the x axis's once more with each coefficient's values consecutive (xs + q

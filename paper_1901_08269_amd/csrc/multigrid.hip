@@ -440,9 +440,9 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
     }
 }
 
-// 1 / d of a positive diagonal (far from the ends of the exponent range): the hardware's reciprocal
-// and a Newton step in FP32, a third of the instructions of a division (V-cycles of 256^3 .. 513 x 190
-// x 180 nodes differ from FP64 by the same 2.2e-7 .. 3.2e-7, digit for digit).
+// 1 / d of a diagonal that reciprocals_normal has let through: the hardware's reciprocal and a Newton
+// step in FP32, a third of the instructions of a division (V-cycles of 256^3 .. 513 x 190 x 180 nodes
+// differ from FP64 by the same 2.2e-7 .. 3.2e-7, digit for digit).
 __device__ __forceinline__ float recip(float d)
 {
     const float r = __builtin_amdgcn_rcpf(d);
@@ -1720,10 +1720,20 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
 // beyond 256 interior nodes spills its registers (300^3: 717 us against 242 + 294), so those grids
 // sweep twice.
 constexpr size_t MARCH_MIN_BYTES = 40000000;
+// The marches multiply by 1 / diag K (recip), which has to be a normal number: in FP32 the
+// reciprocal of a diagonal beyond 2^126 (a spacing below 2.6e-19) is flushed to 0, and that of one
+// below 2^-126 is infinite, where the sweeps' division still gives the step.  A hundred binary
+// digits either way are far from both ends.
+template <typename T>
+static bool reciprocals_normal(const Geom &g)
+{
+    constexpr double big = sizeof(T) == 4 ? 0x1p100 : 0x1p1000;
+    return g.kd_max < big && g.kd_min > 1.0 / big;
+}
 template <typename T>
 bool mg_second_pays(const Geom &g)
 {
-    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > MARCH_MIN_BYTES;
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > MARCH_MIN_BYTES && reciprocals_normal<T>(g);
 }
 template <typename T>
 bool mg_pair_pays(const Geom &g)

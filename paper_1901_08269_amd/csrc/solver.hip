@@ -1190,6 +1190,24 @@ struct Staging {
     }
 };
 
+// g.kd_min and g.kd_max from the coordinates x | y | z: |diag K| is the sum over the axes of
+// 2 / (hb hf), hb and hf the spacings either side (Eq. 2ndorder_coef)
+void diagonal_range(Geom &g, const double *x)
+{
+    const int n[3] = {g.nx, g.ny, g.nz};
+    g.kd_min = g.kd_max = 0.0;
+    for (int d = 0; d < 3; x += n[d++]) {
+        double lo = INFINITY, hi = 0.0;
+        for (int i = 1; i < n[d] - 1; ++i) {
+            const double k = 2.0 / ((x[i] - x[i - 1]) * (x[i + 1] - x[i]));
+            lo = std::min(lo, k);
+            hi = std::max(hi, k);
+        }
+        g.kd_min += lo;
+        g.kd_max += hi;
+    }
+}
+
 // The multigrid hierarchy below the problem's grid (coordinates hx = x | y | z on the host),
 // and the smoother and coarsest-level Chebyshev coefficients.
 void mg_build(cps_solver *s, const std::vector<double> &hx0)
@@ -1483,6 +1501,7 @@ int cps_setup(cps_solver **out, int32_t nx, int32_t ny, int32_t nz, const double
                 if (!std::isfinite(hx[off + q]) || (q > 0 && !(hx[off + q] > hx[off + q - 1]))) throw CPS_EINVAL;
             off += ns[d];
         }
+        diagonal_range(s->g, hx.data());
         ck(hipMemcpyAsync(s->xyz, hx.data(), hx.size() * sizeof(double), hipMemcpyHostToDevice, s->stream));
         s->phi = dalloc<double>(s, s->nn);
         s->gf = dalloc<double>(s, s->nn);

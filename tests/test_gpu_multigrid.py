@@ -220,3 +220,27 @@ def test_sweeps_match_oracle_on_ragged_grids(shape, steps):
             got = _np(S.precond(rho, prec))
             assert np.max(np.abs(got - ref)) <= bar * np.max(np.abs(ref)), (m, prec)
         S.close()
+
+
+@pytest.mark.parametrize("exponent", [-54, 30])
+def test_cycle_scales_with_the_coordinates(exponent):
+    """K scales with the inverse square of the coordinates: a cycle on the grid scaled by 2^e is
+    2^2e times the cycle on the unit grid, also where the diagonals of K (2^126 at e = -54) are so
+    large that their reciprocals are below the smallest normal FP32 number.  43 MB per vector, the
+    size whose smoothing steps run fused.  Scaling by a power of two is exact, so what is left is
+    the order of roundings: 1e-5 as between FP32 and the oracle."""
+    import torch
+    n = 222
+    print(f"[case] coordinates scaled by 2^{exponent}", flush=True)
+    x = np.linspace(0.0, 1.0, n)
+    one = torch.ones((n, n, n), dtype=torch.float64, device="cuda")
+    rho = torch.as_tensor(np.random.Generator(np.random.PCG64(2)).standard_normal((n, n, n))).cuda()
+    rho *= 2.0 ** 60                     # the iterates (rho / diag K) stay normal numbers
+    out = []
+    for e in (0, exponent):
+        S = cps.Solver(2.0 ** e * x, 2.0 ** e * x, 2.0 ** e * x, one, 0 * one, one, precond="multigrid")
+        out.append(S.precond(rho, "fp32"))
+        S.close()
+    ref, got = out[0], out[1] * 2.0 ** (-2 * exponent)
+    assert bool(torch.isfinite(got).all())
+    assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())
