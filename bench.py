@@ -180,8 +180,8 @@ def main():
     t0 = time.perf_counter()
     stats = []
     for q in range(args.steps):
-        # every 8th V-cycle smooths the problem's grid sweep by sweep, timed by events that each
-        # sweep's launch stamps with the kernel's own start and end; sweeps queued after
+        # the smoothing kernels on the problem's grid are timed in every 8th V-cycle, by events
+        # that each launch stamps with the kernel's own start and end; launches queued after
         # convergence are left out
         u, st = step("mixed", 8, overlap=True)
         stats.append(st)
@@ -275,10 +275,10 @@ def main():
             got = u.reshape(-1)[samples[0]]
             parity["headline_solution_vs_oracle_rel_maxdiff"] = float(torch.max(torch.abs(got - samples[1])) / samples[2])
 
-    # roofline of the smoother's sweep, k_cheb4: every Chebyshev sweep of the multigrid smoother
-    # on the problem's grid (first steps of a pass: 3 vectors per point; the others: 4) in the
-    # sampled cycles, timed live by the library with events that each sweep's launch stamps; the
-    # other cycles form the same steps in k_mg_second and k_mg_pair
+    # roofline of the smoother on the problem's grid, timed live by the library with events that
+    # each launch stamps: on large grids k_mg_second (2 vectors per point) and k_mg_pair (two steps,
+    # 3 vectors; its irregular rows' launch is in the time), else a launch per Chebyshev sweep (first
+    # sweeps of a pass 3 vectors, the others 4)
     sweeps = sum(s_["sweep_launches"] for s_ in stats)
     sweep_ms = sum(s_["sweep_ms"] for s_ in stats)
     sweep_bytes = sum(s_["sweep_bytes"] for s_ in stats)
@@ -293,21 +293,23 @@ def main():
     from paper_1901_08269_amd import profiling
     traffic, traffic_note = None, "no counter report for this workload"
     tag = f"{args.workload}_{args.N}"
-    rep = profiling.read_traffic(os.path.join(ROOT, "profiles", f"k_cheb4_{tag}_traffic.md"))
+    rep = profiling.read_traffic(os.path.join(ROOT, "profiles", f"smoother_{tag}_traffic.md"))
     if rep is not None:
         if rep.get("kernel_source_sha256_16") == profiling.source_hash():
             traffic = float(rep["traffic_bytes_per_launch"])
-            traffic_note = f"profiles/k_cheb4_{tag}_traffic.md (FETCH_SIZE+WRITE_SIZE, copy-calibrated)"
+            traffic_note = f"profiles/smoother_{tag}_traffic.md (FETCH_SIZE+WRITE_SIZE, copy-calibrated)"
         else:
             traffic_note = "kernel sources changed since the counters were taken"
-    roofline = {"kernel": "k_cheb4<float, *> (every smoother sweep on the problem's grid in the sampled cycles: first "
-                          "steps of a pass <float, true, 2> and the others <float, false, 1>; per-launch averages)",
+    smoother = ("k_mg_second<float, *> and k_mg_pair<float, *> (every smoothing launch on the problem's grid in the "
+                "sampled cycles, per-launch averages)") if sweeps and not full_n else \
+        "smoother sweeps on the problem's grid in the sampled cycles (per-launch averages)"
+    roofline = {"kernel": smoother,
                 "bound": "hbm", "achieved": achieved, "peak": metrics.MI355X_HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": (achieved / metrics.MI355X_HBM_PEAK_GBS) if achieved else None, "traffic": traffic,
                 "traffic_source": traffic_note,
                 "avg_launch_us": avg_ms * 1e3, "launches": sweeps,
                 "bytes_per_launch": sweep_bytes / max(sweeps, 1),
-                "full_sweeps_only": {"kernel": "k_cheb4<float, false, 1>", "launches": full_n,
+                "full_sweeps_only": {"kernel": "sweeps that read an x_{k-1}", "launches": full_n,
                                      "avg_launch_us": full_ms * 1e3 / max(full_n, 1), "achieved": full_gbs,
                                      "frac": (full_gbs / metrics.MI355X_HBM_PEAK_GBS) if full_gbs else None}}
 

@@ -76,9 +76,9 @@ typedef struct cps_options {
                             * grid (multigrid: every smoothing step there but the pointwise first
                             * step of a pre-smoothing pass; Chebyshev: steps 1 .. inner_iters - 1)
                             * in every n-th preconditioner apply, each by a pair of HIP events that
-                            * its launch stamps with the kernel's start and end (stats); a
-                            * timed multigrid apply runs the steps that others fuse one by
-                            * one (equal to rounding, on small grids bit for bit); sweeps
+                            * its launch stamps with the kernel's start and end (stats; steps
+                            * that one launch forms together, on large grids, are one sweep);
+                            * the solution is the one without timing, bit for bit; sweeps
                             * queued after convergence are left out; 0: off */
     double inner_tol;      /* CPS_MIXED: residual reduction asked of each FP32 inner solve */
     double lam_lo, lam_hi; /* Chebyshev interval for the spectrum of diag(K)^-1 K (default
@@ -136,7 +136,8 @@ typedef struct cps_stats {
     int64_t sweep_points;       /* interior points one sweep processes */
     double sweep_bytes;         /* kernel_timing: algorithmic bytes the timed sweeps move (every
                                  * vector a sweep reads or writes, once per interior point: three
-                                 * for the first step of a pass, four for the others) */
+                                 * for the first step of a pass, four for the others; two for the
+                                 * second step from zero and three for two steps in one launch) */
     double sweep_full_ms;       /* kernel_timing: the part of sweep_ms spent in full-traffic
                                  * sweeps (those that read an x_{k-1}: four vectors) */
     int64_t sweep_full_launches;

@@ -108,20 +108,21 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
 // Two smoothing steps on the problem's grid in one pass: y = x + c2a (rho - K x) / diag K, then
 // out = y + c1 (y - x) + c2 (rho - K y) / diag K.  yi (0 at the solid nodes) takes y at the
 // irregular nodes; y is stored nowhere else.  mg_pair_pays: the grids where this is the faster way
-// (no others are accepted).
+// (no others are accepted).  ev (optional): events that the launches stamp with their kernels' start
+// and end -- the march's two, then those of the irregular rows, launched if there are any.
 template <typename T>
 bool mg_pair_pays(const Geom &g);
 template <typename T>
 void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
-                    double c2a, double c1, double c2, const DevState *st);
+                    double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev = nullptr);
 // out = x_1 + c1 x_1 + c2 (rho - K x_1) / diag K with x_1 = c2a rho / diag K, which is read at the
 // irregular nodes alone (launch_first with all_x1 = false) and is 0 at the solid ones.
-// mg_second_pays: the grids where this is the faster way.
+// mg_second_pays: the grids where this is the faster way.  ev (optional): the launch's two events.
 template <typename T>
 bool mg_second_pays(const Geom &g);
 template <typename T>
 void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
-                      double c1, double c2, const DevState *st);
+                      double c1, double c2, const DevState *st, const hipEvent_t *ev = nullptr);
 // The coarsest level's `steps` Chebyshev steps (coefficients c1, c2) from 0 in one workgroup
 // of MG_LDS_THREADS threads; the level has at most MG_LDS_NODES interior nodes, at most
 // MG_LDS_PADDED nodes with its walls (6885 for the 9 x 9 x 85 points that the coarsening rule

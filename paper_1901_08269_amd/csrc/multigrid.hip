@@ -15,6 +15,7 @@
 //                 w e[a + 1]); the weights carry 4 zeros of padding
 //   restriction   for each interior coarse index I (fine point 2I): the weights rw[3I + q]
 //                 of fine points 2I - 1 + q, q = 0 .. 2, already divided by the row sum
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include "cps_kernels.h"
@@ -1741,19 +1742,27 @@ bool mg_pair_pays(const Geom &g)
     return mg_second_pays<T>(g) && (sizeof(T) == 4 || g.nx - 2 <= 256);
 }
 
+// a launch that stamps the events ev[0], ev[1] (ev non-null) with the kernel's start and end
+template <typename... Args>
+static void timed_launch(const hipEvent_t *ev, void (*kernel)(Args...), dim3 grid, dim3 block, hipStream_t s, Args... args)
+{
+    if (ev) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, ev[0], ev[1], 0, args...);
+    else kernel<<<grid, block, 0, s>>>(args...);
+}
+
 template <typename T>
 void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
-                    double c2a, double c1, double c2, const DevState *st)
+                    double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev)
 {
     const Geom &g = L.g;
     if (ir.n > 0)
-        k_mg_pair_irregular<T><<<(8 * ir.n + NT - 1) / NT, NT, 0, L.stream>>>(g, cf, ir, L.skip, x, rho, yi, out, (T)c2a,
-                                                                            (T)c1, (T)c2, st);
+        timed_launch(ev ? ev + 2 : nullptr, k_mg_pair_irregular<T>, dim3((8 * ir.n + NT - 1) / NT), dim3(NT), L.stream, g, cf,
+                     ir, L.skip, x, rho, yi, out, (T)c2a, (T)c1, (T)c2, st);
     const auto launch = [&](auto kernel, int &per_cu) {
         const Tiling tl = march_tiling(per_cu, reinterpret_cast<const void *>(kernel), 64 * Pair<T>::waves,
                                        (g.nx - 2 + 255) / 256, (g.ny - 2 + Pair<T>::rows - 1) / Pair<T>::rows, g.nz - 2);
-        kernel<<<tl.nblk, dim3(64, Pair<T>::waves), 0, L.stream>>>(g, tl, cf, L.skip, x, rho, yi, out, (T)c2a, (T)c1, (T)c2,
-                                                                 st);
+        timed_launch(ev, kernel, dim3(tl.nblk), dim3(64, Pair<T>::waves), L.stream, g, tl, cf, L.skip, x, rho,
+                     (const T *)yi, out, (T)c2a, (T)c1, (T)c2, st);
     };
     static int per_cu[2] = {0, 0};
     if constexpr (sizeof(T) == 4) {
@@ -1767,23 +1776,18 @@ void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const 
 
 template <typename T>
 void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
-                      double c1, double c2, const DevState *st)
+                      double c1, double c2, const DevState *st, const hipEvent_t *ev)
 {
     const Geom &g = L.g;
     constexpr int NTH = 64 * Second<T>::waves;
     const bool seg = g.nx - 2 > 256;
-    const void *fn = seg ? reinterpret_cast<const void *>(&k_mg_second<T, true>)
-                         : reinterpret_cast<const void *>(&k_mg_second<T, false>);
+    const auto kernel = seg ? &k_mg_second<T, true> : &k_mg_second<T, false>;
     static int per_cu[2] = {0, 0};
-    const Tiling tl = march_tiling(per_cu[seg], fn, NTH, (g.nx - 2 + 255) / 256,
+    const Tiling tl = march_tiling(per_cu[seg], reinterpret_cast<const void *>(kernel), NTH, (g.nx - 2 + 255) / 256,
                                    (g.ny - 2 + Second<T>::rows - 1) / Second<T>::rows, g.nz - 2);
     const int nb = tl.nblk + (8 * ir.n + NTH - 1) / NTH;
-    if (seg)
-        k_mg_second<T, true><<<nb, dim3(64, Second<T>::waves), 0, L.stream>>>(g, tl, cf, ir, L.skip, x1, rho, out, (T)c2a,
-                                                                            (T)c1, (T)c2, st);
-    else
-        k_mg_second<T, false><<<nb, dim3(64, Second<T>::waves), 0, L.stream>>>(g, tl, cf, ir, L.skip, x1, rho, out, (T)c2a,
-                                                                             (T)c1, (T)c2, st);
+    timed_launch(ev, kernel, dim3(nb), dim3(64, Second<T>::waves), L.stream, g, tl, cf, ir, L.skip, x1, rho, out, (T)c2a,
+                 (T)c1, (T)c2, st);
 }
 
 template <typename T>
@@ -1881,13 +1885,13 @@ template bool mg_pair_pays<float>(const Geom &);
 template bool mg_second_pays<double>(const Geom &);
 template bool mg_second_pays<float>(const Geom &);
 template void launch_mg_pair<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *, const double *,
-                                     double *, double *, double, double, double, const DevState *);
+                                     double *, double *, double, double, double, const DevState *, const hipEvent_t *);
 template void launch_mg_pair<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *, const float *,
-                                    float *, float *, double, double, double, const DevState *);
+                                    float *, float *, double, double, double, const DevState *, const hipEvent_t *);
 
 template void launch_mg_second<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *,
-                                       const double *, double *, double, double, double, const DevState *);
+                                       const double *, double *, double, double, double, const DevState *, const hipEvent_t *);
 template void launch_mg_second<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *,
-                                      const float *, float *, double, double, double, const DevState *);
+                                      const float *, float *, double, double, double, const DevState *, const hipEvent_t *);
 
 }  // namespace cps

@@ -14,6 +14,7 @@
 #include <mutex>
 #include <new>
 #include <utility>
+#include <tuple>
 #include <vector>
 
 #include "cps.h"
@@ -116,7 +117,7 @@ struct cps_solver {
     int64_t iter_enq = 0;         // BiCGSTAB iterations enqueued since the solve started
     std::vector<int64_t> tev_iter;  // per timed sweep: the iteration it belongs to
     std::vector<char> tev_ok;       // per timed sweep: ran (not after the solve had converged)
-    std::vector<int> tev_n;         // per timed sweep: sweeps (1)
+    std::vector<int> tev_n;         // per timed sweep: sweeps (1, or 0)
     std::vector<int> tev_vec;       // per timed sweep: vectors it reads and writes
     // residual history of the last solve: per iteration the recursive ||D^-1 r|| / ||D^-1 b||,
     // per restart pass or refinement step the true (||r||/||b||, ||D^-1 r||/||D^-1 b||)
@@ -426,15 +427,16 @@ hipEvent_t timing_event(cps_solver *s)
 // Sweep timing: every kernel_timing-th preconditioner apply is sampled (sampled_run); each of
 // its sweeps on the problem's grid gets a pair of events that its launch stamps with the
 // kernel's own start and end (timed_sweep), so the timing holds the sweeps' execution and no
-// launch gaps or queue time.
+// launch gaps or queue time.  A launch that forms two steps is one sweep here.
 bool sampled_run(cps_solver *s)
 {
     const int period = s->opt.kernel_timing;
     return period > 0 && (s->sweep_count++ % period) == 0;
 }
 
-// events for one timed sweep that reads and writes `nvec` vectors
-std::pair<hipEvent_t, hipEvent_t> timed_sweep(cps_solver *s, int nvec)
+// events for one timed sweep that reads and writes `nvec` vectors (n = 0: for a launch whose time
+// belongs to the sweep before)
+std::pair<hipEvent_t, hipEvent_t> timed_sweep(cps_solver *s, int nvec, int n = 1)
 {
     hipEvent_t e0 = timing_event(s), e1 = timing_event(s);
     const size_t pair = s->tev_used / 2 - 1;
@@ -446,7 +448,7 @@ std::pair<hipEvent_t, hipEvent_t> timed_sweep(cps_solver *s, int nvec)
     }
     s->tev_iter[pair] = s->iter_enq;
     s->tev_ok[pair] = 1;
-    s->tev_n[pair] = 1;
+    s->tev_n[pair] = n;
     s->tev_vec[pair] = nvec;
     return {e0, e1};
 }
@@ -660,8 +662,8 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
         return;
     }
     const int nu = s->opt.mg_nu;
-    // on large grids the second step forms x_1 itself, in a cycle that is not timed sweep by sweep
-    const bool second = nu == 2 && !samp && mg_second_pays<T>(s->g);
+    // on large grids the second step forms x_1 itself
+    const bool second = nu == 2 && mg_second_pays<T>(s->g);
     launch_first<T>(kind, L, cf, ir, r, ps, v, a, s->mg_c2[0], st, !second);
     if (s->irr_map && nu >= 2 && nu - 1 <= MG_TB_H - 2) {
         // a small problem (irr_map is there up to MG_TB_MAX_POINTS): its passes temporally blocked
@@ -690,8 +692,11 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
         return;
     }
     T *x;
+    hipEvent_t ev[4];
+    const auto stamp = [&](int q, int nvec, int n) { std::tie(ev[2 * q], ev[2 * q + 1]) = timed_sweep(s, nvec, n); };
     if (second) {
-        launch_mg_second<T>(L, cf, ir, a, ps, b, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st);
+        if (samp) stamp(0, 2, 1);
+        launch_mg_second<T>(L, cf, ir, a, ps, b, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st, samp ? ev : nullptr);
         x = b;
     } else {
         x = mg_smooth<T>(s, 0, L, cf, ir, ps, nullptr, nullptr, a, b, nullptr, 1, nu, s->mg_c1.data(), s->mg_c2.data(), st,
@@ -706,10 +711,13 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
                                 mg_vecs<T>(s->mg[1])[0], mg_first<T>(s, 1), st);
     T *e = mg_level<T>(s, 1, st);
     launch_mg_prolong_add<T>(s->stream, mg_transfer<T>(s->mg[0]), s->skip, s->g.W, e, x);
-    // a sampled cycle smooths sweep by sweep, each with its own stamps
-    if (nu == 2 && !samp && mg_pair_pays<T>(s->g))
-        launch_mg_pair<T>(L, cf, ir, x, ps, res, dst, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st);
-    else
+    if (nu == 2 && mg_pair_pays<T>(s->g)) {
+        if (samp) {
+            stamp(0, 3, 1);
+            if (ir.n > 0) stamp(1, 0, 0);
+        }
+        launch_mg_pair<T>(L, cf, ir, x, ps, res, dst, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st, samp ? ev : nullptr);
+    } else
         mg_smooth<T>(s, 0, L, cf, ir, ps, x, nullptr, x, res, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
 }
 

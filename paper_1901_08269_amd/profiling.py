@@ -34,18 +34,18 @@ import re
 import sqlite3
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-# what defines the measured sweep kernel: the data layout header, and in sweeps.hip the
-# Chebyshev section from its heading to the end of k_cheb4 (its helpers and the kernel);
-# a traffic report is stale once any of it changes
+# what defines the measured smoothing kernels of large grids: the data layout header, and in
+# multigrid.hip the section from the shared helpers of its marches to the end of k_mg_second (with
+# k_mg_pair between); a traffic report is stale once any of it changes
 KERNEL_HEADER = "csrc/cps_device.h"
-KERNEL_FILE = "csrc/sweeps.hip"
-KERNEL_START = "// Chebyshev-Jacobi steps on K phi = rho"
-KERNEL_NAME = " k_cheb4("
+KERNEL_FILE = "csrc/multigrid.hip"
+KERNEL_START = "// A wave-uniform value moved to a scalar register."
+KERNEL_NAME = " k_mg_second("
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 
 def kernel_source():
-    """The source text the sweep kernel is compiled from (see KERNEL_*)."""
+    """The source text the smoothing kernels are compiled from (see KERNEL_*)."""
     with open(os.path.join(HERE, KERNEL_FILE)) as fh:
         src = fh.read()
     a = src.index(KERNEL_START)

@@ -114,6 +114,36 @@ def test_sweep_timing_counts_and_leaves_the_solution_unchanged(precision, precon
     assert st1["iters"] == st0["iters"] and bool((u0 == u1).all())
 
 
+# Grids above 40 MB per vector, whose smoothing steps run fused: FP32 (43 MB), FP64 with one row
+# segment (42 MB), and FP64 rows of more than 256 nodes, whose post-smoothing runs sweep by sweep.
+@pytest.mark.parametrize("precision,shape", [("mixed", (222, 223, 221)), ("fp64", (176, 174, 177)),
+                                             ("fp64", (290, 140, 131))])
+def test_sweep_timing_leaves_large_solves_unchanged(precision, shape):
+    """A timed cycle takes the kernels of an untimed one: the solve is bitwise the one without
+    timing, and the stats count the launches that form the steps, with the vectors they move (2
+    for the second step of the first pass, 3 for both steps of the second, or 3 and 4)."""
+    print(f"[case] sweep timing {shape} {precision}", flush=True)
+    grids = tuple(W.tanh_grid(n, 1.1) for n in shape)
+    w = W.polynomial_case(0, [W.Sphere((0.52, 0.47, 0.5), 0.2)], rng_seed=4, grids=grids)
+    sol = []
+    for timing in (0, 1, 3):
+        S = cps.Solver.from_workload(w, precision=precision, kernel_timing=timing)
+        sol.append(S.solve(1e-10))
+        S.close()
+    (u0, st0), (u1, st1), (u3, st3) = sol
+    assert st1["iters"] == st0["iters"] == st3["iters"]
+    assert bool((u0 == u1).all()) and bool((u0 == u3).all())
+    n, nf, pts = st1["sweep_launches"], st1["sweep_full_launches"], st1["sweep_points"]
+    vb = 4 if precision == "mixed" else 8
+    print(f"{n} timed launches ({nf} full-traffic), {1e3 * st1['sweep_ms'] / max(n, 1):.2f} us each")
+    assert pts == math.prod(m - 2 for m in shape) and n > st3["sweep_launches"] > 0
+    if shape[0] - 2 <= 256 or precision == "mixed":       # k_mg_second, k_mg_pair
+        assert nf == 0 and n % 2 == 0 and st1["sweep_bytes"] == n // 2 * (2 + 3) * vb * pts
+    else:                                                 # k_mg_second, a pass's two sweeps
+        assert n % 3 == 0 and nf == n // 3 and st1["sweep_bytes"] == n // 3 * (2 + 3 + 4) * vb * pts
+    assert 0.0 < st1["sweep_ms"] / n < 5.0 and st0["sweep_launches"] == 0
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_host_pointer_setup_and_solve_match_device_pointers(precision):
     """The C-ABI with host arrays (device_ptrs = 0: the library uploads phi, g and f before
