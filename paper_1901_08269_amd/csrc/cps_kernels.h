@@ -97,14 +97,22 @@ void launch_mg_restrict(hipStream_t s, const MgTransfer<T> &t, const T *r, T *rc
 template <typename T>
 void launch_mg_diag(hipStream_t s, int nx, int ny, int nz, const Coef<T> &cf, const int8_t *type, const int *irr_map,
                     const T *k7, T *diag);
+// The tiles of the kernels that march over the problem's grid (those that the grid uses): they go by
+// how many blocks the current device holds at once, looked up here, so a solver keeps its own.
+struct MgMarches {
+    bool set = false;
+    Tiling rr{}, second{}, pair{};   // of launch_mg_resid_restrict, launch_mg_second, launch_mg_pair
+};
+template <typename T>
+MgMarches mg_marches(const Geom &g, const MgTransfer<T> &t);
 // rc = R (rho - K x) from the problem's grid (geometry g, skip bits, tables cf) into the
 // first coarse level, the fine residual never stored: ri holds the residual at the
 // irregular nodes (launch_resid_irregular) and 0 at the solid ones.  first: as for
 // launch_mg_restrict.
 template <typename T>
-void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, const uint32_t *skip, const T *x,
-                              const T *rho, const T *ri, const MgTransfer<T> &t, T *rc, const MgFirst<T> &first,
-                              const DevState *st);
+void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Tiling &tl, const Coef<T> &cf, const uint32_t *skip,
+                              const T *x, const T *rho, const T *ri, const MgTransfer<T> &t, T *rc,
+                              const MgFirst<T> &first, const DevState *st);
 // Two smoothing steps on the problem's grid in one pass: y = x + c2a (rho - K x) / diag K, then
 // out = y + c1 (y - x) + c2 (rho - K y) / diag K.  yi (0 at the solid nodes) takes y at the
 // irregular nodes; y is stored nowhere else.  mg_pair_pays: the grids where this is the faster way
@@ -113,16 +121,16 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
 template <typename T>
 bool mg_pair_pays(const Geom &g);
 template <typename T>
-void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
-                    double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev = nullptr);
+void launch_mg_pair(const Launch &L, const Tiling &tl, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho,
+                    T *yi, T *out, double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev = nullptr);
 // out = x_1 + c1 x_1 + c2 (rho - K x_1) / diag K with x_1 = c2a rho / diag K, which is read at the
 // irregular nodes alone (launch_first with all_x1 = false) and is 0 at the solid ones.
 // mg_second_pays: the grids where this is the faster way.  ev (optional): the launch's two events.
 template <typename T>
 bool mg_second_pays(const Geom &g);
 template <typename T>
-void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
-                      double c1, double c2, const DevState *st, const hipEvent_t *ev = nullptr);
+void launch_mg_second(const Launch &L, const Tiling &tl, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho,
+                      T *out, double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev = nullptr);
 // The coarsest level's `steps` Chebyshev steps (coefficients c1, c2) from 0 in one workgroup
 // of MG_LDS_THREADS threads; the level has at most MG_LDS_NODES interior nodes, at most
 // MG_LDS_PADDED nodes with its walls (6885 for the 9 x 9 x 85 points that the coarsening rule

@@ -1643,17 +1643,12 @@ void launch_mg_restrict(hipStream_t s, const MgTransfer<T> &t, const T *r, T *rc
 }
 
 // Tiles of a kernel whose blocks march over tiles_x x tiles_y columns of nzi planes.  The march is
-// bound by the latency of its plane steps: all blocks run in one round, as many as fit on the
-// device at once (z-chunks of at least min_tz planes).  per_cu: the kernel's blocks per CU, 0 before
-// its first launch.
-static Tiling march_tiling(int &per_cu, const void *fn, int threads, int tiles_x, int tiles_y, int nzi, int min_tz = 2)
+// bound by the latency of its plane steps: all blocks run in one round, as many as fit on the current
+// device at once (z-chunks of at least min_tz planes).
+static Tiling march_tiling(const void *fn, int threads, int tiles_x, int tiles_y, int nzi, int min_tz = 2)
 {
-    if (!per_cu) {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, threads, 0) != hipSuccess || nb < 1) nb = 1;
-        per_cu = nb;
-    }
-    int dev = 0, ncu = 0;
+    int per_cu = 0, dev = 0, ncu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0) != hipSuccess || per_cu < 1) per_cu = 1;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
         ncu = 256;
@@ -1679,10 +1674,23 @@ static bool resid_restrict_short(const Geom &g)
     return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= RRS_MAX_BYTES;
 }
 
+// the marching kernel of a grid: the fifth-node path (more registers) only where some lane 63 owns
+// its second coarse node (128) and that node's last fine point (257) is interior; with an odd nx that
+// is so from nx = 259, where one segment still covers the coarse row
+static bool rr_fifth(const Geom &g) { return g.nx - 2 >= 257; }
+static bool rr_half(const Geom &g) { return g.nx - 2 <= 128; }
 template <typename T>
-void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, const uint32_t *skip, const T *x,
-                              const T *rho, const T *ri, const MgTransfer<T> &t, T *rc, const MgFirst<T> &first,
-                              const DevState *st)
+static auto rr_kernel(const Geom &g)
+{
+    return rr_fifth(g) ? &k_mg_resid_restrict<T, true, false>
+           : rr_half(g) ? &k_mg_resid_restrict<T, false, true>
+                        : &k_mg_resid_restrict<T, false, false>;
+}
+
+template <typename T>
+void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Tiling &tl, const Coef<T> &cf, const uint32_t *skip,
+                              const T *x, const T *rho, const T *ri, const MgTransfer<T> &t, T *rc,
+                              const MgFirst<T> &first, const DevState *st)
 {
     if (resid_restrict_short<T>(g)) {
         const int gpr = (g.nx - 2 + 3) / 4;
@@ -1693,25 +1701,8 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Coef<T> &cf, c
                                                                           rc, first, st);
         return;
     }
-    // the fifth-node path (more registers) only where some lane 63 owns its second coarse node
-    // (128) and that node's last fine point (257) is interior; with an odd nx that is so from
-    // nx = 259, where one segment still covers the coarse row
-    const int ncx = t.nc[0], ncy = t.nc[1], ncz = t.nc[2];
-    const bool fifth = g.nx - 2 >= 257, half = g.nx - 2 <= 128;
-    const void *fn = fifth ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, true, false>)
-                     : half ? reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false, true>)
-                            : reinterpret_cast<const void *>(&k_mg_resid_restrict<T, false, false>);
-    static int per_cu[3] = {0, 0, 0};
-    const int rows = half ? 2 * RR_ROWS + 1 : RR_ROWS;
-    const Tiling tl = march_tiling(per_cu[fifth ? 0 : half ? 1 : 2], fn, 64 * (RR_ROWS + 1), (ncx - 2 + 127) / 128,
-                                   (ncy - 2 + rows - 1) / rows, ncz - 2, half ? 1 : 2);
-#define CPS_RR_LAUNCH(FIFTH, HALF)                                                                                     \
-    k_mg_resid_restrict<T, FIFTH, HALF><<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(                                     \
-        g, tl, cf, skip, x, rho, ri, ncx, ncy, ncz, t.ax[0], t.ax[1], t.ax[2], rc, first, st)
-    if (fifth) CPS_RR_LAUNCH(true, false);
-    else if (half) CPS_RR_LAUNCH(false, true);
-    else CPS_RR_LAUNCH(false, false);
-#undef CPS_RR_LAUNCH
+    rr_kernel<T>(g)<<<tl.nblk, dim3(64, RR_ROWS + 1), 0, s>>>(g, tl, cf, skip, x, rho, ri, t.nc[0], t.nc[1], t.nc[2],
+                                                              t.ax[0], t.ax[1], t.ax[2], rc, first, st);
 }
 
 // Which grids take these marches: those with more than MARCH_MIN_BYTES per vector.  On smaller ones
@@ -1750,44 +1741,60 @@ static void timed_launch(const hipEvent_t *ev, void (*kernel)(Args...), dim3 gri
     else kernel<<<grid, block, 0, s>>>(args...);
 }
 
+// the kernels of a grid: more than one segment per row (SEG) or not; the FP64 pair has none of the
+// former (mg_pair_pays)
 template <typename T>
-void launch_mg_pair(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *yi, T *out,
-                    double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev)
+static auto pair_kernel(const Geom &g)
+{
+    if constexpr (sizeof(T) == 4) return g.nx - 2 > 256 ? &k_mg_pair<T, true> : &k_mg_pair<T, false>;
+    else return &k_mg_pair<T, false>;
+}
+template <typename T>
+static auto second_kernel(const Geom &g)
+{
+    return g.nx - 2 > 256 ? &k_mg_second<T, true> : &k_mg_second<T, false>;
+}
+
+template <typename T>
+MgMarches mg_marches(const Geom &g, const MgTransfer<T> &t)
+{
+    MgMarches m;
+    const int segs = (g.nx - 2 + 255) / 256;
+    const auto tiling = [&](auto kernel, int waves, int rows) {
+        return march_tiling(reinterpret_cast<const void *>(kernel), 64 * waves, segs, (g.ny - 2 + rows - 1) / rows, g.nz - 2);
+    };
+    if (!resid_restrict_short<T>(g)) {
+        const bool half = rr_half(g);
+        const int rows = half ? 2 * RR_ROWS + 1 : RR_ROWS;
+        m.rr = march_tiling(reinterpret_cast<const void *>(rr_kernel<T>(g)), 64 * (RR_ROWS + 1), (t.nc[0] - 2 + 127) / 128,
+                            (t.nc[1] - 2 + rows - 1) / rows, t.nc[2] - 2, half ? 1 : 2);
+    }
+    if (mg_second_pays<T>(g)) m.second = tiling(second_kernel<T>(g), Second<T>::waves, Second<T>::rows);
+    if (mg_pair_pays<T>(g)) m.pair = tiling(pair_kernel<T>(g), Pair<T>::waves, Pair<T>::rows);
+    m.set = true;
+    return m;
+}
+
+template <typename T>
+void launch_mg_pair(const Launch &L, const Tiling &tl, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho,
+                    T *yi, T *out, double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev)
 {
     const Geom &g = L.g;
     if (ir.n > 0)
         timed_launch(ev ? ev + 2 : nullptr, k_mg_pair_irregular<T>, dim3((8 * ir.n + NT - 1) / NT), dim3(NT), L.stream, g, cf,
                      ir, L.skip, x, rho, yi, out, (T)c2a, (T)c1, (T)c2, st);
-    const auto launch = [&](auto kernel, int &per_cu) {
-        const Tiling tl = march_tiling(per_cu, reinterpret_cast<const void *>(kernel), 64 * Pair<T>::waves,
-                                       (g.nx - 2 + 255) / 256, (g.ny - 2 + Pair<T>::rows - 1) / Pair<T>::rows, g.nz - 2);
-        timed_launch(ev, kernel, dim3(tl.nblk), dim3(64, Pair<T>::waves), L.stream, g, tl, cf, L.skip, x, rho,
-                     (const T *)yi, out, (T)c2a, (T)c1, (T)c2, st);
-    };
-    static int per_cu[2] = {0, 0};
-    if constexpr (sizeof(T) == 4) {
-        if (g.nx - 2 > 256) {
-            launch(k_mg_pair<T, true>, per_cu[1]);
-            return;
-        }
-    }
-    launch(k_mg_pair<T, false>, per_cu[0]);
+    timed_launch(ev, pair_kernel<T>(g), dim3(tl.nblk), dim3(64, Pair<T>::waves), L.stream, g, tl, cf, L.skip, x, rho,
+                 (const T *)yi, out, (T)c2a, (T)c1, (T)c2, st);
 }
 
 template <typename T>
-void launch_mg_second(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho, T *out, double c2a,
-                      double c1, double c2, const DevState *st, const hipEvent_t *ev)
+void launch_mg_second(const Launch &L, const Tiling &tl, const Coef<T> &cf, const Irr<T> &ir, const T *x1, const T *rho,
+                      T *out, double c2a, double c1, double c2, const DevState *st, const hipEvent_t *ev)
 {
-    const Geom &g = L.g;
     constexpr int NTH = 64 * Second<T>::waves;
-    const bool seg = g.nx - 2 > 256;
-    const auto kernel = seg ? &k_mg_second<T, true> : &k_mg_second<T, false>;
-    static int per_cu[2] = {0, 0};
-    const Tiling tl = march_tiling(per_cu[seg], reinterpret_cast<const void *>(kernel), NTH, (g.nx - 2 + 255) / 256,
-                                   (g.ny - 2 + Second<T>::rows - 1) / Second<T>::rows, g.nz - 2);
     const int nb = tl.nblk + (8 * ir.n + NTH - 1) / NTH;
-    timed_launch(ev, kernel, dim3(nb), dim3(64, Second<T>::waves), L.stream, g, tl, cf, ir, L.skip, x1, rho, out, (T)c2a,
-                 (T)c1, (T)c2, st);
+    timed_launch(ev, second_kernel<T>(L.g), dim3(nb), dim3(64, Second<T>::waves), L.stream, L.g, tl, cf, ir, L.skip, x1,
+                 rho, out, (T)c2a, (T)c1, (T)c2, st);
 }
 
 template <typename T>
@@ -1869,29 +1876,31 @@ template void launch_mg_diag<double>(hipStream_t, int, int, int, const Coef<doub
                                      const double *, double *);
 template void launch_mg_diag<float>(hipStream_t, int, int, int, const Coef<float> &, const int8_t *, const int *,
                                     const float *, float *);
-template void launch_mg_resid_restrict<double>(hipStream_t, const Geom &, const Coef<double> &, const uint32_t *, const double *, const double *,
-                                                const double *, const MgTransfer<double> &, double *,
-                                                const MgFirst<double> &, const DevState *);
-template void launch_mg_resid_restrict<float>(hipStream_t, const Geom &, const Coef<float> &, const uint32_t *, const float *, const float *,
-                                               const float *, const MgTransfer<float> &, float *,
-                                               const MgFirst<float> &, const DevState *);
+template void launch_mg_resid_restrict<double>(hipStream_t, const Geom &, const Tiling &, const Coef<double> &, const uint32_t *,
+                                              const double *, const double *, const double *, const MgTransfer<double> &,
+                                              double *, const MgFirst<double> &, const DevState *);
+template void launch_mg_resid_restrict<float>(hipStream_t, const Geom &, const Tiling &, const Coef<float> &, const uint32_t *,
+                                              const float *, const float *, const float *, const MgTransfer<float> &,
+                                              float *, const MgFirst<float> &, const DevState *);
 template void launch_mg_prolong_add<double>(hipStream_t, const MgTransfer<double> &, const uint32_t *, int,
                                             const double *, double *);
 template void launch_mg_prolong_add<float>(hipStream_t, const MgTransfer<float> &, const uint32_t *, int, const float *,
                                            float *);
 
+template MgMarches mg_marches<double>(const Geom &, const MgTransfer<double> &);
+template MgMarches mg_marches<float>(const Geom &, const MgTransfer<float> &);
 template bool mg_pair_pays<double>(const Geom &);
 template bool mg_pair_pays<float>(const Geom &);
 template bool mg_second_pays<double>(const Geom &);
 template bool mg_second_pays<float>(const Geom &);
-template void launch_mg_pair<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *, const double *,
+template void launch_mg_pair<double>(const Launch &, const Tiling &, const Coef<double> &, const Irr<double> &, const double *, const double *,
                                      double *, double *, double, double, double, const DevState *, const hipEvent_t *);
-template void launch_mg_pair<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *, const float *,
+template void launch_mg_pair<float>(const Launch &, const Tiling &, const Coef<float> &, const Irr<float> &, const float *, const float *,
                                     float *, float *, double, double, double, const DevState *, const hipEvent_t *);
 
-template void launch_mg_second<double>(const Launch &, const Coef<double> &, const Irr<double> &, const double *,
+template void launch_mg_second<double>(const Launch &, const Tiling &, const Coef<double> &, const Irr<double> &, const double *,
                                        const double *, double *, double, double, double, const DevState *, const hipEvent_t *);
-template void launch_mg_second<float>(const Launch &, const Coef<float> &, const Irr<float> &, const float *,
+template void launch_mg_second<float>(const Launch &, const Tiling &, const Coef<float> &, const Irr<float> &, const float *,
                                       const float *, float *, double, double, double, const DevState *, const hipEvent_t *);
 
 }  // namespace cps

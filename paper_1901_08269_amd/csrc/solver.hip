@@ -133,6 +133,7 @@ struct cps_solver {
     std::vector<MgLevel> mg;            // mg[0] is this grid
     std::vector<double> mg_c1, mg_c2;   // smoother steps on [mg_smooth_lo, lam_hi]
     std::vector<double> mg_cc1, mg_cc2; // coarsest-level steps on [lambda_1, lam_hi]
+    MgMarches mg_march64, mg_march32;   // set on first use of the precision
     double *mg_zero64 = nullptr;        // zeros, the size of level 1
     float *mg_zero32 = nullptr;
     int sweep_rev[MG_MAX_LEVELS] = {};  // per level: z direction of its next sweep (alternates)
@@ -662,6 +663,9 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
         return;
     }
     const int nu = s->opt.mg_nu;
+    MgMarches *mm;
+    if constexpr (sizeof(T) == 8) mm = &s->mg_march64; else mm = &s->mg_march32;
+    if (!mm->set) *mm = mg_marches<T>(s->g, mg_transfer<T>(s->mg[0]));
     // on large grids the second step forms x_1 itself
     const bool second = nu == 2 && mg_second_pays<T>(s->g);
     launch_first<T>(kind, L, cf, ir, r, ps, v, a, s->mg_c2[0], st, !second);
@@ -696,7 +700,7 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
     const auto stamp = [&](int q, int nvec, int n) { std::tie(ev[2 * q], ev[2 * q + 1]) = timed_sweep(s, nvec, n); };
     if (second) {
         if (samp) stamp(0, 2, 1);
-        launch_mg_second<T>(L, cf, ir, a, ps, b, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st, samp ? ev : nullptr);
+        launch_mg_second<T>(L, mm->second, cf, ir, a, ps, b, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st, samp ? ev : nullptr);
         x = b;
     } else {
         x = mg_smooth<T>(s, 0, L, cf, ir, ps, nullptr, nullptr, a, b, nullptr, 1, nu, s->mg_c1.data(), s->mg_c2.data(), st,
@@ -707,7 +711,7 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
     // then serves as the post-smoothing's second iterate
     T *res = (x == a) ? b : a;
     launch_resid_irregular<T>(L, cf, ir, x, ps, res, st);
-    launch_mg_resid_restrict<T>(s->stream, s->g, cf, L.skip, x, ps, res, mg_transfer<T>(s->mg[0]),
+    launch_mg_resid_restrict<T>(s->stream, s->g, mm->rr, cf, L.skip, x, ps, res, mg_transfer<T>(s->mg[0]),
                                 mg_vecs<T>(s->mg[1])[0], mg_first<T>(s, 1), st);
     T *e = mg_level<T>(s, 1, st);
     launch_mg_prolong_add<T>(s->stream, mg_transfer<T>(s->mg[0]), s->skip, s->g.W, e, x);
@@ -716,7 +720,7 @@ void mg_precond(cps_solver *s, Vecs<T> &V, int kind, const T *r, T *ps, const T 
             stamp(0, 3, 1);
             if (ir.n > 0) stamp(1, 0, 0);
         }
-        launch_mg_pair<T>(L, cf, ir, x, ps, res, dst, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st, samp ? ev : nullptr);
+        launch_mg_pair<T>(L, mm->pair, cf, ir, x, ps, res, dst, s->mg_c2[0], s->mg_c1[1], s->mg_c2[1], st, samp ? ev : nullptr);
     } else
         mg_smooth<T>(s, 0, L, cf, ir, ps, x, nullptr, x, res, dst, 0, nu, s->mg_c1.data(), s->mg_c2.data(), st, samp);
 }

@@ -2,6 +2,8 @@
 include/cps.h declares (no compute calls here)."""
 import ctypes
 import os
+import shutil
+import subprocess
 
 import pytest
 
@@ -64,3 +66,22 @@ def test_multigrid_options_validated_before_device_calls():
         h = ctypes.c_void_p()
         rc = lib.cps_setup(ctypes.byref(h), n, n, n, dp(x), dp(x), dp(x), dp(a), dp(a), dp(a), ctypes.byref(o))
         assert rc == -1, (name, val, rc)
+
+
+@pytest.mark.skipif(not os.path.exists(cps.LIB_PATH) or not shutil.which("nm"), reason="libcps.so not built, or no nm")
+def test_library_keeps_no_unguarded_state():
+    """Threads with solvers of their own share nothing but what a mutex guards: the pools of device and
+    pinned blocks, the set-up streams and the scratch addresses.  Every other writable variable of the
+    library (of its own, not of the HIP and C++ runtimes) would be shared without one, so there is none."""
+    guarded = {"pinned_mu", "pinned_free", "cache_mu", "cache_blocks", "scratch_mu", "scratch_dev", "mu", "per_dev"}
+    out = subprocess.run(["nm", "-C", cps.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    names = set()
+    for line in out.splitlines():
+        f = line.split(maxsplit=2)
+        if len(f) < 3 or f[1] not in "bBdDuvV" or f[2].endswith(")"):     # kernels' handles end with their arguments
+            continue
+        n = f[2].split("::")[-1]
+        if f[2].startswith(("guard variable", "_", "DW.ref", "__", "typeinfo", "vtable", "completed")) or n == "scratch":
+            continue                                                     # scratch: the handle of a device array
+        names.add(n)
+    assert names <= guarded, names - guarded
