@@ -993,6 +993,9 @@ void nck(hipError_t e)
     if (e != hipSuccess) throw NetFail{CPS_EDEVICE};
 }
 
+// an error that an earlier call of the program left behind (and reported then) is not this call's
+void forget_errors() { (void)hipGetLastError(); }
+
 inline unsigned nblk(size_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 // Device address of `scratch` on device `dev`, looked up once per device with that device
@@ -1380,6 +1383,7 @@ int cps_model_forward(cps_model *m, const float *inputs, int32_t batch, float *p
 {
     if (!m || !inputs || !pred || batch < 1 || batch > m->spec.batch) return CPS_EINVAL;
     try {
+        forget_errors();
         const size_t n3 = (size_t)m->spec.nc * m->spec.nc * m->spec.nc, ci = m->spec.in_ch;
         const bool in_place = cps::device_array(pred, batch * n3 * sizeof(float), m->device);
         forward(m, batch, readable(m, inputs, batch * n3 * ci, 0, m->spec.batch * n3 * ci), in_place ? pred : m->pred);
@@ -1397,6 +1401,7 @@ int cps_model_train_step(cps_model *m, const float *inputs, const float *target,
 {
     if (!m || !inputs || !target || batch < 1 || batch > m->spec.batch) return CPS_EINVAL;
     try {
+        forget_errors();
         const size_t n3 = (size_t)m->spec.nc * m->spec.nc * m->spec.nc, ci = m->spec.in_ch, most = m->spec.batch * n3;
         forward(m, batch, readable(m, inputs, batch * n3 * ci, 0, most * ci), m->pred);
         backward(m, batch, readable(m, target, batch * n3, 1, most), readable(m, mask, batch * n3, 2, most));

@@ -87,6 +87,29 @@ def test_arrays_outside_device_memory():
         assert np.array_equal(x, y)
 
 
+def test_network_runs_after_a_failed_call_of_the_program():
+    """An error that an earlier, unrelated HIP call of the program left behind is not the
+    network's: its calls go through."""
+    import ctypes as C
+    import torch
+    inp, tgt, _ = _batch(8, 2, 3)
+    L = cps.load_library()
+    m = learned.Model(8, batch=2, channels=CH, seed=1)
+    ref = m.forward(inp)
+    pred = torch.empty_like(ref)
+    torch.cuda.synchronize()
+    p = lambda t: C.c_void_p(t.data_ptr())
+    loss = C.c_double()
+    L.hipSetDevice(4096)                              # fails: no such device
+    rc = m.L.cps_model_forward(m.h, p(inp), 2, p(pred))
+    L.hipSetDevice(4096)
+    rc2 = m.L.cps_model_train_step(m.h, p(inp), p(tgt), None, 2, C.c_float(1e-3), 1, C.byref(loss))
+    L.hipGetLastError()
+    assert rc == 0 and rc2 == 0
+    assert bool((pred == ref).all()) and np.isfinite(loss.value)
+    m.close()
+
+
 def test_adam_steps_vs_oracle():
     """Two training steps with the Adam update: the parameters after each step against the
     oracle's Adam (Kingma & Ba, Algorithm 1) applied to the same starting parameters and the
