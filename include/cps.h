@@ -106,7 +106,7 @@ typedef struct cps_options {
      * incomplete factorisation without fill), sip_iters iterations from phi = 0 per apply
      * (the paper runs 8 inner iterations of its modified strongly implicit procedure,
      * Sec. 4).  The substitutions run hyperplane by hyperplane (i + j + k = const) in tiles of
-     * 16^3 nodes, one launch per hyperplane of tiles: slower on a GPU than the parallel inner
+     * up to 16^3 nodes, one launch per hyperplane of tiles: slower on a GPU than the parallel inner
      * solvers. */
     int32_t sip_iters;       /* 1..64 (default 8) */
     int32_t fp64_finish;     /* CPS_MIXED, 1 (default): when a refinement step reduces

@@ -177,17 +177,28 @@ void launch_mg_irr_map(hipStream_t s, int nirr, const int *nodes, int *map);
 template <typename T>
 void launch_mg_prolong_add(hipStream_t s, const MgTransfer<T> &t, const uint32_t *skip_f, int W, const T *e, T *x);
 
-// sip.hip: the strongly implicit procedure for K, in tiles of SIP_TS^3 nodes.  The factors F
-// and F32 hold 8 values for each of sip_factor_nodes(...) nodes (whole tiles).
+// sip.hip: the strongly implicit procedure for K, in tiles of at most SIP_TS nodes per axis.  The
+// factors F and F32 hold 8 values for each of sip_factor_nodes(...) nodes (whole tiles).
 constexpr int SIP_TS = 16, SIP_TN = SIP_TS * SIP_TS * SIP_TS;
+constexpr int SIP_STEPS = 3 * SIP_TS - 2;   // hyperplanes of the largest tile
+// A tile's nodes in hyperplane order (node: packed i + TS j + TS^2 k; cell: its place in the LDS tile
+// without the face layer), each node's position in it, and the first position of each hyperplane
+// (past the tile's last: its node count).
+struct SipOrder {
+    alignas(16) uint16_t cell[SIP_TN];
+    uint16_t node[SIP_TN], pos[SIP_TN];
+    int start[SIP_STEPS + 1];
+};
+SipOrder sip_order(int nx, int ny, int nz);
 size_t sip_factor_nodes(int nx, int ny, int nz);
-void launch_sip_factor(hipStream_t st, int nx, int ny, int nz, const Coef<double> &cf, const int8_t *type,
-                       const int *irr_map, const double *k7, double alpha, double *F, float *F32);
+// order: the grid's sip_order on the device
+void launch_sip_factor(hipStream_t st, int nx, int ny, int nz, const SipOrder *order, const Coef<double> &cf,
+                       const int8_t *type, const int *irr_map, const double *k7, double alpha, double *F, float *F32);
 // one iteration: L v = r, U delta = v (delta over v), phi = delta (first) or phi += delta;
 // v and phi are written at every interior node (0 where it is not an unknown)
 template <typename T>
-void launch_sip_iteration(hipStream_t st, int nx, int ny, int nz, const T *F, const T *r, T *v, T *phi, int first,
-                          const DevState *dst);
+void launch_sip_iteration(hipStream_t st, int nx, int ny, int nz, const SipOrder *order, const T *F, const T *r, T *v,
+                          T *phi, int first, const DevState *dst);
 
 // setup.hip
 struct SetupOut {

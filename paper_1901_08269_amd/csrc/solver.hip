@@ -145,6 +145,7 @@ struct cps_solver {
     double *sip64 = nullptr;
     float *sip32 = nullptr;
     int *sip_map = nullptr;
+    SipOrder *sip_ord = nullptr;
     double *sip_w64[2] = {nullptr, nullptr};
     float *sip_w32[2] = {nullptr, nullptr};
     // host-side facts
@@ -747,7 +748,7 @@ void sip_precond(cps_solver *s, const T *ps, T *dst, const DevState *st)
             launch_resid<T>(L, cf, ir, dst, ps, w[0], st, next_rev(s, 0));
             rin = w[0];
         }
-        launch_sip_iteration<T>(s->stream, s->nx, s->ny, s->nz, F, rin, w[1], dst, it == 0, st);
+        launch_sip_iteration<T>(s->stream, s->nx, s->ny, s->nz, s->sip_ord, F, rin, w[1], dst, it == 0, st);
     }
 }
 
@@ -759,7 +760,11 @@ void sip_build(cps_solver *s)
     const size_t nf = 8 * sip_factor_nodes(s->nx, s->ny, s->nz);    // every one is written
     s->sip64 = dalloc<double>(s, nf);
     s->sip32 = dalloc<float>(s, nf);
-    launch_sip_factor(s->stream, s->nx, s->ny, s->nz, s->cf64(), s->type, s->sip_map, s->irr_k64, s->opt.sip_alpha,
+    s->sip_ord = dalloc<SipOrder>(s, 1);
+    const SipOrder order = sip_order(s->nx, s->ny, s->nz);
+    ck(hipMemcpyAsync(s->sip_ord, &order, sizeof(order), hipMemcpyHostToDevice, s->stream));
+    sync(s);
+    launch_sip_factor(s->stream, s->nx, s->ny, s->nz, s->sip_ord, s->cf64(), s->type, s->sip_map, s->irr_k64, s->opt.sip_alpha,
                       s->sip64, s->sip32);
 }
 

@@ -98,3 +98,26 @@ def test_sip_options_validated():
     for kw in ({"sip_iters": 0}, {"sip_iters": 65}, {"sip_alpha": -0.1}, {"sip_alpha": 1.5}):
         with pytest.raises(cps.CpsError):
             cps.Solver.from_workload(w, precond="sip", **kw)
+
+
+# Interior nodes at the edges of the tiles' rule: fewer than a tile's 16 along an axis, one more
+# than a tile (two tiles of 9), one more than two tiles (three of 11), a single node.
+@pytest.mark.parametrize("shape", [(5, 40, 23), (19, 19, 18), (35, 6, 51), (40, 35, 4), (3, 21, 66), (17, 3, 3)])
+def test_sip_apply_matches_oracle_on_thin_grids(shape):
+    print(f"[case] sip thin {shape}", flush=True)
+    grids = tuple(W.tanh_grid(n, 0.8) for n in shape)
+    bodies = [W.Sphere((0.5, 0.48, 0.52), 0.26)] if min(shape) >= 18 else []
+    w = W.polynomial_case(0, bodies, rng_seed=2, grids=grids)
+    P = oracle.Problem.from_workload(w)
+    t = P.types()
+    unk = (t == 1) | (t == 2)
+    rho = np.random.Generator(np.random.PCG64(8)).standard_normal(P.shape) * unk
+    F = P.sip_factors(0.9)
+    for iters in (1, 4):
+        ref = P.precond_sip(rho, iters, factors=F)
+        S = cps.Solver.from_workload(w, precond="sip", sip_iters=iters, sip_alpha=0.9)
+        for prec, bar in (("fp64", 1e-11), ("fp32", 2e-5)):
+            got = S.precond(rho, precision=prec).cpu().numpy()
+            assert np.max(np.abs(got - ref)) <= bar * np.max(np.abs(ref)), (iters, prec)
+            assert np.all(got[~unk] == 0.0)
+        S.close()

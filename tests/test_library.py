@@ -85,3 +85,16 @@ def test_library_keeps_no_unguarded_state():
             continue                                                     # scratch: the handle of a device array
         names.add(n)
     assert names <= guarded, names - guarded
+
+
+@pytest.mark.skipif(not os.path.exists(cps.LIB_PATH), reason="libcps.so not built")
+@pytest.mark.parametrize("shape", [(3, 3, 3), (3, 400, 300), (400, 5, 300), (300, 400, 3), (9, 9, 300), (19, 19, 19),
+                                   (35, 51, 67), (66, 66, 66), (131, 131, 131), (514, 514, 514)])
+def test_sip_factors_take_little_more_than_the_grid(shape):
+    """The strongly implicit procedure keeps eight values per node of whole tiles: at most 1.5 times the
+    grid's nodes, also where axes are shorter than a tile's 16 nodes or a little longer than a few tiles."""
+    lib = ctypes.CDLL(cps.LIB_PATH)
+    nodes = lib._ZN3cps16sip_factor_nodesEiii
+    nodes.restype, nodes.argtypes = ctypes.c_size_t, [ctypes.c_int] * 3
+    nx, ny, nz = shape
+    assert (nx - 2) * (ny - 2) * (nz - 2) <= nodes(nx, ny, nz) <= 1.5 * nx * ny * nz
