@@ -261,8 +261,9 @@ BF16_PEAK_TFLOPS = 2500.0       # dense BF16 matrix peak
 def mfma_report(db, title, cmd):
     """Per network kernel (one --pmc pass of SQ_VALU_MFMA_BUSY_CYCLES, GRBM_GUI_ACTIVE and
     SQ_INSTS_VALU_MFMA_MOPS_BF16): dispatches, mean duration, MFMA busy share (busy cycles
-    over active cycles times the SIMD count, as rocprofv3's MfmaUtil) and BF16 matrix FLOPs
-    (512 per MOPS unit) per second against the dense BF16 peak."""
+    over active cycles times the SIMD count; GRBM_GUI_ACTIVE comes once per XCD, and the GPU is
+    active for the mean of the eight) and BF16 matrix FLOPs (512 per MOPS unit) per second
+    against the dense BF16 peak."""
     con = sqlite3.connect(db)
     acc = {}
     for name, disp, dur, cname, val in con.execute(
@@ -272,9 +273,11 @@ def mfma_report(db, title, cmd):
         k = acc.setdefault(short_name(name), {})
         d = k.setdefault(disp, {"dur": dur})
         d[cname] = d.get(cname, 0.0) + val
+        if cname == "GRBM_GUI_ACTIVE":
+            d["xcds"] = d.get("xcds", 0) + 1
     con.close()
     out = [f"# {title}", "", "Command (run from the repository root on an MI355X):", "", "```", cmd, "```", "",
-           f"MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE x {SIMDS} SIMDs); BF16 TFLOP/s = "
+           f"MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (GRBM_GUI_ACTIVE, mean over the XCDs, x {SIMDS} SIMDs); BF16 TFLOP/s = "
            f"512 x SQ_INSTS_VALU_MFMA_MOPS_BF16 / duration, against {BF16_PEAK_TFLOPS:.0f} TFLOP/s dense.", "",
            "| kernel | dispatches | mean us | MFMA busy % | BF16 TFLOP/s | of peak |",
            "|---|---:|---:|---:|---:|---:|"]
@@ -284,7 +287,7 @@ def mfma_report(db, title, cmd):
         ds = list(disps.values())
         dur = sum(d["dur"] for d in ds)
         busy = sum(d.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) for d in ds)
-        act = sum(d.get("GRBM_GUI_ACTIVE", 0.0) for d in ds)
+        act = sum(d.get("GRBM_GUI_ACTIVE", 0.0) / d.get("xcds", 1) for d in ds)
         fl = 512.0 * sum(d.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0.0) for d in ds)
         rows.append((dur, n, len(ds), busy, act, fl))
         tot_dur += dur
@@ -316,7 +319,7 @@ def counters_report(dbs, kernels, title, cmd):
     * mean L1-to-L2 read latency in cycles (TCP_TCC_READ_REQ_LATENCY_sum over
       TCP_TCC_READ_REQ_sum) and mean L2-to-memory read latency (TCC_EA0_RDREQ_LEVEL_sum over
       TCC_EA0_RDREQ_sum), the L2 hit share (TCC_HIT_sum over TCC_HIT_sum + TCC_MISS_sum);
-    * the share of active GPU cycles (GRBM_GUI_ACTIVE) in which the address unit is busy
+    * the share of active GPU cycles (GRBM_GUI_ACTIVE, mean over the XCDs) in which the address unit is busy
       (TA_BUSY_avr) or its address path is stalled by the cache (TA_ADDR_STALLED_BY_TC_CYCLES
       per TA instance)."""
     acc = {}
@@ -370,7 +373,7 @@ def counters_report(dbs, kernels, title, cmd):
         waves = mean(n, "SQ_WAVES")
         res = None if W is None or not B or not S else 4.0 * W / (B / S) / SIMDS
         hit, miss = mean(n, "TCC_HIT_sum"), mean(n, "TCC_MISS_sum")
-        gui = mean(n, "GRBM_GUI_ACTIVE")
+        gui = ratio(mean(n, "GRBM_GUI_ACTIVE"), inst(n, "GRBM_GUI_ACTIVE"))
         stall, ta_n = mean(n, "TA_ADDR_STALLED_BY_TC_CYCLES"), inst(n, "TA_ADDR_STALLED_BY_TC_CYCLES")
         return [("waves resident per SIMD", res),
                 ("wave time waiting, %", ratio(mean(n, "SQ_WAIT_ANY"), W, 100.0)),

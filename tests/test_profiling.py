@@ -177,3 +177,36 @@ def test_counters_report_sums_instances_and_derives_figures(tmp_path):
     assert float(lines["L2 hit share, %"]) == 30.0
     assert float(lines["L1-to-L2 read latency, cycles"]) == 500.0
     assert "k_other" not in rep
+
+
+def test_shares_of_active_cycles_count_every_xcd_once(tmp_path):
+    """GRBM_GUI_ACTIVE comes once per XCD, each the cycles of the whole dispatch: the GPU was active for
+    their mean, not their sum, and the shares of MFMA and address units are of that."""
+    def db(path, name, rows):
+        con = sqlite3.connect(str(path))
+        con.execute("create table pmc_events (name text, dispatch_id int, duration real, counter_name text, "
+                    "counter_value real)")
+        for disp, c, v in rows:
+            con.execute("insert into pmc_events values (?,?,?,?,?)", (name, disp, 1000.0, c, v))
+        con.commit()
+        con.close()
+        return str(path)
+
+    # two dispatches on eight XCDs, 2400 cycles each; a quarter of them MFMA on every SIMD, whose
+    # busy cycles come as 32 sums of 32 SIMDs
+    rows = []
+    for disp in (1, 2):
+        rows += [(disp, "GRBM_GUI_ACTIVE", 2400.0)] * 8
+        rows += [(disp, "SQ_VALU_MFMA_BUSY_CYCLES", 600.0 * 32)] * 32
+        rows += [(disp, "SQ_INSTS_VALU_MFMA_MOPS_BF16", 1e6 / 32)] * 32
+    rep = profiling.mfma_report(db(tmp_path / "m.db", "void cpsnet::k_x<1>(int)", rows), "t", "c")
+    assert "| `cpsnet::k_x<1>` | 2 | 1.00 | 25.0 | 512.0 | 0.2048 |" in rep
+    assert "| all network kernels | 2 | 2.0 total | 25.0 | 512.0 | 0.2048 |" in rep
+
+    k = "cps::k_y<float>"
+    rows = [(1, "GRBM_GUI_ACTIVE", 2400.0)] * 8 + [(1, "TA_BUSY_avr", 1200.0)]
+    rows += [(1, "TA_ADDR_STALLED_BY_TC_CYCLES", 240.0)] * 256
+    rep = profiling.counters_report([db(tmp_path / "t.db", f"void {k}(cps::Geom)", rows)], [k], "t", "c")
+    lines = {l.split("|")[1].strip(): l.split("|")[2].strip() for l in rep.splitlines() if l.startswith("| ")}
+    assert float(lines["address unit busy, % of active cycles"]) == 50.0
+    assert float(lines["address path stalled by the cache, % of active cycles"]) == 10.0
