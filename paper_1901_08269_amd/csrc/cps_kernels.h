@@ -27,6 +27,9 @@ template <typename T>
 void launch_cheb(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *xc, const T *xm1, const T *rho, T *xn,
                  double c1, double c2, const DevState *st, int rev, hipEvent_t ev0 = nullptr,
                  hipEvent_t ev1 = nullptr);
+// the grids whose sweeps run in the short form, in which no lane idles on short rows
+template <typename T>
+bool sweeps_short(const Geom &g);
 // r = rho - K x at the unknown nodes (r is written there only)
 template <typename T>
 void launch_resid(const Launch &L, const Coef<T> &cf, const Irr<T> &ir, const T *x, const T *rho, T *r,

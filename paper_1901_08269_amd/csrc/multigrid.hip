@@ -1705,13 +1705,20 @@ void launch_mg_resid_restrict(hipStream_t s, const Geom &g, const Tiling &tl, co
                                                               t.ax[0], t.ax[1], t.ax[2], rc, first, st);
 }
 
-// Which grids take these marches: those with more than MARCH_MIN_BYTES per vector.  On smaller ones
-// the sweeps run from the Infinity Cache and their launches cost less than the marches' few
-// wavefronts.  Measured (us, pair with its irregular rows against two sweeps): FP32 130^3 23 / 15,
-// 202^3 (32 MB) 41 / 38; FP64 162^3 (33 MB) 42 / 42.  The FP64 pair with the edge nodes of rows
-// beyond 256 interior nodes spills its registers (300^3: 717 us against 242 + 294), so those grids
-// sweep twice.
+// Which grids take these marches: those with more than MARCH_MIN_BYTES per vector; where the sweeps
+// would be short ones (up to 65 MB), only with at least MARCH_MIN_FILL of the lanes on the rows: a
+// wavefront takes 256 nodes of a row, and the short sweeps idle none.  On smaller grids the sweeps run
+// from the Infinity Cache and their launches cost less than the marches' few wavefronts.  Measured
+// (6 iterations of a solve in ms, marches against sweeps): FP32 cubes 180^3 (23 MB) 2.89 / 2.87, 202^3
+// 3.41 / 3.46, 220^3 (42 MB) 4.01 / 4.12, 245^3 4.99 / 5.28; lanes in use at 43 to 49 MB: 400x180x180 (0.78)
+// 4.99 / 4.95, 520x150x150 (0.67) 4.72 / 4.59, 150x280x280 (0.58) 4.75 / 4.64, 102x340x340 (0.39) 5.49 /
+// 5.03, 34x600x600 (0.13) 9.76 / 6.95; beyond 65 MB 130x370x370 (0.50) 6.99 / 7.69, 34x740x740 14.3 / 14.9.
+// FP64 162^3 (33 MB) 3.68 / 3.68, 175^3 (42 MB, 0.68) 4.24 / 4.25, 190^3 (0.73) 4.86 / 5.00, 130x200x200
+// (0.50) 4.42 / 4.25, 66x300x300 (0.25) 6.43 / 5.25; beyond 65 MB 130x260x260 6.43 / 7.33.  The FP64 pair
+// with the edge nodes of rows beyond 256 interior nodes spills its registers (300^3: 717 us against
+// 242 + 294), so those grids sweep twice.
 constexpr size_t MARCH_MIN_BYTES = 40000000;
+constexpr double MARCH_MIN_FILL = 0.7;
 // The marches multiply by 1 / diag K (recip), which has to be a normal number: in FP32 the
 // reciprocal of a diagonal beyond 2^126 (a spacing below 2.6e-19) is flushed to 0, and that of one
 // below 2^-126 is infinite, where the sweeps' division still gives the step.  A hundred binary
@@ -1725,7 +1732,9 @@ static bool reciprocals_normal(const Geom &g)
 template <typename T>
 bool mg_second_pays(const Geom &g)
 {
-    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > MARCH_MIN_BYTES && reciprocals_normal<T>(g);
+    const int segs = (g.nx - 2 + 255) / 256;
+    return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) > MARCH_MIN_BYTES && reciprocals_normal<T>(g) &&
+           (!sweeps_short<T>(g) || g.nx - 2 >= MARCH_MIN_FILL * 256 * segs);
 }
 template <typename T>
 bool mg_pair_pays(const Geom &g)

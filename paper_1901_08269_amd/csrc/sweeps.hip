@@ -1189,7 +1189,7 @@ static inline dim3 tile_block() { return dim3(TX, TY, 1); }
 // 228^3 (95 MB) 77 / 94 against 72 / 92.
 constexpr size_t SHORT_MAX_BYTES = 65000000;
 template <typename T>
-static bool sweeps_short(const Geom &g)
+bool sweeps_short(const Geom &g)
 {
     return (size_t)(g.nx - 2) * (g.ny - 2) * (g.nz - 2) * sizeof(T) <= SHORT_MAX_BYTES;
 }
@@ -1396,6 +1396,8 @@ void launch_scale(hipStream_t s, size_t n, double *x, double alpha)
 }
 
 // explicit instantiations
+template bool sweeps_short<double>(const Geom &);
+template bool sweeps_short<float>(const Geom &);
 template void launch_apply<double, double>(int, const Launch &, const Coef<double> &, const Irr<double> &,
                                            const double *, double *, const double *, const double *, DevState *);
 template void launch_apply<double, float>(int, const Launch &, const Coef<double> &, const Irr<double> &,

@@ -115,9 +115,10 @@ def test_sweep_timing_counts_and_leaves_the_solution_unchanged(precision, precon
 
 
 # Grids above 40 MB per vector, whose smoothing steps run fused: FP32 (43 MB), FP64 with one row
-# segment (42 MB), and FP64 rows of more than 256 nodes, whose post-smoothing runs sweep by sweep.
-@pytest.mark.parametrize("precision,shape", [("mixed", (222, 223, 221)), ("fp64", (176, 174, 177)),
-                                             ("fp64", (290, 140, 131))])
+# segment (43 MB), and FP64 rows of more than 256 nodes (73 MB), whose post-smoothing runs sweep by
+# sweep.
+@pytest.mark.parametrize("precision,shape", [("mixed", (222, 223, 221)), ("fp64", (182, 171, 177)),
+                                             ("fp64", (290, 181, 180))])
 def test_sweep_timing_leaves_large_solves_unchanged(precision, shape):
     """A timed cycle takes the kernels of an untimed one: the solve is bitwise the one without
     timing, and the stats count the launches that form the steps, with the vectors they move (2
@@ -142,6 +143,28 @@ def test_sweep_timing_leaves_large_solves_unchanged(precision, shape):
     else:                                                 # k_mg_second, a pass's two sweeps
         assert n % 3 == 0 and nf == n // 3 and st1["sweep_bytes"] == n // 3 * (2 + 3 + 4) * vb * pts
     assert 0.0 < st1["sweep_ms"] / n < 5.0 and st0["sweep_launches"] == 0
+
+
+@pytest.mark.parametrize("precision,shape,fused", [("mixed", (102, 331, 330), False), ("mixed", (290, 200, 190), False),
+                                                   ("fp64", (66, 290, 290), False), ("fp64", (140, 240, 250), True),
+                                                   ("mixed", (66, 520, 505), True)])
+def test_short_rows_are_smoothed_sweep_by_sweep(precision, shape, fused):
+    """The fused kernels give a wavefront 256 nodes of a row: where rows leave many of its lanes idle and
+    the short sweeps, which idle none, take the grid (40 to 65 MB per vector), these smooth it.  The
+    timing's byte counts tell the two apart; the solution has the residual asked for."""
+    print(f"[case] route of {shape} {precision}", flush=True)
+    grids = tuple(W.tanh_grid(n, 0.9) for n in shape)
+    w = W.polynomial_case(0, [], rng_seed=6, grids=grids)
+    S = cps.Solver.from_workload(w, precision=precision, kernel_timing=1)
+    _, st = S.solve(1e-9)
+    S.close()
+    n, nf = st["sweep_launches"], st["sweep_full_launches"]
+    vectors = st["sweep_bytes"] / ((4 if precision == "mixed" else 8) * math.prod(m - 2 for m in shape))
+    assert st["rel_residual"] <= 1e-9 and st["rel_residual_jacobi"] <= 1e-9 and n > 0
+    if fused:
+        assert nf == 0 and vectors == n // 2 * (2 + 3)
+    else:
+        assert nf == n // 3 and vectors == n // 3 * (3 + 3 + 4)
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
