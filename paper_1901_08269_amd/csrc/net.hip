@@ -352,6 +352,8 @@ __device__ __forceinline__ bf16x4 mask4(bf16x4 a, uint2 k)
 // nine MFMAs.
 // Measured at 64^3, batch 8: 734 us per layer on average for the version that staged X once
 // per tap and gathered its operands by 2-byte LDS reads, 83 us for this one (10.3 -> 1.16 ms of a training step).
+// SPLIT is held to the registers of six waves per SIMD (two blocks a CU), which spills 11 of them: 168 us
+// a launch at 64^3, batch 8 against 205 without; the other form keeps its 91 (64 us with the limit, 56 without).
 template <bool SPLIT>
 __global__ void __launch_bounds__(768, SPLIT ? 6 : 1) k_wgrad(int n, int V, int Cin, int Cout, int wchunk, TapRows tr,
                                                const bf16 *__restrict__ G, const bf16 *__restrict__ X,
@@ -1135,7 +1137,8 @@ void launch_wgrad(cps_model *m, int n, int V, int Cin, int Cout, int wchunk, int
     const size_t lds = std::max(std::max(rows * 32 + 6 * WG_VS * sizeof(uint16_t), red),
                                 groups * COLSUM_LDS * sizeof(float));
     const void *fn = split ? reinterpret_cast<const void *>(&k_wgrad<true>) : reinterpret_cast<const void *>(&k_wgrad<false>);
-    // more than 64 KB of LDS (grids of more than about 128 cells per axis) has to be asked for
+    // more than 64 KB of LDS has to be asked for: from 26 / 69 / 112 / 154 cells per axis of the level on
+    // with 64 / 48 / 32 / 16 output channels of the block (192 bytes per cell of a row, 8 KB per 16 channels)
     if (lds > 65536) nck(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const int nblocks = (int)run_blocks(nchunk, split ? tco * tci : tci), grid = nblocks + (COLSUM_PARTS + groups - 1) / groups;
     if (split)

@@ -826,7 +826,8 @@ __global__ void k_gather3(int ncx, int ncy, int ncz, int nfx, int nfy, const int
 // Bound by a block's own chain (two wavefronts a SIMD: 215 registers for the 6 x 6 solves in place):
 // loads one after another and divergent lanes.  The nodes of a window, of a march and of Q-bar
 // are loaded at once, and no lane takes a row's 27 f values or its whole K row by itself (us, against
-// that): 256^3 with 8 spheres 397 against 537, 128^3 star 130 against 166, 32^3 43 against 53.
+// that): 256^3 with 8 spheres 397 against 537, 128^3 star 130 against 166, 32^3 43 against 53 (alone on the
+// GPU; beside the multigrid hierarchy and the warm start, as in the benchmark's step, 541 at 256^3).
 constexpr int BR_ROWS = 4;          // rows per block
 constexpr int BR_LANES = 32;        // lanes per row
 __global__ void __launch_bounds__(BR_ROWS * BR_LANES) k_build_rows(

@@ -315,6 +315,8 @@ def counters_report(dbs, kernels, title, cmd):
       their count) and the SIMD count;
     * the share of wave time spent waiting (SQ_WAIT_ANY), waiting for issue
       (SQ_WAIT_INST_ANY) and executing (SQ_ACTIVE_INST_ANY), each over SQ_WAVE_CYCLES;
+    * the share of the SIMDs' cycles in which their vector ALU works: 4 SQ_ACTIVE_INST_VALU
+      (quad-cycles) over the busy cycles of one engine and the SIMD count;
     * instructions per wave (SQ_INSTS_* over SQ_WAVES);
     * mean L1-to-L2 read latency in cycles (TCP_TCC_READ_REQ_LATENCY_sum over
       TCP_TCC_READ_REQ_sum) and mean L2-to-memory read latency (TCC_EA0_RDREQ_LEVEL_sum over
@@ -370,7 +372,7 @@ def counters_report(dbs, kernels, title, cmd):
 
     def derived(n):
         W, B, S = mean(n, "SQ_WAVE_CYCLES"), mean(n, "SQ_BUSY_CYCLES"), inst(n, "SQ_BUSY_CYCLES")
-        waves = mean(n, "SQ_WAVES")
+        waves, valu = mean(n, "SQ_WAVES"), mean(n, "SQ_ACTIVE_INST_VALU")
         res = None if W is None or not B or not S else 4.0 * W / (B / S) / SIMDS
         hit, miss = mean(n, "TCC_HIT_sum"), mean(n, "TCC_MISS_sum")
         gui = ratio(mean(n, "GRBM_GUI_ACTIVE"), inst(n, "GRBM_GUI_ACTIVE"))
@@ -379,6 +381,8 @@ def counters_report(dbs, kernels, title, cmd):
                 ("wave time waiting, %", ratio(mean(n, "SQ_WAIT_ANY"), W, 100.0)),
                 ("wave time waiting for issue, %", ratio(mean(n, "SQ_WAIT_INST_ANY"), W, 100.0)),
                 ("wave time executing, %", ratio(mean(n, "SQ_ACTIVE_INST_ANY"), W, 100.0)),
+                ("vector ALU busy, % of the SIMDs' cycles",
+                 None if valu is None or not B or not S else 400.0 * valu / (B / S) / SIMDS),
                 ("VALU instructions per wave", ratio(mean(n, "SQ_INSTS_VALU"), waves)),
                 ("vector loads per wave", ratio(mean(n, "SQ_INSTS_VMEM_RD"), waves)),
                 ("L1-to-L2 read latency, cycles",
