@@ -442,8 +442,9 @@ __global__ void __launch_bounds__(64 * (RR_ROWS + 1)) k_mg_resid_restrict(Geom g
 }
 
 // 1 / d of a diagonal that reciprocals_normal has let through: the hardware's reciprocal and a Newton
-// step in FP32, a third of the instructions of a division (V-cycles of 256^3 .. 513 x 190 x 180 nodes
-// differ from FP64 by the same 2.2e-7 .. 3.2e-7, digit for digit).
+// step in FP32, a third of the instructions of a division.  c2 r (1 / d) rounds once more than
+// c2 r / d: FP32 V-cycles of six grids of 10 to 27 M nodes differ from FP64 by 1.9e-7 .. 2.9e-7 in the
+// 2-norm with either.
 __device__ __forceinline__ float recip(float d)
 {
     const float r = __builtin_amdgcn_rcpf(d);
@@ -462,8 +463,8 @@ __device__ __forceinline__ double recip(double d) { return 1.0 / d; }
 // Irregular nodes: y is read from yi (0 at the solid nodes), z is not written; k_mg_pair_irregular
 // forms both, before.
 // A block's waves fill a CU's registers: 12 in FP32, 8 in FP64; 1 / diag K is formed once for both
-// steps.  Bound by registers (8 to 12 wavefronts a CU) and the vector instructions of the two
-// steps.  Measured with k_mg_pair_irregular, against the two sweeps (us): 256^3 FP32 48 + 8 against
+// steps.  Bound by its few wavefronts (registers; 2.6 a SIMD in FP32, which wait half of their time)
+// and the vector instructions of the two steps (half of the cycles).  Measured with k_mg_pair_irregular, against the two sweeps (us): 256^3 FP32 48 + 8 against
 // 41 + 48, FP64 109 + 9 against 90 + 119; 512^3 FP32 473 + 25 against 393 + 491.
 template <typename T>
 struct Pair {
@@ -685,7 +686,8 @@ __global__ void __launch_bounds__(64 * Pair<T>::waves)
 // x_1 = c2a rho / diag K formed here instead of stored and read: rho in, x_2 out, 2 vectors instead
 // of 3, and the vector update before it writes one less.  The march of k_mg_pair, with x_1 of a
 // plane's rows in place of y.  x_1 holds the step at the irregular nodes and 0 at the solid ones;
-// the irregular rows run in the blocks after the tiles, eight lanes a row.
+// the irregular rows run in the blocks after the tiles, eight lanes a row.  Bound as k_mg_pair is (3.5
+// wavefronts a SIMD, waiting 62 % of their time; vector ALUs busy in 54 % of the cycles).
 // Measured against the stored x_1 (us, this step / the two vector updates before it): 256^3 FP32
 // 41 / 50 + 34 against 45 / 63 + 48, FP64 88 / 113 + 80 against 100 / 145 + 109; 512^3 FP32
 // 352 / 440 + 321 against 393 / 576 + 452.  Loading a plane ahead costs 5 to 15 %, as in the other
