@@ -128,9 +128,11 @@ class Model:
     def train_step(self, inputs, target, mask=None, lr=1e-3, update=True):
         loss = C.c_double()
         B = inputs.shape[0]
-        self._ck(self.L.cps_model_train_step(self.h, _p(inputs.contiguous()), _p(target.contiguous()),
-                                             _p(mask.contiguous()) if mask is not None else None, B, lr,
-                                             int(update), C.byref(loss)), "train_step")
+        # held here until the call returns: the library works on these arrays in place
+        inputs, target = inputs.contiguous(), target.contiguous()
+        mask = mask.contiguous() if mask is not None else None
+        self._ck(self.L.cps_model_train_step(self.h, _p(inputs), _p(target), _p(mask), B, lr, int(update),
+                                             C.byref(loss)), "train_step")
         return loss.value
 
     def restrict(self, solver, u=None, out=None, noalloc=False):

@@ -110,6 +110,24 @@ def test_network_runs_after_a_failed_call_of_the_program():
     m.close()
 
 
+def test_train_step_takes_strided_tensors():
+    """Inputs, targets and masks that are views with other strides are made contiguous for the call and
+    live until its end: the step is the one of contiguous tensors, bit for bit."""
+    print("[case] network strided tensors", flush=True)
+    nc, B = 16, 2
+    inp, tgt, msk = _batch(nc, B, 9)
+    res = []
+    for strided in (False, True):
+        a = [t.transpose(-1, -2).contiguous().transpose(-1, -2) if strided else t for t in (inp, tgt, msk)]
+        assert all(t.is_contiguous() != strided for t in a)
+        m = learned.Model(nc, batch=B, channels=CH, seed=4)
+        loss = m.train_step(*a)
+        res.append((np.array(loss), *m.params(grads=True), m.forward(a[0]).cpu().numpy()))
+        m.close()
+    for x, y in zip(*res):
+        assert np.array_equal(x, y)
+
+
 def test_adam_steps_vs_oracle():
     """Two training steps with the Adam update: the parameters after each step against the
     oracle's Adam (Kingma & Ba, Algorithm 1) applied to the same starting parameters and the
